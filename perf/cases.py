@@ -3,7 +3,8 @@
 A case is a dict of plain values.  `listed()` gives the fixed ones, `draw(rng)` one more of the same ranges.
 `prepare(case, seed)` makes what such a program holds before the call (weights, adapters, activations, the context, the
 segment table of the batch), `run(state)` is one pass through the public entry points, `work(case)` the bytes and
-operations the pass cannot do without, `tolerance(case)` how far two correct implementations may lie apart.
+operations the pass cannot do without, `tolerance(case)` how far two correct implementations may lie apart, `exact(case,
+seed)` the outputs in 64 bits.
 
 Three kinds of pass:
   linear    `layers` projections of one shape, each with weights and adapters of its own, on one batch: forward through
@@ -372,3 +373,86 @@ def tolerance(case):
     if case["kind"] == "siblings" and case["swiglu"]:
         return {"rel": 1.2e-2, "max": 0.12}
     return {"rel": 7e-3, "max": 0.06}
+
+
+# ----------------------------------------------------------------------------------------------------------------------
+# the same pass in 64 bits
+# ----------------------------------------------------------------------------------------------------------------------
+def exact(case, seed):
+    """What `run` returns for the first pass on these inputs, in fp64 by plain torch: the definition, run of tokens by run of tokens."""
+    st = prepare(case, seed)
+    return _exact_update(st) if case["kind"] == "update" else _exact_layers(st)
+
+
+def _exact_layers(st):
+    case, (ranks, seg_start, seg_adapter, seg_is_train, scale) = st["case"], st["batch"]
+    flip, d_outs = st["layout"] == binding.LAYOUT_OUT_IN, st["d_outs"]
+    P, D, swiglu = len(d_outs), sum(d_outs), case["kind"] == "siblings" and case["swiglu"]
+    cols = [slice(sum(d_outs[:j]), sum(d_outs[:j + 1])) for j in range(P)]
+    wide = lambda t: (t.t() if flip else t).double()
+    segs = [(slice(int(seg_start[k]), int(seg_start[k + 1])), int(seg_adapter[k]), bool(seg_is_train[k]))
+            for k in range(len(seg_adapter)) if seg_start[k + 1] > seg_start[k]]
+    tr = torch.zeros(case["tokens"], dtype=torch.bool, device="cuda")
+    for rows, _, t in segs:
+        tr[rows] = t
+    out = []
+    for L in st["layers"]:
+        W, A, B = wide(L["W"]), L["A"].tensors, L["B"].tensors
+        zeros = lambda table: [torch.zeros_like(wide(t)) if t is not None else None for t in table.tensors]
+        dA, dB = (zeros(L["dA"]), zeros(L["dB"])) if st["train"] else ([], [])
+        for m in L["micro"]:
+            x = m["x"].double()
+            y, h = x @ W, torch.zeros((case["tokens"], int(ranks.max()) * P), dtype=torch.float64, device="cuda")
+            for rows, a, t in segs:
+                if a < 0:
+                    continue
+                r, hs, b = int(ranks[a]), x[rows] @ wide(A[a]), wide(B[a])
+                h[rows, :r * P] = hs
+                for j in range(P):
+                    y[rows, cols[j]] += scale * (hs[:, j * r:(j + 1) * r] @ b[:, cols[j]])
+            pre = y
+            if swiglu:
+                gate, up = pre[:, :D // 2], pre[:, D // 2:]
+                sig = torch.sigmoid(gate)
+                y = gate * sig * up
+            out.append(y)
+            if not st["train"]:
+                continue
+            zero = lambda t: torch.where(tr[:, None], t, torch.zeros_like(t))
+            if m["h"] is not None:
+                out.append(zero(h))
+            dy = zero(m["dy"].double())
+            if swiglu:
+                dout = m["dout"].double()
+                dy = zero(torch.cat([dout * up * sig * (1 + gate * (1 - sig)), dout * gate * sig], 1))
+                out.append(zero(pre))
+            dx = zero(dy @ W.t())
+            for rows, a, t in segs:
+                if not t:
+                    continue
+                r, hs, b, d = int(ranks[a]), h[rows], wide(B[a]), dy[rows]
+                dh = scale * torch.cat([d[:, c] @ b[:, c].t() for c in cols], 1)
+                for j in range(P):
+                    dB[a][:, cols[j]] += scale * (hs[:, j * r:(j + 1) * r].t() @ d[:, cols[j]])
+                dA[a] += x[rows].t() @ dh
+                dx[rows] += dh @ wide(A[a]).t()
+            out.append(dx)
+            if swiglu:
+                out.append(dy)
+        out += [t.t().contiguous() if flip else t for t in dA + dB if t is not None]
+    return out
+
+
+def _exact_update(st):
+    f = lambda v: float(np.float32(v))  # (the hyper-parameters are 32-bit numbers at the boundary)
+    lr, b1, b2, eps, wd, step = f(1e-4), f(0.9), f(0.999), f(1e-8), f(0.01), 10
+    out = []
+    for t in st["tables"]:
+        w = (t["master"] if t["master"] is not None else t["param"]).double()
+        g = t["grad"].double()
+        m = b1 * t["m"].double() + (1 - b1) * g
+        v = b2 * t["v"].double() + (1 - b2) * g * g
+        w = w * (1 - lr * wd) - lr * (m / (1 - b1 ** step)) / ((v / (1 - b2 ** step)).sqrt() + eps)
+        mean = (w + sum(o.double() for o in t["others"])) / st["case"]["copies"]
+        out += [w, m, v, mean] + ([w] if t["master"] is not None else [])
+    return out
