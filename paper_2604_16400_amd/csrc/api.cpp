@@ -1096,6 +1096,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     {
         Prof prof(c, st, "gemm_fwd");
         if (f32) {
+            g.n_rows = s->n_tokens;
             HIP_TRY(launch_gemm_f32(g, tr, st));
         } else {
             HIP_TRY(run_gemm(c, g, L.all, s->n_tokens, s->d_out, c->tile_fwd, tr, st, swiglu));
@@ -1313,7 +1314,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         {
             Prof prof(c, gs, "grad_dB");
             if (f32) {
-                HIP_TRY(launch_grad_f32(ga, L.n_grad, gs));
+                HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, gs));
             } else if (P == 1) {
                 HIP_TRY(launch_grad(ga, L.n_grad, L.rpad, gs));
             } else {
@@ -1377,7 +1378,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         ga.out_transposed = tr ? 0 : 1;
         {
             Prof prof(c, gs, "grad_dA");
-            if (f32) HIP_TRY(launch_grad_f32(ga, L.n_grad, gs));
+            if (f32) HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, gs));
             else HIP_TRY(launch_grad(ga, L.n_grad, L.rpad, gs));
         }
         if (overlap) HIP_TRY(hipEventRecord(c->ev_join, c->side));
@@ -1406,6 +1407,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         g.zeros = c->d_zeros;
         Prof prof(c, st, "gemm_dx");
         if (f32) {
+            g.n_rows = n_train;
             HIP_TRY(launch_gemm_f32(g, !tr, st));
         } else {
             HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, st));

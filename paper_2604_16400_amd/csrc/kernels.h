@@ -253,8 +253,8 @@ hipError_t launch_fedavg(const FedAvgArgs &a, bool bf16, hipStream_t st);
 hipError_t launch_adamw(const AdamWArgs &a, bool bf16, hipStream_t st);
 
 // fp32 element type: same argument blocks, plain fp32 FMA kernels
-hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st);
+hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st);  // a.n_rows: rows of the order
 hipError_t launch_skinny_f32(const SkinnyArgs &a, int n_items, bool t_kmajor, hipStream_t st);
-hipError_t launch_grad_f32(const GradArgs &a, int n_grad, hipStream_t st);
+hipError_t launch_grad_f32(const GradArgs &a, int n_grad, int rpad, hipStream_t st);
 
 }  // namespace collm

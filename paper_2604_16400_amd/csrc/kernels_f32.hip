@@ -1,7 +1,14 @@
 // fp32 kernels of the mixed-batch LoRA linear layer: the same three passes as the bf16 path
-// (GEMM with low-rank extension, skinny rank-wide pass, adapter gradients) with plain fp32
-// fused multiply-add and ascending-index sums.  The fp32 element type exists for exactness
-// checks on small layers, not for speed; the kernels are simple LDS-tiled loops.
+// (GEMM with low-rank extension, skinny rank-wide pass, adapter gradients) in 32 bits throughout.
+// The fp32 element type exists for exactness on small layers.  What bounds such a pass is the chain of
+// dependent steps in one wave (load, multiply, load ..), not bytes or flops: every kernel is cut into many
+// short waves, each with all loads of 64 K values in flight and its own range of the contraction, and the
+// waves of a block add their sums in LDS in wave order.  v_mfma_f32_16x16x4_f32 (fp32 products and sums)
+// does the multiplying because its operands come straight from memory: lane l supplies one K value
+// (group l / 16) of row or column l % 16, so a lane that loads four consecutive K values feeds four of them.
+// Measured on 256 -> 256, 64 tokens, rank 8 (us; before: one thread per output of the narrow passes with a serial sum,
+// 64 x 64 LDS tiles): GEMM 35 -> 6.3 (forward), 34 -> 7.6 (dX), rank-wide passes 22 -> 4.5, gradients 20 -> 4.2; the
+// shorter chains also halve the distance from the 64-bit result (3.3e-7 -> 1.4e-7).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -12,186 +19,283 @@
 
 namespace collm {
 
-constexpr int kF32Tile = 64;
+constexpr int kF32Tile = 64;  // rows per row tile of the plan (extension steps are listed per tile)
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr uint32_t kF32Oob = 0x80000000u;  // beyond any buffer (tensors are limited to 2 GiB): reads as zero
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t f32_rsrc(const void *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ floatx4 f32_load4(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+__device__ __forceinline__ float f32_load1(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
+__device__ __forceinline__ floatx4 mfma_f32(float a, float b, floatx4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
 // y[tok(m)][n] = sum_k a[tok(m)][k] b(k, n) + sum_q hs[m][q] table_a(q, n)
-template <bool B_KMAJOR>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs p)
+//
+// One block = 16 RT rows x 64 columns; its KW waves split K (and the extension steps) between them.  Column i of
+// 16-column block c is n0 + 4 i + c: a lane's four columns are then consecutive both where it loads the second
+// operand ([K][N]) and where it stores.
+template <bool B_KMAJOR, int RT, int KW>
+__global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
 {
-    __shared__ float As[16][kF32Tile + 1];
-    __shared__ float Bs[16][kF32Tile + 1];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int n0 = blockIdx.x * kF32Tile, m0 = blockIdx.y * kF32Tile;
-    const float *__restrict__ A = reinterpret_cast<const float *>(p.a);
-    const float *__restrict__ B = reinterpret_cast<const float *>(p.b);
+    constexpr int ROWS = 16 * RT, LD = 64 + 4;
+    __shared__ __align__(16) float red[KW * ROWS * LD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int n0 = blockIdx.x * 64, m0 = blockIdx.y * ROWS;
     const int K = p.K, N = p.N;
+    const int n = n0 + 4 * l16;  // first of this lane's four columns (N is a multiple of 4)
+    const __amdgpu_buffer_rsrc_t ra = f32_rsrc(p.a, 0x7fffffffu), rb = f32_rsrc(p.b, 0x7fffffffu);
 
-    float acc[4][4];
+    uint32_t aoff[RT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int t = 0; t < RT; ++t) {
+        const int tok = p.row_tok[m0 + t * 16 + l16];
+        aoff[t] = tok >= 0 ? (uint32_t)tok * (uint32_t)p.lda * 4u : kF32Oob;
+    }
+    floatx4 acc[RT][4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[t][c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    const int lr = tid >> 2, lq = tid & 3;  // loader coordinates for K-contiguous sources
-    const int a_tok = p.row_tok[m0 + lr];
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            const int k = k0 + lq * 4;
-            if (a_tok >= 0 && k < K) v = *reinterpret_cast<const float4 *>(A + (int64_t)a_tok * p.lda + k);
-            As[lq * 4 + 0][lr] = v.x;
-            As[lq * 4 + 1][lr] = v.y;
-            As[lq * 4 + 2][lr] = v.z;
-            As[lq * 4 + 3][lr] = v.w;
+    const int per = (((K + KW - 1) / KW) + 15) & ~15;
+    const int k_lo = wave * per, k_hi = (k_lo + per) < K ? (k_lo + per) : K;
+    // 16 K values per step (this lane: k + 4 kg .. + 3), U steps of loads in flight
+    constexpr int U = RT == 1 ? 4 : 2;
+    for (int k0 = k_lo; k0 < k_hi; k0 += 16 * U) {
+        floatx4 xa[U][RT], wb[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * 16 + kg * 4;
+            const bool on = k < k_hi;
+#pragma unroll
+            for (int t = 0; t < RT; ++t) xa[u][t] = f32_load4(ra, on && aoff[t] != kF32Oob ? aoff[t] + (uint32_t)k * 4u : kF32Oob);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // [K][N]: K value k + j, columns n .. n + 3; [N][K]: column n + j, K values k .. k + 3
+                const uint32_t off = B_KMAJOR ? ((uint32_t)(n + j) * (uint32_t)p.ldb + (uint32_t)k) * 4u
+                                              : ((uint32_t)(k + j) * (uint32_t)p.ldb + (uint32_t)n) * 4u;
+                wb[u][j] = f32_load4(rb, on && n < N ? off : kF32Oob);
+            }
         }
-        if constexpr (B_KMAJOR) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            const int k = k0 + lq * 4;
-            if (n0 + lr < N && k < K) v = *reinterpret_cast<const float4 *>(B + (int64_t)(n0 + lr) * p.ldb + k);
-            Bs[lq * 4 + 0][lr] = v.x;
-            Bs[lq * 4 + 1][lr] = v.y;
-            Bs[lq * 4 + 2][lr] = v.z;
-            Bs[lq * 4 + 3][lr] = v.w;
-        } else {
-            const int kk = tid >> 4, nq = tid & 15;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (k0 + kk < K && n0 + nq * 4 < N)
-                v = *reinterpret_cast<const float4 *>(B + (int64_t)(k0 + kk) * p.ldb + n0 + nq * 4);
-            Bs[kk][nq * 4 + 0] = v.x;
-            Bs[kk][nq * 4 + 1] = v.y;
-            Bs[kk][nq * 4 + 2] = v.z;
-            Bs[kk][nq * 4 + 3] = v.w;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int t = 0; t < RT; ++t)
+                        acc[t][c] = mfma_f32(B_KMAJOR ? wb[u][c][e] : wb[u][e][c], xa[u][t][e], acc[t][c]);
+    }
+
+    // Low-rank extension: one step = 16 rank indices of one adapter's table against the rows of its run.  The
+    // products of a step are summed apart and added to the rows of the run only, so that a table's infinities
+    // and NaNs stay out of other adapters' rows.
+    const float *__restrict__ Hs = reinterpret_cast<const float *>(p.hs);
+    const int tile = m0 / kF32Tile, in_tile = m0 - tile * kF32Tile;
+    const int e0 = p.ext_off[tile], e1 = p.ext_off[tile + 1];
+    for (int e = e0 + wave; e < e1; e += KW) {
+        const ExtStep st = p.ext[e];
+        const int koff = (int)(st.koff_rank & 0xffffu), rk = (int)(st.koff_rank >> 16);
+        const int row_lo = (int)(st.rows & 0xffffu) - in_tile, row_hi = (int)(st.rows >> 16) - in_tile;
+        if (rk == 0 || row_hi <= 0 || row_lo >= ROWS) continue;
+        const uint32_t tab_bytes = (uint32_t)rk * (uint32_t)(B_KMAJOR ? N : p.ext_ld) * 4u;
+        const __amdgpu_buffer_rsrc_t rt = f32_rsrc(reinterpret_cast<const void *>(st.tab), tab_bytes);
+        const int q = koff + kg * 4;
+        floatx4 tb[4], hv[RT];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (B_KMAJOR) {
+                // table rows are output columns, `rank` long: any rank, so element by element
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    tb[j][i] = f32_load1(rt, n < N && q + i < rk ? ((uint32_t)(n + j) * (uint32_t)rk + (uint32_t)(q + i)) * 4u : kF32Oob);
+            } else {
+                tb[j] = f32_load4(rt, n < N && q + j < rk ? ((uint32_t)(q + j) * (uint32_t)p.ext_ld + (uint32_t)n) * 4u : kF32Oob);
+            }
         }
-        __syncthreads();
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
+        for (int t = 0; t < RT; ++t) {
+            // (zeros lie behind the rank, up to the row's padded length)
+            const int r = t * 16 + l16;
+            hv[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (r >= row_lo && r < row_hi) hv[t] = *reinterpret_cast<const floatx4 *>(Hs + (int64_t)(m0 + r) * p.hs_ld + q);
+        }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+        for (int t = 0; t < RT; ++t) {
+            floatx4 add[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
+            for (int c = 0; c < 4; ++c) add[c] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-
-    // low-rank extension, straight from global memory (tables and activations are small)
-    const float *__restrict__ Hs = reinterpret_cast<const float *>(p.hs);
-    const int e0 = p.ext_off[blockIdx.y], e1 = p.ext_off[blockIdx.y + 1];
-    for (int e = e0; e < e1; ++e) {
-        const ExtStep st = p.ext[e];
-        const int koff = (int)(st.koff_rank & 0xffffu), rk = (int)(st.koff_rank >> 16);
-        const int row_lo = (int)(st.rows & 0xffffu), row_hi = (int)(st.rows >> 16);
-        const float *__restrict__ tab = reinterpret_cast<const float *>(st.tab);
-        const int q1 = (koff + kKStep) < rk ? (koff + kKStep) : rk;
+                for (int c = 0; c < 4; ++c) add[c] = mfma_f32(B_KMAJOR ? tb[c][i] : tb[i][c], hv[t][i], add[c]);
+            const int r = t * 16 + l16;
+            if (r >= row_lo && r < row_hi)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = ty * 4 + i;
-            if (r < row_lo || r >= row_hi) continue;
-            for (int q = koff; q < q1; ++q) {
-                const float hv = Hs[(int64_t)(m0 + r) * p.hs_ld + q];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int n = n0 + tx * 4 + j;
-                    if (n < N) {
-                        const float tv = B_KMAJOR ? tab[(int64_t)n * rk + q] : tab[(int64_t)q * p.ext_ld + n];
-                        acc[i][j] = fmaf(hv, tv, acc[i][j]);
-                    }
-                }
-            }
+                for (int c = 0; c < 4; ++c) acc[t][c] += add[c];
         }
     }
 
+    // lane holds row l16 and, in register j of block c, column 16 kg + 4 j + c
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<floatx4 *>(red + (wave * ROWS + t * 16 + l16) * LD + kg * 16 + j * 4) =
+                floatx4{acc[t][0][j], acc[t][1][j], acc[t][2][j], acc[t][3][j]};
+    __syncthreads();
     float *__restrict__ Out = reinterpret_cast<float *>(p.out);
+    for (int idx = tid; idx < ROWS * 16; idx += KW * 64) {
+        const int r = idx >> 4, c = (idx & 15) * 4;
+        const int tok = p.row_tok[m0 + r];
+        if (tok < 0 || n0 + c >= N) continue;
+        floatx4 sum = *reinterpret_cast<const floatx4 *>(red + r * LD + c);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int tok = p.row_tok[m0 + ty * 4 + i];
-        if (tok < 0) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n < N) Out[(int64_t)tok * p.ldo + n] = acc[i][j];
-        }
+        for (int w = 1; w < KW; ++w) sum += *reinterpret_cast<const floatx4 *>(red + (w * ROWS + r) * LD + c);
+        *reinterpret_cast<floatx4 *>(Out + (int64_t)tok * p.ldo + n0 + c) = sum;
     }
 }
 
-// out[m][q] = sum_k in[tok(m)][k] table_a(k, q), k ascending; one item per block
+// out[m][q] = sum_k in[tok(m)][k] table_a(k, q): one block = one item (up to 16 rows of one adapter) x 16 columns of
+// the output row (blockIdx.y; columns beyond the rank are cleared); its eight waves split K.
+constexpr int kF32SkinnyWaves = 8;
 template <bool T_KMAJOR>
-__global__ void __launch_bounds__(256) skinny_f32_kernel(SkinnyArgs p)
+__global__ void __launch_bounds__(kF32SkinnyWaves * 64) skinny_f32_kernel(SkinnyArgs p)
 {
+    constexpr int KW = kF32SkinnyWaves, LD = 16 + 4;
+    __shared__ __align__(16) float red[KW * 16 * LD];
     const SkinnyItem it = p.items[blockIdx.x];
     const int rank = it.rank, K = p.K;
-    const float *__restrict__ In = reinterpret_cast<const float *>(p.in);
-    const float *__restrict__ tab = reinterpret_cast<const float *>(p.tab[it.adapter]);
-    float *__restrict__ scaled = reinterpret_cast<float *>(p.bf_out);
-    for (int idx = threadIdx.x; idx < it.n_rows * rank; idx += blockDim.x) {
-        const int m = idx / rank, q = idx - m * rank;
-        const int row = it.row_lo + m;
-        const int tok = p.row_tok[row];
-        const float *x = In + (int64_t)tok * p.ld_in;
-        float acc = 0.f;
-        for (int k = 0; k < K; ++k) {
-            const float tv = T_KMAJOR ? tab[(int64_t)q * K + k] : tab[(int64_t)k * rank + q];
-            acc = fmaf(x[k], tv, acc);
-        }
-        if (p.f32_out) {
-            if (p.f32_by_token) {
-                if (p.tok_train[tok]) p.f32_out[(int64_t)tok * p.f32_ld + q] = acc * p.f32_mult;
-            } else {
-                p.f32_out[(int64_t)row * p.f32_ld + q] = acc * p.f32_mult;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int q0 = blockIdx.y * 16, q = q0 + l16;
+    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (q0 < rank) {
+        const __amdgpu_buffer_rsrc_t rx = f32_rsrc(p.in, p.in_bytes);
+        const __amdgpu_buffer_rsrc_t rt = f32_rsrc(reinterpret_cast<const void *>(p.tab[it.adapter]), (uint32_t)rank * (uint32_t)K * 4u);
+        const int tok = l16 < it.n_rows ? p.row_tok[it.row_lo + l16] : -1;
+        const uint32_t xoff = tok >= 0 ? (uint32_t)tok * (uint32_t)p.ld_in * 4u : kF32Oob;
+        const int per = (((K + KW - 1) / KW) + 15) & ~15;
+        const int k_lo = wave * per, k_hi = (k_lo + per) < K ? (k_lo + per) : K;
+        constexpr int U = 8;  // 128 K values of loads in flight
+        for (int k0 = k_lo; k0 < k_hi; k0 += 16 * U) {
+            floatx4 xv[U], tv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * 16 + kg * 4;
+                const bool on = k < k_hi;
+                xv[u] = f32_load4(rx, on && xoff != kF32Oob ? xoff + (uint32_t)k * 4u : kF32Oob);
+                if constexpr (T_KMAJOR) {
+                    tv[u] = f32_load4(rt, on && q < rank ? ((uint32_t)q * (uint32_t)K + (uint32_t)k) * 4u : kF32Oob);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        tv[u][e] = f32_load1(rt, on && q < rank ? ((uint32_t)(k + e) * (uint32_t)rank + (uint32_t)q) * 4u : kF32Oob);
+                }
             }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc = mfma_f32(tv[u][e], xv[u][e], acc);
         }
-        if (scaled) scaled[(int64_t)row * p.bf_ld + q] = acc * p.bf_mult;
     }
-    // zero fill beyond the rank
-    for (int idx = threadIdx.x; idx < it.n_rows * 256; idx += blockDim.x) {
-        const int m = idx >> 8, q = rank + (idx & 255);
-        const int row = it.row_lo + m;
-        const int tok = p.row_tok[row];
-        if (p.f32_out && q < p.f32_cols) {
-            if (p.f32_by_token) {
-                if (p.tok_train[tok]) p.f32_out[(int64_t)tok * p.f32_ld + q] = 0.f;
-            } else {
-                p.f32_out[(int64_t)row * p.f32_ld + q] = 0.f;
-            }
+    // lane holds row l16, columns 4 kg ..
+    *reinterpret_cast<floatx4 *>(red + (wave * 16 + l16) * LD + kg * 4) = acc;
+    __syncthreads();
+    if (tid >= 256) return;
+    const int m = tid >> 4, qo = q0 + (tid & 15);
+    if (m >= it.n_rows) return;
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < KW; ++w) sum += red[(w * 16 + m) * LD + (tid & 15)];
+    if (qo >= rank) sum = 0.f;
+    const int row = it.row_lo + m;
+    const int tok = p.row_tok[row];
+    if (p.f32_out && qo < p.f32_cols) {
+        if (p.f32_by_token) {
+            if (p.tok_train[tok]) p.f32_out[(int64_t)tok * p.f32_ld + qo] = sum * p.f32_mult;
+        } else {
+            p.f32_out[(int64_t)row * p.f32_ld + qo] = sum * p.f32_mult;
         }
-        if (scaled && q < p.bf_ld) scaled[(int64_t)row * p.bf_ld + q] = 0.f;
     }
+    if (p.bf_out && qo < p.bf_ld) reinterpret_cast<float *>(p.bf_out)[(int64_t)row * p.bf_ld + qo] = sum * p.bf_mult;
 }
 
-// out_a(q, n) = sum_t small[t][q] big[tok(t)][n], t ascending over the adapter's rows
-__global__ void __launch_bounds__(256) grad_f32_kernel(GradArgs p)
+// out_a(q, n) = sum_t small[t][q] big[tok(t)][n] over the adapter's rows t: one block = one trained adapter x 64 columns
+// x 16 rank indices (blockIdx.z); its eight waves split the rows.  Column i of block c is n0 + 4 i + c, as above.
+constexpr int kF32GradWaves = 8;
+__global__ void __launch_bounds__(kF32GradWaves * 64) grad_f32_kernel(GradArgs p)
 {
+    constexpr int KW = kF32GradWaves, LD = 64 + 4;
+    __shared__ __align__(16) float red[KW * 16 * LD];
     const GradItem it = p.items[blockIdx.y];
-    const int n = blockIdx.x * 256 + threadIdx.x;
     const int N = p.N, rank = it.rank;
-    if (n >= N) return;
-    const float *__restrict__ Big = reinterpret_cast<const float *>(p.big);
+    const int q0 = blockIdx.z * 16;
+    if (q0 >= rank) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int n0 = blockIdx.x * 64, n = n0 + 4 * l16, q = q0 + l16;
+    const __amdgpu_buffer_rsrc_t rb = f32_rsrc(p.big, p.big_bytes);
+    const float *__restrict__ Small = p.small_;
+    const int n_rows = it.row_hi - it.row_lo;
+    const int per = (((n_rows + KW - 1) / KW) + 3) & ~3;
+    const int t_lo = it.row_lo + wave * per, t_hi = (t_lo + per) < it.row_hi ? (t_lo + per) : it.row_hi;
+    floatx4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    constexpr int U = 8;  // 32 rows of loads in flight
+    for (int t0 = t_lo; t0 < t_hi; t0 += 4 * U) {
+        int tok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + u * 4 + kg;
+            tok[u] = t < t_hi ? p.row_tok[t] : -1;
+        }
+        floatx4 bv[U];
+        float sv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + u * 4 + kg;
+            bv[u] = f32_load4(rb, tok[u] >= 0 && n < N ? ((uint32_t)tok[u] * (uint32_t)p.ld_big + (uint32_t)n) * 4u : kF32Oob);
+            sv[u] = 0.f;
+            if (tok[u] >= 0 && q < rank) sv[u] = Small[(p.small_by_token ? (int64_t)tok[u] : (int64_t)t) * p.ld_small + q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] = mfma_f32(bv[u][c], sv[u] * p.small_mult, acc[c]);
+    }
+    // lane holds rank index l16 and, in register j of block c, column 16 kg + 4 j + c
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<floatx4 *>(red + (wave * 16 + l16) * LD + kg * 16 + j * 4) = floatx4{acc[0][j], acc[1][j], acc[2][j], acc[3][j]};
+    __syncthreads();
     float *out = reinterpret_cast<float *>(p.out_tab[it.adapter]);
-    for (int q0 = 0; q0 < rank; q0 += 8) {
-        float acc[8];
+    const int qn = rank - q0 < 16 ? rank - q0 : 16;
+    for (int idx = tid; idx < 64 * qn; idx += KW * 64) {
+        // (consecutive threads write consecutive addresses in either layout)
+        const int qi = p.out_transposed ? idx % qn : idx >> 6, c = p.out_transposed ? idx / qn : idx & 63;
+        if (n0 + c >= N) continue;
+        float sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-        for (int t = it.row_lo; t < it.row_hi; ++t) {
-            const int tok = p.row_tok[t];
-            const float bv = Big[(int64_t)tok * p.ld_big + n];
-            const float *s = p.small_ + (p.small_by_token ? (int64_t)tok : (int64_t)t) * p.ld_small;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (q0 + e < rank) acc[e] = fmaf(s[q0 + e] * p.small_mult, bv, acc[e]);
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int q = q0 + e;
-            if (q < rank) {
-                float *dst = p.out_transposed ? out + (int64_t)n * rank + q : out + (int64_t)q * N + n;
-                *dst = p.accumulate ? (*dst + acc[e]) : acc[e];
-            }
-        }
+        for (int w = 0; w < KW; ++w) sum += red[(w * 16 + qi) * LD + c];
+        float *dst = p.out_transposed ? out + (int64_t)(n0 + c) * rank + q0 + qi : out + (int64_t)(q0 + qi) * N + n0 + c;
+        *dst = p.accumulate ? (*dst + sum) : sum;
     }
 }
 
@@ -267,25 +371,36 @@ hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t st)
 
 hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
 {
-    const dim3 grid((a.N + kF32Tile - 1) / kF32Tile, a.tiles_m);
-    if (grid.x == 0 || grid.y == 0) return hipSuccess;
-    if (b_kmajor) COLLM_LAUNCH(gemm_f32_kernel<true>, grid, dim3(256), 0, st, a);
-    else COLLM_LAUNCH(gemm_f32_kernel<false>, grid, dim3(256), 0, st, a);
+    const int cols = (a.N + 63) / 64, rows = a.n_rows;  // (the row order is padded to a multiple of 256 rows)
+    if (cols <= 0 || rows <= 0) return hipSuccess;
+    // 16 rows and eight waves per block while those blocks leave CUs without a second one; then 32 rows and four waves
+    // (half the reads of the second operand)
+    if ((int64_t)cols * ((rows + 15) / 16) < 512) {
+        if (b_kmajor) COLLM_LAUNCH((gemm_f32_kernel<true, 1, 8>), dim3(cols, (rows + 15) / 16), dim3(512), 0, st, a);
+        else COLLM_LAUNCH((gemm_f32_kernel<false, 1, 8>), dim3(cols, (rows + 15) / 16), dim3(512), 0, st, a);
+    } else {
+        if (b_kmajor) COLLM_LAUNCH((gemm_f32_kernel<true, 2, 4>), dim3(cols, (rows + 31) / 32), dim3(256), 0, st, a);
+        else COLLM_LAUNCH((gemm_f32_kernel<false, 2, 4>), dim3(cols, (rows + 31) / 32), dim3(256), 0, st, a);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_skinny_f32(const SkinnyArgs &a, int n_items, bool t_kmajor, hipStream_t st)
 {
     if (n_items <= 0) return hipSuccess;
-    if (t_kmajor) COLLM_LAUNCH(skinny_f32_kernel<true>, dim3(n_items), dim3(256), 0, st, a);
-    else COLLM_LAUNCH(skinny_f32_kernel<false>, dim3(n_items), dim3(256), 0, st, a);
+    // 16 columns of the widest output row per block
+    const int width = std::max(a.f32_out ? a.f32_cols : 0, a.bf_out ? (int)a.bf_ld : 0);
+    const dim3 grid(n_items, (width + 15) / 16);
+    if (grid.y == 0) return hipSuccess;
+    if (t_kmajor) COLLM_LAUNCH(skinny_f32_kernel<true>, grid, dim3(kF32SkinnyWaves * 64), 0, st, a);
+    else COLLM_LAUNCH(skinny_f32_kernel<false>, grid, dim3(kF32SkinnyWaves * 64), 0, st, a);
     return hipGetLastError();
 }
 
-hipError_t launch_grad_f32(const GradArgs &a, int n_grad, hipStream_t st)
+hipError_t launch_grad_f32(const GradArgs &a, int n_grad, int rpad, hipStream_t st)
 {
     if (n_grad <= 0 || a.N <= 0) return hipSuccess;
-    COLLM_LAUNCH(grad_f32_kernel, dim3((a.N + 255) / 256, n_grad), dim3(256), 0, st, a);
+    COLLM_LAUNCH(grad_f32_kernel, dim3((a.N + 63) / 64, n_grad, (rpad + 15) / 16), dim3(kF32GradWaves * 64), 0, st, a);
     return hipGetLastError();
 }
 

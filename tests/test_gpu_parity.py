@@ -160,6 +160,39 @@ def test_shuffled_segment_order(dtype):
     _run_full(ws)
 
 
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("d_in,d_out,lens", [
+    (4, 4, [1, 2, 1]),                      # one row block, a K below one step of loads
+    (68, 132, [17, 47, 65, 3]),             # ragged rows, columns and K; 16-row blocks
+    (1024, 68, [33, 15, 16, 1]),            # several rounds of loads per wave
+    (128, 1028, [200, 31, 260, 45]),        # enough blocks for 32-row blocks in the forward GEMM
+])
+def test_fp32_row_blocks_and_contraction_ranges(d_in, d_out, lens, transposed):
+    # ranks below, at and above the 16 columns of a block, up to the largest; h_save wider than every rank
+    w = _adhoc("f32", d_in, d_out, [3, 17, 16, 256], lens + [5], [0, 1, 2, 3, -1][: len(lens)] + [3], [1, 0, 1, 1][: len(lens)] + [1],
+               scale=0.5)
+    _run_full(w, transposed=transposed)
+    _run_full(w, transposed=transposed, h_save=False)
+
+
+def test_fp32_table_values_stay_in_their_adapters_rows():
+    # an adapter whose expand table holds infinities shares row blocks with others: only its own rows see them
+    import torch
+
+    w = _adhoc("f32", 64, 64, [8, 8], [5, 6, 9], [0, 1, -1], [0, 0, 0])
+    t = wl.make_tensors(w)
+    ctx = make_ctx(w)
+    layer = DeviceLayer(w, t, ctx)
+    layer.B[1].fill_(float("inf"))
+    layer.fwd()
+    torch.cuda.synchronize()
+    y = to_host(layer.y)
+    rest = layer.tok_adapter != 1
+    y_ref, _ = oracle.lora_linear_fwd(t.x, t.W, t.A, t.B, layer.tok_adapter, w.scale)
+    assert not np.isfinite(y[~rest]).any() and maxrel(y[rest], y_ref[rest]) <= TOL["f32"]
+    ctx.close()
+
+
 def test_all_inference_batch_and_all_training_batch():
     w = _adhoc("bf16", 128, 256, [16, 16], [10, 20, 30], [0, 1, -1], [0, 0, 0])
     t = wl.make_tensors(w)
