@@ -123,6 +123,8 @@ struct Tiling {
     int tail_cols = 0;
 };
 
+constexpr int kSplitBlocks = 512;  // 128x128 tiles that run at once: two per CU
+
 // can_split: the 128x128 tiles behind the large ones may have K cut into slices (see run_gemm), which lets a few
 // such tiles use the whole GPU
 Tiling pick_tiling(int rows, int cols, int K, bool can_split)
@@ -137,7 +139,7 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
     //    two rounds on the blocks' different speeds smooth the rounds out (0.62 per round, 0.3 for a
     //    nearly empty last one);
     //  - whole rounds of 256x256 tiles over the first rows and 128x128 tiles over the rest, as two
-    //    launches: the sum of both plus 0.1 for the idle CUs at the boundary between them; fewer than 448
+    //    launches: the sum of both plus 0.1 for the idle CUs at the boundary between them; at most 256
     //    small tiles with K in slices cost their share of a full round plus the kernel that adds the slices.
     auto cost_large = [](double tiles) {
         const double x = tiles / 256.0, whole = std::floor(x), part = x - whole;
@@ -162,7 +164,7 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
         const int tail = (std::max(rows, 1) - 256 * m + 127) / 128;
         if (m >= 1 && tail >= 1) {
             const double tail_tiles = (double)tail * tn128;
-            const double tail_cost = (can_split && K >= 1024 && tail_tiles < 448) ? 0.65 * tail_tiles / 512.0 + 0.05
+            const double tail_cost = (can_split && K >= 1024 && tail_tiles <= kSplitBlocks / 2) ? 0.65 * tail_tiles / 512.0 + 0.05
                                                                                  : cost_small(tail_tiles);
             const double cost = cost_large((double)m * tn) + tail_cost + 0.1;
             if (cost < best_cost) {
@@ -206,13 +208,16 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
     // Few tiles against a long contraction (decode-sized batches, or the small tiles behind whole rounds of large
     // ones): too few blocks to fill the GPU, each walking all of K with one tile of loads in flight.  Cut K into
     // slices so that up to two blocks per CU exist, as long as a slice keeps 512 K values and the fp32 partial sums
-    // fit the workspace; a second kernel adds the slices.  Returns false if the launch should be a plain one.
+    // fit the workspace; a second kernel adds the slices.  Never more blocks than the 512 that run at once: those
+    // beyond would be a second round.  Measured, forward GEMM in us with 1 / 2 / 3 slices: 172 tiles of K = 4096
+    // 45 / 38 / 49; 256 tiles of K = 8192 81 / 68 / 82; 320 tiles of K = 5120 59 / 76 / 69; 363 of K = 11008 129 / 143 / 152.
+    // Returns false if the launch should be a plain one.
     auto try_split = [&](int tiles_m, int row_base, int n_rows_here, hipError_t &err) -> bool {
         if (!can_split || forced_tile >= 0) return false;
         const int tiles_n = (cols + 127) / 128;
         const long tiles = (long)tiles_m * tiles_n;
         const long per_slice = (long)tiles_m * 128 * cols * 4;
-        long want = c->gemm_split > 1 ? c->gemm_split : (tiles < 448 ? (448 + tiles - 1) / tiles : 1);
+        long want = c->gemm_split > 1 ? c->gemm_split : kSplitBlocks / std::max(tiles, 1L);
         want = std::min<long>({want, c->gemm_split > 1 ? g.K / 64 : g.K / 512, (long)c->part_bytes / per_slice, 64L});
         if (want < 2) return false;
         GemmArgs gs = g;

@@ -248,7 +248,7 @@ __device__ __forceinline__ void warm_cache(const void *base, uint64_t bytes, int
 // SIBS: sibling projections side by side in the columns; the low-rank extension then loads the rows' operand per
 // batch at the sibling's offset inside each adapter's ranks (see the extension below).
 // SPLITK: the GEMM itself with K cut into gridDim.y slices (few rows against a long contraction: too few tiles to
-// fill the GPU).  A block takes one tile and one slice; slice 0 also runs the tile's extension steps; the fp32
+// fill the GPU).  A block takes one tile, one slice and its share of the tile's extension steps; the fp32
 // sums go to the workspace and gemm_finish_kernel adds the slices, rounds once and scatters the rows.
 // LDS stages of the PARTIAL loop (128x128 tiles: 32 KiB each).  The loop is bound by what a wave has to issue per
 // tile (its direct loads, then its fragment reads and MFMAs, one wave per SIMD), not by the latency of the loads
@@ -371,8 +371,16 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
     }
 
     // extension steps of this row tile; the first batch is fetched now, long before it is needed
-    const int e0 = PARTIAL ? 0 : __builtin_amdgcn_readfirstlane(p.ext_off[tile_m]);
-    const int e1 = PARTIAL ? 0 : ((SPLITK && blockIdx.y != 0) ? e0 : __builtin_amdgcn_readfirstlane(p.ext_off[tile_m + 1]));
+    int e0 = PARTIAL ? 0 : __builtin_amdgcn_readfirstlane(p.ext_off[tile_m]);
+    int e1 = PARTIAL ? 0 : __builtin_amdgcn_readfirstlane(p.ext_off[tile_m + 1]);
+    if constexpr (SPLITK) {
+        // the slices share the tile's batches of extension steps: a decode batch of 64 adapters has more steps in its
+        // one row tile than K tiles, and a slice that ran them all would finish last
+        const int batches = (e1 - e0 + kExtBatch - 1) / kExtBatch, n_sl = (int)gridDim.y, sl = (int)blockIdx.y;
+        const int lo = batches * sl / n_sl, hi = batches * (sl + 1) / n_sl;
+        e1 = e1 < e0 + hi * kExtBatch ? e1 : e0 + hi * kExtBatch;
+        e0 += lo * kExtBatch;
+    }
     // The records of a batch come through the scalar cache (their own counter, so waiting for them
     // does not wait for the direct loads in flight).  Load and wait are one statement: registers
     // that a load is still writing must never be visible to the compiler, which may move or spill

@@ -295,6 +295,18 @@ def test_gemm_with_few_rows_cut_into_k_slices(transposed):
     _run_full(_adhoc("bf16", 8192, 64, [16], [1], [0], [0]), transposed=transposed)   # one token
 
 
+@pytest.mark.parametrize("gemm_split", [2, 5, 64])
+@pytest.mark.parametrize("transposed", [False, True])
+def test_k_slices_share_the_extension_steps(transposed, gemm_split):
+    # 100 rows of 25 adapters in one row tile, ranks on both sides of a group of 64 rank indices and one below 16:
+    # fewer batches of steps than slices, more, and a slice that starts inside the second group
+    rng = np.random.default_rng(4)
+    ranks = list(rng.choice([8, 16, 64, 136], size=24)) + [5]
+    ads = list(rng.integers(0, 25, size=88)) + [-1, 3, 24, 7]
+    w = _adhoc("bf16", 392, 264, ranks, [1] * 88 + [2, 3, 4, 3], ads, [0] * 89 + [1, 1, 1], scale=0.5)
+    _run_full(w, transposed=transposed, gemm_split=gemm_split)
+
+
 @pytest.mark.parametrize("transposed", [False, True])
 def test_rank_wide_passes_as_row_tiles(transposed):
     # Runs of at least 8 rows of an adapter whose rank is a multiple of 8 go through the tiled pass (128-row
