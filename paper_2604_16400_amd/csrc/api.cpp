@@ -857,10 +857,14 @@ int collm_ctx_create(collm_ctx **out, int device, int32_t max_tokens, int32_t ma
         return fail(COLLM_E_NOMEM);
     if (hipMemset(c->d_copy_counter, 0, 64) != hipSuccess) return fail(COLLM_E_HIP);
     if (hipMemset(c->d_zeros, 0, 256) != hipSuccess) return fail(COLLM_E_HIP);
+    // the events order the two streams of this GPU and nothing else: no system-scope cache flush when they are recorded
+    // (the gaps they leave on the caller's stream shrink from 6-7 to 4-5 us; whoever waits for the caller's stream
+    // gets that flush from the wait)
+    constexpr unsigned kOrderOnly = hipEventDisableTiming | hipEventDisableSystemFence;
     if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_dh, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) != hipSuccess)
+        hipEventCreateWithFlags(&c->ev_fork, kOrderOnly) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_dh, kOrderOnly) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_join, kOrderOnly) != hipSuccess)
         return fail(COLLM_E_HIP);
     if (hipDeviceSynchronize() != hipSuccess) return fail(COLLM_E_HIP);
     c->workspace_bytes = ws;
@@ -1208,7 +1212,13 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // The adapter gradients depend on little (dB_a: h and dy; dA_a: dh and x) and are bound by memory
     // latency, as is dh: they run on a second stream beside dh and the dX GEMM, which joins the
     // caller's stream again before the call returns.  (Serial when kernels are being timed.)
-    const bool overlap = dA && !c->profile;
+    // Small batches stay on the caller's stream: the three dependences between the streams cost 15 us on the GPU and
+    // 30 us of host time per call, more than the gradient kernels run one after the other.  Measured, forward +
+    // backward in us, two streams / one: 0.9 MB of training rows of dy and x 89 / 47, 7.3 MB 104 / 83 and 106 / 102,
+    // 15 MB 96 / 104 and 126 / 132; with rank 64 the kernels are longer: 3.7 MB 102 / 107, 15 MB 130 / 166.
+    constexpr int64_t kSerialGradBytes = (int64_t)8 << 20;
+    const bool alone = (int64_t)n_train * (s->d_in + s->d_out) * (f32 ? 4 : 2) <= kSerialGradBytes && (f32 || L.rpad <= 32);
+    const bool overlap = dA && !alone && !c->profile;
     hipStream_t gs = overlap ? c->side : st;
     GradArgs ga{};
     const int64_t esz = f32 ? 4 : 2;
@@ -1308,11 +1318,15 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
             // the small operand as a scaled bf16 copy in training row order (half the bytes of the fp32 one, no
             // conversion in the kernel): left by the recomputing pass, or packed from h_save here.  The forward
             // call's copy of s h (all rows) in the same buffer is dead once that call's GEMM has run.
-            if (h_save)
+            // (small batches skip the packing kernel: their gradient kernel converts as it reads)
+            const bool pack = h_save && !(alone && P == 1);
+            if (pack)
                 HIP_TRY(launch_pack_rows(h_save, c->max_rank, c->max_rank, c->d_plan + L.train.off_row_tok,
                                          L.train.n_rows, s->scale, c->d_hs, L.rpad, gs));
-            ga.small_bf = c->d_hs;
-            ga.ld_small_bf = L.rpad;
+            if (pack || !h_save) {
+                ga.small_bf = c->d_hs;
+                ga.ld_small_bf = L.rpad;
+            }
         }
         ga.out_tab = reinterpret_cast<const uint64_t *>(c->d_plan + L.off_dB_ptr);
         ga.out_transposed = tr ? 1 : 0;
