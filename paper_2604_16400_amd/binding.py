@@ -8,6 +8,7 @@ if the library cannot be loaded, or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import List, Optional, Sequence
 
@@ -15,6 +16,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcollm_lora.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 COLLM_F32 = 0
 COLLM_BF16 = 1
@@ -51,6 +53,7 @@ class collm_adamw(ctypes.Structure):
 
 
 _lib = None
+_marshal = None  # argument marshalling of the compute calls (csrc/marshal.cpp), loaded with the library
 _i32p = ctypes.POINTER(ctypes.c_int32)
 _u8p = ctypes.POINTER(ctypes.c_uint8)
 _vpp = ctypes.POINTER(ctypes.c_void_p)
@@ -58,21 +61,27 @@ _vpp = ctypes.POINTER(ctypes.c_void_p)
 
 def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     """Loads libcollm_lora.so (building it first only if it does not exist)."""
-    global _lib
+    global _lib, _marshal
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    missing = [p for p in (LIB_PATH, MARSHAL_PATH) if not os.path.exists(p)]
+    if missing:
         if not build_if_missing:
-            raise FileNotFoundError(LIB_PATH)
+            raise FileNotFoundError(missing[0])
         from . import build as _build
 
         _build.build()
     try:
         # the HIP runtime PyTorch has loaded must be the one this library binds to
-        import torch  # noqa: F401
+        import torch
     except Exception:  # pragma: no cover - torch is only needed for device memory
-        pass
+        torch = None
     lib = ctypes.CDLL(LIB_PATH)
+    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+    marshal = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(marshal)
+    if torch is not None:
+        marshal.set_types(torch.bfloat16, torch.float32, PointerTable)
     vp, i32, sp = ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(collm_shape)
     lib.collm_ctx_create.argtypes = [_vpp, ctypes.c_int, i32, i32, i32, i32, i32]
     lib.collm_ctx_create.restype = ctypes.c_int
@@ -133,6 +142,7 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.collm_adapter_adamw.argtypes = [ctypes.c_int, ctypes.c_int, vp, vp, vp, vp, vp, ctypes.c_int64,
                                         ctypes.POINTER(collm_adamw), vp]
     lib.collm_adapter_adamw.restype = ctypes.c_int
+    _marshal = marshal
     _lib = lib
     return lib
 
@@ -324,15 +334,18 @@ class Context:
 
     @staticmethod
     def _stream(stream):
-        import torch
-
-        s = torch.cuda.current_stream() if stream is None else stream
-        return ctypes.c_void_p(s.cuda_stream)
+        return ctypes.c_void_p(_stream_number(stream))
 
     def collm_lora_linear_fwd(self, x, W, A: List, B: List, rank, seg_start, seg_adapter, seg_is_train,
                               scale: float, y, h_save=None, stream=None, layout: int = 0):
         """y <- x W + scale (x A_a) B_a per segment; h_save (optional) <- x A_a on training rows.
         layout LAYOUT_OUT_IN: W, A_a, B_a are given transposed ([d_out, d_in], [rank, d_in], [d_out, rank])."""
+        st_n = _stream_number(stream)
+        rc = _marshal.linear_fwd(self._h.value, x, W, A, B, rank, seg_start, seg_adapter, seg_is_train, scale, layout, st_n, y, h_save)
+        if rc is not None:
+            if rc != 0:
+                _check(rc, "collm_lora_linear_fwd")
+            return y
         ss, sa, st = _seg_arrays(seg_start, seg_adapter, seg_is_train)
         rk = np.ascontiguousarray(rank, dtype=np.int32)
         sh = self._shape(x, W, len(sa), len(rk), scale, layout)
@@ -348,6 +361,13 @@ class Context:
                               dB: Optional[List] = None, accumulate: bool = False, stream=None, layout: int = 0):
         """Training rows: dx <- dy W^T + dh A_a^T; dA_a, dB_a (fp32) summed over the adapter's tokens.
         layout LAYOUT_OUT_IN: W, A_a, B_a, dA_a, dB_a are all transposed."""
+        st_n = _stream_number(stream)
+        rc = _marshal.linear_bwd(self._h.value, x, W, A, B, rank, seg_start, seg_adapter, seg_is_train, scale, layout, st_n, dy, h_save,
+                                 dx, dA, dB, 1 if accumulate else 0)
+        if rc is not None:
+            if rc != 0:
+                _check(rc, "collm_lora_linear_bwd")
+            return
         ss, sa, st = _seg_arrays(seg_start, seg_adapter, seg_is_train)
         rk = np.ascontiguousarray(rank, dtype=np.int32)
         sh = self._shape(x, W, len(sa), len(rk), scale, layout)
@@ -443,11 +463,20 @@ def _dtype_of(t):
     raise TypeError("tensor must be bfloat16 or float32")
 
 
-def _stream_handle(stream):
+def _stream_number(stream) -> int:
+    """The stream's handle; None is the current stream of the current device (asked for anew on every call)."""
     import torch
 
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    # (a fifth of the time torch.cuda.current_stream() takes to make a Stream object)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _stream_handle(stream):
+    return ctypes.c_void_p(_stream_number(stream))
 
 
 def collm_swiglu_bwd(seg_start, seg_is_train, pre_act, dout, dy, stream=None):
@@ -466,6 +495,11 @@ def collm_adapter_fedavg(copies: Sequence, dst, stream=None):
     """dst <- mean of the adapter copies (same shape and element type), summed in list order."""
     lib = load_library()
     tab = copies if isinstance(copies, PointerTable) else PointerTable(copies)
+    rc = _marshal.adapter_fedavg(tab, len(tab), dst, _stream_number(stream))
+    if rc is not None:
+        if rc != 0:
+            _check(rc, "collm_adapter_fedavg")
+        return dst
     _check(lib.collm_adapter_fedavg(dst.device.index or 0, _dtype_of(dst), len(tab), tab.array, dst.data_ptr(),
                                     dst.numel(), _stream_handle(stream)), "collm_adapter_fedavg")
     return dst
@@ -475,6 +509,11 @@ def collm_adapter_adamw(param, grad, m, v, lr: float, beta1: float, beta2: float
                         weight_decay: float, step: int, master=None, stream=None):
     """One AdamW step on `param` (and its optional fp32 `master` copy) from the fp32 `grad`."""
     lib = load_library()
+    rc = _marshal.adapter_adamw(param, grad, m, v, lr, beta1, beta2, eps, weight_decay, step, master, _stream_number(stream))
+    if rc is not None:
+        if rc != 0:
+            _check(rc, "collm_adapter_adamw")
+        return param
     hp = collm_adamw(lr, beta1, beta2, eps, weight_decay, int(step))
     _check(lib.collm_adapter_adamw(param.device.index or 0, _dtype_of(param), param.data_ptr(),
                                    None if master is None else master.data_ptr(), grad.data_ptr(), m.data_ptr(),

@@ -4,12 +4,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcollm_lora.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")  # the Python binding's argument marshalling (CPython extension)
 SOURCES = ["api.cpp", "planner.cpp", "kernels_bf16.hip", "kernels_f32.hip", "kernels_adapter.hip"]
 HEADERS = ["plan.h", "planner.h", "kernels.h"]
 
@@ -59,6 +61,13 @@ def build(force: bool = False, verbose: bool = False) -> str:
         tmp = LIB + ".tmp.%d" % os.getpid()
         run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
         os.replace(tmp, LIB)
+    src = os.path.join(CSRC, "marshal.cpp")
+    if force or _stale(MARSHAL, [src, hdrs[-1]]):
+        # (the C ABI it calls is the library's beside it)
+        tmp = MARSHAL + ".tmp.%d" % os.getpid()
+        run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
+             "-I", sysconfig.get_paths()["include"], src, "-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN", "-o", tmp])
+        os.replace(tmp, MARSHAL)
     return LIB
 
 

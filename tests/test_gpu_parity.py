@@ -329,6 +329,35 @@ def test_rank_wide_passes_as_row_tiles(transposed):
     _run_full(w, transposed=transposed, wide_min_rows=0)
 
 
+def test_both_marshalling_routes_give_the_same_call():
+    # pointer tables and plain arrays (compiled marshalling) against lists and other integer types (general path),
+    # on the current stream and on a given one: the same bits
+    import torch
+
+    w = _adhoc("bf16", 128, 192, [16, 8, 24], [40, 1, 1, 90, 33], [0, 1, -1, 2, 1], [1, 0, 0, 1, 0])
+    t = wl.make_tensors(w)
+    ctx = make_ctx(w)
+    a, b = DeviceLayer(w, t, ctx), DeviceLayer(w, t, ctx)
+    a.fwd()
+    a.bwd()
+    torch.cuda.synchronize()
+    tab = binding.PointerTable
+    A, B, dA, dB = tab(b.A), tab(b.B), tab(b.dA), tab(b.dB)
+    batch = (np.asarray(w.ranks, np.int32), np.asarray(w.seg_start, np.int32), np.asarray(w.seg_adapter, np.int32),
+             np.asarray(w.seg_is_train, np.uint8), w.scale)
+    for stream in (None, torch.cuda.Stream()):
+        for o in [b.y, b.dx, b.h_save] + b.dA + b.dB:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        ctx.collm_lora_linear_fwd(b.x, b.W, A, B, *batch, b.y, b.h_save, stream=stream)
+        ctx.collm_lora_linear_bwd(b.x, b.W, A, B, *batch, b.dy, b.h_save, b.dx, dA, dB, stream=stream)
+        torch.cuda.synchronize()
+        for p, q in zip([a.y, a.dx, a.h_save] + a.dA + a.dB, [b.y, b.dx, b.h_save] + b.dA + b.dB):
+            assert np.array_equal(to_host(p), to_host(q), equal_nan=True)
+    check_full(b, TOL["bf16"])
+    ctx.close()
+
+
 def test_two_contexts_on_two_streams_interleaved():
     # Two contexts with different batches, each on a stream of its own, called alternately without waiting in
     # between (forward A, forward B, backward A, backward B, twice): a context's plan, workspace and gradient

@@ -232,3 +232,35 @@ def test_gemm_tile_order_visits_every_tile_once_and_keeps_bands_together():
     assert binding.host_tile_order(256, 32, 32, 28672)[0] == 0
     assert binding.host_tile_order(128, 16, 32, 4096)[0] == 0
 
+
+
+def test_marshalling_takes_the_plain_forms_and_leaves_the_rest():
+    """The compiled marshalling calls the library for contiguous int32 / uint8 arrays and pointer tables (here it reports
+    the missing context) and hands everything else back to the binding's general path."""
+    import torch
+
+    binding.load_library()
+    m = binding._marshal
+    x, W = torch.zeros(3, 8, dtype=torch.bfloat16), torch.zeros(8, 16, dtype=torch.bfloat16)
+    tab = binding.PointerTable([torch.zeros(8), None])
+    rank, ss = np.array([8, 4], np.int32), np.array([0, 1, 3], np.int32)
+    sa, st = np.array([0, -1], np.int32), np.array([1, 0], np.uint8)
+    good = [None, x, W, tab, tab, rank, ss, sa, st, 2.0, 0, 0, W, None]
+    assert m.linear_fwd(*good) == -1                                   # COLLM_E_NULL: no context
+    back = good[:13] + [None, None, tab, tab, 0]
+    assert m.linear_bwd(*back) == -1 and m.linear_bwd(*(back[:15] + [None, None, 1])) == -1
+    for at, other in [(3, [torch.zeros(8), None]), (4, None), (5, [8, 4]), (5, rank.astype(np.int64)), (5, np.array([8, 1, 4, 1], np.int32)[::2]),
+                      (6, ss.astype(">i4")), (6, ss[:2]), (7, sa.reshape(1, 2)), (8, st.astype(bool)), (8, st[:1]), (9, "2"), (10, 1 << 40),
+                      (1, x.half()), (1, x[0]), (2, None), (12, None), (13, 5)]:
+        args = list(good)
+        args[at] = other
+        assert m.linear_fwd(*args) is None, (at, other)
+    with pytest.raises(TypeError):
+        m.linear_fwd(*good[:-1])
+    e = torch.zeros(0)
+    assert m.adapter_adamw(e, e, e, e, 1e-4, 0.9, 0.999, 1e-8, 0.0, 1, None, 0) == 0     # nothing to do
+    assert m.adapter_adamw(e, e, e, e, 1e-4, 0.9, 0.999, 1e-8, 0.0, 0, None, 0) == -2    # COLLM_E_SHAPE: steps count from 1
+    assert m.adapter_adamw(e, e, e, e, 1e-4, 0.9, 0.999, 1e-8, 0.0, 1.5, None, 0) is None
+    assert m.adapter_adamw(e.half(), e, e, e, 1e-4, 0.9, 0.999, 1e-8, 0.0, 1, None, 0) is None
+    copies = binding.PointerTable([x, x])
+    assert m.adapter_fedavg(copies, 0, x, 0) == -2 and m.adapter_fedavg([x, x], 2, x, 0) is None
