@@ -188,6 +188,38 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
     return best;
 }
 
+// Few tiles against a long contraction (decode-sized batches, or the small tiles behind whole rounds of large
+// ones): too few blocks to fill the GPU, each walking all of K with one tile of loads in flight.  K is cut into
+// slices so that up to two blocks per CU exist, as long as a slice keeps 512 K values (256 up to one block per CU, where
+// a block's chain of K tiles is the time) and the fp32 partial sums fit the workspace; a second kernel adds the slices.
+// Never more blocks than the 512 that run at once: those beyond would be a second round.  Measured, forward GEMM in us
+// with 1 / 2 / 3 slices: 172 tiles of K = 4096 45 / 38 / 49; 256 tiles of K = 8192 81 / 68 / 82; 320 tiles of K = 5120
+// 59 / 76 / 69; 363 of K = 11008 129 / 143 / 152.  With at least 512 / 256 K values per slice: 8 tiles of K = 1024 14.0 / 11.9,
+// 64 tiles of K = 1024 19.3 / 17.7 (256 blocks), but 128 tiles of K = 1024 22.7 / 25.1 and 32 of K = 4096 19.0 / 21.1 (512).
+long gemm_slices(const collm_ctx *c, int tiles_m, int cols, int K)
+{
+    const long tiles = std::max((long)tiles_m * ((cols + 127) / 128), 1L);
+    const long per_slice = std::max((long)tiles_m * 128 * cols * 4, 1L);
+    const long want = c->gemm_split > 1 ? std::min<long>(c->gemm_split, K / 64)
+                                        : std::max(std::min<long>(kSplitBlocks / tiles, K / 512), std::min<long>(kSplitBlocks / 2 / tiles, K / 256));
+    return std::min<long>({want, (long)c->part_bytes / per_slice, 64L});
+}
+
+// Whether the rank-wide pass in front of a GEMM should fetch the GEMM's weight into the last-level cache (run_skinny has
+// the conditions on the pass itself).  Not where the GEMM is cut into slices and the weight is large: its 512 blocks
+// keep enough loads in flight to stream the weight from memory at full rate, so the fetch only makes the pass longer
+// (33 MB: 4-5 us, of which the GEMM gives back 1-3).  Measured, whole forward call in us with / without the fetch,
+// 4096 -> 4096: 8 rows 32 / 29, 64 rows 36 / 32, 256 rows 47 / 44, 512 rows level, 1003 rows (one slice) 65 / 71;
+// 1024 -> 1024 (2 MB): 22 / 24 and 26 / 28.
+bool warm_pays(const collm_ctx *c, int rows, int cols, int K)
+{
+    constexpr int64_t kWarmSlicedMaxBytes = (int64_t)8 << 20;
+    if ((int64_t)cols * K * 2 <= kWarmSlicedMaxBytes) return true;
+    const bool can_split = c->gemm_split != 1;
+    const Tiling t = pick_tiling(rows, cols, K, can_split);
+    return !(can_split && t.tile == kTile128x128 && t.tail_tiles_m == 0 && gemm_slices(c, t.big_tiles_m, cols, K) >= 2);
+}
+
 // One GEMM over the row order `R`: a single launch, or whole rounds of large tiles followed by
 // small tiles over the remaining rows.
 hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows, int cols, int forced_tile,
@@ -205,20 +237,11 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
     g.tiles_m = t.big_tiles_m;
     g.ext_off = c->d_plan + R.off_ext_off;
     g.ext = reinterpret_cast<const ExtStep *>(c->d_plan + R.off_ext);
-    // Few tiles against a long contraction (decode-sized batches, or the small tiles behind whole rounds of large
-    // ones): too few blocks to fill the GPU, each walking all of K with one tile of loads in flight.  Cut K into
-    // slices so that up to two blocks per CU exist, as long as a slice keeps 512 K values and the fp32 partial sums
-    // fit the workspace; a second kernel adds the slices.  Never more blocks than the 512 that run at once: those
-    // beyond would be a second round.  Measured, forward GEMM in us with 1 / 2 / 3 slices: 172 tiles of K = 4096
-    // 45 / 38 / 49; 256 tiles of K = 8192 81 / 68 / 82; 320 tiles of K = 5120 59 / 76 / 69; 363 of K = 11008 129 / 143 / 152.
-    // Returns false if the launch should be a plain one.
+    // few tiles against a long contraction: see gemm_slices.  Returns false if the launch should be a plain one.
     auto try_split = [&](int tiles_m, int row_base, int n_rows_here, hipError_t &err) -> bool {
         if (!can_split || forced_tile >= 0) return false;
         const int tiles_n = (cols + 127) / 128;
-        const long tiles = (long)tiles_m * tiles_n;
-        const long per_slice = (long)tiles_m * 128 * cols * 4;
-        long want = c->gemm_split > 1 ? c->gemm_split : kSplitBlocks / std::max(tiles, 1L);
-        want = std::min<long>({want, c->gemm_split > 1 ? g.K / 64 : g.K / 512, (long)c->part_bytes / per_slice, 64L});
+        const long want = gemm_slices(c, tiles_m, cols, g.K);
         if (want < 2) return false;
         GemmArgs gs = g;
         gs.tiles_m = tiles_m;
@@ -1070,7 +1093,8 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // counterpart in the other direction uses
     const bool tr = s->layout == COLLM_LAYOUT_OUT_IN;
     rc = run_skinny(c, s, L.all, x, s->d_in, L.off_A_ptr, tr, h_save, c->max_rank, c->max_rank, 1, 1.0f,
-                    c->d_hs, s->scale, "shrink", st, nullptr, f32 ? nullptr : W, (uint64_t)s->d_in * s->d_out * 2);
+                    c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, s->n_tokens, s->d_out, s->d_in)) ? W : nullptr,
+                    (uint64_t)s->d_in * s->d_out * 2);
     if (rc != COLLM_OK) return rc;
 
     GemmArgs g{};
@@ -1358,7 +1382,8 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         // dh came out of the pass over dy above, together with dB
     } else if (P == 1) {
         rc = run_skinny(c, s, L.train, dy, s->d_out, L.off_B_ptr, !tr, c->d_dh32, L.rpad, L.rpad, 0, s->scale,
-                        c->d_dhs, s->scale, "dh", st, nullptr, (f32 || !dx) ? nullptr : W, (uint64_t)s->d_in * s->d_out * 2);
+                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, n_train, s->d_in, s->d_out) ? W : nullptr,
+                        (uint64_t)s->d_in * s->d_out * 2);
         if (rc != COLLM_OK) return rc;
     } else {
         // one pass per sibling over its columns of dy and of the tables, each writing its columns of dh
