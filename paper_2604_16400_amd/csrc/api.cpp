@@ -133,7 +133,8 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
     // efficient inner loop) and 128x128 (two blocks per CU, four times as many tiles).  The cost of
     // a choice is the time its tiles take over the 256 CUs in units of one full round of 256x256
     // tiles; the constants are read off measurements on 4096- to 13824-wide layers:
-    //  - 256x256: a GPU that is not filled once clocks higher (0.5 + 0.5 x); after whole rounds a last
+    //  - 256x256: a GPU that is not filled once clocks higher, but a tile's start, end and waits for memory stay
+    //    (0.65 + 0.35 x: 64 tiles 0.70, 112 0.75, 144 0.84-0.94, 172 0.89); after whole rounds a last
     //    round that keeps a fraction f of the CUs busy costs 0.6 + 0.7 f, at most 1;
     //  - 128x128: a round of 512 tiles costs 0.65, one that leaves every CU a single block 0.39; from
     //    two rounds on the blocks' different speeds smooth the rounds out (0.62 per round, 0.3 for a
@@ -143,7 +144,7 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
     //    small tiles with K in slices cost their share of a full round plus the kernel that adds the slices.
     auto cost_large = [](double tiles) {
         const double x = tiles / 256.0, whole = std::floor(x), part = x - whole;
-        if (x <= 1.0) return 0.5 + 0.5 * x;
+        if (x <= 1.0) return 0.65 + 0.35 * x;
         return whole + (part == 0.0 ? 0.0 : std::min(1.0, 0.6 + 0.7 * part));
     };
     auto cost_small = [](double tiles) {
@@ -196,12 +197,18 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
 // with 1 / 2 / 3 slices: 172 tiles of K = 4096 45 / 38 / 49; 256 tiles of K = 8192 81 / 68 / 82; 320 tiles of K = 5120
 // 59 / 76 / 69; 363 of K = 11008 129 / 143 / 152.  With at least 512 / 256 K values per slice: 8 tiles of K = 1024 14.0 / 11.9,
 // 64 tiles of K = 1024 19.3 / 17.7 (256 blocks), but 128 tiles of K = 1024 22.7 / 25.1 and 32 of K = 4096 19.0 / 21.1 (512).
-long gemm_slices(const collm_ctx *c, int tiles_m, int cols, int K)
+// Long contractions whose tiles fill one round only partly: three slices make nearly two whole rounds of up to 341 tiles,
+// and a block's start and end no longer count (288 tiles, 1 / 3 slices: K = 8192 86 / 85, 16384 215 / 174, 20480 265 / 214,
+// 28672 368 / 292; 330 tiles of K = 20480 262 / 225, but of K = 12288 123 / 144); 384 tiles gain from two only with W as
+// [K][N] (K = 20480 312 / 307, 28672 436 / 420; [N][K] 303 / 313).
+long gemm_slices(const collm_ctx *c, int tiles_m, int cols, int K, bool b_kmajor)
 {
     const long tiles = std::max((long)tiles_m * ((cols + 127) / 128), 1L);
     const long per_slice = std::max((long)tiles_m * 128 * cols * 4, 1L);
-    const long want = c->gemm_split > 1 ? std::min<long>(c->gemm_split, K / 64)
-                                        : std::max(std::min<long>(kSplitBlocks / tiles, K / 512), std::min<long>(kSplitBlocks / 2 / tiles, K / 256));
+    long want = std::max(std::min<long>(kSplitBlocks / tiles, K / 512), std::min<long>(kSplitBlocks / 2 / tiles, K / 256));
+    if (tiles > kSplitBlocks / 2 && tiles <= 2 * kSplitBlocks / 3 && K >= 16384) want = 3;
+    else if (tiles > kSplitBlocks / 2 && tiles <= 3 * kSplitBlocks / 4 && K >= 20480 && !b_kmajor) want = 2;
+    if (c->gemm_split > 1) want = std::min<long>(c->gemm_split, K / 64);
     return std::min<long>({want, (long)c->part_bytes / per_slice, 64L});
 }
 
@@ -211,13 +218,13 @@ long gemm_slices(const collm_ctx *c, int tiles_m, int cols, int K)
 // (33 MB: 4-5 us, of which the GEMM gives back 1-3).  Measured, whole forward call in us with / without the fetch,
 // 4096 -> 4096: 8 rows 32 / 29, 64 rows 36 / 32, 256 rows 47 / 44, 512 rows level, 1003 rows (one slice) 65 / 71;
 // 1024 -> 1024 (2 MB): 22 / 24 and 26 / 28.
-bool warm_pays(const collm_ctx *c, int rows, int cols, int K)
+bool warm_pays(const collm_ctx *c, int rows, int cols, int K, bool b_kmajor)
 {
     constexpr int64_t kWarmSlicedMaxBytes = (int64_t)8 << 20;
     if ((int64_t)cols * K * 2 <= kWarmSlicedMaxBytes) return true;
     const bool can_split = c->gemm_split != 1;
     const Tiling t = pick_tiling(rows, cols, K, can_split);
-    return !(can_split && t.tile == kTile128x128 && t.tail_tiles_m == 0 && gemm_slices(c, t.big_tiles_m, cols, K) >= 2);
+    return !(can_split && t.tile == kTile128x128 && t.tail_tiles_m == 0 && gemm_slices(c, t.big_tiles_m, cols, K, b_kmajor) >= 2);
 }
 
 // One GEMM over the row order `R`: a single launch, or whole rounds of large tiles followed by
@@ -241,7 +248,7 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
     auto try_split = [&](int tiles_m, int row_base, int n_rows_here, hipError_t &err) -> bool {
         if (!can_split || forced_tile >= 0) return false;
         const int tiles_n = (cols + 127) / 128;
-        const long want = gemm_slices(c, tiles_m, cols, g.K);
+        const long want = gemm_slices(c, tiles_m, cols, g.K, b_kmajor);
         if (want < 2) return false;
         GemmArgs gs = g;
         gs.tiles_m = tiles_m;
@@ -1093,7 +1100,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // counterpart in the other direction uses
     const bool tr = s->layout == COLLM_LAYOUT_OUT_IN;
     rc = run_skinny(c, s, L.all, x, s->d_in, L.off_A_ptr, tr, h_save, c->max_rank, c->max_rank, 1, 1.0f,
-                    c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, s->n_tokens, s->d_out, s->d_in)) ? W : nullptr,
+                    c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, s->n_tokens, s->d_out, s->d_in, tr)) ? W : nullptr,
                     (uint64_t)s->d_in * s->d_out * 2);
     if (rc != COLLM_OK) return rc;
 
@@ -1382,7 +1389,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         // dh came out of the pass over dy above, together with dB
     } else if (P == 1) {
         rc = run_skinny(c, s, L.train, dy, s->d_out, L.off_B_ptr, !tr, c->d_dh32, L.rpad, L.rpad, 0, s->scale,
-                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, n_train, s->d_in, s->d_out) ? W : nullptr,
+                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, n_train, s->d_in, s->d_out, !tr) ? W : nullptr,
                         (uint64_t)s->d_in * s->d_out * 2);
         if (rc != COLLM_OK) return rc;
     } else {

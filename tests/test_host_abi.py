@@ -264,3 +264,14 @@ def test_marshalling_takes_the_plain_forms_and_leaves_the_rest():
     assert m.adapter_adamw(e.half(), e, e, e, 1e-4, 0.9, 0.999, 1e-8, 0.0, 1, None, 0) is None
     copies = binding.PointerTable([x, x])
     assert m.adapter_fedavg(copies, 0, x, 0) == -2 and m.adapter_fedavg([x, x], 2, x, 0) is None
+
+
+@pytest.mark.parametrize("rows,cols,K,tile", [
+    (512, 8448, 4096, binding.TILE_128x128),     # 264 small tiles: one round of them, not 66 large ones on 256 CUs
+    (1024, 4224, 4096, binding.TILE_128x128),
+    (2048, 4096, 4096, binding.TILE_128x128),    # 512: exactly one round
+    (3000, 3000, 3000, binding.TILE_256x256),    # 576 would start a second round
+    (4096, 4096, 4096, binding.TILE_256x256),
+])
+def test_tile_choice_below_one_round(rows, cols, K, tile):
+    assert binding.host_tiling(rows, cols, K)[0] == tile
