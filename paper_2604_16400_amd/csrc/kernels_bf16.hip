@@ -590,8 +590,16 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
                 uint16_t e[8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) e[q] = 0;
+                const uint16_t *src = reinterpret_cast<const uint16_t *>(((uint64_t)thi << 32) | tlo) + (int64_t)(n0 + r) * rk + q0;
+                if ((rk & 3) == 0) {
+                    // (a multiple of 4: two halves of 8 bytes, each inside the rank or beyond it)
+                    uint2 a = make_uint2(0u, 0u), b = make_uint2(0u, 0u);
+                    if (n0 + r < N && q0 < rk) a = *reinterpret_cast<const uint2 *>(src);
+                    if (n0 + r < N && q0 + 4 < rk) b = *reinterpret_cast<const uint2 *>(src + 4);
+                    *reinterpret_cast<uint4 *>(tb + (r8 + i * (NT / 8)) * 128 + c8 * 16) = make_uint4(a.x, a.y, b.x, b.y);
+                    return;
+                }
                 if (n0 + r < N) {
-                    const uint16_t *src = reinterpret_cast<const uint16_t *>(((uint64_t)thi << 32) | tlo) + (int64_t)(n0 + r) * rk + q0;
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
                         if (q0 + q < rk) e[q] = src[q];
@@ -1353,28 +1361,25 @@ __global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyAr
     // N-major table: the chunk [CHK][rank] is contiguous; copy it to LDS rows of PITCH bytes
     constexpr int NCP = T_KMAJOR ? 1 : (CHK * RP * 2 / 16 + 63) / 64;  // 16-byte pieces per lane
     uint4 creg[D][NCP];
-    const bool fast_copy = (rank & 7) == 0;
-    const int cpr = rank >> 3;  // 16-byte pieces per table row
-    // piece c of the chunk is piece c % cpr of row c / cpr; the division is done once
+    // (the chunk starts at a multiple of 32 rows, so its pieces are 16-byte aligned whatever the rank)
+    const int n_pieces = (CHK * rank) >> 3;
+    // piece c holds elements 8 c .. 8 c + 7 of the chunk: first one at row crow, column ccol; the division is done once
     int crow[NCP], ccol[NCP];
     if constexpr (!T_KMAJOR) {
 #pragma unroll
         for (int i = 0; i < NCP; ++i) {
-            const int c = lane + i * 64;
-            crow[i] = fast_copy ? c / cpr : 0;
-            ccol[i] = fast_copy ? c - crow[i] * cpr : 0;
+            const int e = (lane + i * 64) * 8;
+            crow[i] = e / rank;
+            ccol[i] = e - crow[i] * rank;
         }
     }
     auto load_t_nmajor = [&](int k0, int buf) {
         if constexpr (!T_KMAJOR) {
-            // (issued for every rank, out of range where the slow copy below does the work: the number of loads
-            // per chunk must not depend on a branch, or the compiler cannot count how many may still be in flight
-            // and waits for more of them than the chunk it needs)
 #pragma unroll
             for (int i = 0; i < NCP; ++i) {
                 const int c = lane + i * 64;
                 // rows beyond K lie beyond the table and read as zero
-                creg[buf][i] = buf16(rt, (fast_copy && c < CHK * cpr) ? ((uint32_t)k0 * (uint32_t)rank) * 2u + (uint32_t)c * 16u : kOob);
+                creg[buf][i] = buf16(rt, c < n_pieces ? ((uint32_t)k0 * (uint32_t)rank) * 2u + (uint32_t)c * 16u : kOob);
             }
         }
     };
@@ -1383,20 +1388,33 @@ __global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyAr
     // Left to itself the compiler issues the first chunk's loads last in the prologue, and the loop then waits
     // for all loads at the top of every round.
     auto fence_chunk = [] { asm volatile("" ::: "memory"); };
-    auto store_t_nmajor = [&](int k0, int buf) {
+    // A piece goes to one LDS row where the rank is a multiple of 8; else it may reach into the next row (ranks that are
+    // multiples of 4: in halves of 8 bytes) or several (element by element).  901 rows against a [4104][12 .. 64] table:
+    // 33.5 us with the table read element by element for ranks 12 and 20, 10.7 us in pieces.
+    auto store_t_nmajor = [&](int buf) {
         if constexpr (!T_KMAJOR) {
-            if (fast_copy) {
 #pragma unroll
-                for (int i = 0; i < NCP; ++i)
-                    if (lane + i * 64 < CHK * cpr)
-                        *reinterpret_cast<uint4 *>(stage + crow[i] * C::PITCH + ccol[i] * 16) = creg[buf][i];
-            } else {
-                // ranks that are no multiple of 8: element by element
-                const uint16_t *tab = reinterpret_cast<const uint16_t *>(p.tab[it.adapter]);
-                for (int e = lane; e < CHK * rank; e += 64) {
-                    const int r = e / rank, q = e - r * rank;
-                    const int k = k0 + r;
-                    reinterpret_cast<uint16_t *>(stage + r * C::PITCH)[q] = k < K ? tab[(int64_t)k * rank + q] : (uint16_t)0;
+            for (int i = 0; i < NCP; ++i) {
+                if (lane + i * 64 >= n_pieces) continue;
+                const uint4 v = creg[buf][i];
+                uint8_t *dst = stage + crow[i] * C::PITCH;
+                if ((rank & 7) == 0) {
+                    *reinterpret_cast<uint4 *>(dst + ccol[i] * 2) = v;
+                } else if ((rank & 3) == 0) {
+                    *reinterpret_cast<uint2 *>(dst + ccol[i] * 2) = make_uint2(v.x, v.y);
+                    const bool wrap = ccol[i] + 4 >= rank;
+                    *reinterpret_cast<uint2 *>(dst + (wrap ? C::PITCH : (ccol[i] + 4) * 2)) = make_uint2(v.z, v.w);
+                } else {
+                    int col = ccol[i];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const uint32_t w = e < 2 ? v.x : (e < 4 ? v.y : (e < 6 ? v.z : v.w));
+                        *reinterpret_cast<uint16_t *>(dst + col * 2) = (uint16_t)(w >> ((e & 1) * 16));
+                        if (++col == rank) {
+                            col = 0;
+                            dst += C::PITCH;
+                        }
+                    }
                 }
             }
         }
@@ -1420,7 +1438,7 @@ __global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyAr
 #pragma unroll
             for (int d = 0; d < D; ++d) {
                 const int k0 = kb + d * CHK;  // chunks beyond the wave's range were loaded as zeros
-                store_t_nmajor(k0, d);
+                store_t_nmajor(d);
 #pragma unroll
                 for (int s = 0; s < STEPS; ++s) {
 #pragma unroll

@@ -161,6 +161,16 @@ def test_shuffled_segment_order(dtype):
 
 
 @pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("ranks,rows", [([12, 20, 4, 60], 300), ([1, 7, 13, 30], 300), ([12, 5, 16, 20], 4200), ([100, 129, 36, 255], 90)])
+def test_ranks_that_are_no_multiples_of_8(ranks, rows, transposed):
+    # table rows that straddle the 16-byte pieces they are loaded in: halves of 8 bytes (multiples of 4) and single
+    # elements, one and two row tiles per item, every table width; K that ends inside a chunk
+    w = _adhoc("bf16", 168, 136, ranks, [rows // 2, 1, rows // 4, 3, rows // 4], [0, 1, 2, -1, 3], [1, 0, 1, 0, 1], scale=0.5)
+    _run_full(w, transposed=transposed)
+    _run_full(w, transposed=transposed, h_save=False)
+
+
+@pytest.mark.parametrize("transposed", [False, True])
 @pytest.mark.parametrize("d_in,d_out,lens", [
     (4, 4, [1, 2, 1]),                      # one row block, a K below one step of loads
     (68, 132, [17, 47, 65, 3]),             # ragged rows, columns and K; 16-row blocks
