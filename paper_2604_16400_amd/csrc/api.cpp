@@ -642,7 +642,7 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
         a.part = sums->part;
         a.part_rows = sums->part_rows;
         a.part_ld = sums->part_ld;
-        HIP_TRY(launch_skinny_finish(a, R.n_items, R.item_rows, sums->n_slices, st));
+        HIP_TRY(launch_skinny_finish(a, nullptr, 0, 0, R.n_items, R.item_rows / kSkinnyRows, sums->n_slices, st));
         return COLLM_OK;
     }
     Prof prof(c, st, name);
@@ -650,6 +650,7 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
         HIP_TRY(launch_skinny_f32(a, R.n_items, t_kmajor, st));
         return COLLM_OK;
     }
+    int n_wsplit = 1;
     if (R.n_wide > 0) {
         // Long runs: 128-row tiles through the GEMM machinery.  A block fills a CU (four LDS stages), so K is cut
         // so that at most one block per CU exists, as long as a slice keeps 512 K values and the partial sums fit
@@ -680,14 +681,14 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
                                   (long)kSkinnyMaxSplit});
         ns = std::max<long>(ns, 1);
         g.k_per_split = round_up((int)((K + ns - 1) / ns), 64);
-        const int n_wsplit = (K + g.k_per_split - 1) / g.k_per_split;
+        n_wsplit = (K + g.k_per_split - 1) / g.k_per_split;
         HIP_TRY(launch_wide(g, R.n_wide, rpad, n_wsplit, t_kmajor, st));
-        SkinnyArgs w = a;
-        w.items = g.items;
-        HIP_TRY(launch_skinny_finish(w, R.n_wide, kWideRows, n_wsplit, st));
     }
     if (R.n_items > 0)
         HIP_TRY(launch_skinny(a, R.n_items, rpad, R.item_rows / kSkinnyRows, n_split, t_kmajor, st));
+    // (the sums of the two kinds of items lie in different rows of the workspace)
+    HIP_TRY(launch_skinny_finish(a, reinterpret_cast<const SkinnyItem *>(c->d_plan + R.off_wide), R.n_wide, n_wsplit,
+                                 n_split > 1 ? R.n_items : 0, R.item_rows / kSkinnyRows, n_split, st));
     return COLLM_OK;
 }
 

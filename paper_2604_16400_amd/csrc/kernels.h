@@ -188,7 +188,10 @@ hipError_t launch_gemm_swiglu(const GemmArgs &a, int tile_cfg, hipStream_t st);
 // a, lda, K, a_bytes, row_tok and the fields of the rank-wide pass; everything else is ignored.  Items hold up
 // to kWideRows rows; ranks must be multiples of 8.  The caller adds the slices with launch_skinny_finish.
 hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st);
-hipError_t launch_skinny_finish(const SkinnyArgs &a, int n_items, int item_rows, int n_split, hipStream_t st);
+// adds the K slices of n_wide tiled items (`wide`, wide_split slices) and of n_items others (a.items, row_tiles = 1 or 2 groups
+// of 16 rows each, n_split slices) and does the pass's stores
+hipError_t launch_skinny_finish(const SkinnyArgs &a, const SkinnyItem *wide, int n_wide, int wide_split, int n_items, int row_tiles, int n_split,
+                                hipStream_t st);
 int gemm_tile_rows(int tile_cfg);
 int gemm_tile_cols(int tile_cfg);
 // items hold up to 16 * row_tiles rows (row_tiles <= skinny_max_row_tiles(rpad)); n_split slices of K

@@ -1499,34 +1499,54 @@ __global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyAr
     }
 }
 
-// Sum of n values that lie `stride` floats apart, added in index order; four loads are in flight at a time
+// Sum of n values that lie `stride` floats apart, added in index order; eight loads are in flight at a time, then four
 // (the kernels that add K slices are bound by the latency of these loads, not by their bytes).
+template <int COUNT>
+__device__ __forceinline__ floatx4 add_slices(floatx4 sum, const float *first, int64_t stride)
+{
+    floatx4 v[COUNT];
+#pragma unroll
+    for (int j = 0; j < COUNT; ++j) v[j] = *reinterpret_cast<const floatx4 *>(first + j * stride);
+#pragma unroll
+    for (int j = 0; j < COUNT; ++j) sum += v[j];
+    return sum;
+}
+
 __device__ __forceinline__ floatx4 sum_slices(const float *first, int64_t stride, int n)
 {
     floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
     int i = 0;
-    for (; i + 4 <= n; i += 4) {
-        const floatx4 v0 = *reinterpret_cast<const floatx4 *>(first + (i + 0) * stride);
-        const floatx4 v1 = *reinterpret_cast<const floatx4 *>(first + (i + 1) * stride);
-        const floatx4 v2 = *reinterpret_cast<const floatx4 *>(first + (i + 2) * stride);
-        const floatx4 v3 = *reinterpret_cast<const floatx4 *>(first + (i + 3) * stride);
-        sum += v0;
-        sum += v1;
-        sum += v2;
-        sum += v3;
+    for (; i + 8 <= n; i += 8) sum = add_slices<8>(sum, first + i * stride, stride);
+    if (i + 4 <= n) {
+        sum = add_slices<4>(sum, first + i * stride, stride);
+        i += 4;
     }
     for (; i < n; ++i) sum += *reinterpret_cast<const floatx4 *>(first + i * stride);
     return sum;
 }
 
-// adds the K slices of every item in slice order and writes the results; block (i, j) takes rows
-// 16 j .. 16 j + 15 of item i
-__global__ void __launch_bounds__(256) skinny_finish_kernel(SkinnyArgs p, int n_split)
+// adds the K slices of every item in slice order and writes the results.  Bound by its launch and a chain of dependent
+// loads (item -> slices -> token), not by bytes, so one launch serves both kinds of items of a pass (1367 rows of
+// 11008 values, 20 and 8 slices: 6.2 + 5.0 us as two launches with four slices in flight, 5.1 us as one with eight; the
+// forward and backward calls over two such batches 692 -> 664 us).  Blocks are groups of 16 rows: those of the tiled
+// items first, kWideRows / 16 an item, then those of the others, 1 << log_rt an item.
+__global__ void __launch_bounds__(256) skinny_finish_kernel(SkinnyArgs p, const SkinnyItem *wide, int n_wide, int wide_split, int log_rt, int n_split)
 {
-    const SkinnyItem it = p.items[blockIdx.x];
+    constexpr int kWideTiles = kWideRows / 16;
+    int b = (int)blockIdx.x, tile;
+    SkinnyItem it;
+    if (b < n_wide * kWideTiles) {
+        it = wide[b / kWideTiles];
+        tile = b % kWideTiles;
+        n_split = wide_split;
+    } else {
+        b -= n_wide * kWideTiles;
+        it = p.items[b >> log_rt];
+        tile = b & ((1 << log_rt) - 1);
+    }
     const int rp = ((p.n_sib > 1 ? it.rank / p.n_sib : it.rank) + 15) & ~15;
     const int nq = rp >> 2;
-    const int m_lo = blockIdx.y * 16, m_hi = it.n_rows < m_lo + 16 ? it.n_rows : m_lo + 16;
+    const int m_lo = tile * 16, m_hi = it.n_rows < m_lo + 16 ? it.n_rows : m_lo + 16;
     for (int idx = threadIdx.x; idx < (m_hi - m_lo) * nq; idx += 256) {
         const int m = m_lo + idx / nq, q = (idx % nq) * 4;
         const floatx4 sum = sum_slices(p.part + (int64_t)(it.row_lo + m) * p.part_ld + q, (int64_t)p.part_rows * p.part_ld, n_split);
@@ -2054,10 +2074,13 @@ hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bo
     return t_kmajor ? launch(gemm_lora_kernel<128, 128, 4, 2, true, true>) : launch(gemm_lora_kernel<128, 128, 4, 2, false, true>);
 }
 
-hipError_t launch_skinny_finish(const SkinnyArgs &a, int n_items, int item_rows, int n_split, hipStream_t st)
+hipError_t launch_skinny_finish(const SkinnyArgs &a, const SkinnyItem *wide, int n_wide, int wide_split, int n_items, int row_tiles, int n_split,
+                                hipStream_t st)
 {
-    if (n_items <= 0) return hipSuccess;
-    COLLM_LAUNCH(skinny_finish_kernel, dim3(n_items, (item_rows + 15) / 16), dim3(256), 0, st, a, n_split);
+    const int blocks = n_wide * (kWideRows / 16) + n_items * row_tiles;
+    if (blocks <= 0) return hipSuccess;
+    if (!a.part || row_tiles < 1 || row_tiles > 2) return hipErrorInvalidValue;
+    COLLM_LAUNCH(skinny_finish_kernel, dim3(blocks), dim3(256), 0, st, a, wide, n_wide, wide_split, row_tiles - 1, n_split);
     return hipGetLastError();
 }
 
@@ -2137,7 +2160,6 @@ static hipError_t launch_skinny_t(const SkinnyArgs &a, int n_items, int n_split,
     b.n_items = n_items;
     if (!b.warm_base || b.warm_bytes < 16) b.warm_blocks = 0;
     COLLM_LAUNCH(kern, dim3(n_items + b.warm_blocks, n_split), dim3(C::KW * 64), smem, st, b);
-    if (n_split > 1) COLLM_LAUNCH(skinny_finish_kernel, dim3(n_items, RT), dim3(256), 0, st, a, n_split);
     return hipGetLastError();
 }
 

@@ -339,6 +339,16 @@ def test_rank_wide_passes_as_row_tiles(transposed):
     _run_full(w, transposed=transposed, wide_min_rows=0)
 
 
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("rows", [150, 2100])
+def test_one_finish_for_tiled_and_row_items(rows, transposed):
+    # both kinds of items in one pass, each with its contraction in slices (different numbers of them), in both
+    # directions: whole and partial tiles of 128 rows beside items of 1 to 32 rows, and base rows between them
+    for d_in, d_out in ((8200, 72), (72, 8200)):
+        w = _adhoc("bf16", d_in, d_out, [64, 12, 128], [rows, 40, 1, 3, 17, 40], [0, 1, 1, -1, 2, 0], [1, 1, 0, 0, 1, 0], scale=0.5)
+        _run_full(w, transposed=transposed, h_save=rows == 150)
+
+
 def test_both_marshalling_routes_give_the_same_call():
     # pointer tables and plain arrays (compiled marshalling) against lists and other integer types (general path),
     # on the current stream and on a given one: the same bits
