@@ -1393,26 +1393,34 @@ __global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyAr
     // 33.5 us with the table read element by element for ranks 12 and 20, 10.7 us in pieces.
     auto store_t_nmajor = [&](int buf) {
         if constexpr (!T_KMAJOR) {
+            // (the addresses of the other ranks' halves and elements are worked out anew for every chunk: hoisted out of the
+            // loop they take a hundred registers, and one wave per SIMD instead of two; rank 48, 16384 rows: 124 / 117 us)
+            if ((rank & 7) == 0) {
 #pragma unroll
-            for (int i = 0; i < NCP; ++i) {
-                if (lane + i * 64 >= n_pieces) continue;
-                const uint4 v = creg[buf][i];
-                uint8_t *dst = stage + crow[i] * C::PITCH;
-                if ((rank & 7) == 0) {
-                    *reinterpret_cast<uint4 *>(dst + ccol[i] * 2) = v;
-                } else if ((rank & 3) == 0) {
-                    *reinterpret_cast<uint2 *>(dst + ccol[i] * 2) = make_uint2(v.x, v.y);
-                    const bool wrap = ccol[i] + 4 >= rank;
-                    *reinterpret_cast<uint2 *>(dst + (wrap ? C::PITCH : (ccol[i] + 4) * 2)) = make_uint2(v.z, v.w);
-                } else {
-                    int col = ccol[i];
+                for (int i = 0; i < NCP; ++i)
+                    if (lane + i * 64 < n_pieces)
+                        *reinterpret_cast<uint4 *>(stage + crow[i] * C::PITCH + ccol[i] * 2) = creg[buf][i];
+            } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const uint32_t w = e < 2 ? v.x : (e < 4 ? v.y : (e < 6 ? v.z : v.w));
-                        *reinterpret_cast<uint16_t *>(dst + col * 2) = (uint16_t)(w >> ((e & 1) * 16));
-                        if (++col == rank) {
-                            col = 0;
-                            dst += C::PITCH;
+                for (int i = 0; i < NCP; ++i) {
+                    if (lane + i * 64 >= n_pieces) continue;
+                    const uint4 v = creg[buf][i];
+                    int row = crow[i], col = ccol[i];
+                    asm volatile("" : "+v"(row), "+v"(col));
+                    uint8_t *dst = stage + row * C::PITCH;
+                    if ((rank & 3) == 0) {
+                        *reinterpret_cast<uint2 *>(dst + col * 2) = make_uint2(v.x, v.y);
+                        const bool wrap = col + 4 >= rank;
+                        *reinterpret_cast<uint2 *>(dst + (wrap ? C::PITCH : (col + 4) * 2)) = make_uint2(v.z, v.w);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const uint32_t w = e < 2 ? v.x : (e < 4 ? v.y : (e < 6 ? v.z : v.w));
+                            *reinterpret_cast<uint16_t *>(dst + col * 2) = (uint16_t)(w >> ((e & 1) * 16));
+                            if (++col == rank) {
+                                col = 0;
+                                dst += C::PITCH;
+                            }
                         }
                     }
                 }
