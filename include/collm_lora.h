@@ -271,6 +271,13 @@ int collm_debug_host_tiling(int rows, int cols, int K, int can_split, int32_t *t
                             int32_t *tail_tiles_m, int32_t *tail_cols);
 
 /*
+ * Debug, HOST only (no GPU): into how many slices the library would cut the contraction length K of a GEMM of
+ * tiles_m row tiles of 128 rows by `cols` columns in 128x128 tiles, with workspace_bytes for the partial sums
+ * (1: not cut).  b_kmajor: second operand as [cols][K].
+ */
+int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int64_t workspace_bytes, int32_t *slices);
+
+/*
  * Debug, HOST only (no GPU): the order in which the workgroups of a GEMM launch of tiles_m x tiles_n tiles take
  * the tiles.  Workgroup ids go round-robin to the GPU's 8 XCDs (each with an L2 of its own); every XCD gets a
  * contiguous run of an order that walks groups of 8 row tiles column by column, and the grid is walked in bands

@@ -114,6 +114,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.collm_debug_device_token_map.restype = ctypes.c_int
     lib.collm_debug_host_tiling.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _i32p, _i32p, _i32p,
                                             _i32p]
+    lib.collm_debug_host_gemm_slices.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64, _i32p]
+    lib.collm_debug_host_gemm_slices.restype = ctypes.c_int
     lib.collm_debug_host_tiling.restype = ctypes.c_int
     lib.collm_debug_host_tile_order.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _i32p,
                                                 _i32p, _i32p]
@@ -189,6 +191,15 @@ def host_tiling(rows: int, cols: int, K: int, can_split: bool = True):
     _check(lib.collm_debug_host_tiling(rows, cols, K, 1 if can_split else 0, *[ctypes.byref(o) for o in out]),
            "collm_debug_host_tiling")
     return tuple(o.value for o in out)
+
+
+def host_gemm_slices(tiles_m: int, cols: int, K: int, b_kmajor: bool = False, workspace_bytes: int = 64 << 20) -> int:
+    """Slices of K the library would cut a GEMM of tiles_m x ceil(cols / 128) tiles of 128x128 into (host logic, no GPU)."""
+    lib = load_library()
+    n = ctypes.c_int32(-9)
+    _check(lib.collm_debug_host_gemm_slices(tiles_m, cols, K, 1 if b_kmajor else 0, workspace_bytes, ctypes.byref(n)),
+           "collm_debug_host_gemm_slices")
+    return n.value
 
 
 def host_tile_order(tile_rows: int, tiles_m: int, tiles_n: int, K: int, band: int = -1):

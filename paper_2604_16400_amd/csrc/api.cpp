@@ -191,25 +191,47 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
 
 // Few tiles against a long contraction (decode-sized batches, or the small tiles behind whole rounds of large
 // ones): too few blocks to fill the GPU, each walking all of K with one tile of loads in flight.  K is cut into
-// slices so that up to two blocks per CU exist, as long as a slice keeps 512 K values (256 up to one block per CU, where
+// slices so that up to two blocks per CU exist, as long as a slice keeps 512 K values (320 up to one block per CU, where
 // a block's chain of K tiles is the time) and the fp32 partial sums fit the workspace; a second kernel adds the slices.
-// Never more blocks than the 512 that run at once: those beyond would be a second round.  Measured, forward GEMM in us
-// with 1 / 2 / 3 slices: 172 tiles of K = 4096 45 / 38 / 49; 256 tiles of K = 8192 81 / 68 / 82; 320 tiles of K = 5120
-// 59 / 76 / 69; 363 of K = 11008 129 / 143 / 152.  With at least 512 / 256 K values per slice: 8 tiles of K = 1024 14.0 / 11.9,
-// 64 tiles of K = 1024 19.3 / 17.7 (256 blocks), but 128 tiles of K = 1024 22.7 / 25.1 and 32 of K = 4096 19.0 / 21.1 (512).
+// Up to 256 tiles never more blocks than the 512 that run at once: those beyond would be a second round.  Measured, forward
+// GEMM in us with 1 / 2 / 3 slices: 172 tiles of K = 4096 45 / 38 / 49; 256 tiles of K = 8192 81 / 68 / 82; 320 tiles of
+// K = 5120 59 / 76 / 69.
+// Whole forward call in us, weights cold, by the fewest values of a slice 512 / 320 / 256 (slices): 8 tiles of K = 1024 20.6 /
+// 19.0 / 18.5 (2, 3, 4), 64 tiles 24.8 / 24.8 / 26.6; 32 tiles of K = 2048 25.9 / 25.0 / 26.9 (4, 6, 8); 16 tiles of K = 3072 26.7 /
+// 26.4 / 27.5 (6, 9, 12).  Below K = 1024 one slice: K = 512 and 4 / 32 / 128 tiles 14.8 / 15.2 / 15.4, with two 17.2 / 18.8 / 26.0.
+// Exactly 512 blocks in eight slices or more are slower than one slice less, up to K = 16384: 64 tiles of K = 4096 41.1 / 38.4,
+// 32 of K = 8192 46.9 / 44.0, 16 of K = 16384 47.1 / 45.1; but 64 of K = 28672 129 / 140.
 // Long contractions whose tiles fill one round only partly: three slices make nearly two whole rounds of up to 341 tiles,
-// and a block's start and end no longer count (288 tiles, 1 / 3 slices: K = 8192 86 / 85, 16384 215 / 174, 20480 265 / 214,
-// 28672 368 / 292; 330 tiles of K = 20480 262 / 225, but of K = 12288 123 / 144); 384 tiles gain from two only with W as
-// [K][N] (K = 20480 312 / 307, 28672 436 / 420; [N][K] 303 / 313).
-long gemm_slices(const collm_ctx *c, int tiles_m, int cols, int K, bool b_kmajor)
+// and a block's start and end no longer count.  With a power of two of row tiles one slice is slower for the same number of
+// tiles, and slices pay earlier.  Whole forward call, 1 / 2 / 3 slices (row x column tiles): 8x36 of K = 8192 121 / 148 /
+// 119, 11008 160 / 197 / 157, 14336 198 / 236 / 181; 4x84 of K = 14336 269 / 244 / 218; the GEMM alone, 3x110 of K = 14336
+// 196 / 232 / 196, 16384 223 / 260 / 222, 28672 382 / 451 / 361; 2x129 of K = 14336 184 / 231 / 192.  Beyond, two slices: 8x44 tiles of K = 8192
+// 161 / 153 and 148 / 155 ([N][K]), 14336 266 / 240 and 265 / 252; 4x86 of K = 20480 362 / 321 and 372 / 340, but 4x88 385 / 384
+// and 372 / 399; not with other numbers of row tiles (6x64 of K = 20480 280 / 318, 3x115 304 / 373) or more tiles (8x48 367 / 377).
+long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, bool b_kmajor)
 {
     const long tiles = std::max((long)tiles_m * ((cols + 127) / 128), 1L);
-    const long per_slice = std::max((long)tiles_m * 128 * cols * 4, 1L);
-    long want = std::max(std::min<long>(kSplitBlocks / tiles, K / 512), std::min<long>(kSplitBlocks / 2 / tiles, K / 256));
-    if (tiles > kSplitBlocks / 2 && tiles <= 2 * kSplitBlocks / 3 && K >= 16384) want = 3;
-    else if (tiles > kSplitBlocks / 2 && tiles <= 3 * kSplitBlocks / 4 && K >= 20480 && !b_kmajor) want = 2;
-    if (c->gemm_split > 1) want = std::min<long>(c->gemm_split, K / 64);
-    return std::min<long>({want, (long)c->part_bytes / per_slice, 64L});
+    const long fit = (long)(part_bytes / std::max((int64_t)tiles_m * 128 * cols * 4, (int64_t)1));
+    if (forced > 1) return std::min<long>({forced, K / 64, fit, 64L});
+    if (tiles > kSplitBlocks / 2) {
+        const bool pow2 = tiles_m > 1 && (tiles_m & (tiles_m - 1)) == 0;
+        long want = 1;
+        if (tiles <= 2 * kSplitBlocks / 3) {
+            if (K >= (pow2 && tiles >= 264 ? 11264 : 16384)) want = 3;
+        } else if (pow2 && tiles <= 360) {
+            if (tiles_m >= 8 ? K >= 11264 : (K >= 20480 && !b_kmajor)) want = 2;
+        }
+        return want <= fit ? want : 1;  // (all of them or none: fewer slices would be another round)
+    }
+    long blocks_slices = kSplitBlocks / tiles;
+    if (blocks_slices >= 8 && blocks_slices * tiles == kSplitBlocks && K <= 16384) --blocks_slices;
+    long want = std::min<long>(blocks_slices, K / 512);
+    if (K >= 1024) want = std::max(want, std::min<long>(kSplitBlocks / 2 / tiles, K / 320));
+    return std::min<long>({want, fit, 64L});
+}
+long gemm_slices(const collm_ctx *c, int tiles_m, int cols, int K, bool b_kmajor)
+{
+    return gemm_slices(c->gemm_split, (int64_t)c->part_bytes, tiles_m, cols, K, b_kmajor);
 }
 
 // Whether the rank-wide pass in front of a GEMM should fetch the GEMM's weight into the last-level cache (run_skinny has
@@ -951,6 +973,14 @@ int collm_debug_host_tiling(int rows, int cols, int K, int can_split, int32_t *t
     *big_tiles_m = t.big_tiles_m;
     *tail_tiles_m = t.tail_tiles_m;
     *tail_cols = t.tail_cols;
+    return COLLM_OK;
+}
+
+int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int64_t workspace_bytes, int32_t *slices)
+{
+    if (!slices) return COLLM_E_NULL;
+    if (tiles_m <= 0 || cols <= 0 || K <= 0 || workspace_bytes < 0) return COLLM_E_SHAPE;
+    *slices = (int32_t)std::max(1L, gemm_slices(-1, workspace_bytes, tiles_m, cols, K, b_kmajor != 0));
     return COLLM_OK;
 }
 

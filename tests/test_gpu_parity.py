@@ -305,6 +305,40 @@ def test_gemm_with_few_rows_cut_into_k_slices(transposed):
     _run_full(_adhoc("bf16", 8192, 64, [16], [1], [0], [0]), transposed=transposed)   # one token
 
 
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("rows,K,cols,slices", [
+    (500, 11264, 66 * 128 - 8, 3),      # 4 x 66 tiles, the last of each ragged
+    (300, 16384, 96 * 128 - 40, 3),     # 3 x 96
+    (1000, 11264, 43 * 128 - 16, 2),    # 8 x 43
+    (20, 1024, 8 * 128 - 24, 3),        # 1 x 8, slices of 384, 384 and 256 values
+])
+def test_gemm_slices_chosen_by_the_library(rows, K, cols, slices, transposed):
+    # the long contractions are too much work for the oracle: plain fp32 products of the same bf16 operands on the GPU,
+    # with s h rounded to bf16 as the layer keeps it.  Bound: one bf16 rounding of y and of s h (2^-8 of the value each)
+    import torch
+
+    assert binding.host_gemm_slices((rows + 127) // 128, cols, K, transposed) == slices
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + K)
+    rnd = lambda a, b, std: torch.randn((a, b), generator=gen, device="cuda").mul_(std).to(torch.bfloat16)
+    ranks, lens, ads = [16, 40], [rows // 3, 1, rows - rows // 3 - 8, 7], [0, 1, -1, 1]
+    x, W = rnd(rows, K, 1.0), rnd(K, cols, 0.02)
+    A, B = [rnd(K, r, K ** -0.5) for r in ranks], [rnd(r, cols, 0.1) for r in ranks]
+    tp = (lambda t: t.t().contiguous()) if transposed else (lambda t: t)
+    y = torch.full((rows, cols), float("nan"), dtype=torch.bfloat16, device="cuda")
+    start = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ctx = binding.Context(rows, len(lens), len(ranks), max(ranks), max(K, cols))
+    ctx.collm_lora_linear_fwd(x, tp(W), [tp(a) for a in A], [tp(b) for b in B], ranks, start, ads, [0] * 4, 2.0, y,
+                              layout=1 if transposed else 0)
+    ref = x.float() @ W.float()
+    for k, a in enumerate(ads):
+        if a >= 0:
+            r = slice(start[k], start[k + 1])
+            ref[r] += (2.0 * (x[r].float() @ A[a].float())).to(torch.bfloat16).float() @ B[a].float()
+    assert maxrel(to_host(y), to_host(ref)) <= 2 * 2.0 ** -8
+    ctx.close()
+
+
 @pytest.mark.parametrize("gemm_split", [2, 5, 64])
 @pytest.mark.parametrize("transposed", [False, True])
 def test_k_slices_share_the_extension_steps(transposed, gemm_split):

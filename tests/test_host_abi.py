@@ -275,3 +275,26 @@ def test_marshalling_takes_the_plain_forms_and_leaves_the_rest():
 ])
 def test_tile_choice_below_one_round(rows, cols, K, tile):
     assert binding.host_tiling(rows, cols, K)[0] == tile
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n,K,want", [
+    (1, 4, 512, 1), (8, 16, 768, 1), (1, 4, 1016, 1), (1, 8, 1024, 3), (8, 8, 1024, 3), (8, 12, 1024, 2),   # from K = 1024 on
+    (1, 16, 3072, 9), (1, 32, 2048, 6), (2, 100, 4096, 2), (16, 16, 8192, 2),
+    (1, 64, 4096, 7), (1, 32, 8192, 15), (1, 64, 16384, 7), (1, 64, 28672, 8), (8, 16, 8192, 4),            # exactly 512 blocks
+    (1, 257, 16376, 1), (1, 257, 16384, 3), (11, 31, 16384, 3), (11, 31, 16376, 1), (18, 19, 16384, 1),     # 257, 341, 342 tiles
+    (4, 66, 11264, 3), (4, 66, 11256, 1), (2, 129, 11264, 1), (3, 96, 11264, 1), (8, 43, 11264, 2), (8, 43, 11256, 1),
+    (8, 45, 28672, 2), (19, 19, 28672, 1), (6, 64, 28672, 1), (3, 115, 28672, 1), (5, 77, 28672, 1), (16, 32, 28672, 1)])
+def test_gemm_slices_at_the_lines_of_the_rule(tiles_m, tiles_n, K, want):
+    assert binding.host_gemm_slices(tiles_m, tiles_n * 128, K) == want
+    assert binding.host_gemm_slices(tiles_m, tiles_n * 128 - 120, K, True) == want  # (the same tiles, the last one ragged)
+
+
+def test_gemm_slices_by_layout_and_workspace():
+    for K, in_out, out_in in [(20472, 1, 1), (20480, 2, 1), (28672, 2, 1)]:
+        assert (binding.host_gemm_slices(4, 86 * 128, K), binding.host_gemm_slices(4, 86 * 128, K, True)) == (in_out, out_in)
+    # 341 tiles in three slices just fit 64 MiB; a workspace for two of the three leaves the contraction whole, one for
+    # four of seven slices leaves four
+    assert binding.host_gemm_slices(11, 31 * 128, 16384, workspace_bytes=3 * 341 * 65536) == 3
+    assert binding.host_gemm_slices(11, 31 * 128, 16384, workspace_bytes=3 * 341 * 65536 - 1) == 1
+    assert binding.host_gemm_slices(1, 64 * 128, 4096, workspace_bytes=4 * 64 * 65536) == 4
+    assert binding.host_gemm_slices(1, 64 * 128, 4096, workspace_bytes=0) == 1
