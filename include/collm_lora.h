@@ -278,6 +278,12 @@ int collm_debug_host_tiling(int rows, int cols, int K, int can_split, int32_t *t
 int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int64_t workspace_bytes, int32_t *slices);
 
 /*
+ * Debug, HOST only (no GPU): bytes of LDS a block of the bf16 adapter-gradient kernel asks for at this (largest) rank, alone
+ * or where the dX GEMM may start beside it on another stream.
+ */
+int collm_debug_host_grad_lds(int rank, int beside_gemm, int32_t *bytes);
+
+/*
  * Debug, HOST only (no GPU): the order in which the workgroups of a GEMM launch of tiles_m x tiles_n tiles take
  * the tiles.  Workgroup ids go round-robin to the GPU's 8 XCDs (each with an L2 of its own); every XCD gets a
  * contiguous run of an order that walks groups of 8 row tiles column by column, and the grid is walked in bands

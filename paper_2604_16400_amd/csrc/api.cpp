@@ -984,6 +984,14 @@ int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int
     return COLLM_OK;
 }
 
+int collm_debug_host_grad_lds(int rank, int beside_gemm, int32_t *bytes)
+{
+    if (!bytes) return COLLM_E_NULL;
+    if (rank < 1 || rank > kMaxRank) return COLLM_E_RANK;
+    *bytes = grad_lds(round_up(rank, kKStep), beside_gemm != 0);
+    return COLLM_OK;
+}
+
 int collm_debug_host_row_order(const collm_shape *s, const int32_t *rank, const int32_t *seg_start,
                                const int32_t *seg_adapter, const uint8_t *seg_is_train, int tile_rows,
                                int training_rows_only, int32_t *row_tok, int32_t *tile_steps)
@@ -1287,6 +1295,10 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     ga.row_tok = c->d_plan + L.train.off_row_tok;
     ga.items = reinterpret_cast<const GradItem *>(c->d_plan + L.off_grad);
     ga.accumulate = accumulate ? 1 : 0;
+    if (overlap && dx && !f32) {
+        const int tile = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, c->gemm_split != 1).tile;
+        ga.beside_gemm = tile == kTile128x128 ? 1 : 0;
+    }
 
     // Narrow ranks (all at most 16), tables as [rank][d_out]: dh and dB_a both come from ONE pass over the training
     // rows of dy (kernels.h, DualArgs), which is the largest operand of the backward pass beside W.  The rows of

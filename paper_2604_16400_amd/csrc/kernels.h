@@ -133,6 +133,7 @@ struct GradArgs {
     const uint64_t *out_tab;  // adapter -> fp32 output
     int out_transposed;       // 0: out[q][n] (row length N); 1: out[n][q] (row length rank)
     int accumulate;
+    int beside_gemm;          // launch_grad: a GEMM of 128x128 tiles may start on another stream while this runs (see grad_lds)
     // one of n_sib sibling projections (bf16 copy of the small operand, out_transposed = 0 only): the items'
     // ranks are n_sib times the adapter's, the small operand is columns sib * rank .. of the copy, and the
     // result goes to out[q][out_off + n] with row length ld_out.  n_sib 0 or 1: none of this.
@@ -202,6 +203,8 @@ int skinny_waves(int rpad);  // waves of a block, which split the block's K slic
 int skinny_chunk(int rpad);  // K values a wave fetches at a time
 int skinny_depth(int rpad, int row_tiles);  // chunks a wave keeps in flight
 hipError_t launch_grad(const GradArgs &a, int n_grad, int rpad, hipStream_t st);
+int grad_lds(int rpad, bool beside_gemm);  // bytes of LDS a block of launch_grad asks for
+constexpr int kSmallTileLds = 2 * (128 + 128) * 128;  // bytes of LDS of a 128x128 GEMM block (two stages); two such blocks run on a CU
 // dst[t][q] = bf16(mult * src[row_tok[t]][q]) for n_rows rows and ld_dst (multiple of 8) columns; columns from
 // src_cols on are zero
 hipError_t launch_pack_rows(const float *src, int64_t ld_src, int src_cols, const int32_t *row_tok, int n_rows,

@@ -2015,6 +2015,7 @@ static hipError_t launch_gemm_t(const GemmArgs &a, hipStream_t st)
     constexpr int stage_bytes = 2 * (BM + BN) * 128 + ((!SIBS && BM * BN == 256 * 256) ? BM * 128 : 0);
     constexpr int epi_bytes = BM * BN * 2 + BM * 2 * 16;  // per wave (BM/2) rows of (BN/2) * 2 + 16 bytes
     constexpr int smem = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
+    static_assert(BM * BN != 128 * 128 || smem == kSmallTileLds, "what grad_lds assumes");
     static_assert(!SWIGLU || smem >= BM * (BN / 2) * 4, "the up halves of all rows pass through LDS as fp32");
     auto kern = gemm_lora_kernel<BM, BN, 2, 2, KM, false, SWIGLU, false, SIBS>;
     static bool attr_done = false;
@@ -2110,7 +2111,7 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p, int n_spli
 hipError_t launch_gemm_splitk(const GemmArgs &a, int n_split, bool b_kmajor, hipStream_t st)
 {
     if (n_split < 1 || !a.part || a.k_per_split % 64 != 0 || a.part_ld < a.N || a.part_ld % 4 != 0) return hipErrorInvalidValue;
-    constexpr int smem = 2 * (128 + 128) * 128;
+    constexpr int smem = kSmallTileLds;
     const int tiles = a.tiles_m * a.tiles_n;
     if (tiles <= 0) return hipSuccess;
     auto launch = [&](auto kern) -> hipError_t {
@@ -2208,6 +2209,25 @@ hipError_t launch_skinny(const SkinnyArgs &a, int n_items, int rpad, int row_til
 #undef COLLM_SK
 }
 
+// A block of rank 16 needs 52 KiB of LDS.  Where a GEMM of 128x128 tiles (64 KiB a block, two blocks per CU) starts on
+// another stream while such blocks run, a GEMM block beside one lies at 52 .. 116 KiB, and once the gradient block is gone
+// neither the 52 KiB below it nor the 44 KiB above hold a second GEMM block: that CU runs one block at a time for the rest of
+// the GEMM, and a GEMM of one round becomes one of two.  So such blocks ask for as much as a GEMM block and leave its place
+// behind (the wider ranks need more than that anyway).  dX of 1536 rows, 11008 -> 4096 (384 blocks for 512 places): 162 us, but 265
+// where the dB kernel was still running at its start.  Whole backward call, before / after: that one 301 / 193 us, 384 rows
+// of four adapters 28672 -> 8192 387 / 276, 4096 -> 11008 123 / 85, 1536 rows of 16 adapters 4096 -> 4096 120 / 85.  Not beside 256x256 tiles, which need a CU's whole
+// LDS: two gradient blocks per CU instead of three make those calls up to 3 % longer (6000 rows 1024 -> 8192 157 / 161).
+static constexpr int grad_lds_bytes(int need, bool beside_gemm)
+{
+    return beside_gemm && need < kSmallTileLds ? kSmallTileLds : need;
+}
+
+int grad_lds(int rpad, bool beside_gemm)
+{
+    return grad_lds_bytes(rpad <= 16 ? GradCfg<16>::SMEM : (rpad <= 32 ? GradCfg<32>::SMEM : (rpad <= 64 ? GradCfg<64>::SMEM : GradCfg<128>::SMEM)),
+                          beside_gemm);
+}
+
 template <int RP, bool SMALL_BF>
 static hipError_t launch_grad_t(const GradArgs &a, int n_grad, int rpad, hipStream_t st)
 {
@@ -2216,12 +2236,12 @@ static hipError_t launch_grad_t(const GradArgs &a, int n_grad, int rpad, hipStre
     static bool attr_done = false;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, grad_lds_bytes(C::SMEM, true));
         if (e != hipSuccess) return e;
         attr_done = true;
     }
     const dim3 grid((a.N + 63) / 64, n_grad, (rpad + RP - 1) / RP);
-    COLLM_LAUNCH(kern, grid, dim3(C::KW * 64), C::SMEM, st, a);
+    COLLM_LAUNCH(kern, grid, dim3(C::KW * 64), grad_lds_bytes(C::SMEM, a.beside_gemm != 0), st, a);
     return hipGetLastError();
 }
 

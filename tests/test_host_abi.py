@@ -298,3 +298,27 @@ def test_gemm_slices_by_layout_and_workspace():
     assert binding.host_gemm_slices(11, 31 * 128, 16384, workspace_bytes=3 * 341 * 65536 - 1) == 1
     assert binding.host_gemm_slices(1, 64 * 128, 4096, workspace_bytes=4 * 64 * 65536) == 4
     assert binding.host_gemm_slices(1, 64 * 128, 4096, workspace_bytes=0) == 1
+
+
+@pytest.mark.parametrize("rank", [1, 16, 17, 32, 48, 64, 65, 256])
+def test_gradient_blocks_leave_room_for_two_gemm_blocks(rank):
+    """A CU's LDS, first fit: gradient blocks, GEMM blocks of 128x128 tiles in what they leave, then the gradient blocks end.
+    Two GEMM blocks must fit however many gradient blocks there were."""
+    cu, gemm = 160 << 10, 64 << 10
+
+    def place(held, size):
+        at = 0
+        for lo, hi in sorted(held):
+            if lo - at >= size:
+                break
+            at = max(at, hi)
+        return (at, at + size) if at + size <= cu else None
+
+    grad = binding.host_grad_lds(rank, True)
+    assert grad >= binding.host_grad_lds(rank, False)
+    for n in range(1, cu // grad + 1):
+        grads, gemms = [(k * grad, (k + 1) * grad) for k in range(n)], []
+        for held in (grads, []):
+            while (b := place(held + gemms, gemm)) is not None:
+                gemms.append(b)
+        assert len(gemms) == 2, (n, grad, gemms)
