@@ -77,11 +77,6 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     except Exception:  # pragma: no cover - torch is only needed for device memory
         torch = None
     lib = ctypes.CDLL(LIB_PATH)
-    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
-    marshal = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(marshal)
-    if torch is not None:
-        marshal.set_types(torch.bfloat16, torch.float32, PointerTable)
     vp, i32, sp = ctypes.c_void_p, ctypes.c_int32, ctypes.POINTER(collm_shape)
     lib.collm_ctx_create.argtypes = [_vpp, ctypes.c_int, i32, i32, i32, i32, i32]
     lib.collm_ctx_create.restype = ctypes.c_int
@@ -146,7 +141,13 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.collm_adapter_adamw.argtypes = [ctypes.c_int, ctypes.c_int, vp, vp, vp, vp, vp, ctypes.c_int64,
                                         ctypes.POINTER(collm_adamw), vp]
     lib.collm_adapter_adamw.restype = ctypes.c_int
-    _marshal = marshal
+    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+    _marshal = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(_marshal)
+    if torch is not None:
+        entry = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+        _marshal.bind(torch.bfloat16, torch.float32, PointerTable, entry(lib.collm_lora_linear_fwd), entry(lib.collm_lora_linear_bwd),
+                      entry(lib.collm_adapter_adamw), entry(lib.collm_adapter_fedavg))
     _lib = lib
     return lib
 

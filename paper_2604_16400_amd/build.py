@@ -63,10 +63,10 @@ def build(force: bool = False, verbose: bool = False) -> str:
         os.replace(tmp, LIB)
     src = os.path.join(CSRC, "marshal.cpp")
     if force or _stale(MARSHAL, [src, hdrs[-1]]):
-        # (the C ABI it calls is the library's beside it)
+        # (it links nothing: the binding hands it the entry points of the library it has loaded)
         tmp = MARSHAL + ".tmp.%d" % os.getpid()
         run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
-             "-I", sysconfig.get_paths()["include"], src, "-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN", "-o", tmp])
+             "-I", sysconfig.get_paths()["include"], src, "-o", tmp])
         os.replace(tmp, MARSHAL)
     return LIB
 

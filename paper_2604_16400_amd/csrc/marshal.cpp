@@ -6,7 +6,8 @@
 // same name, calls the C entry point with the interpreter lock released and returns its status - or returns None,
 // without having called anything, where an argument is not of the plain form it expects (contiguous int32 / uint8 arrays,
 // pointer tables made beforehand, bfloat16 or float32 tensors): the binding then takes its general path, which
-// converts what can be converted and raises for the rest.  Nothing is kept between calls.
+// converts what can be converted and raises for the rest.  Nothing is kept between calls.  The entry points are the
+// addresses the binding hands over (bind), not symbols to link: another copy of the library in the process would answer to them.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
@@ -16,6 +17,10 @@
 namespace {
 
 PyObject *g_bf16 = nullptr, *g_f32 = nullptr, *g_table = nullptr;  // torch.bfloat16, torch.float32, the binding's PointerTable
+decltype(&collm_lora_linear_fwd) g_linear_fwd = nullptr;
+decltype(&collm_lora_linear_bwd) g_linear_bwd = nullptr;
+decltype(&collm_adapter_adamw) g_adamw = nullptr;
+decltype(&collm_adapter_fedavg) g_fedavg = nullptr;
 PyObject *s_data_ptr, *s_dtype, *s_shape, *s_array, *s_numel, *s_device, *s_index;
 
 // Arguments of one call as they are read; `ok` falls at the first one that is not of the expected form.
@@ -204,10 +209,10 @@ PyObject *linear_fwd(PyObject *, PyObject *const *args, Py_ssize_t n)
     COLLM_ARGS(14);
     Layer l(r);
     void *y = r.tensor(args[12]), *h = r.tensor(args[13], true);
-    if (!r.ok) Py_RETURN_NONE;
+    if (!r.ok || !g_table) Py_RETURN_NONE;
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = collm_lora_linear_fwd(l.ctx, &l.sh, l.x, l.W, l.A, l.B, l.rank, l.seg_start, l.seg_adapter, l.seg_is_train, y, (float *)h, l.stream);
+    rc = g_linear_fwd(l.ctx, &l.sh, l.x, l.W, l.A, l.B, l.rank, l.seg_start, l.seg_adapter, l.seg_is_train, y, (float *)h, l.stream);
     Py_END_ALLOW_THREADS
     return status(rc);
 }
@@ -220,10 +225,10 @@ PyObject *linear_bwd(PyObject *, PyObject *const *args, Py_ssize_t n)
     void *dy = r.tensor(args[12]), *h = r.tensor(args[13], true), *dx = r.tensor(args[14], true);
     float *const *dA = (float *const *)r.table(args[15], true), *const *dB = (float *const *)r.table(args[16], true);
     const int acc = r.int32(args[17]);
-    if (!r.ok) Py_RETURN_NONE;
+    if (!r.ok || !g_table) Py_RETURN_NONE;
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = collm_lora_linear_bwd(l.ctx, &l.sh, l.x, l.W, l.A, l.B, l.rank, l.seg_start, l.seg_adapter, l.seg_is_train, dy, (const float *)h, dx, dA,
+    rc = g_linear_bwd(l.ctx, &l.sh, l.x, l.W, l.A, l.B, l.rank, l.seg_start, l.seg_adapter, l.seg_is_train, dy, (const float *)h, dx, dA,
                                dB, acc, l.stream);
     Py_END_ALLOW_THREADS
     return status(rc);
@@ -245,10 +250,10 @@ PyObject *adapter_adamw(PyObject *, PyObject *const *args, Py_ssize_t n)
     hp.weight_decay = (float)r.real(args[8]);
     hp.step = r.int32(args[9]);
     void *master = r.tensor(args[10], true), *stream = r.pointer(args[11]);
-    if (!r.ok) Py_RETURN_NONE;
+    if (!r.ok || !g_table) Py_RETURN_NONE;
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = collm_adapter_adamw(dev, dt, param, (float *)master, (const float *)grad, (float *)m, (float *)v, elems, &hp, stream);
+    rc = g_adamw(dev, dt, param, (float *)master, (const float *)grad, (float *)m, (float *)v, elems, &hp, stream);
     Py_END_ALLOW_THREADS
     return status(rc);
 }
@@ -263,33 +268,37 @@ PyObject *adapter_fedavg(PyObject *, PyObject *const *args, Py_ssize_t n)
     void *dst = r.tensor(args[2]);
     const int64_t elems = r.numel(args[2]);
     void *stream = r.pointer(args[3]);
-    if (!r.ok) Py_RETURN_NONE;
+    if (!r.ok || !g_table) Py_RETURN_NONE;
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = collm_adapter_fedavg(dev, dt, copies, src, dst, elems, stream);
+    rc = g_fedavg(dev, dt, copies, src, dst, elems, stream);
     Py_END_ALLOW_THREADS
     return status(rc);
 }
 
-// the two element types as torch has them, the class of pointer tables
-PyObject *set_types(PyObject *, PyObject *const *args, Py_ssize_t n)
+// the two element types as torch has them, the class of pointer tables, and the addresses of the four entry points
+PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
-    if (n != 3) {
-        PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
-        return nullptr;
-    }
+    COLLM_ARGS(7);
+    void *f[4];
+    for (int i = 0; i < 4; ++i) f[i] = r.pointer(args[3 + i]);
+    if (!r.ok || !f[0] || !f[1] || !f[2] || !f[3]) Py_RETURN_FALSE;
+    g_linear_fwd = reinterpret_cast<decltype(g_linear_fwd)>(f[0]);
+    g_linear_bwd = reinterpret_cast<decltype(g_linear_bwd)>(f[1]);
+    g_adamw = reinterpret_cast<decltype(g_adamw)>(f[2]);
+    g_fedavg = reinterpret_cast<decltype(g_fedavg)>(f[3]);
     Py_INCREF(args[0]);
     Py_INCREF(args[1]);
     Py_INCREF(args[2]);
     Py_XSETREF(g_bf16, args[0]);
     Py_XSETREF(g_f32, args[1]);
     Py_XSETREF(g_table, args[2]);
-    Py_RETURN_NONE;
+    Py_RETURN_TRUE;
 }
 
 #define COLLM_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {COLLM_METHOD(linear_fwd),     COLLM_METHOD(linear_bwd), COLLM_METHOD(adapter_adamw),
-                         COLLM_METHOD(adapter_fedavg), COLLM_METHOD(set_types), {nullptr, nullptr, 0, nullptr}};
+                         COLLM_METHOD(adapter_fedavg), COLLM_METHOD(bind), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -3,6 +3,7 @@ host-only integer bookkeeping equals the oracle's bit for bit."""
 import ctypes
 import os
 import re
+import sys
 
 import numpy as np
 import pytest
@@ -322,3 +323,59 @@ def test_gradient_blocks_leave_room_for_two_gemm_blocks(rank):
             while (b := place(held + gemms, gemm)) is not None:
                 gemms.append(b)
         assert len(gemms) == 2, (n, grad, gemms)
+
+
+_BINDING_COPY = """
+import importlib.util, os, sys, types
+import torch
+
+def load(path, name):
+    spec = importlib.util.spec_from_file_location(name, os.path.join(path, "__init__.py"), submodule_search_locations=[path])
+    sys.modules[name] = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(sys.modules[name])
+    b = importlib.import_module(name + ".binding")
+    b.load_library()
+    return b
+
+# a tensor on a device that does not exist: the library reports it and launches nothing
+class T:
+    dtype, device = torch.float32, types.SimpleNamespace(index=9999)
+    def data_ptr(self): return 4096
+    def numel(self): return 8
+
+stream = types.SimpleNamespace(cuda_stream=0)
+def adamw(b):
+    try:
+        b.collm_adapter_adamw(T(), T(), T(), T(), 1e-4, 0.9, 0.999, 1e-8, 0.0, 1, stream=stream)
+    except b.CollmError as e:
+        return str(e)
+"""
+
+
+def _run_binding_copy(tmp_path, code, **env):
+    import shutil
+    import subprocess
+
+    src = os.path.dirname(binding.LIB_PATH)
+    copy = tmp_path / "copy"
+    copy.mkdir()
+    for f in ("__init__.py", "binding.py", "build.py", os.path.basename(binding.LIB_PATH)), os.path.basename(binding.MARSHAL_PATH)):
+        shutil.copy2(os.path.join(src, f), copy / f)
+    shutil.copytree(os.path.join(src, "csrc"), copy / "csrc")
+    r = subprocess.run([sys.executable, "-W", "ignore", "-c", _BINDING_COPY + code, src, str(copy)], capture_output=True, text=True,
+                       env={**os.environ, **env}, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+def test_each_binding_calls_its_own_library(tmp_path):
+    """Two copies of the package in one process: the compiled marshalling of each calls the library its binding has loaded (the
+    text of the last error is kept per library)."""
+    out = _run_binding_copy(tmp_path, """
+first, second = load(sys.argv[1], "first"), load(sys.argv[2], "second")
+assert first._marshal is not None and second._marshal is not None and first.LIB_PATH != second.LIB_PATH
+assert adamw(second) and second._lib.collm_last_error() and not first._lib.collm_last_error(), "called the other library"
+assert adamw(first) and first._lib.collm_last_error()
+print("ok")
+""")
+    assert out.strip().endswith("ok"), out
