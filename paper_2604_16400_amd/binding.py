@@ -10,13 +10,14 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
+import sysconfig
 from typing import List, Optional, Sequence
 
 import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcollm_lora.so")
-MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 COLLM_F32 = 0
 COLLM_BF16 = 1
@@ -53,7 +54,7 @@ class collm_adamw(ctypes.Structure):
 
 
 _lib = None
-_marshal = None  # argument marshalling of the compute calls (csrc/marshal.cpp), loaded with the library
+_marshal = None  # compiled argument marshalling of the compute calls (csrc/marshal.cpp); None: every call by the ctypes route
 _i32p = ctypes.POINTER(ctypes.c_int32)
 _u8p = ctypes.POINTER(ctypes.c_uint8)
 _vpp = ctypes.POINTER(ctypes.c_void_p)
@@ -64,13 +65,15 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     global _lib, _marshal
     if _lib is not None:
         return _lib
-    missing = [p for p in (LIB_PATH, MARSHAL_PATH) if not os.path.exists(p)]
-    if missing:
-        if not build_if_missing:
-            raise FileNotFoundError(missing[0])
+    if build_if_missing and not (os.path.exists(LIB_PATH) and os.path.exists(MARSHAL_PATH)):
         from . import build as _build
 
-        _build.build()
+        if os.path.exists(LIB_PATH):
+            _build.build_marshal()
+        else:
+            _build.build()
+    if not os.path.exists(LIB_PATH):
+        raise FileNotFoundError(LIB_PATH)
     try:
         # the HIP runtime PyTorch has loaded must be the one this library binds to
         import torch
@@ -141,13 +144,14 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.collm_adapter_adamw.argtypes = [ctypes.c_int, ctypes.c_int, vp, vp, vp, vp, vp, ctypes.c_int64,
                                         ctypes.POINTER(collm_adamw), vp]
     lib.collm_adapter_adamw.restype = ctypes.c_int
-    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
-    _marshal = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(_marshal)
-    if torch is not None:
+    if torch is not None and os.path.exists(MARSHAL_PATH):
+        spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+        marshal = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(marshal)
         entry = lambda f: ctypes.cast(f, ctypes.c_void_p).value
-        _marshal.bind(torch.bfloat16, torch.float32, PointerTable, entry(lib.collm_lora_linear_fwd), entry(lib.collm_lora_linear_bwd),
-                      entry(lib.collm_adapter_adamw), entry(lib.collm_adapter_fedavg))
+        marshal.bind(torch.bfloat16, torch.float32, PointerTable, entry(lib.collm_lora_linear_fwd), entry(lib.collm_lora_linear_bwd),
+                     entry(lib.collm_adapter_adamw), entry(lib.collm_adapter_fedavg))
+        _marshal = marshal
     _lib = lib
     return lib
 
@@ -362,12 +366,13 @@ class Context:
                               scale: float, y, h_save=None, stream=None, layout: int = 0):
         """y <- x W + scale (x A_a) B_a per segment; h_save (optional) <- x A_a on training rows.
         layout LAYOUT_OUT_IN: W, A_a, B_a are given transposed ([d_out, d_in], [rank, d_in], [d_out, rank])."""
-        st_n = _stream_number(stream)
-        rc = _marshal.linear_fwd(self._h.value, x, W, A, B, rank, seg_start, seg_adapter, seg_is_train, scale, layout, st_n, y, h_save)
-        if rc is not None:
-            if rc != 0:
-                _check(rc, "collm_lora_linear_fwd")
-            return y
+        if _marshal is not None:
+            rc = _marshal.linear_fwd(self._h.value, x, W, A, B, rank, seg_start, seg_adapter, seg_is_train, scale, layout,
+                                     _stream_number(stream), y, h_save)
+            if rc is not None:
+                if rc != 0:
+                    _check(rc, "collm_lora_linear_fwd")
+                return y
         ss, sa, st = _seg_arrays(seg_start, seg_adapter, seg_is_train)
         rk = np.ascontiguousarray(rank, dtype=np.int32)
         sh = self._shape(x, W, len(sa), len(rk), scale, layout)
@@ -383,13 +388,13 @@ class Context:
                               dB: Optional[List] = None, accumulate: bool = False, stream=None, layout: int = 0):
         """Training rows: dx <- dy W^T + dh A_a^T; dA_a, dB_a (fp32) summed over the adapter's tokens.
         layout LAYOUT_OUT_IN: W, A_a, B_a, dA_a, dB_a are all transposed."""
-        st_n = _stream_number(stream)
-        rc = _marshal.linear_bwd(self._h.value, x, W, A, B, rank, seg_start, seg_adapter, seg_is_train, scale, layout, st_n, dy, h_save,
-                                 dx, dA, dB, 1 if accumulate else 0)
-        if rc is not None:
-            if rc != 0:
-                _check(rc, "collm_lora_linear_bwd")
-            return
+        if _marshal is not None:
+            rc = _marshal.linear_bwd(self._h.value, x, W, A, B, rank, seg_start, seg_adapter, seg_is_train, scale, layout,
+                                     _stream_number(stream), dy, h_save, dx, dA, dB, 1 if accumulate else 0)
+            if rc is not None:
+                if rc != 0:
+                    _check(rc, "collm_lora_linear_bwd")
+                return
         ss, sa, st = _seg_arrays(seg_start, seg_adapter, seg_is_train)
         rk = np.ascontiguousarray(rank, dtype=np.int32)
         sh = self._shape(x, W, len(sa), len(rk), scale, layout)
@@ -517,11 +522,12 @@ def collm_adapter_fedavg(copies: Sequence, dst, stream=None):
     """dst <- mean of the adapter copies (same shape and element type), summed in list order."""
     lib = load_library()
     tab = copies if isinstance(copies, PointerTable) else PointerTable(copies)
-    rc = _marshal.adapter_fedavg(tab, len(tab), dst, _stream_number(stream))
-    if rc is not None:
-        if rc != 0:
-            _check(rc, "collm_adapter_fedavg")
-        return dst
+    if _marshal is not None:
+        rc = _marshal.adapter_fedavg(tab, len(tab), dst, _stream_number(stream))
+        if rc is not None:
+            if rc != 0:
+                _check(rc, "collm_adapter_fedavg")
+            return dst
     _check(lib.collm_adapter_fedavg(dst.device.index or 0, _dtype_of(dst), len(tab), tab.array, dst.data_ptr(),
                                     dst.numel(), _stream_handle(stream)), "collm_adapter_fedavg")
     return dst
@@ -531,11 +537,12 @@ def collm_adapter_adamw(param, grad, m, v, lr: float, beta1: float, beta2: float
                         weight_decay: float, step: int, master=None, stream=None):
     """One AdamW step on `param` (and its optional fp32 `master` copy) from the fp32 `grad`."""
     lib = load_library()
-    rc = _marshal.adapter_adamw(param, grad, m, v, lr, beta1, beta2, eps, weight_decay, step, master, _stream_number(stream))
-    if rc is not None:
-        if rc != 0:
-            _check(rc, "collm_adapter_adamw")
-        return param
+    if _marshal is not None:
+        rc = _marshal.adapter_adamw(param, grad, m, v, lr, beta1, beta2, eps, weight_decay, step, master, _stream_number(stream))
+        if rc is not None:
+            if rc != 0:
+                _check(rc, "collm_adapter_adamw")
+            return param
     hp = collm_adamw(lr, beta1, beta2, eps, weight_decay, int(step))
     _check(lib.collm_adapter_adamw(param.device.index or 0, _dtype_of(param), param.data_ptr(),
                                    None if master is None else master.data_ptr(), grad.data_ptr(), m.data_ptr(),

@@ -5,13 +5,15 @@ import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcollm_lora.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")  # the Python binding's argument marshalling (CPython extension)
+# the Python binding's argument marshalling (CPython extension), named after the interpreter it is built for
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["api.cpp", "planner.cpp", "kernels_bf16.hip", "kernels_f32.hip", "kernels_adapter.hip"]
 HEADERS = ["plan.h", "planner.h", "kernels.h"]
 
@@ -30,6 +32,37 @@ def _stale(out: str, deps) -> bool:
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def _run(cmd, verbose: bool = False) -> None:
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
+    if r.returncode != 0:
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + " ".join(cmd) + "\n" + out)
+    if verbose and out.strip():
+        print(out, flush=True)
+
+
+def build_marshal(force: bool = False, verbose: bool = False) -> bool:
+    """Builds the extension with the host compiler.  The binding works without it (every call then takes its ctypes route), so
+    a missing compiler or missing Python headers are a warning; returns whether the file is there."""
+    src = os.path.join(CSRC, "marshal.cpp")
+    stale = _stale(MARSHAL, [src, os.path.join(ROOT, "include", "collm_lora.h")])
+    if not force and not stale:
+        return True
+    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    try:
+        # (it links nothing: the binding hands it the entry points of the library it has loaded)
+        _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
+              "-I", sysconfig.get_paths()["include"], src, "-o", tmp], verbose)
+        os.replace(tmp, MARSHAL)
+    except (OSError, RuntimeError) as e:
+        warnings.warn("the binding's compiled marshalling was not built, calls take the slower ctypes route: %s" % e)
+        if stale and os.path.exists(MARSHAL):
+            os.remove(MARSHAL)  # (of another source than the library: not to be loaded beside it)
+    return os.path.exists(MARSHAL)
+
+
 def build(force: bool = False, verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build")
@@ -45,29 +78,13 @@ def build(force: bool = False, verbose: bool = False) -> str:
             lang = ["-x", "hip"]
             jobs.append([hipcc] + FLAGS + lang + ["-c", s, "-o", o])
 
-    def run(cmd):
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-        out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
-        if r.returncode != 0:
-            raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + out)
-        if verbose and out.strip():
-            print(out, flush=True)
-
     with ThreadPoolExecutor(max_workers=4) as ex:
-        list(ex.map(run, jobs))
+        list(ex.map(lambda cmd: _run(cmd, verbose), jobs))
     if force or jobs or _stale(LIB, objs):
         tmp = LIB + ".tmp.%d" % os.getpid()
-        run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
+        _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs, verbose)
         os.replace(tmp, LIB)
-    src = os.path.join(CSRC, "marshal.cpp")
-    if force or _stale(MARSHAL, [src, hdrs[-1]]):
-        # (it links nothing: the binding hands it the entry points of the library it has loaded)
-        tmp = MARSHAL + ".tmp.%d" % os.getpid()
-        run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
-             "-I", sysconfig.get_paths()["include"], src, "-o", tmp])
-        os.replace(tmp, MARSHAL)
+    build_marshal(force, verbose)
     return LIB
 
 

@@ -352,14 +352,15 @@ def adamw(b):
 """
 
 
-def _run_binding_copy(tmp_path, code, **env):
+def _run_binding_copy(tmp_path, keep_marshal, code, **env):
     import shutil
     import subprocess
 
     src = os.path.dirname(binding.LIB_PATH)
     copy = tmp_path / "copy"
     copy.mkdir()
-    for f in ("__init__.py", "binding.py", "build.py", os.path.basename(binding.LIB_PATH)), os.path.basename(binding.MARSHAL_PATH)):
+    for f in ("__init__.py", "binding.py", "build.py", os.path.basename(binding.LIB_PATH)) + \
+            ((os.path.basename(binding.MARSHAL_PATH),) if keep_marshal else ()):
         shutil.copy2(os.path.join(src, f), copy / f)
     shutil.copytree(os.path.join(src, "csrc"), copy / "csrc")
     r = subprocess.run([sys.executable, "-W", "ignore", "-c", _BINDING_COPY + code, src, str(copy)], capture_output=True, text=True,
@@ -368,10 +369,28 @@ def _run_binding_copy(tmp_path, code, **env):
     return r.stdout
 
 
+def test_the_binding_works_without_its_compiled_marshalling(tmp_path):
+    """A library without the extension and without a compiler to build it: every call takes the ctypes route."""
+    out = _run_binding_copy(tmp_path, False, """
+b = load(sys.argv[2], "alone")
+assert b._marshal is None
+e = torch.zeros(0)
+b.collm_adapter_adamw(e, e, e, e, 1e-4, 0.9, 0.999, 1e-8, 0.0, 1, stream=stream)
+print(adamw(b))
+""", CXX="/nonexistent/c++")
+    assert "collm_adapter_adamw: status" in out, out
+
+
+def test_the_extension_is_named_after_its_interpreter():
+    import sysconfig
+
+    assert binding.MARSHAL_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and os.path.exists(binding.MARSHAL_PATH)
+
+
 def test_each_binding_calls_its_own_library(tmp_path):
     """Two copies of the package in one process: the compiled marshalling of each calls the library its binding has loaded (the
     text of the last error is kept per library)."""
-    out = _run_binding_copy(tmp_path, """
+    out = _run_binding_copy(tmp_path, True, """
 first, second = load(sys.argv[1], "first"), load(sys.argv[2], "second")
 assert first._marshal is not None and second._marshal is not None and first.LIB_PATH != second.LIB_PATH
 assert adamw(second) and second._lib.collm_last_error() and not first._lib.collm_last_error(), "called the other library"
