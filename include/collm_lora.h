@@ -323,6 +323,12 @@ int collm_debug_set_tiles(collm_ctx *ctx, int fwd_tile, int bwd_tile);
 int collm_debug_set_gemm_split(collm_ctx *ctx, int n_slices);
 
 /*
+ * Debug/tuning: where the adapter gradients of a backward call run.  -1: let the library choose; 0: on the caller's
+ * stream, one kernel after the other; 1: on the context's second stream, beside dh and the dX GEMM.  Affects only speed.
+ */
+int collm_debug_set_grad_streams(collm_ctx *ctx, int mode);
+
+/*
  * Debug/tuning: which rows the rank-wide passes (h = x A, dh = dy B^T) run as 128-row tiles
  * rather than 16-row items: runs of at least min_rows rows of one adapter whose rank is a
  * multiple of 8.  0: never; -1: let the library choose (every such adapter when the widest

@@ -89,6 +89,7 @@ struct collm_ctx {
     int tile_fwd = -1, tile_bwd = -1;  // forced GEMM tile shapes (-1 = choose)
     int wide_min_rows = -1;            // forced threshold of the tiled rank-wide pass (-1 = choose, 0 = never)
     int dual_pass = -1;                // dh and dB from one pass over dy: -1 = where it pays, 0 = never, 1 = wherever it applies
+    int grad_streams = -1;             // adapter gradients: -1 = choose, 0 = on the caller's stream, 1 = on the second stream
     int gemm_split = -1;               // forced number of K slices of a GEMM with few rows (-1 = choose, 1 = never)
     int n_cus = 0;                     // compute units of the device
     int key_wide = 0, key_nsib = 0;
@@ -1044,6 +1045,14 @@ int collm_debug_set_dual_pass(collm_ctx *c, int mode)
     return COLLM_OK;
 }
 
+int collm_debug_set_grad_streams(collm_ctx *c, int mode)
+{
+    if (!c) return COLLM_E_NULL;
+    if (mode < -1 || mode > 1) return COLLM_E_SHAPE;
+    c->grad_streams = mode;
+    return COLLM_OK;
+}
+
 int collm_debug_set_wide_pass(collm_ctx *c, int min_rows)
 {
     if (!c) return COLLM_E_NULL;
@@ -1287,7 +1296,8 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // backward in us, two streams / one: 0.9 MB of training rows of dy and x 89 / 47, 7.3 MB 104 / 83 and 106 / 102,
     // 15 MB 96 / 104 and 126 / 132; with rank 64 the kernels are longer: 3.7 MB 102 / 107, 15 MB 130 / 166.
     constexpr int64_t kSerialGradBytes = (int64_t)8 << 20;
-    const bool alone = (int64_t)n_train * (s->d_in + s->d_out) * (f32 ? 4 : 2) <= kSerialGradBytes && (f32 || L.rpad <= 32);
+    const bool alone = c->grad_streams >= 0 ? c->grad_streams == 0
+                                            : (int64_t)n_train * (s->d_in + s->d_out) * (f32 ? 4 : 2) <= kSerialGradBytes && (f32 || L.rpad <= 32);
     const bool overlap = dA && !alone && !c->profile;
     hipStream_t gs = overlap ? c->side : st;
     GradArgs ga{};

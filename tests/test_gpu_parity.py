@@ -15,11 +15,13 @@ from gpu_util import TOL, DeviceLayer, check_full, make_ctx, maxrel, to_dev, to_
 pytestmark = pytest.mark.gpu
 
 
-def _run_full(w, tol=None, h_save=True, transposed=False, wide_min_rows=None, gemm_split=None, dual_pass=None, **kw):
+def _run_full(w, tol=None, h_save=True, transposed=False, wide_min_rows=None, gemm_split=None, dual_pass=None, grad_streams=None, **kw):
     t = wl.make_tensors(w)
     ctx = make_ctx(w, **kw)
     if dual_pass is not None:
         ctx.set_dual_pass(dual_pass)
+    if grad_streams is not None:
+        ctx.set_grad_streams(grad_streams)
     if wide_min_rows is not None:
         ctx.set_wide_pass(wide_min_rows)
     if gemm_split is not None:
@@ -446,6 +448,33 @@ def test_two_contexts_on_two_streams_interleaved():
     check_full(lb, TOL["bf16"])
     ca.close()
     cb.close()
+
+
+@pytest.mark.parametrize("grad_streams", [0, 1])
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("dtype,ranks", [("bf16", [16, 12, 3]), ("bf16", [32, 8, 20]), ("bf16", [64, 5, 136]), ("f32", [16, 12, 3]), ("f32", [256, 7, 40])])
+def test_adapter_gradients_on_either_stream(dtype, ranks, transposed, grad_streams):
+    # both routes of the backward call at sizes the library would send one way only, h kept and recomputed, for every width
+    # of the gradient kernel; two calls on two streams whose contexts take different routes, nothing waited for in between
+    import torch
+
+    w = _adhoc(dtype, 520, 264, ranks, [300, 1, 45, 2, 170, 60], [0, 1, 2, 0, -1, 1], [1, 0, 1, 0, 0, 1], scale=0.3)
+    _run_full(w, transposed=transposed, grad_streams=grad_streams)
+    _run_full(w, transposed=transposed, grad_streams=grad_streams, h_save=False)
+    layers, streams = [], [torch.cuda.Stream(), torch.cuda.Stream()]
+    for mode in (grad_streams, 1 - grad_streams):
+        ctx = make_ctx(w)
+        ctx.set_grad_streams(mode)
+        layers.append(DeviceLayer(w, wl.make_tensors(w), ctx, transposed=transposed))
+    torch.cuda.synchronize()
+    for _ in range(2):
+        for step in ("fwd", "bwd"):
+            for layer, stream in zip(layers, streams):
+                with torch.cuda.stream(stream):
+                    getattr(layer, step)()
+    for layer in layers:
+        check_full(layer, TOL[dtype])
+        layer.ctx.close()
 
 
 @pytest.mark.parametrize("transposed", [False, True])

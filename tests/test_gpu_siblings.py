@@ -33,12 +33,13 @@ class SiblingCase:
         _, self.tok_adapter, self.tok_train = oracle.token_map(self.seg_start, self.seg_adapter, self.seg_is_train)
 
 
-def _run(case: SiblingCase, h_save=True, accumulate=False):
+def _run(case: SiblingCase, h_save=True, accumulate=False, grad_streams=-1):
     import torch
 
     P, T, D = case.P, case.T, case.D
     max_rank = P * int(case.ranks.max())
     ctx = binding.Context(max(T, 1), len(case.seg_adapter), len(case.ranks), max_rank, max(case.d_in, D))
+    ctx.set_grad_streams(grad_streams)
     nan = float("nan")
     x, W, dy = to_dev(case.x, "bf16"), to_dev(case.W, "bf16"), to_dev(np.where(case.tok_train[:, None] != 0, case.dy, np.nan).astype(np.float32), "bf16")
     A, B = [to_dev(a, "bf16") for a in case.A], [to_dev(b, "bf16") for b in case.B]
@@ -115,6 +116,15 @@ def test_three_siblings_qkv_like():
                     [0, 0, 0, 0, 1, 0, 0, 1])
     _run(c)
     _run(c, h_save=False)
+
+
+@pytest.mark.parametrize("grad_streams", [0, 1])
+def test_sibling_gradients_on_either_stream(grad_streams):
+    for ranks in ([8, 8], [16, 8], [48, 16]):
+        c = SiblingCase(264, (256, 72), ranks, [200, 1, 33, 90], [0, 1, -1, 1], [1, 0, 0, 1])
+        _run(c, grad_streams=grad_streams)
+        _run(c, h_save=False, grad_streams=grad_streams)
+        _run(c, accumulate=True, grad_streams=grad_streams)
 
 
 def test_two_siblings_wide_ranks_and_large_tiles():
