@@ -284,6 +284,12 @@ int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int
 int collm_debug_host_grad_lds(int rank, int beside_gemm, int32_t *bytes);
 
 /*
+ * Debug, HOST only (no GPU): whether a backward call with gradients of adapters of ranks up to max_rank over n_train training
+ * tokens runs them on the caller's stream (*streams = 1) or beside dh and dX on a second one (2).
+ */
+int collm_debug_host_grad_streams(int n_train, int d_in, int d_out, int dtype, int max_rank, int32_t *streams);
+
+/*
  * Debug, HOST only (no GPU): the order in which the workgroups of a GEMM launch of tiles_m x tiles_n tiles take
  * the tiles.  Workgroup ids go round-robin to the GPU's 8 XCDs (each with an L2 of its own); every XCD gets a
  * contiguous run of an order that walks groups of 8 row tiles column by column, and the grid is walked in bands

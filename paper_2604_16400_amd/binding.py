@@ -115,6 +115,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.collm_debug_host_gemm_slices.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64, _i32p]
     lib.collm_debug_host_gemm_slices.restype = ctypes.c_int
     lib.collm_debug_host_tiling.restype = ctypes.c_int
+    lib.collm_debug_host_grad_streams.argtypes = [ctypes.c_int] * 5 + [_i32p]
+    lib.collm_debug_host_grad_streams.restype = ctypes.c_int
     lib.collm_debug_host_grad_lds.argtypes = [ctypes.c_int, ctypes.c_int, _i32p]
     lib.collm_debug_host_grad_lds.restype = ctypes.c_int
     lib.collm_debug_host_tile_order.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _i32p,
@@ -208,6 +210,14 @@ def host_gemm_slices(tiles_m: int, cols: int, K: int, b_kmajor: bool = False, wo
     n = ctypes.c_int32(-9)
     _check(lib.collm_debug_host_gemm_slices(tiles_m, cols, K, 1 if b_kmajor else 0, workspace_bytes, ctypes.byref(n)),
            "collm_debug_host_gemm_slices")
+    return n.value
+
+
+def host_grad_streams(n_train: int, d_in: int, d_out: int, dtype: int, max_rank: int) -> int:
+    """Streams a backward call with adapter gradients would use (host logic, no GPU)."""
+    lib = load_library()
+    n = ctypes.c_int32(-9)
+    _check(lib.collm_debug_host_grad_streams(n_train, d_in, d_out, dtype, max_rank, ctypes.byref(n)), "collm_debug_host_grad_streams")
     return n.value
 
 

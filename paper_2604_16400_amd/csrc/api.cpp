@@ -250,6 +250,23 @@ bool warm_pays(const collm_ctx *c, int rows, int cols, int K, bool b_kmajor)
     return !(can_split && t.tile == kTile128x128 && t.tail_tiles_m == 0 && gemm_slices(c, t.big_tiles_m, cols, K, b_kmajor) >= 2);
 }
 
+// Whether the adapter gradients of a backward call stay on the caller's stream.  On the second stream they run beside dh and
+// the dX GEMM, but the three dependences between the streams cost 10 us on the GPU and more of host time per call.  The line
+// lies where one stream stops saving time of a loop that the host keeps up with (forward + backward, wall) and starts to cost the
+// GPU some (backward, queued ahead).  Two streams / one, us, by MiB of training rows of dy and x; wall and GPU:
+//   rank 8, 16   0.4: 67 / 45 and 36 / 27;  1.9: 92 / 70 and 40 / 41;  3.8: 90 / 75 and 41 / 44 or 43 / 42;  6.0: 84 / 85 and 46 / 50;
+//                7.5: 91 / 90 and 49 / 55
+//   rank 32      0.4: 73 / 54 and 35 / 33;  1.9: 98 / 74 and 39 / 43;  3.0: 94 / 80 and 44 / 50;  6.0: 91 / 94 and 45 / 57
+//   rank 64      0.8: 96 / 79 and 43 / 49;  3.0: 93 / 98 and 50 / 62: the gradient kernels themselves are too long
+//   fp32         2.0: 69 / 56 and 35 / 31;  8.0: 100 / 98 and 54 / 55;  16: 156 / 169 and 91 / 105
+// (the width of the gradient kernel's launch is the largest rank of the call's adapters, trained or not)
+bool grads_alone(int n_train, int d_in, int d_out, bool f32, int rpad)
+{
+    const int64_t bytes = (int64_t)n_train * ((int64_t)d_in + d_out) * (f32 ? 4 : 2);
+    const int64_t MiB = (int64_t)1 << 20;
+    return bytes <= (f32 ? 8 * MiB : (rpad <= 16 ? 5 * MiB : (rpad <= 32 ? 2 * MiB : 0)));
+}
+
 // One GEMM over the row order `R`: a single launch, or whole rounds of large tiles followed by
 // small tiles over the remaining rows.
 hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows, int cols, int forced_tile,
@@ -993,6 +1010,16 @@ int collm_debug_host_grad_lds(int rank, int beside_gemm, int32_t *bytes)
     return COLLM_OK;
 }
 
+int collm_debug_host_grad_streams(int n_train, int d_in, int d_out, int dtype, int max_rank, int32_t *streams)
+{
+    if (!streams) return COLLM_E_NULL;
+    if (n_train < 0 || d_in <= 0 || d_out <= 0) return COLLM_E_SHAPE;
+    if (dtype != COLLM_F32 && dtype != COLLM_BF16) return COLLM_E_DTYPE;
+    if (max_rank < 1 || max_rank > kMaxRank) return COLLM_E_RANK;
+    *streams = grads_alone(n_train, d_in, d_out, dtype == COLLM_F32, round_up(max_rank, kKStep)) ? 1 : 2;
+    return COLLM_OK;
+}
+
 int collm_debug_host_row_order(const collm_shape *s, const int32_t *rank, const int32_t *seg_start,
                                const int32_t *seg_adapter, const uint8_t *seg_is_train, int tile_rows,
                                int training_rows_only, int32_t *row_tok, int32_t *tile_steps)
@@ -1291,13 +1318,8 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // The adapter gradients depend on little (dB_a: h and dy; dA_a: dh and x) and are bound by memory
     // latency, as is dh: they run on a second stream beside dh and the dX GEMM, which joins the
     // caller's stream again before the call returns.  (Serial when kernels are being timed.)
-    // Small batches stay on the caller's stream: the three dependences between the streams cost 15 us on the GPU and
-    // 30 us of host time per call, more than the gradient kernels run one after the other.  Measured, forward +
-    // backward in us, two streams / one: 0.9 MB of training rows of dy and x 89 / 47, 7.3 MB 104 / 83 and 106 / 102,
-    // 15 MB 96 / 104 and 126 / 132; with rank 64 the kernels are longer: 3.7 MB 102 / 107, 15 MB 130 / 166.
-    constexpr int64_t kSerialGradBytes = (int64_t)8 << 20;
-    const bool alone = c->grad_streams >= 0 ? c->grad_streams == 0
-                                            : (int64_t)n_train * (s->d_in + s->d_out) * (f32 ? 4 : 2) <= kSerialGradBytes && (f32 || L.rpad <= 32);
+    // Small batches stay on the caller's stream (see grads_alone).
+    const bool alone = c->grad_streams >= 0 ? c->grad_streams == 0 : grads_alone(n_train, s->d_in, s->d_out, f32, L.rpad);
     const bool overlap = dA && !alone && !c->profile;
     hipStream_t gs = overlap ? c->side : st;
     GradArgs ga{};

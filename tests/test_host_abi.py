@@ -398,3 +398,14 @@ assert adamw(first) and first._lib.collm_last_error()
 print("ok")
 """)
     assert out.strip().endswith("ok"), out
+
+
+@pytest.mark.parametrize("n_train,d_in,d_out,dtype,rank,streams", [
+    (768, 2048, 2048, binding.COLLM_BF16, 16, 2), (384, 1024, 4096, binding.COLLM_BF16, 16, 1),     # 6 and 3.75 MiB
+    (768, 1024, 1024, binding.COLLM_BF16, 32, 2), (192, 1024, 4096, binding.COLLM_BF16, 32, 1),     # 3 and 1.9 MiB
+    (1280, 1024, 1024, binding.COLLM_BF16, 16, 1), (1281, 1024, 1024, binding.COLLM_BF16, 16, 2),   # at and above 5 MiB
+    (512, 1024, 1024, binding.COLLM_BF16, 17, 1), (513, 1024, 1024, binding.COLLM_BF16, 32, 2),     # at and above 2 MiB
+    (1, 256, 256, binding.COLLM_BF16, 33, 2),
+    (1024, 1024, 1024, binding.COLLM_F32, 256, 1), (1025, 1024, 1024, binding.COLLM_F32, 4, 2)])    # at and above 8 MiB
+def test_streams_of_the_backward_call(n_train, d_in, d_out, dtype, rank, streams):
+    assert binding.host_grad_streams(n_train, d_in, d_out, dtype, rank) == streams
