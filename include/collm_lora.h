@@ -273,9 +273,10 @@ int collm_debug_host_tiling(int rows, int cols, int K, int can_split, int32_t *t
 /*
  * Debug, HOST only (no GPU): into how many slices the library would cut the contraction length K of a GEMM of
  * tiles_m row tiles of 128 rows by `cols` columns in 128x128 tiles, with workspace_bytes for the partial sums
- * (1: not cut).  b_kmajor: second operand as [cols][K].
+ * (1: not cut).  b_kmajor: second operand as [cols][K].  steps: 16-wide low-rank K-steps of all the row tiles.
  */
-int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int64_t workspace_bytes, int32_t *slices);
+int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int steps, int64_t workspace_bytes,
+                                 int32_t *slices);
 
 /*
  * Debug, HOST only (no GPU): bytes of LDS a block of the bf16 adapter-gradient kernel asks for at this (largest) rank, alone

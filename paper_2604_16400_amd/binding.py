@@ -112,7 +112,7 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.collm_debug_device_token_map.restype = ctypes.c_int
     lib.collm_debug_host_tiling.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _i32p, _i32p, _i32p,
                                             _i32p]
-    lib.collm_debug_host_gemm_slices.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64, _i32p]
+    lib.collm_debug_host_gemm_slices.argtypes = [ctypes.c_int] * 5 + [ctypes.c_int64, _i32p]
     lib.collm_debug_host_gemm_slices.restype = ctypes.c_int
     lib.collm_debug_host_tiling.restype = ctypes.c_int
     lib.collm_debug_host_grad_streams.argtypes = [ctypes.c_int] * 5 + [_i32p]
@@ -204,11 +204,12 @@ def host_tiling(rows: int, cols: int, K: int, can_split: bool = True):
     return tuple(o.value for o in out)
 
 
-def host_gemm_slices(tiles_m: int, cols: int, K: int, b_kmajor: bool = False, workspace_bytes: int = 64 << 20) -> int:
-    """Slices of K the library would cut a GEMM of tiles_m x ceil(cols / 128) tiles of 128x128 into (host logic, no GPU)."""
+def host_gemm_slices(tiles_m: int, cols: int, K: int, b_kmajor: bool = False, workspace_bytes: int = 64 << 20, steps: int = 0) -> int:
+    """Slices of K the library would cut a GEMM of tiles_m x ceil(cols / 128) tiles of 128x128 into, with `steps` extension steps
+    over all row tiles (host logic, no GPU)."""
     lib = load_library()
     n = ctypes.c_int32(-9)
-    _check(lib.collm_debug_host_gemm_slices(tiles_m, cols, K, 1 if b_kmajor else 0, workspace_bytes, ctypes.byref(n)),
+    _check(lib.collm_debug_host_gemm_slices(tiles_m, cols, K, 1 if b_kmajor else 0, steps, workspace_bytes, ctypes.byref(n)),
            "collm_debug_host_gemm_slices")
     return n.value
 

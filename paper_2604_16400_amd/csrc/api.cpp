@@ -192,16 +192,17 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
 
 // Few tiles against a long contraction (decode-sized batches, or the small tiles behind whole rounds of large
 // ones): too few blocks to fill the GPU, each walking all of K with one tile of loads in flight.  K is cut into
-// slices so that up to two blocks per CU exist, as long as a slice keeps 512 K values (320 up to one block per CU, where
-// a block's chain of K tiles is the time) and the fp32 partial sums fit the workspace; a second kernel adds the slices.
-// Up to 256 tiles never more blocks than the 512 that run at once: those beyond would be a second round.  Measured, forward
-// GEMM in us with 1 / 2 / 3 slices: 172 tiles of K = 4096 45 / 38 / 49; 256 tiles of K = 8192 81 / 68 / 82; 320 tiles of
-// K = 5120 59 / 76 / 69.
-// Whole forward call in us, weights cold, by the fewest values of a slice 512 / 320 / 256 (slices): 8 tiles of K = 1024 20.6 /
-// 19.0 / 18.5 (2, 3, 4), 64 tiles 24.8 / 24.8 / 26.6; 32 tiles of K = 2048 25.9 / 25.0 / 26.9 (4, 6, 8); 16 tiles of K = 3072 26.7 /
-// 26.4 / 27.5 (6, 9, 12).  Below K = 1024 one slice: K = 512 and 4 / 32 / 128 tiles 14.8 / 15.2 / 15.4, with two 17.2 / 18.8 / 26.0.
-// Exactly 512 blocks in eight slices or more are slower than one slice less, up to K = 16384: 64 tiles of K = 4096 41.1 / 38.4,
-// 32 of K = 8192 46.9 / 44.0, 16 of K = 16384 47.1 / 45.1; but 64 of K = 28672 129 / 140.
+// slices so that up to two blocks per CU exist, as long as the fp32 partial sums fit the workspace; a second kernel adds the
+// slices.  The slices share a row tile's extension steps too, and a step costs about as much as 32 K values (its table rows
+// come one trip to memory later), so the rule counts K + 32 steps.  Forward calls with every number of slices, weights cold, in
+// us; 818 shapes of 4 to 256 tiles, K = 256 to 28672, 8 to 96 steps: the rule is 1.2 % off the best on average, 18 % at worst.
+//  - Up to one block per CU, where a block's chain is the time, a slice keeps 288: 8 tiles of K = 2048 (16 rows) 33 / 20 us with one slice / 8;
+//    16 of K = 8192 143 / 45 with 16 (128 rows, 96 steps).
+//  - Up to two blocks per CU it keeps 688: 64 tiles of K = 8192 52 / 45 with 4 / 7, but of K = 2048 (64 rows) 27.8 / 29.2.
+//  - None below 1024: K = 512 and 32 tiles of 64 rows 22.1 / 21.8 with one / two, but with 96 steps 50 / 31 with 4.  With several row tiles
+//    the sums weigh more, and none below 1408: 64 tiles (256 rows) of K = 1024 25.3 / 28.8, of K = 1536 31.2 / 30.3 with 4.
+//  - 512 blocks in eight slices or more whose length is a power of two are slower than one slice less (the slices start in the
+//    same memory channels): 64 tiles of K = 4096 35.1 / 32.0, 8192 50.4 / 44.9; K = 14336 72.7 / 87.2 ([N][K]: seven of 2048).
 // Long contractions whose tiles fill one round only partly: three slices make nearly two whole rounds of up to 341 tiles,
 // and a block's start and end no longer count.  With a power of two of row tiles one slice is slower for the same number of
 // tiles, and slices pay earlier.  Whole forward call, 1 / 2 / 3 slices (row x column tiles): 8x36 of K = 8192 121 / 148 /
@@ -209,7 +210,8 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
 // 196 / 232 / 196, 16384 223 / 260 / 222, 28672 382 / 451 / 361; 2x129 of K = 14336 184 / 231 / 192.  Beyond, two slices: 8x44 tiles of K = 8192
 // 161 / 153 and 148 / 155 ([N][K]), 14336 266 / 240 and 265 / 252; 4x86 of K = 20480 362 / 321 and 372 / 340, but 4x88 385 / 384
 // and 372 / 399; not with other numbers of row tiles (6x64 of K = 20480 280 / 318, 3x115 304 / 373) or more tiles (8x48 367 / 377).
-long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, bool b_kmajor)
+// steps: extension steps of all the row tiles.
+long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, bool b_kmajor, int steps)
 {
     const long tiles = std::max((long)tiles_m * ((cols + 127) / 128), 1L);
     const long fit = (long)(part_bytes / std::max((int64_t)tiles_m * 128 * cols * 4, (int64_t)1));
@@ -224,15 +226,27 @@ long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, b
         }
         return want <= fit ? want : 1;  // (all of them or none: fewer slices would be another round)
     }
-    long blocks_slices = kSplitBlocks / tiles;
-    if (blocks_slices >= 8 && blocks_slices * tiles == kSplitBlocks && K <= 16384) --blocks_slices;
-    long want = std::min<long>(blocks_slices, K / 512);
-    if (K >= 1024) want = std::max(want, std::min<long>(kSplitBlocks / 2 / tiles, K / 320));
-    return std::min<long>({want, fit, 64L});
+    const int64_t len = K + (int64_t)32 * steps / std::max(tiles_m, 1);
+    if (len < (tiles_m > 1 && tiles > 32 ? 1408 : 1024)) return 1;
+    const long most = kSplitBlocks / tiles;
+    long two = std::min<long>(most, len / 688);
+    if (two == most && two >= 8 && two * tiles == kSplitBlocks) {
+        const int slice = round_up((int)((K + two - 1) / two), 64);
+        if ((slice & (slice - 1)) == 0) --two;
+    }
+    return std::min<long>({std::max(two, std::min<long>(kSplitBlocks / 2 / tiles, len / 288)), (long)K / 64, fit, 64L});
 }
-long gemm_slices(const collm_ctx *c, int tiles_m, int cols, int K, bool b_kmajor)
+
+// Extension steps of `tiles_m` row tiles of 128 rows from row tile `first` on, as the plan lists them.
+int steps_of(const collm_ctx *c, const RowOrderLayout &R, int first, int tiles_m)
 {
-    return gemm_slices(c->gemm_split, (int64_t)c->part_bytes, tiles_m, cols, K, b_kmajor);
+    const int32_t *off = c->plan.data() + (R.bm == 128 ? R.off_ext_off : R.off_ext_off_half) + first;
+    return off[tiles_m] - off[0];
+}
+
+long gemm_slices(const collm_ctx *c, const RowOrderLayout &R, int first, int tiles_m, int cols, int K, bool b_kmajor)
+{
+    return gemm_slices(c->gemm_split, (int64_t)c->part_bytes, tiles_m, cols, K, b_kmajor, steps_of(c, R, first, tiles_m));
 }
 
 // Whether the rank-wide pass in front of a GEMM should fetch the GEMM's weight into the last-level cache (run_skinny has
@@ -241,13 +255,13 @@ long gemm_slices(const collm_ctx *c, int tiles_m, int cols, int K, bool b_kmajor
 // (33 MB: 4-5 us, of which the GEMM gives back 1-3).  Measured, whole forward call in us with / without the fetch,
 // 4096 -> 4096: 8 rows 32 / 29, 64 rows 36 / 32, 256 rows 47 / 44, 512 rows level, 1003 rows (one slice) 65 / 71;
 // 1024 -> 1024 (2 MB): 22 / 24 and 26 / 28.
-bool warm_pays(const collm_ctx *c, int rows, int cols, int K, bool b_kmajor)
+bool warm_pays(const collm_ctx *c, const RowOrderLayout &R, int rows, int cols, int K, bool b_kmajor)
 {
     constexpr int64_t kWarmSlicedMaxBytes = (int64_t)8 << 20;
     if ((int64_t)cols * K * 2 <= kWarmSlicedMaxBytes) return true;
     const bool can_split = c->gemm_split != 1;
     const Tiling t = pick_tiling(rows, cols, K, can_split);
-    return !(can_split && t.tile == kTile128x128 && t.tail_tiles_m == 0 && gemm_slices(c, t.big_tiles_m, cols, K, b_kmajor) >= 2);
+    return !(can_split && t.tile == kTile128x128 && t.tail_tiles_m == 0 && gemm_slices(c, R, 0, t.big_tiles_m, cols, K, b_kmajor) >= 2);
 }
 
 // Whether the adapter gradients of a backward call stay on the caller's stream.  On the second stream they run beside dh and
@@ -288,7 +302,7 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
     auto try_split = [&](int tiles_m, int row_base, int n_rows_here, hipError_t &err) -> bool {
         if (!can_split || forced_tile >= 0) return false;
         const int tiles_n = (cols + 127) / 128;
-        const long want = gemm_slices(c, tiles_m, cols, g.K, b_kmajor);
+        const long want = gemm_slices(c, R, row_base / 128, tiles_m, cols, g.K, b_kmajor);
         if (want < 2) return false;
         GemmArgs gs = g;
         gs.tiles_m = tiles_m;
@@ -994,11 +1008,11 @@ int collm_debug_host_tiling(int rows, int cols, int K, int can_split, int32_t *t
     return COLLM_OK;
 }
 
-int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int64_t workspace_bytes, int32_t *slices)
+int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int steps, int64_t workspace_bytes, int32_t *slices)
 {
     if (!slices) return COLLM_E_NULL;
-    if (tiles_m <= 0 || cols <= 0 || K <= 0 || workspace_bytes < 0) return COLLM_E_SHAPE;
-    *slices = (int32_t)std::max(1L, gemm_slices(-1, workspace_bytes, tiles_m, cols, K, b_kmajor != 0));
+    if (tiles_m <= 0 || cols <= 0 || K <= 0 || steps < 0 || workspace_bytes < 0) return COLLM_E_SHAPE;
+    *slices = (int32_t)std::max(1L, gemm_slices(-1, workspace_bytes, tiles_m, cols, K, b_kmajor != 0, steps));
     return COLLM_OK;
 }
 
@@ -1175,7 +1189,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // counterpart in the other direction uses
     const bool tr = s->layout == COLLM_LAYOUT_OUT_IN;
     rc = run_skinny(c, s, L.all, x, s->d_in, L.off_A_ptr, tr, h_save, c->max_rank, c->max_rank, 1, 1.0f,
-                    c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, s->n_tokens, s->d_out, s->d_in, tr)) ? W : nullptr,
+                    c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, L.all, s->n_tokens, s->d_out, s->d_in, tr)) ? W : nullptr,
                     (uint64_t)s->d_in * s->d_out * 2);
     if (rc != COLLM_OK) return rc;
 
@@ -1464,7 +1478,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         // dh came out of the pass over dy above, together with dB
     } else if (P == 1) {
         rc = run_skinny(c, s, L.train, dy, s->d_out, L.off_B_ptr, !tr, c->d_dh32, L.rpad, L.rpad, 0, s->scale,
-                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, n_train, s->d_in, s->d_out, !tr) ? W : nullptr,
+                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, L.train, n_train, s->d_in, s->d_out, !tr) ? W : nullptr,
                         (uint64_t)s->d_in * s->d_out * 2);
         if (rc != COLLM_OK) return rc;
     } else {

@@ -312,14 +312,14 @@ def test_gemm_with_few_rows_cut_into_k_slices(transposed):
     (500, 11264, 66 * 128 - 8, 3),      # 4 x 66 tiles, the last of each ragged
     (300, 16384, 96 * 128 - 40, 3),     # 3 x 96
     (1000, 11264, 43 * 128 - 16, 2),    # 8 x 43
-    (20, 1024, 8 * 128 - 24, 3),        # 1 x 8, slices of 384, 384 and 256 values
+    (20, 1024, 8 * 128 - 24, 4),        # 1 x 8, with the four steps of its two adapters
 ])
 def test_gemm_slices_chosen_by_the_library(rows, K, cols, slices, transposed):
     # the long contractions are too much work for the oracle: plain fp32 products of the same bf16 operands on the GPU,
     # with s h rounded to bf16 as the layer keeps it.  Bound: one bf16 rounding of y and of s h (2^-8 of the value each)
     import torch
 
-    assert binding.host_gemm_slices((rows + 127) // 128, cols, K, transposed) == slices
+    assert binding.host_gemm_slices((rows + 127) // 128, cols, K, transposed, steps=4) == slices
     gen = torch.Generator(device="cuda")
     gen.manual_seed(rows + K)
     rnd = lambda a, b, std: torch.randn((a, b), generator=gen, device="cuda").mul_(std).to(torch.bfloat16)
@@ -339,6 +339,15 @@ def test_gemm_slices_chosen_by_the_library(rows, K, cols, slices, transposed):
             ref[r] += (2.0 * (x[r].float() @ A[a].float())).to(torch.bfloat16).float() @ B[a].float()
     assert maxrel(to_host(y), to_host(ref)) <= 2 * 2.0 ** -8
     ctx.close()
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("K", [64, 200, 512])
+def test_short_contractions_are_cut_for_their_extension_steps(K, transposed):
+    # 25 adapters of rank 64 in one row tile: 100 steps against 1 to 8 K tiles, slices down to one K tile each
+    rank, ads = [64] * 25, list(range(25)) * 4
+    assert binding.host_gemm_slices(1, 264, K, transposed, steps=100) == K // 64
+    _run_full(_adhoc("bf16", K, 264, rank, [1] * 100, ads, [0] * 90 + [1] * 10, scale=0.5), transposed=transposed)
 
 
 @pytest.mark.parametrize("gemm_split", [2, 5, 64])

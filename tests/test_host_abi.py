@@ -279,15 +279,24 @@ def test_tile_choice_below_one_round(rows, cols, K, tile):
 
 
 @pytest.mark.parametrize("tiles_m,tiles_n,K,want", [
-    (1, 4, 512, 1), (8, 16, 768, 1), (1, 4, 1016, 1), (1, 8, 1024, 3), (8, 8, 1024, 3), (8, 12, 1024, 2),   # from K = 1024 on
-    (1, 16, 3072, 9), (1, 32, 2048, 6), (2, 100, 4096, 2), (16, 16, 8192, 2),
-    (1, 64, 4096, 7), (1, 32, 8192, 15), (1, 64, 16384, 7), (1, 64, 28672, 8), (8, 16, 8192, 4),            # exactly 512 blocks
+    (1, 4, 512, 1), (8, 16, 768, 1), (1, 4, 1016, 1), (1, 8, 1024, 3), (8, 4, 1024, 3),                      # from K = 1024 on
+    (8, 8, 1400, 1), (8, 8, 1408, 4), (8, 12, 1408, 2), (3, 11, 1400, 1), (1, 33, 1024, 3),                 # 1408 with several row tiles
+    (1, 16, 3072, 10), (1, 32, 2048, 7), (1, 64, 2048, 4), (1, 64, 4096, 5), (2, 100, 4096, 2), (16, 16, 8192, 2),
+    (1, 64, 6144, 8), (1, 64, 8192, 7), (1, 32, 8192, 11), (1, 32, 16384, 15), (1, 64, 16384, 7), (1, 64, 28672, 8), (8, 16, 8192, 4),
     (1, 257, 16376, 1), (1, 257, 16384, 3), (11, 31, 16384, 3), (11, 31, 16376, 1), (18, 19, 16384, 1),     # 257, 341, 342 tiles
     (4, 66, 11264, 3), (4, 66, 11256, 1), (2, 129, 11264, 1), (3, 96, 11264, 1), (8, 43, 11264, 2), (8, 43, 11256, 1),
     (8, 45, 28672, 2), (19, 19, 28672, 1), (6, 64, 28672, 1), (3, 115, 28672, 1), (5, 77, 28672, 1), (16, 32, 28672, 1)])
 def test_gemm_slices_at_the_lines_of_the_rule(tiles_m, tiles_n, K, want):
     assert binding.host_gemm_slices(tiles_m, tiles_n * 128, K) == want
     assert binding.host_gemm_slices(tiles_m, tiles_n * 128 - 120, K, True) == want  # (the same tiles, the last one ragged)
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n,K,steps,want", [
+    (1, 32, 512, 0, 1), (1, 32, 512, 15, 1), (1, 32, 512, 16, 3), (1, 32, 512, 96, 8), (2, 32, 512, 56, 4), (2, 32, 512, 55, 1),
+    (1, 32, 256, 96, 4), (1, 16, 2048, 96, 16), (1, 64, 2048, 96, 7), (1, 300, 512, 96, 1)])
+def test_gemm_slices_count_the_extension_steps(tiles_m, tiles_n, K, steps, want):
+    # a decode batch of many adapters has more steps in its row tile than K tiles; slices of 64 K values at least
+    assert binding.host_gemm_slices(tiles_m, tiles_n * 128, K, steps=steps) == want
 
 
 def test_gemm_slices_by_layout_and_workspace():
@@ -297,8 +306,8 @@ def test_gemm_slices_by_layout_and_workspace():
     # four of seven slices leaves four
     assert binding.host_gemm_slices(11, 31 * 128, 16384, workspace_bytes=3 * 341 * 65536) == 3
     assert binding.host_gemm_slices(11, 31 * 128, 16384, workspace_bytes=3 * 341 * 65536 - 1) == 1
-    assert binding.host_gemm_slices(1, 64 * 128, 4096, workspace_bytes=4 * 64 * 65536) == 4
-    assert binding.host_gemm_slices(1, 64 * 128, 4096, workspace_bytes=0) == 1
+    assert binding.host_gemm_slices(1, 64 * 128, 8192, workspace_bytes=4 * 64 * 65536) == 4
+    assert binding.host_gemm_slices(1, 64 * 128, 8192, workspace_bytes=0) == 1
 
 
 @pytest.mark.parametrize("rank", [1, 16, 17, 32, 48, 64, 65, 256])
