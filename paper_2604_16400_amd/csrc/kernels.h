@@ -258,7 +258,7 @@ hipError_t launch_swiglu_bwd(const SwigluBwdArgs &a, hipStream_t st);
 hipError_t launch_fedavg(const FedAvgArgs &a, bool bf16, hipStream_t st);
 hipError_t launch_adamw(const AdamWArgs &a, bool bf16, hipStream_t st);
 
-// fp32 element type: same argument blocks, plain fp32 FMA kernels
+// fp32 element type: same argument blocks, fp32 MFMAs (16x16x4)
 hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st);  // a.n_rows: rows of the order
 hipError_t launch_skinny_f32(const SkinnyArgs &a, int n_items, bool t_kmajor, hipStream_t st);
 hipError_t launch_grad_f32(const GradArgs &a, int n_grad, int rpad, hipStream_t st);

@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
                 const uint64_t addr = in ? (((uint64_t)thi << 32) | tlo) + ((uint64_t)(n0 + r) * rk + q0) * 2u : zeros;
                 dma16g(addr, lds_wave + b_base + i * (NT / 64) * 1024);
             } else {
-                // some rank is no multiple of 8: table rows are not 16-byte aligned; element by element
+                // some rank is no multiple of 8: table rows are not 16-byte aligned; halves of 8 bytes or element by element
                 uint8_t *tb = smem + b_base;
                 const int rk = (int)(kr >> 16), q0 = (int)(kr & 0xffffu) + (cl & 1) * 8;
                 uint16_t e[8];
@@ -1394,7 +1394,7 @@ __global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyAr
     auto store_t_nmajor = [&](int buf) {
         if constexpr (!T_KMAJOR) {
             // (the addresses of the other ranks' halves and elements are worked out anew for every chunk: hoisted out of the
-            // loop they take a hundred registers, and one wave per SIMD instead of two; rank 48, 16384 rows: 124 / 117 us)
+            // loop they take a hundred registers, and one wave per SIMD instead of two; rank 48, 16384 rows: 124 / 116 us)
             if ((rank & 7) == 0) {
 #pragma unroll
                 for (int i = 0; i < NCP; ++i)

@@ -2,8 +2,8 @@
 // (GEMM with low-rank extension, skinny rank-wide pass, adapter gradients) in 32 bits throughout.
 // The fp32 element type exists for exactness on small layers.  What bounds such a pass is the chain of
 // dependent steps in one wave (load, multiply, load ..), not bytes or flops: every kernel is cut into many
-// short waves, each with all loads of 64 K values in flight and its own range of the contraction, and the
-// waves of a block add their sums in LDS in wave order.  v_mfma_f32_16x16x4_f32 (fp32 products and sums)
+// short waves, each with its own range of the contraction and many loads in flight (64 K values in the 16-row GEMM, 32 in the
+// 32-row one, 128 in the rank-wide pass, 32 rows in the gradients), and the waves of a block add their sums in LDS in wave order.  v_mfma_f32_16x16x4_f32 (fp32 products and sums)
 // does the multiplying because its operands come straight from memory: lane l supplies one K value
 // (group l / 16) of row or column l % 16, so a lane that loads four consecutive K values feeds four of them.
 // Measured on 256 -> 256, 64 tokens, rank 8 (us; before: one thread per output of the narrow passes with a serial sum,
