@@ -142,7 +142,11 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
     //    nearly empty last one);
     //  - whole rounds of 256x256 tiles over the first rows and 128x128 tiles over the rest, as two
     //    launches: the sum of both plus 0.1 for the idle CUs at the boundary between them; at most 256
-    //    small tiles with K in slices cost their share of a full round plus the kernel that adds the slices.
+    //    small tiles with K in slices cost their share of a full round plus the kernel that adds the slices;
+    //  - against more than two rounds of 128x128 tiles (the third is as long as a whole one unless nearly empty) up to 447 small
+    //    tiles cost that share too, as they start on the CUs the large ones leave, and part of a first round 0.5 + 0.5 x.
+    //    Forward calls with 128x128 tiles / large and small ones, us: 5427 rows 5192 -> 3920 344 / 281, 1325 rows 4256 -> 14656 235 / 197,
+    //    1107 rows 17488 -> 16952 1113 / 864; up to two rounds the other way, 636 rows 6808 -> 24704 307 / 352.
     auto cost_large = [](double tiles) {
         const double x = tiles / 256.0, whole = std::floor(x), part = x - whole;
         if (x <= 1.0) return 0.65 + 0.35 * x;
@@ -172,6 +176,10 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
             if (cost < best_cost) {
                 best = Tiling{kTile256x256, m, tail};
                 best_cost = cost;
+            } else if (best.tile == kTile128x128 && (long)rows128 * tn128 > 2 * kSplitBlocks && can_split && K >= 1024 && tail_tiles < 448) {
+                const double first = (double)m * tn / 256.0;
+                const double share = (first < 1.0 ? 0.5 + 0.5 * first : first) + 0.65 * tail_tiles / 512.0 + 0.05 + 0.1;
+                if (share < best_cost) best = Tiling{kTile256x256, m, tail};
             }
         }
     }

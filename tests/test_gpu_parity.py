@@ -307,19 +307,11 @@ def test_gemm_with_few_rows_cut_into_k_slices(transposed):
     _run_full(_adhoc("bf16", 8192, 64, [16], [1], [0], [0]), transposed=transposed)   # one token
 
 
-@pytest.mark.parametrize("transposed", [False, True])
-@pytest.mark.parametrize("rows,K,cols,slices", [
-    (500, 11264, 66 * 128 - 8, 3),      # 4 x 66 tiles, the last of each ragged
-    (300, 16384, 96 * 128 - 40, 3),     # 3 x 96
-    (1000, 11264, 43 * 128 - 16, 2),    # 8 x 43
-    (20, 1024, 8 * 128 - 24, 4),        # 1 x 8, with the four steps of its two adapters
-])
-def test_gemm_slices_chosen_by_the_library(rows, K, cols, slices, transposed):
+def _forward_against_fp32(rows, K, cols, transposed):
     # the long contractions are too much work for the oracle: plain fp32 products of the same bf16 operands on the GPU,
     # with s h rounded to bf16 as the layer keeps it.  Bound: one bf16 rounding of y and of s h (2^-8 of the value each)
     import torch
 
-    assert binding.host_gemm_slices((rows + 127) // 128, cols, K, transposed, steps=4) == slices
     gen = torch.Generator(device="cuda")
     gen.manual_seed(rows + K)
     rnd = lambda a, b, std: torch.randn((a, b), generator=gen, device="cuda").mul_(std).to(torch.bfloat16)
@@ -339,6 +331,25 @@ def test_gemm_slices_chosen_by_the_library(rows, K, cols, slices, transposed):
             ref[r] += (2.0 * (x[r].float() @ A[a].float())).to(torch.bfloat16).float() @ B[a].float()
     assert maxrel(to_host(y), to_host(ref)) <= 2 * 2.0 ** -8
     ctx.close()
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("rows,K,cols,slices", [
+    (500, 11264, 66 * 128 - 8, 3),      # 4 x 66 tiles, the last of each ragged
+    (300, 16384, 96 * 128 - 40, 3),     # 3 x 96
+    (1000, 11264, 43 * 128 - 16, 2),    # 8 x 43
+    (20, 1024, 8 * 128 - 24, 4),        # 1 x 8, with the four steps of its two adapters
+])
+def test_gemm_slices_chosen_by_the_library(rows, K, cols, slices, transposed):
+    assert binding.host_gemm_slices((rows + 127) // 128, cols, K, transposed, steps=4) == slices
+    _forward_against_fp32(rows, K, cols, transposed)
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("rows,cols,big,tail", [(1325, 14656, 4, 3), (1107, 16952, 3, 3)])  # whole round and part of one, 345 and 399 small tiles
+def test_small_tiles_behind_large_ones_without_k_slices(rows, cols, big, tail, transposed):
+    assert binding.host_tiling(rows, cols, 1032) == (0, big, tail, 0)
+    _forward_against_fp32(rows, 1032, cols, transposed)
 
 
 @pytest.mark.parametrize("transposed", [False, True])

@@ -278,6 +278,14 @@ def test_tile_choice_below_one_round(rows, cols, K, tile):
     assert binding.host_tiling(rows, cols, K)[0] == tile
 
 
+@pytest.mark.parametrize("rows,cols,K,want", [
+    (5427, 3920, 5192, (0, 16, 11, 0)), (1107, 16952, 17488, (0, 3, 3, 0)),  # more than two rounds of small tiles
+    (5427, 3920, 1023, (2, 43, 0, 0)),                                       # too short for K slices
+    (1498, 10880, 6040, (2, 12, 0, 0)), (636, 24704, 6808, (2, 5, 0, 0))])   # 1020 and 965 small tiles: at most two rounds
+def test_small_tiles_behind_large_ones_beat_a_third_round(rows, cols, K, want):
+    assert binding.host_tiling(rows, cols, K) == want
+
+
 @pytest.mark.parametrize("tiles_m,tiles_n,K,want", [
     (1, 4, 512, 1), (8, 16, 768, 1), (1, 4, 1016, 1), (1, 8, 1024, 3), (8, 4, 1024, 3),                      # from K = 1024 on
     (8, 8, 1400, 1), (8, 8, 1408, 4), (8, 12, 1408, 2), (3, 11, 1400, 1), (1, 33, 1024, 3),                 # 1408 with several row tiles
