@@ -371,6 +371,19 @@ hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t st)
 
 hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
 {
+    // (row blocks are the grid's second dimension, which holds 65536: more rows than that go in several launches)
+    constexpr int kRows = 65534 * 32;
+    static_assert(kRows % kF32Tile == 0, "launches start at a row tile");
+    if (a.n_rows > kRows) {
+        GemmArgs first = a, rest = a;
+        first.n_rows = kRows;
+        rest.n_rows = a.n_rows - kRows;
+        rest.row_tok = a.row_tok + kRows;
+        rest.hs = reinterpret_cast<decltype(a.hs)>(reinterpret_cast<const float *>(a.hs) + (int64_t)kRows * a.hs_ld);
+        rest.ext_off = a.ext_off + kRows / kF32Tile;
+        const hipError_t e = launch_gemm_f32(first, b_kmajor, st);
+        return e == hipSuccess ? launch_gemm_f32(rest, b_kmajor, st) : e;
+    }
     const int cols = (a.N + 63) / 64, rows = a.n_rows;  // (the row order is padded to a multiple of 256 rows)
     if (cols <= 0 || rows <= 0) return hipSuccess;
     // 16 rows and eight waves per block while those blocks leave CUs without a second one; then 32 rows and four waves

@@ -892,3 +892,24 @@ def test_adapter_update_error_statuses():
     with pytest.raises(binding.CollmError) as e:
         binding.collm_adapter_fedavg([a, a[1:33]], a[:32])
     assert e.value.status == -7
+
+
+def test_fp32_rows_beyond_one_launch():
+    # 65537 blocks of 32 rows: more than the second dimension of a grid holds; the last rows have an adapter of their own.
+    # Bound: four products, the rank's two and their sums in fp32 (16 roundings)
+    import torch
+
+    T = 65536 * 32 + 5
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    rnd = lambda a, b: torch.randn((a, b), generator=gen, device="cuda")
+    x, W, A, B = rnd(T, 4), rnd(4, 4), [rnd(4, 1), rnd(4, 2)], [rnd(1, 4), rnd(2, 4)]
+    y = torch.full((T, 4), float("nan"), device="cuda")
+    ctx = binding.Context(T, 2, 2, 2, 4)
+    ctx.collm_lora_linear_fwd(x, W, A, B, [1, 2], [0, T - 70, T], [0, 1], [0, 0], 1.0, y)
+    x, W = x.double(), W.double()
+    for k, r in enumerate((slice(0, T - 70), slice(T - 70, T))):
+        a, b = A[k].double(), B[k].double()
+        assert bool(((y[r].double() - (x[r] @ W + (x[r] @ a) @ b)).abs()
+                     <= 16 * 2.0 ** -24 * (x[r].abs() @ W.abs() + (x[r].abs() @ a.abs()) @ b.abs())).all()), k
+    ctx.close()
