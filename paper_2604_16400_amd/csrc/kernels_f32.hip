@@ -11,6 +11,7 @@
 // shorter chains also halve the distance from the 64-bit result (3.3e-7 -> 1.4e-7).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include <algorithm>
 #include <cstring>
@@ -42,14 +43,31 @@ __device__ __forceinline__ floatx4 mfma_f32(float a, float b, floatx4 c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// An adapter's table: element(s) from index i on, zero unless `on`.  Through the buffer below 2 GiB (BIG false); larger tables, to
+// which 32-bit offsets do not reach, with a 64-bit address.
+template <bool BIG, typename I>
+__device__ __forceinline__ floatx4 table4(const float *tab, __amdgpu_buffer_rsrc_t rt, bool on, I i)
+{
+    if constexpr (BIG) return on ? *reinterpret_cast<const floatx4 *>(tab + i) : floatx4{0.f, 0.f, 0.f, 0.f};
+    else return f32_load4(rt, on ? i * 4u : kF32Oob);
+}
+template <bool BIG, typename I>
+__device__ __forceinline__ float table1(const float *tab, __amdgpu_buffer_rsrc_t rt, bool on, I i)
+{
+    if constexpr (BIG) return on ? tab[i] : 0.f;
+    else return f32_load1(rt, on ? i * 4u : kF32Oob);
+}
+static bool table_is_big(int rank, int d) { return (int64_t)rank * d * 4 > 0x7fffffff; }
+
 // y[tok(m)][n] = sum_k a[tok(m)][k] b(k, n) + sum_q hs[m][q] table_a(q, n)
 //
 // One block = 16 RT rows x 64 columns; its KW waves split K (and the extension steps) between them.  Column i of
 // 16-column block c is n0 + 4 i + c: a lane's four columns are then consecutive both where it loads the second
 // operand ([K][N]) and where it stores.
-template <bool B_KMAJOR, int RT, int KW>
+template <bool B_KMAJOR, int RT, int KW, bool BIG>
 __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
 {
+    using idx_t = std::conditional_t<BIG, uint64_t, uint32_t>;
     constexpr int ROWS = 16 * RT, LD = 64 + 4;
     __shared__ __align__(16) float red[KW * ROWS * LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -114,7 +132,8 @@ __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
         const int row_lo = (int)(st.rows & 0xffffu) - in_tile, row_hi = (int)(st.rows >> 16) - in_tile;
         if (rk == 0 || row_hi <= 0 || row_lo >= ROWS) continue;
         const uint32_t tab_bytes = (uint32_t)rk * (uint32_t)(B_KMAJOR ? N : p.ext_ld) * 4u;
-        const __amdgpu_buffer_rsrc_t rt = f32_rsrc(reinterpret_cast<const void *>(st.tab), tab_bytes);
+        const float *tab = reinterpret_cast<const float *>(st.tab);
+        const __amdgpu_buffer_rsrc_t rt = f32_rsrc(tab, tab_bytes);
         const int q = koff + kg * 4;
         floatx4 tb[4], hv[RT];
 #pragma unroll
@@ -123,9 +142,9 @@ __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
                 // table rows are output columns, `rank` long: any rank, so element by element
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    tb[j][i] = f32_load1(rt, n < N && q + i < rk ? ((uint32_t)(n + j) * (uint32_t)rk + (uint32_t)(q + i)) * 4u : kF32Oob);
+                    tb[j][i] = table1<BIG>(tab, rt, n < N && q + i < rk, (idx_t)(n + j) * (idx_t)rk + (idx_t)(q + i));
             } else {
-                tb[j] = f32_load4(rt, n < N && q + j < rk ? ((uint32_t)(q + j) * (uint32_t)p.ext_ld + (uint32_t)n) * 4u : kF32Oob);
+                tb[j] = table4<BIG>(tab, rt, n < N && q + j < rk, (idx_t)(q + j) * (idx_t)p.ext_ld + (idx_t)n);
             }
         }
 #pragma unroll
@@ -174,9 +193,10 @@ __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
 // out[m][q] = sum_k in[tok(m)][k] table_a(k, q): one block = one item (up to 16 rows of one adapter) x 16 columns of
 // the output row (blockIdx.y; columns beyond the rank are cleared); its eight waves split K.
 constexpr int kF32SkinnyWaves = 8;
-template <bool T_KMAJOR>
+template <bool T_KMAJOR, bool BIG>
 __global__ void __launch_bounds__(kF32SkinnyWaves * 64) skinny_f32_kernel(SkinnyArgs p)
 {
+    using idx_t = std::conditional_t<BIG, uint64_t, uint32_t>;
     constexpr int KW = kF32SkinnyWaves, LD = 16 + 4;
     __shared__ __align__(16) float red[KW * 16 * LD];
     const SkinnyItem it = p.items[blockIdx.x];
@@ -187,7 +207,8 @@ __global__ void __launch_bounds__(kF32SkinnyWaves * 64) skinny_f32_kernel(Skinny
     floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
     if (q0 < rank) {
         const __amdgpu_buffer_rsrc_t rx = f32_rsrc(p.in, p.in_bytes);
-        const __amdgpu_buffer_rsrc_t rt = f32_rsrc(reinterpret_cast<const void *>(p.tab[it.adapter]), (uint32_t)rank * (uint32_t)K * 4u);
+        const float *tab = reinterpret_cast<const float *>(p.tab[it.adapter]);
+        const __amdgpu_buffer_rsrc_t rt = f32_rsrc(tab, (uint32_t)rank * (uint32_t)K * 4u);
         const int tok = l16 < it.n_rows ? p.row_tok[it.row_lo + l16] : -1;
         const uint32_t xoff = tok >= 0 ? (uint32_t)tok * (uint32_t)p.ld_in * 4u : kF32Oob;
         const int per = (((K + KW - 1) / KW) + 15) & ~15;
@@ -201,11 +222,11 @@ __global__ void __launch_bounds__(kF32SkinnyWaves * 64) skinny_f32_kernel(Skinny
                 const bool on = k < k_hi;
                 xv[u] = f32_load4(rx, on && xoff != kF32Oob ? xoff + (uint32_t)k * 4u : kF32Oob);
                 if constexpr (T_KMAJOR) {
-                    tv[u] = f32_load4(rt, on && q < rank ? ((uint32_t)q * (uint32_t)K + (uint32_t)k) * 4u : kF32Oob);
+                    tv[u] = table4<BIG>(tab, rt, on && q < rank, (idx_t)q * (idx_t)K + (idx_t)k);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        tv[u][e] = f32_load1(rt, on && q < rank ? ((uint32_t)(k + e) * (uint32_t)rank + (uint32_t)q) * 4u : kF32Oob);
+                        tv[u][e] = table1<BIG>(tab, rt, on && q < rank, (idx_t)(k + e) * (idx_t)rank + (idx_t)q);
                 }
             }
 #pragma unroll
@@ -388,12 +409,18 @@ hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
     if (cols <= 0 || rows <= 0) return hipSuccess;
     // 16 rows and eight waves per block while those blocks leave CUs without a second one; then 32 rows and four waves
     // (half the reads of the second operand)
-    if ((int64_t)cols * ((rows + 15) / 16) < 512) {
-        if (b_kmajor) COLLM_LAUNCH((gemm_f32_kernel<true, 1, 8>), dim3(cols, (rows + 15) / 16), dim3(512), 0, st, a);
-        else COLLM_LAUNCH((gemm_f32_kernel<false, 1, 8>), dim3(cols, (rows + 15) / 16), dim3(512), 0, st, a);
+    auto launch = [&](auto kern, int block_rows, int threads) {
+        COLLM_LAUNCH(kern, dim3(cols, (rows + block_rows - 1) / block_rows), dim3(threads), 0, st, a);
+    };
+    if (a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) {  // (hs_ld: at least the largest rank)
+        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, true>, 32, 256);
+        else launch(gemm_f32_kernel<false, 2, 4, true>, 32, 256);
+    } else if ((int64_t)cols * ((rows + 15) / 16) < 512) {
+        if (b_kmajor) launch(gemm_f32_kernel<true, 1, 8, false>, 16, 512);
+        else launch(gemm_f32_kernel<false, 1, 8, false>, 16, 512);
     } else {
-        if (b_kmajor) COLLM_LAUNCH((gemm_f32_kernel<true, 2, 4>), dim3(cols, (rows + 31) / 32), dim3(256), 0, st, a);
-        else COLLM_LAUNCH((gemm_f32_kernel<false, 2, 4>), dim3(cols, (rows + 31) / 32), dim3(256), 0, st, a);
+        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, false>, 32, 256);
+        else launch(gemm_f32_kernel<false, 2, 4, false>, 32, 256);
     }
     return hipGetLastError();
 }
@@ -405,8 +432,9 @@ hipError_t launch_skinny_f32(const SkinnyArgs &a, int n_items, bool t_kmajor, hi
     const int width = std::max(a.f32_out ? a.f32_cols : 0, a.bf_out ? (int)a.bf_ld : 0);
     const dim3 grid(n_items, (width + 15) / 16);
     if (grid.y == 0) return hipSuccess;
-    if (t_kmajor) COLLM_LAUNCH(skinny_f32_kernel<true>, grid, dim3(kF32SkinnyWaves * 64), 0, st, a);
-    else COLLM_LAUNCH(skinny_f32_kernel<false>, grid, dim3(kF32SkinnyWaves * 64), 0, st, a);
+    auto launch = [&](auto kern) { COLLM_LAUNCH(kern, grid, dim3(kF32SkinnyWaves * 64), 0, st, a); };
+    if (table_is_big(width, a.K)) launch(t_kmajor ? skinny_f32_kernel<true, true> : skinny_f32_kernel<false, true>);
+    else launch(t_kmajor ? skinny_f32_kernel<true, false> : skinny_f32_kernel<false, false>);
     return hipGetLastError();
 }
 

@@ -913,3 +913,27 @@ def test_fp32_rows_beyond_one_launch():
         assert bool(((y[r].double() - (x[r] @ W + (x[r] @ a) @ b)).abs()
                      <= 16 * 2.0 ** -24 * (x[r].abs() @ W.abs() + (x[r].abs() @ a.abs()) @ b.abs())).all()), k
     ctx.close()
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("wide", ["in", "out"])
+def test_fp32_tables_beyond_32_bit_offsets(wide, transposed):
+    # a table of rank 256 and 4 GiB + 64 KiB, zero but for its far end.  Bound: the terms that are not zero, in fp32
+    import torch
+
+    d = (1 << 22) + 64
+    d_in, d_out = (d, 4) if wide == "in" else (4, d)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    rnd = lambda a, b: torch.randn((a, b), generator=gen, device="cuda")
+    x, W, y = rnd(2, d_in), torch.zeros((d_in, d_out), device="cuda"), torch.full((2, d_out), float("nan"), device="cuda")
+    A, B = torch.zeros((d_in, 256), device="cuda"), torch.zeros((256, d_out), device="cuda")
+    A[-64:] = rnd(min(d_in, 64), 256)
+    B[:, -64:] = rnd(256, min(d_out, 64))
+    tp = (lambda t: t.t().contiguous()) if transposed else (lambda t: t)
+    ctx = binding.Context(2, 1, 1, 256, d)
+    ctx.collm_lora_linear_fwd(x, tp(W), [tp(A)], [tp(B)], [256], [0, 2], [0], [0], 1.0, y, layout=1 if transposed else 0)
+    far = [t.double() for t in (x[:, -64:], A[-64:], B[:, -64:])]
+    ref, bound = far[0] @ far[1] @ far[2], (64 + 256 + 16) * 2.0 ** -24 * (far[0].abs() @ far[1].abs() @ far[2].abs())
+    assert bool(((y[:, -64:].double() - ref).abs() <= bound).all()) and not bool(y[:, :-64].any())
+    ctx.close()
