@@ -261,7 +261,8 @@ int collm_debug_device_token_map(collm_ctx *ctx, int32_t *tok_segment, int32_t *
 
 /*
  * Debug, HOST only (no GPU): how the library would cut a GEMM of `rows` x `cols` outputs with
- * contraction length K into tiles: *tile = 0 (256x256) or 2 (128x128) for the first
+ * contraction length K into tiles of the two sizes that exist for every GEMM (siblings side by side, the SwiGLU epilogue, dX beside
+ * the gradient kernels; collm_debug_host_plain_gemm for the others): *tile = 0 (256x256) or 2 (128x128) for the first
  * *big_tiles_m row tiles, then *tail_tiles_m row tiles of 128 rows as 128x128 tiles (0: none).
  * *tail_cols (0: none; only with 256x256 tiles and no row tail): that many 256-wide tile columns
  * at the right edge run as 128x128 tiles over all rows in a second launch.
@@ -277,6 +278,15 @@ int collm_debug_host_tiling(int rows, int cols, int K, int can_split, int32_t *t
  */
 int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int steps, int64_t workspace_bytes,
                                  int32_t *slices);
+
+/*
+ * Debug, HOST only (no GPU): the same for a plain GEMM (one projection, forward or dX without gradient kernels beside it), which may
+ * also take tiles between the two sizes: *tile = 0 (256x256), 1 (256x128), 2 (128x128), 3 (128x192) or 4 (256x192) for the
+ * first rows; *slices of K and *one_per_cu (0/1: at most one block per CU, with a ring of LDS stages) of 128x128 tiles that
+ * are the whole GEMM.  steps: 16-wide low-rank K-steps of all the 128-row tiles.
+ */
+int collm_debug_host_plain_gemm(int rows, int cols, int K, int b_kmajor, int steps, int64_t workspace_bytes, int32_t *tile,
+                                int32_t *slices, int32_t *one_per_cu);
 
 /*
  * Debug, HOST only (no GPU): bytes of LDS a block of the bf16 adapter-gradient kernel asks for at this (largest) rank, alone
@@ -315,7 +325,8 @@ int collm_debug_host_row_order(const collm_shape *shape, const int32_t *rank, co
 
 /*
  * Debug/tuning: force the tile shape of the forward GEMM and of the dX GEMM
- * (0: 256x256, 2: 128x128 rows x columns of the output; -1: let the library choose from the
+ * (0: 256x256, 1: 256x128, 2: 128x128, 3: 128x192, 4: 256x192 rows x columns of the output - 1, 3 and 4 stand for 0 or 2 of the
+ * same height where several siblings or the SwiGLU epilogue are computed; -1: let the library choose from the
  * problem size; anything else: COLLM_E_SHAPE).  Affects only speed, never results beyond
  * rounding order.
  */

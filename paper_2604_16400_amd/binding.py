@@ -24,7 +24,7 @@ COLLM_BF16 = 1
 ACT_NONE, ACT_SWIGLU = 0, 1
 LAYOUT_IN_OUT, LAYOUT_OUT_IN = 0, 1  # W [d_in, d_out] (paper, row vectors) / W [d_out, d_in] (module weights)
 
-TILE_AUTO, TILE_256x256, TILE_128x128 = -1, 0, 2
+TILE_AUTO, TILE_256x256, TILE_256x128, TILE_128x128, TILE_128x192, TILE_256x192 = -1, 0, 1, 2, 3, 4
 
 
 class CollmError(RuntimeError):
@@ -114,6 +114,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
                                             _i32p]
     lib.collm_debug_host_gemm_slices.argtypes = [ctypes.c_int] * 5 + [ctypes.c_int64, _i32p]
     lib.collm_debug_host_gemm_slices.restype = ctypes.c_int
+    lib.collm_debug_host_plain_gemm.argtypes = [ctypes.c_int] * 5 + [ctypes.c_int64, _i32p, _i32p, _i32p]
+    lib.collm_debug_host_plain_gemm.restype = ctypes.c_int
     lib.collm_debug_host_tiling.restype = ctypes.c_int
     lib.collm_debug_host_grad_streams.argtypes = [ctypes.c_int] * 5 + [_i32p]
     lib.collm_debug_host_grad_streams.restype = ctypes.c_int
@@ -201,6 +203,15 @@ def host_tiling(rows: int, cols: int, K: int, can_split: bool = True):
     out = [ctypes.c_int32(-9) for _ in range(4)]
     _check(lib.collm_debug_host_tiling(rows, cols, K, 1 if can_split else 0, *[ctypes.byref(o) for o in out]),
            "collm_debug_host_tiling")
+    return tuple(o.value for o in out)
+
+
+def host_plain_gemm(rows: int, cols: int, K: int, b_kmajor: bool = False, steps: int = 0, workspace_bytes: int = 64 << 20):
+    """(tile, slices, one_per_cu) the library would use for a plain GEMM of this size (host logic, no GPU)."""
+    lib = load_library()
+    out = [ctypes.c_int32(-9) for _ in range(3)]
+    _check(lib.collm_debug_host_plain_gemm(rows, cols, K, 1 if b_kmajor else 0, steps, workspace_bytes, *[ctypes.byref(o) for o in out]),
+           "collm_debug_host_plain_gemm")
     return tuple(o.value for o in out)
 
 

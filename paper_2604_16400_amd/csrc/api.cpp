@@ -93,6 +93,8 @@ struct collm_ctx {
     int gemm_split = -1;               // forced number of K slices of a GEMM with few rows (-1 = choose, 1 = never)
     int n_cus = 0;                     // compute units of the device
     int key_wide = 0, key_nsib = 0;
+    int tile_steps_all = 0, tile_steps_train = 0;  // low-rank K-steps of a 128-row tile of the call's batch, about (count_steps)
+    std::vector<int32_t> rows_of;      // ... its rows per adapter
     std::vector<int32_t> sum_rank;     // sibling calls: ranks summed over the siblings
     hipStream_t last_stream = nullptr;
     // the adapter gradients run beside dh and the dX GEMM on a second stream
@@ -128,9 +130,11 @@ constexpr int kSplitBlocks = 512;  // 128x128 tiles that run at once: two per CU
 
 // can_split: the 128x128 tiles behind the large ones may have K cut into slices (see run_gemm), which lets a few
 // such tiles use the whole GPU
-Tiling pick_tiling(int rows, int cols, int K, bool can_split)
+// steps: low-rank K-steps of a 128-row tile, about
+// one_round: the tiles between the two sizes exist for this GEMM (plain tiles, no siblings side by side, no SwiGLU)
+Tiling pick_tiling(int rows, int cols, int K, bool can_split, bool one_round, int steps)
 {
-    // Two shapes are worth choosing between: 256x256 run by four waves (one block per CU, the most
+    // Two shapes are worth choosing between for whole rounds: 256x256 run by four waves (one block per CU, the most
     // efficient inner loop) and 128x128 (two blocks per CU, four times as many tiles).  The cost of
     // a choice is the time its tiles take over the 256 CUs in units of one full round of 256x256
     // tiles; the constants are read off measurements on 4096- to 13824-wide layers:
@@ -183,6 +187,28 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
             }
         }
     }
+    // Tiles between the two sizes, where one block per CU holds the whole GEMM (see the ring in gemm_lora_kernel): a first round
+    // that large tiles fill badly and small ones overfill.  x = blocks / 256.  GEMM alone, weights from memory, geometric means over
+    // 12000 shapes (100 to 8192 rows, 1024 to 16384 wide), time against the choice between the two sizes: 128x192 instead of
+    // 257 .. 340 small tiles 0.88 .. 0.96; 256x128 instead of 340 .. 512 small tiles 0.92 .. 0.95; 256x192 instead of 257 .. 370
+    // large ones' worth of small tiles (200 .. 250 blocks) 0.92 .. 0.93.  Below 257 small tiles K slices or the ring on 128x128 tiles are better.
+    // Not where the extension is long (`steps` of a 128-row tile): one block alone on its CU waits for every batch of tables (about 2 us a
+    // batch, 472 rows of 93 adapters of rank 128, K = 10320, 125 -> 160 us; 935 rows of 31 of rank 32, K = 2304, 53 -> 67).
+    // Nor up to 341 small tiles of K >= 16384, which are cut into three slices (733 rows 25448 -> 5408 386 / 451).
+    const long small_tiles = (long)tn128 * rows128;
+    if (one_round && small_tiles > kSplitBlocks / 2 && (int64_t)steps * 256 <= K && !(K >= 16384 && small_tiles <= 2 * kSplitBlocks / 3)) {
+        const int tn192 = (cols + 191) / 192;
+        auto consider = [&](int tile, int tiles_m, long tiles, double cost) {
+            if (tiles > 256 || cost >= best_cost) return;
+            best = Tiling{tile, tiles_m, 0};
+            best_cost = cost;
+        };
+        const long t192 = (long)rows128 * tn192, t256 = (long)tm * tn128, t256w = (long)tm * tn192;
+        consider(kTile128x192, rows128, t192, 0.43 + 0.11 * t192 / 256.0);
+        consider(kTile256x128, tm, t256, 0.47 + 0.11 * t256 / 256.0);
+        consider(kTile256x192, tm, t256w, 0.71 + 0.11 * t256w / 256.0);
+        if (best.tile != kTile256x256 && best.tile != kTile128x128) return best;
+    }
     // ... or whole rounds over the first tile columns and the last columns of all rows as at most one round of
     // 128x128 tiles (two per CU) in a second launch: a last round that fills part of the CUs with large tiles
     // costs most of a round, 512 small tiles cost 0.65.
@@ -196,6 +222,31 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
         }
     }
     return best;
+}
+
+// Whether 128x128 tiles that are not cut run as one block per CU with the ring of four stages: all of them at once, and no long
+// extension (as in slices_one_per_cu).  0.48 us a K tile instead of 0.85 with two stages, weights from memory.
+bool ring_alone(const Tiling &t, int cols, int K, int steps)
+{
+    return t.tile == kTile128x128 && t.tail_tiles_m == 0 && (long)t.big_tiles_m * ((cols + 127) / 128) <= kSplitBlocks / 2 && (int64_t)steps * 64 <= K;
+}
+
+// Slices of K of a GEMM of few tiles run as at most one block per CU with the ring of four stages (three tiles of loads in flight per
+// CU instead of two, half the partial sums), or 0 where `two` slices on two blocks per CU are better.  GEMM with the kernel
+// that adds the slices against two blocks per CU with two stages, weights from memory, 10000 shapes (1 to 2048 rows, K =
+// 1024 to 28672, 1 to 64 adapters of rank 16 to 64): up to 16 tiles 0.88 .. 0.91, up to 32 0.91, up to 64 0.92, up to 85 0.94; from 86 tiles
+// on (two slices at most) 0.96 .. 1.3.  A slice keeps 192 K values (geometric mean 0.927; 256: 0.929, 512: 0.976).
+//  - A block alone on its CU takes 0.48 us a K tile, one of two 0.90; a slice's sums are written and read once more (about 8 TB/s).  The rule
+//    compares these: a long contraction is better cut for the blocks that exist (714 rows, 72 tiles, K = 26112: three
+//    slices on 216 CUs 124 us, seven on two blocks per CU 109).
+//  - Not where the extension steps of a row tile outweigh K: they are spread over half as many blocks then (64 adapters of
+//    rank 64 at K = 2048 1.2 .. 1.4).
+long slices_one_per_cu(long tiles, int tiles_m, int K, int steps, long fit, long two)
+{
+    if (tiles > kSplitBlocks / 4 || (int64_t)steps / std::max(tiles_m, 1) * 64 > K) return 0;
+    const long one = std::max(1L, std::min<long>({kSplitBlocks / 2 / tiles, K / 192, fit, 64L}));
+    const double ktiles = K / 64.0, sums = tiles * 64.0 * 128.0 * 8.0 / 8e6;  // us (a row tile is mostly not full)
+    return 0.48 * ktiles / one + sums * one <= 0.90 * ktiles / two + sums * two ? one : 0;
 }
 
 // Few tiles against a long contraction (decode-sized batches, or the small tiles behind whole rounds of large
@@ -219,10 +270,12 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split)
 // 161 / 153 and 148 / 155 ([N][K]), 14336 266 / 240 and 265 / 252; 4x86 of K = 20480 362 / 321 and 372 / 340, but 4x88 385 / 384
 // and 372 / 399; not with other numbers of row tiles (6x64 of K = 20480 280 / 318, 3x115 304 / 373) or more tiles (8x48 367 / 377).
 // steps: extension steps of all the row tiles.
-long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, bool b_kmajor, int steps)
+// one_per_cu: null, or (plain tiles, the launch is the whole GEMM) whether the slices run as one block per CU (slices_one_per_cu).
+long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, bool b_kmajor, int steps, bool *one_per_cu)
 {
     const long tiles = std::max((long)tiles_m * ((cols + 127) / 128), 1L);
     const long fit = (long)(part_bytes / std::max((int64_t)tiles_m * 128 * cols * 4, (int64_t)1));
+    if (one_per_cu) *one_per_cu = false;
     if (forced > 1) return std::min<long>({forced, K / 64, fit, 64L});
     if (tiles > kSplitBlocks / 2) {
         const bool pow2 = tiles_m > 1 && (tiles_m & (tiles_m - 1)) == 0;
@@ -242,8 +295,39 @@ long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, b
         const int slice = round_up((int)((K + two - 1) / two), 64);
         if ((slice & (slice - 1)) == 0) --two;
     }
-    return std::min<long>({std::max(two, std::min<long>(kSplitBlocks / 2 / tiles, len / 288)), (long)K / 64, fit, 64L});
+    two = std::min<long>({std::max(two, std::min<long>(kSplitBlocks / 2 / tiles, len / 288)), (long)K / 64, fit, 64L});
+    if (one_per_cu) {
+        const long one = slices_one_per_cu(tiles, tiles_m, K, steps, fit, std::max(two, 1L));
+        *one_per_cu = one > 0;
+        if (one > 0) return one;
+    }
+    return two;
 }
+
+// Low-rank K-steps that a 128-row tile of the batch has on average, over all rows and over the training rows: an adapter reaches
+// into about rows / 128 + 1 tiles.  (The tile choice needs it before the plan, whose steps depend on the tiles, is built.)
+void count_steps(collm_ctx *c, const collm_shape *s, const int32_t *rank, const int32_t *seg_start, const int32_t *seg_adapter,
+                 const uint8_t *seg_is_train)
+{
+    const int N = s->n_adapters;
+    c->rows_of.assign((size_t)2 * std::max(N, 1), 0);
+    int n_train = 0;
+    for (int k = 0; k < s->n_segments; ++k) {
+        const int a = seg_adapter[k], n = seg_start[k + 1] - seg_start[k];
+        if (seg_is_train[k]) n_train += n;
+        if (a < 0 || n == 0) continue;
+        c->rows_of[2 * a] += n;
+        if (seg_is_train[k]) c->rows_of[2 * a + 1] += n;
+    }
+    int64_t steps[2] = {0, 0};
+    for (int a = 0; a < N; ++a)
+        for (int o = 0; o < 2; ++o)
+            if (c->rows_of[2 * a + o] > 0) steps[o] += (int64_t)((rank[a] + kKStep - 1) / kKStep) * (c->rows_of[2 * a + o] + 128);
+    c->tile_steps_all = (int)(steps[0] / round_up(std::max(s->n_tokens, 1), 128));
+    c->tile_steps_train = (int)(steps[1] / round_up(std::max(n_train, 1), 128));
+}
+
+int tile_steps(const collm_ctx *c, const RowOrderLayout &R) { return &R == &c->L.all ? c->tile_steps_all : c->tile_steps_train; }
 
 // Extension steps of `tiles_m` row tiles of 128 rows from row tile `first` on, as the plan lists them.
 int steps_of(const collm_ctx *c, const RowOrderLayout &R, int first, int tiles_m)
@@ -252,9 +336,9 @@ int steps_of(const collm_ctx *c, const RowOrderLayout &R, int first, int tiles_m
     return off[tiles_m] - off[0];
 }
 
-long gemm_slices(const collm_ctx *c, const RowOrderLayout &R, int first, int tiles_m, int cols, int K, bool b_kmajor)
+long gemm_slices(const collm_ctx *c, const RowOrderLayout &R, int first, int tiles_m, int cols, int K, bool b_kmajor, bool *one_per_cu)
 {
-    return gemm_slices(c->gemm_split, (int64_t)c->part_bytes, tiles_m, cols, K, b_kmajor, steps_of(c, R, first, tiles_m));
+    return gemm_slices(c->gemm_split, (int64_t)c->part_bytes, tiles_m, cols, K, b_kmajor, steps_of(c, R, first, tiles_m), one_per_cu);
 }
 
 // Whether the rank-wide pass in front of a GEMM should fetch the GEMM's weight into the last-level cache (run_skinny has
@@ -263,13 +347,16 @@ long gemm_slices(const collm_ctx *c, const RowOrderLayout &R, int first, int til
 // (33 MB: 4-5 us, of which the GEMM gives back 1-3).  Measured, whole forward call in us with / without the fetch,
 // 4096 -> 4096: 8 rows 32 / 29, 64 rows 36 / 32, 256 rows 47 / 44, 512 rows level, 1003 rows (one slice) 65 / 71;
 // 1024 -> 1024 (2 MB): 22 / 24 and 26 / 28.
-bool warm_pays(const collm_ctx *c, const RowOrderLayout &R, int rows, int cols, int K, bool b_kmajor)
+bool warm_pays(const collm_ctx *c, const RowOrderLayout &R, int rows, int cols, int K, bool b_kmajor, bool one_round, bool siblings)
 {
     constexpr int64_t kWarmSlicedMaxBytes = (int64_t)8 << 20;
     if ((int64_t)cols * K * 2 <= kWarmSlicedMaxBytes) return true;
     const bool can_split = c->gemm_split != 1;
-    const Tiling t = pick_tiling(rows, cols, K, can_split);
-    return !(can_split && t.tile == kTile128x128 && t.tail_tiles_m == 0 && gemm_slices(c, R, 0, t.big_tiles_m, cols, K, b_kmajor) >= 2);
+    const Tiling t = pick_tiling(rows, cols, K, can_split, one_round, tile_steps(c, R));
+    if (t.tile != kTile256x256 && t.tile != kTile128x128) return false;
+    bool alone = false;
+    if (one_round && ring_alone(t, cols, K, tile_steps(c, R))) return false;
+    return !(can_split && t.tile == kTile128x128 && t.tail_tiles_m == 0 && gemm_slices(c, R, 0, t.big_tiles_m, cols, K, b_kmajor, siblings ? nullptr : &alone) >= 2);
 }
 
 // Whether the adapter gradients of a backward call stay on the caller's stream.  On the second stream they run beside dh and
@@ -289,10 +376,18 @@ bool grads_alone(int n_train, int d_in, int d_out, bool f32, int rpad)
     return bytes <= (f32 ? 8 * MiB : (rpad <= 16 ? 5 * MiB : (rpad <= 32 ? 2 * MiB : 0)));
 }
 
+// Whether the dX GEMM of a backward call may take the tiles that fill a CU's LDS and one round of CUs (pick_tiling): not
+// where the gradient kernels run beside it on the second stream, as a CU that holds such a tile has no room for their blocks.
+// Backward call, us, with the two sizes only / all of them: 1792 rows 4096 -> 4096 86 / 88, 901 rows 4104 -> 11008 172 / 180.
+bool dx_one_round(const collm_ctx *c, int n_train, int d_in, int d_out, bool f32, int rpad)
+{
+    return c->grad_streams >= 0 ? c->grad_streams == 0 : grads_alone(n_train, d_in, d_out, f32, rpad);
+}
+
 // One GEMM over the row order `R`: a single launch, or whole rounds of large tiles followed by
 // small tiles over the remaining rows.
 hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows, int cols, int forced_tile,
-                    bool b_kmajor, hipStream_t st, bool swiglu = false)
+                    bool b_kmajor, bool one_round, hipStream_t st, bool swiglu = false)
 {
     // SwiGLU epilogue: `cols` counts gate and up columns; a tile holds half as many output columns as it is wide
     auto launch = [&](int tile) {
@@ -300,8 +395,10 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         return swiglu ? launch_gemm_swiglu(g, tile, st) : launch_gemm(g, tile, b_kmajor, st);
     };
     const bool can_split = !swiglu && c->gemm_split != 1;
+    // (the tiles between the two sizes are plain ones: a forced one stands for the size of the same height elsewhere)
+    if (forced_tile >= 0 && (swiglu || g.n_sib > 1)) forced_tile = gemm_tile_rows(forced_tile) == 256 ? kTile256x256 : kTile128x128;
     const Tiling t = forced_tile >= 0 ? Tiling{forced_tile, R.n_rows_pad / gemm_tile_rows(forced_tile), 0}
-                                      : pick_tiling(rows, cols, g.K, can_split);
+                                      : pick_tiling(rows, cols, g.K, can_split, one_round, tile_steps(c, R));
     g.tile_m_base = 0;
     g.tiles_m = t.big_tiles_m;
     g.ext_off = c->d_plan + R.off_ext_off;
@@ -310,7 +407,9 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
     auto try_split = [&](int tiles_m, int row_base, int n_rows_here, hipError_t &err) -> bool {
         if (!can_split || forced_tile >= 0) return false;
         const int tiles_n = (cols + 127) / 128;
-        const long want = gemm_slices(c, R, row_base / 128, tiles_m, cols, g.K, b_kmajor);
+        const bool whole = !swiglu && g.n_sib <= 1 && row_base == 0 && t.tail_tiles_m == 0;
+        bool alone = false;
+        const long want = gemm_slices(c, R, row_base / 128, tiles_m, cols, g.K, b_kmajor, whole ? &alone : nullptr);
         if (want < 2) return false;
         GemmArgs gs = g;
         gs.tiles_m = tiles_m;
@@ -320,6 +419,7 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         gs.part = c->d_part;
         gs.part_rows = tiles_m * 128;
         gs.part_ld = cols;
+        gs.one_per_cu = alone;
         gs.row_base = row_base;
         gs.n_rows = n_rows_here;
         err = launch_gemm_splitk(gs, n_split, b_kmajor, st);
@@ -341,8 +441,10 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         g.ext = reinterpret_cast<const ExtStep *>(c->d_plan + R.off_ext_half);
         return launch_gemm(g, kTile128x128, b_kmajor, st);
     }
+    g.one_per_cu = one_round && forced_tile < 0 && ring_alone(t, cols, g.K, tile_steps(c, R));
     e = launch(t.tile);
     if (e != hipSuccess || t.tail_tiles_m == 0) return e;
+    g.one_per_cu = 0;
     g.tile_m_base = 2 * t.big_tiles_m;
     g.tiles_m = t.tail_tiles_m;
     g.ext_off = c->d_plan + R.off_ext_off_half;
@@ -511,12 +613,14 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     for (int k = 0; k < s->n_segments; ++k)
         if (seg_is_train[k]) n_train += seg_start[k + 1] - seg_start[k];
     const bool can_split = !f32 && c->gemm_split != 1;
-    const int tile_fwd = c->tile_fwd >= 0 ? c->tile_fwd : pick_tiling(s->n_tokens, s->d_out, s->d_in, can_split && n_sib < 16).tile;
-    const int tile_bwd = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, can_split).tile;
-    const int bm_all = f32 ? 64 : gemm_tile_rows(tile_fwd);
-    const int bm_train = f32 ? 64 : gemm_tile_rows(tile_bwd);
+    count_steps(c, s, rank, seg_start, seg_adapter, seg_is_train);
+    const int tile_fwd = c->tile_fwd >= 0 ? c->tile_fwd : pick_tiling(s->n_tokens, s->d_out, s->d_in, can_split && n_sib < 16, n_sib <= 1, c->tile_steps_all).tile;
     int rmax = 1;
     for (int a = 0; a < s->n_adapters; ++a) rmax = std::max(rmax, rank[a]);
+    const bool one_round_dx = dx_one_round(c, n_train, s->d_in, s->d_out, f32, round_up(rmax, kKStep));
+    const int tile_bwd = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, can_split, one_round_dx, c->tile_steps_train).tile;
+    const int bm_all = f32 ? 64 : gemm_tile_rows(tile_fwd);
+    const int bm_train = f32 ? 64 : gemm_tile_rows(tile_bwd);
     // All rows of an adapter take the tiled rank-wide pass when ranks reach 64: there an adapter's table
     // outweighs 16 or 32 rows of activations several times, and the tiled pass fetches it once per 128 rows.
     // Narrow ranks waste its 128 columns of matrix work; measured, it still pays for the dh pass (tables
@@ -1008,7 +1112,7 @@ int collm_debug_host_tiling(int rows, int cols, int K, int can_split, int32_t *t
 {
     if (!tile || !big_tiles_m || !tail_tiles_m || !tail_cols) return COLLM_E_NULL;
     if (rows < 0 || cols <= 0 || K <= 0) return COLLM_E_SHAPE;
-    const Tiling t = pick_tiling(rows, cols, K, can_split != 0);
+    const Tiling t = pick_tiling(rows, cols, K, can_split != 0, false, 0);
     *tile = t.tile;
     *big_tiles_m = t.big_tiles_m;
     *tail_tiles_m = t.tail_tiles_m;
@@ -1020,7 +1124,24 @@ int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int
 {
     if (!slices) return COLLM_E_NULL;
     if (tiles_m <= 0 || cols <= 0 || K <= 0 || steps < 0 || workspace_bytes < 0) return COLLM_E_SHAPE;
-    *slices = (int32_t)std::max(1L, gemm_slices(-1, workspace_bytes, tiles_m, cols, K, b_kmajor != 0, steps));
+    *slices = (int32_t)std::max(1L, gemm_slices(-1, workspace_bytes, tiles_m, cols, K, b_kmajor != 0, steps, nullptr));
+    return COLLM_OK;
+}
+
+int collm_debug_host_plain_gemm(int rows, int cols, int K, int b_kmajor, int steps, int64_t workspace_bytes, int32_t *tile, int32_t *slices,
+                                int32_t *one_per_cu)
+{
+    if (!tile || !slices || !one_per_cu) return COLLM_E_NULL;
+    if (rows <= 0 || cols <= 0 || K <= 0 || steps < 0 || workspace_bytes < 0) return COLLM_E_SHAPE;
+    const Tiling t = pick_tiling(rows, cols, K, true, true, (int)((steps + (rows + 127) / 128 - 1) / ((rows + 127) / 128)));
+    *tile = t.tile;
+    *slices = 1;
+    *one_per_cu = 0;
+    if (t.tile == kTile128x128 && t.tail_tiles_m == 0) {
+        bool alone = false;
+        *slices = (int32_t)std::max(1L, gemm_slices(-1, workspace_bytes, t.big_tiles_m, cols, K, b_kmajor != 0, steps, &alone));
+        *one_per_cu = *slices > 1 ? alone : ring_alone(t, cols, K, steps / t.big_tiles_m);
+    }
     return COLLM_OK;
 }
 
@@ -1071,7 +1192,7 @@ int collm_debug_host_row_order(const collm_shape *s, const int32_t *rank, const 
 int collm_debug_set_tiles(collm_ctx *c, int fwd_tile, int bwd_tile)
 {
     if (!c) return COLLM_E_NULL;
-    auto ok = [](int t) { return t == -1 || t == kTile256x256 || t == kTile128x128; };
+    auto ok = [](int t) { return t >= -1 && t <= kTile256x192; };
     if (!ok(fwd_tile) || !ok(bwd_tile)) return COLLM_E_SHAPE;
     c->tile_fwd = fwd_tile;
     c->tile_bwd = bwd_tile;
@@ -1197,7 +1318,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // counterpart in the other direction uses
     const bool tr = s->layout == COLLM_LAYOUT_OUT_IN;
     rc = run_skinny(c, s, L.all, x, s->d_in, L.off_A_ptr, tr, h_save, c->max_rank, c->max_rank, 1, 1.0f,
-                    c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, L.all, s->n_tokens, s->d_out, s->d_in, tr)) ? W : nullptr,
+                    c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, L.all, s->n_tokens, s->d_out, s->d_in, tr, P <= 1, P > 1)) ? W : nullptr,
                     (uint64_t)s->d_in * s->d_out * 2);
     if (rc != COLLM_OK) return rc;
 
@@ -1236,7 +1357,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
             g.n_rows = s->n_tokens;
             HIP_TRY(launch_gemm_f32(g, tr, st));
         } else {
-            HIP_TRY(run_gemm(c, g, L.all, s->n_tokens, s->d_out, c->tile_fwd, tr, st, swiglu));
+            HIP_TRY(run_gemm(c, g, L.all, s->n_tokens, s->d_out, c->tile_fwd, tr, P <= 1, st, swiglu));
         }
     }
     return COLLM_OK;
@@ -1343,6 +1464,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // Small batches stay on the caller's stream (see grads_alone).
     const bool alone = c->grad_streams >= 0 ? c->grad_streams == 0 : grads_alone(n_train, s->d_in, s->d_out, f32, L.rpad);
     const bool overlap = dA && !alone && !c->profile;
+    const bool one_round = dx_one_round(c, n_train, s->d_in, s->d_out, f32, L.rpad);
     hipStream_t gs = overlap ? c->side : st;
     GradArgs ga{};
     const int64_t esz = f32 ? 4 : 2;
@@ -1350,7 +1472,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     ga.items = reinterpret_cast<const GradItem *>(c->d_plan + L.off_grad);
     ga.accumulate = accumulate ? 1 : 0;
     if (overlap && dx && !f32) {
-        const int tile = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, c->gemm_split != 1).tile;
+        const int tile = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, c->gemm_split != 1, one_round, c->tile_steps_train).tile;
         ga.beside_gemm = tile == kTile128x128 ? 1 : 0;
     }
 
@@ -1486,7 +1608,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         // dh came out of the pass over dy above, together with dB
     } else if (P == 1) {
         rc = run_skinny(c, s, L.train, dy, s->d_out, L.off_B_ptr, !tr, c->d_dh32, L.rpad, L.rpad, 0, s->scale,
-                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, L.train, n_train, s->d_in, s->d_out, !tr) ? W : nullptr,
+                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, L.train, n_train, s->d_in, s->d_out, !tr, one_round, false) ? W : nullptr,
                         (uint64_t)s->d_in * s->d_out * 2);
         if (rc != COLLM_OK) return rc;
     } else {
@@ -1558,7 +1680,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
             g.n_rows = n_train;
             HIP_TRY(launch_gemm_f32(g, !tr, st));
         } else {
-            HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, st));
+            HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, one_round, st));
         }
     }
     if (overlap) HIP_TRY(hipStreamWaitEvent(st, c->ev_join, 0));

@@ -28,7 +28,7 @@ extern thread_local LaunchEvents g_launch_events;
         }                                                                                                         \
     } while (0)
 
-enum { kTile256x256 = 0, kTile128x128 = 2 };  // GEMM tile shapes (rows x columns of the output)
+enum { kTile256x256 = 0, kTile256x128 = 1, kTile128x128 = 2, kTile128x192 = 3, kTile256x192 = 4 };  // GEMM tile shapes (rows x columns of the output)
 
 // out[tok(m)][n] = sum_k a[tok(m)][k] * b(k, n)  +  sum over the row tile's extension steps
 struct GemmArgs {
@@ -43,6 +43,7 @@ struct GemmArgs {
     int tiles_m, tiles_n;
     int tile_m_base;          // first row tile of this launch (a GEMM may be split over launches by rows)
     int band_m;               // row tiles per band of the tile order (0 = one band); set by the launcher
+    int one_per_cu;           // 128x128 tiles: at most one block per CU, run with the deeper ring of stages
     int n_base;               // first output column of this launch (... or by columns); a multiple of 8
     const int32_t *row_tok;   // [tiles_m * BM]
     const int32_t *ext_off;   // [tiles_m + 1]

@@ -169,6 +169,11 @@ template <int N> __device__ __forceinline__ void wait_dma_but() { asm volatile("
 // every load and LDS read of this wave has completed, then meet the other waves
 __device__ __forceinline__ void drain_and_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Chunk swizzle of a 64-column tile of an N-major operand (rows of 128 bytes; a transposing read takes 4 rows x 32 bytes per
+// lane group, the groups 8 rows apart): pairs of chunks move by bits 1 and 3 of the row, so that the 16 pieces of
+// a read fall on all banks evenly.
+__device__ __forceinline__ int sub_swz(int row) { return (((row >> 1) & 1) | (((row >> 3) & 1) << 1)) << 1; }
+
 // Four consecutive extension steps of a row tile, unpacked into wave-uniform registers.
 struct ExtBatch {
     uint32_t kr[kExtBatch];    // koff | rank << 16   (0: no step)
@@ -209,6 +214,24 @@ struct DmaSlots {
     }
 };
 
+// The same for the tiles with a ring of stages: the loads of a tile ride evenly spaced behind the first SPAN of the MFMAs
+// that follow the barrier (PRE MFMAs into phase 3).  slot[0]: phase 3, slot[1 .. 3]: phases 0 .. 2; n0: loads in phase 3.
+template <int NM, int PRE, int ND, int SPAN>
+struct RingSlots {
+    int slot[4][NM];
+    int n0;
+    constexpr RingSlots() : slot{}, n0(0)
+    {
+        for (int ph = 0; ph < 4; ++ph)
+            for (int m = 0; m < NM; ++m) slot[ph][m] = -1;
+        for (int d = 0; d < ND; ++d) {
+            const int t = PRE + d * SPAN / ND;  // counted from phase 3's first MFMA
+            slot[t / NM][t % NM] = d;
+            if (t < NM) ++n0;
+        }
+    }
+};
+
 // Block `blk` of `n_blk` reads its contiguous share of `bytes` bytes at `base` (16-byte aligned), sixteen 16-byte loads
 // per thread in flight (the share of a block is mostly one such round: what counts is that everything is asked for
 // at once), and drops them.  The values are folded into a word that is stored only if it takes a value the data
@@ -232,6 +255,10 @@ __device__ __forceinline__ void warm_cache(const void *base, uint64_t bytes, int
     }
     if (fold == 0x9e3779b9u && bytes == 1) *reinterpret_cast<volatile uint32_t *>(const_cast<void *>(base)) = fold;
 }
+
+constexpr int kRingStages = 4;  // of the 128x128 tile run by one block per CU
+// whether the rows' area of the extension has a place of its own behind the stages
+constexpr bool rows_early(int bm, int bn, int rs) { return rs ? rs == 2 : bm * bn == 256 * 256; }
 
 // PARTIAL: the same tile machinery as a rank-wide pass over long runs of one adapter's rows.  A
 // block takes one item (up to BM rows of one adapter, blockIdx.x), BN of the adapter's rank
@@ -257,10 +284,15 @@ __device__ __forceinline__ void warm_cache(const void *base, uint64_t bytes, int
 // (fewer, cheaper fragment reads) the four stages do.
 constexpr int kWideStages = 4;
 constexpr int wide_stages(bool t_kmajor) { return t_kmajor ? kWideStages : 2; }
+// RS: 0, or the number of LDS stages of a ring in which the loads of RS - 1 tiles are in flight (one block per CU).
 template <int BM, int BN, int WGM, int WGN, bool B_KMAJOR, bool PARTIAL = false, bool SWIGLU = false, bool SPLITK = false,
-          bool SIBS = false>
-__global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 128) ? 2 : 1) gemm_lora_kernel(GemmArgs p)
+          bool SIBS = false, int RS = 0>
+__global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN == 128 * 128) ? 2 : 1) gemm_lora_kernel(GemmArgs p)
 {
+    constexpr int NST = RS ? RS : 2;
+    static_assert(RS == 0 || (!PARTIAL && !SIBS), "ring of stages: plain tiles");
+    // an N-major second operand whose width is no multiple of 128 is kept as 64-column tiles side by side
+    constexpr bool SUB = !B_KMAJOR && BN % 128 != 0;
     // the GEMM tiles run the 16x16x32 MFMA form, the rank-wide pass the 32x32x16 one
     constexpr bool M16 = !PARTIAL;
     static_assert(!SWIGLU || (!B_KMAJOR && !PARTIAL && WGN == 2), "SwiGLU epilogue: N-major, two wave columns");
@@ -276,14 +308,14 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
     constexpr int BTILE = B_KMAJOR ? BN * 128 : 64 * BPITCH;
     constexpr int ATILE = BM * 128;
     constexpr int STAGE = ATILE + BTILE;
-    // LDS map [A0 A1 B0 B1], so that the fragment reads of both stages lie within the immediate-offset range of
+    // LDS map [A0 A1 .. B0 B1 ..], so that the fragment reads of both stages lie within the immediate-offset range of
     // one per-lane base.
     constexpr int A_ST1 = ATILE;
-    constexpr int B_ST0 = 2 * ATILE;
-    constexpr int B_ST1 = 2 * ATILE + BTILE;
+    constexpr int B_ST0 = NST * ATILE;
+    constexpr int B_ST1 = NST * ATILE + BTILE;
     constexpr int ACH = BM * 8 / NT;   // 16-byte chunks of the row tile per thread
     constexpr int BCH = BN * 8 / NT;   // chunks of the second operand's tile per thread
-    constexpr int NG = BN / 8;         // chunks per N-major row
+    constexpr int NG = BN % 128 ? 8 : BN / 8;  // chunks per N-major row
     static_assert((BM * 8) % NT == 0 && (BN * 8) % NT == 0 && NT % NG == 0 && (NT / NG) % 4 == 0, "tile/thread mismatch");
     static_assert(ACH % 4 == 0 || ACH == 2, "row chunks are moved in four (or two) parts per K step");
     extern __shared__ __align__(16) uint8_t smem[];
@@ -448,10 +480,11 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
     uint32_t bstep = 0;  // N-major: advance of one K step, zero for columns beyond N
     const uint32_t bstep_u = 64u * ldb * 2u;  // the same as a wave-uniform value
     const int bng = tid % NG, bk0 = tid / NG;
-    const int bcl = bng ^ ((bk0 & 3) << 2);  // N-major: source chunk of this thread (same for all i)
+    const int bcl = SUB ? bng ^ sub_swz(bk0) : bng ^ ((bk0 & 3) << 2);  // N-major: source chunk of this thread (same for all i)
     // 16x16x32 form: a transposing read takes K rows r .. r + 3 in one lane group and r + 8 .. r + 11 in the next,
     // so rows 8-15 of every 16 are stored with their chunk pairs swapped: the source chunk then depends on i
-    auto bcl_of = [&](int i) { return M16 ? bcl ^ ((((bk0 + i * (NT / NG)) >> 3) & 1) << 1) : bcl; };
+    // (64-column tiles: loads i = 2 t and 2 t + 1 fill K rows 0-31 and 32-63 of tile t)
+    auto bcl_of = [&](int i) { return SUB ? (i >> 1) * 8 + bcl : M16 ? bcl ^ ((((bk0 + i * (NT / NG)) >> 3) & 1) << 1) : bcl; };
     if constexpr (B_KMAJOR) {
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -464,7 +497,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
         bstep = on ? 64u * ldb * 2u : 0u;
 #pragma unroll
         for (int i = 0; i < NB; ++i)
-            boff[i] = col_on(bcl_of(i) * 8) ? ((uint32_t)(bk0 + i * (NT / NG)) * ldb + src_col(bcl_of(i) * 8)) * 2u : kOob;
+            boff[i] = col_on(bcl_of(i) * 8) ? ((uint32_t)(bk0 + (SUB ? i & 1 : i) * (NT / NG)) * ldb + src_col(bcl_of(i) * 8)) * 2u : kOob;
     }
     // byte offset of the tile that starts at K index k0 = 64 kc, for chunk i; tiles that reach
     // beyond K mask their tail (K-major) or run off the end of the buffer (N-major rows)
@@ -502,12 +535,12 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
         constexpr bool even = decltype(even_c)::value;
         const int k0 = kc << 6;
         if (idx < ACH) {
-            const uint32_t dst = lds_wave + (stage ? A_ST1 : 0) + idx * (NT / 64) * 1024;
+            const uint32_t dst = lds_wave + stage * ATILE + idx * (NT / 64) * 1024;
             if constexpr (even) dma16s(ra_t, aoff[idx], (uint32_t)k0 * 2u, dst);
             else dma16(ra_t, a_src(idx, k0, false), dst);
         } else {
             const int i = idx - ACH;
-            const uint32_t dst = lds_wave + (stage ? B_ST1 : B_ST0) + i * (NT / 64) * 1024;
+            const uint32_t dst = lds_wave + B_ST0 + stage * BTILE + i * (NT / 64) * 1024;
             if constexpr (even) dma16s(rb_t, boff[i], B_KMAJOR ? (uint32_t)k0 * 2u : (uint32_t)kc * bstep_u, dst);
             else dma16(rb_t, b_src(i, k0, kc, false), dst);
         }
@@ -550,11 +583,21 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
             // table rows are rank indices: B_a[q][n]; tile row 16 j + i is rank index koff_j + i.
             // All lanes of a load belong to one step, whose table is the load's buffer: rank
             // indices beyond the rank lie beyond it.
-            static_assert(16 % (NT / NG) == 0 || (NT / NG) % 16 == 0, "a direct load must not straddle two steps");
+            static_assert(SUB || 16 % (NT / NG) == 0 || (NT / NG) % 16 == 0, "a direct load must not straddle two steps");
             const int i = D - ACH;
-            const int j = (i * (NT / NG)) >> 4;
-            const int k = bk0 + i * (NT / NG);
-            uint32_t rk = bt.kr[j] >> 16, koff = bt.kr[j] & 0xffffu;
+            const int k = bk0 + (SUB ? i & 1 : i) * (NT / NG);
+            const int j = SUB ? 0 : (i * (NT / NG)) >> 4;
+            uint32_t kr_j = bt.kr[j];
+            uint64_t tab_j = bt.tab[j];
+            if constexpr (SUB) {
+                // 32 K rows per load of the block: two steps, each the part of two waves
+                const int j2 = k >> 4;
+                auto uni = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+                kr_j = uni(pick(j2, bt.kr[0], bt.kr[1], bt.kr[2], bt.kr[3]));
+                tab_j = uni(pick(j2, (uint32_t)bt.tab[0], (uint32_t)bt.tab[1], (uint32_t)bt.tab[2], (uint32_t)bt.tab[3]));
+                tab_j |= (uint64_t)uni(pick(j2, (uint32_t)(bt.tab[0] >> 32), (uint32_t)(bt.tab[1] >> 32), (uint32_t)(bt.tab[2] >> 32), (uint32_t)(bt.tab[3] >> 32))) << 32;
+            }
+            uint32_t rk = kr_j >> 16, koff = kr_j & 0xffffu;
             bool mine = true;
             if constexpr (SWIGLU) {
                 // the step belongs to the gate sibling (first half of the ranks) or the up sibling
@@ -564,7 +607,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
                 mine = (bcl * 8 >= BN / 2) == up;
             }
             const int bcl_i = bcl_of(i);
-            const i32x4 rt = make_rsrc_words(reinterpret_cast<const void *>(bt.tab[j]), rk * (uint32_t)p.ext_ld * 2u);
+            const i32x4 rt = make_rsrc_words(reinterpret_cast<const void *>(tab_j), rk * (uint32_t)p.ext_ld * 2u);
             const uint32_t off = (mine && col_on(bcl_i * 8)) ? ((koff + (uint32_t)(k & 15)) * (uint32_t)p.ext_ld + (uint32_t)src_col(bcl_i * 8)) * 2u : kOob;
             dma16(rt, off, lds_wave + b_base + i * (NT / 64) * 1024);
         } else {
@@ -615,9 +658,9 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
     };
 
     // The 256x256 tiles use what the main loop's two stages leave of the LDS (32 KiB of 160): the rows' area of the
-    // extension lies behind them and is loaded before the main loop starts.
-    constexpr bool ROWS_EARLY = !PARTIAL && !SIBS && BM * BN == 256 * 256;
-    constexpr uint32_t XA_EARLY = 2 * STAGE;
+    // extension lies behind them and is loaded before the main loop starts.  (256x192 with a ring of two likewise.)
+    constexpr bool ROWS_EARLY = !PARTIAL && !SIBS && rows_early(BM, BN, RS);
+    constexpr uint32_t XA_EARLY = NST * STAGE;
     // The load of the step records is waited for behind the direct loads of the first tile (the records' chain of
     // two loads is longer than the one that leads to those loads, and nothing needs the records before the main
     // loop's last tiles).
@@ -664,7 +707,8 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
 #pragma unroll
         for (int ni = 0; ni < NI16; ++ni) {
             const int col = wn * WN + ni * 16 + (r16 & 3) * 4;
-            btr16[ni] = krow * BPITCH + ((((col >> 3) ^ ((krow & 3) << 2) ^ (((krow >> 3) & 1) << 1))) << 4) + (col & 7) * 2;
+            if constexpr (SUB) btr16[ni] = (col >> 6) * 8192 + krow * 128 + ((((col & 63) >> 3) ^ sub_swz(krow)) << 4) + (col & 7) * 2;
+            else btr16[ni] = krow * BPITCH + ((((col >> 3) ^ ((krow & 3) << 2) ^ (((krow >> 3) & 1) << 1))) << 4) + (col & 7) * 2;
         }
     }
     // second-operand fragment ni of the 32-wide K step ks of the tile at tb
@@ -672,15 +716,16 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
         if constexpr (B_KMAJOR) {
             b8[ni] = lds_frag(tb, wn * WN + ni * 16 + r16, ks * 4 + kq);
         } else {
-            const uint8_t *src = tb + btr16[ni] + ks * 32 * BPITCH;
+            constexpr int P = SUB ? 128 : BPITCH;
+            const uint8_t *src = tb + btr16[ni] + ks * 32 * P;
             const bf16x4 lo = lds_tr(src);
-            const bf16x4 hi = lds_tr(src + 4 * BPITCH);
+            const bf16x4 hi = lds_tr(src + 4 * P);
             b8[ni] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         }
     };
     auto read16 = [&](int stage, int ph, int j) {
-        const uint8_t *ta = smem + (stage ? A_ST1 : 0);
-        const uint8_t *tb = smem + (stage ? B_ST1 : B_ST0);
+        const uint8_t *ta = smem + stage * ATILE;
+        const uint8_t *tb = smem + B_ST0 + stage * BTILE;
         if (j < MH) a4[ph & 1][j] = lds_frag(ta, wm * WM + ((ph & 1) * MH + j) * 16 + r16, (ph >> 1) * 4 + kq);
         else read_b16(tb, ph >> 1, j - MH);
     };
@@ -691,21 +736,22 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
     // The reads for phase nph that ride behind MFMA m of the phase before it (`first`: the first MFMA they may
     // follow).  Only two or three other instructions fit behind a 16-cycle MFMA, so an MFMA carries at most one
     // memory instruction: the direct loads sit behind MFMAs 0, 4, 8, .. (DmaSlots), the row fragments behind
-    // first + 2, + 6, .., the second operand's behind the last MFMA that uses the register (3, 7, ..: odd).
+    // first + 2, + 6, .., the second operand's behind the last MFMA that uses the register (3, 7, ..: odd).  Phases of
+    // 16 MFMAs (wave tiles of 128x64) have room for the row fragments early in the phase only.
     auto reads16 = [&](int stage, int nph, int m, int first) {
 #pragma unroll
         for (int i = 0; i < MH; ++i)
-            if (m == (MH == 4 ? first + 2 + 4 * i : first + 2 * i)) read16(stage, nph, i);
+            if (m == (MH == 4 ? (NM16 == 16 ? (first ? first + 1 + i + (i > 1) : 1 + 2 * i) : first + 2 + 4 * i) : first + 2 * i)) read16(stage, nph, i);
         if ((nph & 1) == 0) {
 #pragma unroll
             for (int ni = 0; ni < NI16; ++ni) {
-                const int last_use = ni * MH + MH - 1, early = MH == 4 ? first + 1 + 2 * ni : first + ni;
+                const int last_use = ni * MH + MH - 1, early = MH == 4 ? first + (NM16 > 16) + 2 * ni : first + ni;
                 const int slot = last_use > early ? last_use : early;
                 if (m == slot) read16(stage, nph, MH + ni);
             }
         }
     };
-    static_assert(!M16 || (MH == 4 && NM16 / 4 + 2 + 4 * (MH - 1) < NM16) || (MH == 2 && NM16 == 8), "the read slots above are laid out for four (or two) row blocks per half");
+    static_assert(!M16 || (MH == 4 && (NM16 == 16 || NM16 / 4 + 2 + 4 * (MH - 1) < NM16)) || (MH == 2 && NM16 >= 8), "the read slots above are laid out for four (or two) row blocks per half");
     // N-major operand: byte offset of this lane's transposing read inside the tile for K step 0
     uint32_t btr[NI];
     {
@@ -854,8 +900,71 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
             }
             wait_dma();  // loads of tiles beyond the last one fetch nothing but still signal completion
             };
-            if (k_even) pipeline(std::true_type{});
-            else pipeline(std::false_type{});
+            // Ring of NST stages: the same phases, but the tile's loads go to the stage of the tile before (free since that
+            // tile's barrier), NST - 1 tiles ahead.  With three stages or more a load has a whole K tile or more to land, so the
+            // loads are spread over all phases; with two, over the first 5/8.  Stages are addressed at run time: one loop body.
+            // What it is for: one block per CU, whose loads nothing else hides.  Cycles per K tile (time stamps): 128x128 with
+            // two stages 1280, 128x192 with three 1230, 256x128 with three 1450; with the weight coming from memory 128x128
+            // takes 0.85 us a K tile with two stages, 128x192 0.65 and 256x128 0.72 with three.
+            constexpr RingSlots<NM16, PRE, ND, (4 * NM16 - PRE) * (NST > 2 ? 8 : 5) / 8> RG{};
+            auto ring = [&](auto even_c) {
+                i32x4 ra_t, rb_t;
+#pragma unroll
+                for (int t = 0; t < NST; ++t) {
+                    ra_t = tile_rsrc(ra_w, t);
+                    rb_t = tile_rsrc(rb_w, t);
+#pragma unroll
+                    for (int d = 0; d < (t + 1 < NST ? ND : RG.n0); ++d) dma_chunk(even_c, d, t, t, ra_t, rb_t);
+                }
+                records_are_in();
+                wait_dma_but<(NST - 2) * ND + RG.n0>();
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < MH + NI16; ++j) read16(0, 0, j);
+                int cur = 0, nxt = 1, far = NST - 1;
+                for (int kc = 0; kc < nk; ++kc) {
+#pragma unroll
+                    for (int ph = 0; ph < 3; ++ph) {
+#pragma unroll
+                        for (int m = 0; m < NM16; ++m) {
+                            mma16(ph, m);
+                            reads16(cur, ph + 1, m, 0);
+                            if (RG.slot[ph + 1][m] >= 0) dma_chunk(even_c, RG.slot[ph + 1][m], far, kc + NST - 1, ra_t, rb_t);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+#pragma unroll
+                    for (int m = 0; m < PRE; ++m) {
+                        mma16(3, m);
+                        if (m == 0) ra_t = tile_rsrc(ra_w, kc + NST);
+                        if (m == 1) rb_t = tile_rsrc(rb_w, kc + NST);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    // tile kc + 1 has landed (loads complete in order; those of the tiles behind it are still on their way)
+                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NST - 2) * ND) : "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int m = PRE; m < NM16; ++m) {
+                        mma16(3, m);
+                        reads16(nxt, 0, m, PRE);
+                        if (RG.slot[0][m] >= 0) dma_chunk(even_c, RG.slot[0][m], cur, kc + NST, ra_t, rb_t);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    far = cur;
+                    cur = nxt;
+                    nxt = nxt + 1 == NST ? 0 : nxt + 1;
+                }
+                mfma16_settle();
+                wait_dma();
+            };
+            if constexpr (RS > 0) {
+                if (k_even) ring(std::true_type{});
+                else ring(std::false_type{});
+            } else {
+                if (k_even) pipeline(std::true_type{});
+                else pipeline(std::false_type{});
+            }
         }
         __syncthreads();
     }
@@ -946,9 +1055,9 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
         // own s h (rows of different adapters side by side, what lies beyond a row's rank is never used), a step
         // reads its fragments at its own rank offset and clears the rows outside its row range in registers.
         // Only the tables stream: three areas, the loads of two batches in flight while one multiplies.
-        static_assert(ATILE >= BTILE, "a table area must fit the place of a row area");
+        static_assert(NST > 2 || ATILE >= BTILE, "a table area must fit the place of a row area");
         const uint32_t xa = ROWS_EARLY ? XA_EARLY : 0;
-        uint32_t t_cur = B_ST0, t_nxt = B_ST1, t_far = A_ST1;
+        uint32_t t_cur = B_ST0, t_nxt = B_ST1, t_far = NST > 2 ? B_ST1 + BTILE : A_ST1;
         const int wrow0 = __builtin_amdgcn_readfirstlane(wm * WM);
         auto issue_rows = [&](int g) {
 #pragma unroll
@@ -1084,7 +1193,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
         }
     } else {
         constexpr int EP = WN * 2 + 16;          // bytes per staged row
-        constexpr int LPR = WN / 8, RPI = 64 / LPR;  // lanes per row, rows per store instruction
+        constexpr int LPR = WN / 8;              // lanes per row
         uint8_t *ep = smem + wave * (WM * EP);
         if constexpr (SWIGLU) {
             // Each wave of a pair finishes half of the pair's rows: the gate wave the first half (it receives their
@@ -1156,6 +1265,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
                 }
                 __builtin_amdgcn_wave_barrier();
                 uint16_t *__restrict__ Out = reinterpret_cast<uint16_t *>(p.out);
+                constexpr int RPI = 64 / LPR;  // rows per store instruction
                 const int rr = lane / LPR, cc = lane % LPR;
                 const int n = n0 + cc * 8;
 #pragma unroll 4
@@ -1187,11 +1297,12 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && BM * BN == 128 * 1
         }
         __builtin_amdgcn_wave_barrier();
         uint16_t *__restrict__ Out = reinterpret_cast<uint16_t *>(p.out);
-        const int rr = lane / LPR, cc = lane % LPR;
-        const int n = n0 + wn * WN + cc * 8;
+        static_assert((WM * LPR) % 64 == 0, "whole store instructions");
 #pragma unroll 4
-        for (int it = 0; it < WM / RPI; ++it) {
-            const uint8_t *erow = ep + (it * RPI + rr) * EP;
+        for (int it = 0; it < WM * LPR / 64; ++it) {
+            const int rr = (it * 64 + lane) / LPR, cc = (it * 64 + lane) % LPR;
+            const int n = n0 + wn * WN + cc * 8;
+            const uint8_t *erow = ep + rr * EP;
             const uint4 v = *reinterpret_cast<const uint4 *>(erow + cc * 16);
             const int tok = *reinterpret_cast<const int32_t *>(erow + WN * 2);
             if (tok >= 0 && n < N) *reinterpret_cast<uint4 *>(Out + (int64_t)tok * p.ldo + n) = v;
@@ -2006,18 +2117,19 @@ void host_tile_order(int tiles_m, int tiles_n, int band, int32_t *tm, int32_t *t
     }
 }
 
-template <int BM, int BN, bool KM, bool SWIGLU = false, bool SIBS = false>
+template <int BM, int BN, bool KM, bool SWIGLU = false, bool SIBS = false, int RS = 0>
 static hipError_t launch_gemm_t(const GemmArgs &a, hipStream_t st)
 {
     // four waves, 2 x 2
     constexpr int NT = 256;
-    // two stages; the 256x256 tiles keep the rows' area of the extension behind them
-    constexpr int stage_bytes = 2 * (BM + BN) * 128 + ((!SIBS && BM * BN == 256 * 256) ? BM * 128 : 0);
+    // two stages (or the ring's); some tiles keep the rows' area of the extension behind them
+    constexpr int stage_bytes = (RS ? RS : 2) * (BM + BN) * 128 + ((!SIBS && rows_early(BM, BN, RS)) ? BM * 128 : 0);
     constexpr int epi_bytes = BM * BN * 2 + BM * 2 * 16;  // per wave (BM/2) rows of (BN/2) * 2 + 16 bytes
     constexpr int smem = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
-    static_assert(BM * BN != 128 * 128 || smem == kSmallTileLds, "what grad_lds assumes");
+    static_assert(RS || BM * BN != 128 * 128 || smem == kSmallTileLds, "what grad_lds assumes");
+    static_assert(smem <= 160 * 1024, "LDS of a CU");
     static_assert(!SWIGLU || smem >= BM * (BN / 2) * 4, "the up halves of all rows pass through LDS as fp32");
-    auto kern = gemm_lora_kernel<BM, BN, 2, 2, KM, false, SWIGLU, false, SIBS>;
+    auto kern = gemm_lora_kernel<BM, BN, 2, 2, KM, false, SWIGLU, false, SIBS, RS>;
     static bool attr_done = false;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -2052,7 +2164,16 @@ hipError_t launch_gemm(const GemmArgs &a, int tile_cfg, bool b_kmajor, hipStream
     case kTile256x256:
         return b_kmajor ? launch_gemm_t<256, 256, true>(a, st) : launch_gemm_t<256, 256, false>(a, st);
     case kTile128x128:
+        if (a.one_per_cu)
+            return b_kmajor ? launch_gemm_t<128, 128, true, false, false, kRingStages>(a, st)
+                            : launch_gemm_t<128, 128, false, false, false, kRingStages>(a, st);
         return b_kmajor ? launch_gemm_t<128, 128, true>(a, st) : launch_gemm_t<128, 128, false>(a, st);
+    case kTile128x192:
+        return b_kmajor ? launch_gemm_t<128, 192, true, false, false, 3>(a, st) : launch_gemm_t<128, 192, false, false, false, 3>(a, st);
+    case kTile256x128:
+        return b_kmajor ? launch_gemm_t<256, 128, true, false, false, 3>(a, st) : launch_gemm_t<256, 128, false, false, false, 3>(a, st);
+    case kTile256x192:
+        return b_kmajor ? launch_gemm_t<256, 192, true, false, false, 2>(a, st) : launch_gemm_t<256, 192, false, false, false, 2>(a, st);
     default:
         return hipErrorInvalidValue;
     }
@@ -2111,9 +2232,11 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p, int n_spli
 hipError_t launch_gemm_splitk(const GemmArgs &a, int n_split, bool b_kmajor, hipStream_t st)
 {
     if (n_split < 1 || !a.part || a.k_per_split % 64 != 0 || a.part_ld < a.N || a.part_ld % 4 != 0) return hipErrorInvalidValue;
-    constexpr int smem = kSmallTileLds;
     const int tiles = a.tiles_m * a.tiles_n;
     if (tiles <= 0) return hipSuccess;
+    // one block per CU: the ring of four stages (see gemm_lora_kernel); more blocks: two stages, two blocks per CU
+    const bool ring = a.one_per_cu && a.n_sib <= 1;
+    const int smem = ring ? kRingStages * (128 + 128) * 128 : kSmallTileLds;
     auto launch = [&](auto kern) -> hipError_t {
         static bool attr_done = false;
         if (!attr_done) {
@@ -2126,6 +2249,9 @@ hipError_t launch_gemm_splitk(const GemmArgs &a, int n_split, bool b_kmajor, hip
         return hipGetLastError();
     };
     if (a.n_sib > 1) return b_kmajor ? hipErrorInvalidValue : launch(gemm_lora_kernel<128, 128, 2, 2, false, false, false, true, true>);
+    if (ring)
+        return b_kmajor ? launch(gemm_lora_kernel<128, 128, 2, 2, true, false, false, true, false, kRingStages>)
+                        : launch(gemm_lora_kernel<128, 128, 2, 2, false, false, false, true, false, kRingStages>);
     return b_kmajor ? launch(gemm_lora_kernel<128, 128, 2, 2, true, false, false, true>)
                     : launch(gemm_lora_kernel<128, 128, 2, 2, false, false, false, true>);
 }
@@ -2149,8 +2275,11 @@ hipError_t launch_gemm_swiglu(const GemmArgs &a, int tile_cfg, hipStream_t st)
     }
 }
 
-int gemm_tile_rows(int tile_cfg) { return tile_cfg == kTile128x128 ? 128 : 256; }
-int gemm_tile_cols(int tile_cfg) { return tile_cfg == kTile256x256 ? 256 : 128; }
+int gemm_tile_rows(int tile_cfg) { return tile_cfg == kTile256x256 || tile_cfg == kTile256x128 || tile_cfg == kTile256x192 ? 256 : 128; }
+int gemm_tile_cols(int tile_cfg)
+{
+    return tile_cfg == kTile256x256 ? 256 : (tile_cfg == kTile128x192 || tile_cfg == kTile256x192 ? 192 : 128);
+}
 
 template <int RP, bool KM, int RT>
 static hipError_t launch_skinny_t(const SkinnyArgs &a, int n_items, int n_split, hipStream_t st)

@@ -522,6 +522,45 @@ def test_many_extension_steps_in_one_row_tile(transposed):
         ctx.close()
 
 
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("tile", [binding.TILE_256x128, binding.TILE_128x192, binding.TILE_256x192])
+def test_tiles_between_the_two_sizes(tile, transposed):
+    # Ring of LDS stages: contractions of 1, 2, 3, 4 and 9 K tiles (fewer than the stages, every position of the ring), K no
+    # multiple of 64, columns one chunk beyond a tile and short of one, rows of several row tiles; ranks that are no multiples of 8 or
+    # above 64 (several groups of extension steps), more than 64 steps in a tile; forward and dX.
+    for d_in, d_out, ranks in [(64, 200, [16]), (128, 392, [8, 24]), (136, 192, [12, 20]), (256, 184, [128, 256] * 6), (576, 136, [5, 64, 40])]:
+        n = len(ranks)
+        lens = [1, 300, 18] * n
+        ads, trn = [a for a in range(n) for _ in range(3)], [0, 1, 0] * n
+        if n > 4:
+            lens, ads, trn = [20] * n + [9], list(range(n)) + [-1], [1, 1, 0] * (n // 3) + [0]
+        w = _adhoc("bf16", d_in, d_out, ranks, lens, ads, trn, scale=0.3)
+        t = wl.make_tensors(w)
+        ctx = make_ctx(w)
+        ctx.set_tiles(tile, tile)
+        layer = DeviceLayer(w, t, ctx, transposed=transposed)
+        layer.fwd(h_save=True)
+        layer.bwd(h_save=True)
+        check_full(layer, TOL[w.dtype])
+        ctx.close()
+
+
+@pytest.mark.parametrize("rows,cols,K,want", [
+    (8, 264, 1024, (2, 5, 1)), (200, 136, 1096, (2, 5, 1)), (8, 520, 776, (2, 1, 1)),   # slices of 256 and 64 values, none
+    (150, 24320, 264, (3, 1, 0)), (150, 24840, 264, (1, 1, 0)), (300, 22000, 264, (4, 1, 0))])
+@pytest.mark.parametrize("transposed", [False, True])
+def test_one_round_tiles_chosen_by_the_library(rows, cols, K, want, transposed):
+    assert binding.host_plain_gemm(rows, cols, K, transposed, steps=(rows + 127) // 128) == want
+    w = _adhoc("bf16", K, cols, [8, 16], [rows - 5, 5], [0, 1], [0, 1], scale=0.3)
+    t = wl.make_tensors(w)
+    ctx = make_ctx(w)
+    layer = DeviceLayer(w, t, ctx, transposed=transposed)
+    layer.fwd(h_save=True)
+    layer.bwd(h_save=True)
+    check_full(layer, TOL[w.dtype])
+    ctx.close()
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_random_batches_every_element(seed):
     # Seeded random batches through every path at once: ranks 1..256 (multiples of 8 or not, above 64: several

@@ -307,6 +307,25 @@ def test_gemm_slices_count_the_extension_steps(tiles_m, tiles_n, K, steps, want)
     assert binding.host_gemm_slices(tiles_m, tiles_n * 128, K, steps=steps) == want
 
 
+@pytest.mark.parametrize("rows,cols,K,steps,want", [
+    (1003, 5120, 5120, 0, (binding.TILE_128x192, 1, 0)),                   # 320 small tiles -> 216 blocks
+    (1003, 5120, 5120, 168, (binding.TILE_128x128, 1, 0)),                 # ... not with 21 steps a row tile
+    (1792, 4096, 4096, 0, (binding.TILE_256x128, 1, 0)),                   # 448 -> 224
+    (2048, 4096, 4096, 0, (binding.TILE_256x128, 1, 0)),                   # 512 -> 256
+    (2049, 4096, 4096, 0, (binding.TILE_256x192, 1, 0)),                   # 544 -> 198
+    (901, 11008, 4104, 0, (binding.TILE_256x192, 1, 0)),                   # 688 -> 232
+    (16384, 1024, 8192, 0, (binding.TILE_256x256, 1, 0)), (4096, 4096, 4096, 0, (binding.TILE_256x256, 1, 0)),
+    (733, 5408, 16384, 0, (binding.TILE_128x128, 3, 0)), (733, 5408, 16376, 0, (binding.TILE_128x192, 1, 0)),  # 258 tiles: three slices
+    (256, 16384, 1024, 0, (binding.TILE_128x128, 1, 1)), (256, 16512, 1024, 0, (binding.TILE_128x192, 1, 0)),  # 256 and 258 tiles
+    (8, 4096, 4096, 0, (binding.TILE_128x128, 8, 1)), (8, 4096, 1536, 0, (binding.TILE_128x128, 8, 1)), (8, 4096, 1024, 0, (binding.TILE_128x128, 5, 1)),
+    (8, 4096, 1016, 0, (binding.TILE_128x128, 1, 1)),                      # one block per CU, not cut
+    (64, 11008, 4096, 64, (binding.TILE_128x128, 5, 0)),                   # 86 tiles: five slices on two blocks per CU
+    (64, 4096, 4096, 64, (binding.TILE_128x128, 8, 1)), (64, 4096, 4096, 65, (binding.TILE_128x128, 8, 0)),     # the steps outweigh K
+    (714, 1536, 26112, 0, (binding.TILE_128x128, 7, 0)), (714, 1536, 4096, 0, (binding.TILE_128x128, 3, 1))])  # long contractions
+def test_plain_gemm_choice_at_the_lines_of_the_rule(rows, cols, K, steps, want):
+    assert binding.host_plain_gemm(rows, cols, K, steps=steps) == want
+
+
 def test_gemm_slices_by_layout_and_workspace():
     for K, in_out, out_in in [(20472, 1, 1), (20480, 2, 1), (28672, 2, 1)]:
         assert (binding.host_gemm_slices(4, 86 * 128, K), binding.host_gemm_slices(4, 86 * 128, K, True)) == (in_out, out_in)
