@@ -432,14 +432,14 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         // whole rounds of large tiles over the first columns, small tiles over the other columns of all rows
         const int tn_big = (cols + 255) / 256 - t.tail_cols;
         g.tiles_n = tn_big;
-        e = launch_gemm(g, kTile256x256, b_kmajor, st);
+        e = swiglu ? launch_gemm_swiglu(g, kTile256x256, st) : launch_gemm(g, kTile256x256, b_kmajor, st);
         if (e != hipSuccess) return e;
-        g.n_base = 256 * tn_big;
-        g.tiles_n = (cols - g.n_base + 127) / 128;
+        g.n_base = (swiglu ? 128 : 256) * tn_big;
+        g.tiles_n = (cols - 256 * tn_big + 127) / 128;
         g.tiles_m = (rows + 127) / 128;
         g.ext_off = c->d_plan + R.off_ext_off_half;
         g.ext = reinterpret_cast<const ExtStep *>(c->d_plan + R.off_ext_half);
-        return launch_gemm(g, kTile128x128, b_kmajor, st);
+        return swiglu ? launch_gemm_swiglu(g, kTile128x128, st) : launch_gemm(g, kTile128x128, b_kmajor, st);
     }
     g.one_per_cu = one_round && forced_tile < 0 && ring_alone(t, cols, g.K, tile_steps(c, R));
     e = launch(t.tile);
@@ -514,14 +514,15 @@ int check_common(collm_ctx *ctx, const collm_shape *s, const void *x, const void
 
 bool same_key(collm_ctx *c, const collm_shape *s, const void *const *A, const void *const *B,
               const int32_t *rank, const int32_t *seg_start, const int32_t *seg_adapter,
-              const uint8_t *seg_is_train, int bm_all, int bm_train, int wide)
+              const uint8_t *seg_is_train, int bm_all, int bm_train, int wide, bool fwd)
 {
     if (!c->plan_valid) return false;
     const collm_shape &k = c->key_shape;
     if (k.d_in != s->d_in || k.d_out != s->d_out || k.n_tokens != s->n_tokens ||
         k.n_segments != s->n_segments || k.n_adapters != s->n_adapters || k.dtype != s->dtype)
         return false;
-    if (bm_all != c->key_bm_all || bm_train != c->key_bm_train || wide != c->key_wide) return false;
+    // (a backward call runs over the training rows only: how the plan cuts all rows does not matter to it)
+    if ((fwd && bm_all != c->key_bm_all) || bm_train != c->key_bm_train || wide != c->key_wide) return false;
     const int S = s->n_segments, N = s->n_adapters;
     if (std::memcmp(c->key_seg_start.data(), seg_start, sizeof(int32_t) * (S + 1))) return false;
     if (S && std::memcmp(c->key_seg_adapter.data(), seg_adapter, sizeof(int32_t) * S)) return false;
@@ -606,7 +607,7 @@ int upload(collm_ctx *c, size_t lo, size_t hi, hipStream_t st)
 int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const void *const *B,
                  const int32_t *rank, const int32_t *seg_start, const int32_t *seg_adapter,
                  const uint8_t *seg_is_train, float *const *dA, float *const *dB, bool allow_reuse,
-                 hipStream_t st, const int32_t *rank_ext_all = nullptr, int n_sib = 1)
+                 hipStream_t st, bool fwd, const int32_t *rank_ext_all = nullptr, int n_sib = 1, bool swiglu = false)
 {
     const bool f32 = s->dtype == COLLM_F32;
     int n_train = 0;
@@ -614,7 +615,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
         if (seg_is_train[k]) n_train += seg_start[k + 1] - seg_start[k];
     const bool can_split = !f32 && c->gemm_split != 1;
     count_steps(c, s, rank, seg_start, seg_adapter, seg_is_train);
-    const int tile_fwd = c->tile_fwd >= 0 ? c->tile_fwd : pick_tiling(s->n_tokens, s->d_out, s->d_in, can_split && n_sib < 16, n_sib <= 1, c->tile_steps_all).tile;
+    const int tile_fwd = c->tile_fwd >= 0 ? c->tile_fwd : pick_tiling(s->n_tokens, s->d_out, s->d_in, can_split && !swiglu, n_sib <= 1, c->tile_steps_all).tile;
     int rmax = 1;
     for (int a = 0; a < s->n_adapters; ++a) rmax = std::max(rmax, rank[a]);
     const bool one_round_dx = dx_one_round(c, n_train, s->d_in, s->d_out, f32, round_up(rmax, kKStep));
@@ -634,7 +635,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     // reuses it (every layer and projection of a model sees the same batch): only a call on another stream
     // than the one the plan was uploaded on builds it again, since nothing orders the two streams.
     const bool reuse = allow_reuse && st == c->last_stream && n_sib == c->key_nsib &&
-                       same_key(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, bm_all, bm_train, wide);
+                       same_key(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, bm_all, bm_train, wide, fwd);
     bool upload_all = false;
     c->plan_build_us = c->plan_upload_us = 0.f;
     c->plan_mode = c->plan_bytes_up = 0;
@@ -737,7 +738,7 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
                int32_t off_tab, bool t_kmajor, float *f32_out, int64_t f32_ld, int f32_cols,
                int f32_by_token, float f32_mult, void *bf_out, float bf_mult, const char *name,
                hipStream_t st, const SiblingPass *sp = nullptr, const void *warm = nullptr, uint64_t warm_bytes = 0,
-               const SliceSums *sums = nullptr)
+               const SliceSums *sums = nullptr, int bf_up = 0)
 {
     if (R.n_items == 0 && R.n_wide == 0) return COLLM_OK;
     SkinnyArgs a{};
@@ -779,6 +780,7 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
     a.bf_out = bf_out;
     a.bf_ld = c->L.rpad;
     a.bf_mult = bf_mult;
+    a.bf_up = bf_up;
     // A wave keeps `depth` chunks of K in flight and so needs K / (waves * chunk * depth) round trips to
     // memory; cutting K into slices across blocks shortens that chain at the price of a second kernel that
     // adds the slices (about 6 us with its launch).  Cut only when the chain is longer than about six round
@@ -1303,11 +1305,10 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(c->device));
     c->n_prof = 0;
-    // (with the SwiGLU epilogue the extension steps run over both siblings' ranks, as in the backward GEMM)
     {
         Prof prof(c, st, "plan_copy");
-        rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, nullptr, nullptr, true, st,
-                          P > 1 && !swiglu ? rank1 : nullptr, swiglu ? 16 + P : P);
+        rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, nullptr, nullptr, true, st, true,
+                          P > 1 ? rank1 : nullptr, P, swiglu);
     }
     if (rc != COLLM_OK) return rc;
     const PlanLayout &L = c->L;
@@ -1319,7 +1320,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     const bool tr = s->layout == COLLM_LAYOUT_OUT_IN;
     rc = run_skinny(c, s, L.all, x, s->d_in, L.off_A_ptr, tr, h_save, c->max_rank, c->max_rank, 1, 1.0f,
                     c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, L.all, s->n_tokens, s->d_out, s->d_in, tr, P <= 1, P > 1)) ? W : nullptr,
-                    (uint64_t)s->d_in * s->d_out * 2);
+                    (uint64_t)s->d_in * s->d_out * 2, nullptr, swiglu ? L.rpad / 2 : 0);
     if (rc != COLLM_OK) return rc;
 
     GemmArgs g{};
@@ -1437,7 +1438,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     c->n_prof = 0;
     {
         Prof prof(c, st, "plan_copy");
-        rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, dA, dB, true, st,
+        rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, dA, dB, true, st, false,
                           P > 1 ? rank1 : nullptr, P);
     }
     if (rc != COLLM_OK) return rc;

@@ -58,7 +58,7 @@ struct GemmArgs {
     int n_sib;                // 0 or 1: a single projection
     int sib_col[3];
     // gate/up pair with the SwiGLU epilogue (launch_gemm_swiglu): N = d_ff output columns; the up sibling's columns
-    // of b and of the expand tables start at act_col; pre_act (optional, [tokens][pre_ld]) receives both
+    // of b and of the expand tables start at act_col, its activations at column hs_ld / 2 of hs; pre_act (optional, [tokens][pre_ld]) receives both
     // pre-activations of the rows of training tokens (tok_train: token -> 0/1)
     int act_col;
     void *pre_act;
@@ -100,6 +100,8 @@ struct SkinnyArgs {
     void *bf_out;             // optional scaled copy in the element type, row order
     int bf_ld;
     float bf_mult;
+    int bf_up;                // 0, or: ranks are those of two siblings side by side, and the scaled copy keeps the second
+                              // one's half from column bf_up = bf_ld / 2 on (what the SwiGLU GEMM reads)
     // K split over several blocks (bf16 kernels): sums of the slices, [slice][part_rows][part_ld]
     float *part;
     int part_rows, part_ld;

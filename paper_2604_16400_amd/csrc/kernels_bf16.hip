@@ -267,9 +267,12 @@ constexpr bool rows_early(int bm, int bn, int rs) { return rs ? rs == 2 : bm * b
 // skinny_finish_kernel adds up.
 // SWIGLU (N-major second operand, WGN = 2): a column tile holds BN / 2 gate columns j0 .. and the BN / 2 up
 // columns act_col + j0 .. of the same outputs; the waves of the left half hold the gate values, those
-// of the right half the up values of the same rows.  The extension steps run over both siblings' ranks
-// (rank r each, multiples of 16): a step of the first r multiplies into the gate half only, one of the
-// second r into the up half only.  In the epilogue the two waves that hold the gate and the up values of the
+// of the right half the up values of the same rows.  An extension step is 16 rank indices of
+// both siblings (rank r each, a multiple of 16): one row of the tile's expand table serves both halves (the siblings'
+// columns lie side by side), the gate waves take the rows' gate activations (columns 0 .. of hs), the up waves the up ones
+// (columns hs_ld / 2 ..), each from an LDS area of its own.  (Steps of one sibling each, with zeros in the other half, are
+// twice as many: forward call, before / after, us: 4096 rows 4096 -> 2 x 11008, 32 adapters of rank 64 725 / 678; 4301 rows 1072 ->
+// 2 x 1536, 68 of rank 64 89 / 78; 241 rows 1768 -> 2 x 10496, 8 of rank 64 70 / 60; rank 16 level to -4 %.)  In the epilogue the two waves that hold the gate and the up values of the
 // same rows swap halves through LDS, each finishes half of the rows: silu(gate) * up, rounded once, stored as
 // [rows][N = d_ff]; training rows also keep both pre-activations.
 // SIBS: sibling projections side by side in the columns; the low-rank extension then loads the rows' operand per
@@ -371,7 +374,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
             b_bytes = B_KMAJOR ? p.b_bytes - b_skip : (uint32_t)K * ldb * 2u;
         }
     }
-    const int n0 = SWIGLU ? tile_n * (BN / 2) : (PARTIAL ? 0 : p.n_base) + tile_n * BN;
+    const int n0 = (PARTIAL ? 0 : p.n_base) + tile_n * (SWIGLU ? BN / 2 : BN);
     // tile column c (a multiple of 8) -> column of the second operand and of the expand tables
     auto src_col = [&](int c) -> int {
         if constexpr (SWIGLU) return c < BN / 2 ? n0 + c : p.act_col + n0 + c - BN / 2;
@@ -556,14 +559,15 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
     // piece d of a batch: chunk d of the rows' operand (into the LDS area at byte a_base), or chunk d - ACH of
     // the tables' (area at b_base); called with d known after unrolling: the branches and the step index fold away.
     // once: the rows' operand is not that of the batch but rank indices 64 g .. 64 g + 63 of every row's own s h
-    // (or dh), whatever its adapter: it is loaded once for the whole tile and masked per step when it is used.
-    auto issue_piece = [&](uint32_t a_base, uint32_t b_base, const ExtBatch &bt, const int D, const bool once, const int g) {
+    // (or dh), whatever its adapter: it is loaded once for the whole tile and masked per step when it is used.  (SwiGLU: of
+    // the gate half of the row, or with `up` of the other one.)
+    auto issue_piece = [&](uint32_t a_base, uint32_t b_base, const ExtBatch &bt, const int D, const bool once, const int g, const bool up = false) {
         if (D < ACH && once) {
             const int i = D;
             const int r = r8 + i * (NT / 8);
             const int cl = cl0;
-            const int k = 64 * g + cl * 8;
-            const uint32_t off = k < p.hs_ld ? ((uint32_t)(m0 + r) * (uint32_t)p.hs_ld + (uint32_t)k) * 2u : kOob;
+            const int k = 64 * g + cl * 8, width = SWIGLU ? p.hs_ld >> 1 : p.hs_ld;
+            const uint32_t off = k < width ? ((uint32_t)(m0 + r) * (uint32_t)p.hs_ld + (uint32_t)(k + (up ? width : 0))) * 2u : kOob;
             dma16(rh_w, off, lds_wave + a_base + i * (NT / 64) * 1024);
         } else if (D < ACH) {
             // rows: position c8 of row r holds chunk cl; chunk cl belongs to step cl / 2, rank
@@ -597,18 +601,10 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
                 tab_j = uni(pick(j2, (uint32_t)bt.tab[0], (uint32_t)bt.tab[1], (uint32_t)bt.tab[2], (uint32_t)bt.tab[3]));
                 tab_j |= (uint64_t)uni(pick(j2, (uint32_t)(bt.tab[0] >> 32), (uint32_t)(bt.tab[1] >> 32), (uint32_t)(bt.tab[2] >> 32), (uint32_t)(bt.tab[3] >> 32))) << 32;
             }
-            uint32_t rk = kr_j >> 16, koff = kr_j & 0xffffu;
-            bool mine = true;
-            if constexpr (SWIGLU) {
-                // the step belongs to the gate sibling (first half of the ranks) or the up sibling
-                rk >>= 1;
-                const bool up = koff >= rk;
-                koff -= up ? rk : 0u;
-                mine = (bcl * 8 >= BN / 2) == up;
-            }
+            const uint32_t rk = kr_j >> 16, koff = kr_j & 0xffffu;
             const int bcl_i = bcl_of(i);
             const i32x4 rt = make_rsrc_words(reinterpret_cast<const void *>(tab_j), rk * (uint32_t)p.ext_ld * 2u);
-            const uint32_t off = (mine && col_on(bcl_i * 8)) ? ((koff + (uint32_t)(k & 15)) * (uint32_t)p.ext_ld + (uint32_t)src_col(bcl_i * 8)) * 2u : kOob;
+            const uint32_t off = col_on(bcl_i * 8) ? ((koff + (uint32_t)(k & 15)) * (uint32_t)p.ext_ld + (uint32_t)src_col(bcl_i * 8)) * 2u : kOob;
             dma16(rt, off, lds_wave + b_base + i * (NT / 64) * 1024);
         } else {
             // table rows are output columns: A_a[n][q], row length rank.  The four steps of a
@@ -1057,11 +1053,19 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
         // Only the tables stream: three areas, the loads of two batches in flight while one multiplies.
         static_assert(NST > 2 || ATILE >= BTILE, "a table area must fit the place of a row area");
         const uint32_t xa = ROWS_EARLY ? XA_EARLY : 0;
+        // SwiGLU: the up activations, in the first row area (256x256) or behind the stages
+        constexpr uint32_t XU = ROWS_EARLY ? 0 : NST * STAGE;
+        const uint32_t xa_w = SWIGLU && wn ? XU : xa;  // the area this wave reads
         uint32_t t_cur = B_ST0, t_nxt = B_ST1, t_far = NST > 2 ? B_ST1 + BTILE : A_ST1;
         const int wrow0 = __builtin_amdgcn_readfirstlane(wm * WM);
+        auto issue_up = [&](int g) {
+#pragma unroll
+            for (int d = 0; d < ACH; ++d) issue_piece(XU, 0u, ExtBatch{}, d, true, g, true);
+        };
         auto issue_rows = [&](int g) {
 #pragma unroll
             for (int d = 0; d < ACH; ++d) issue_piece(xa, 0u, ExtBatch{}, d, true, g);
+            if constexpr (SWIGLU) issue_up(g);
         };
         // true if every piece was one direct load (what the waits below count)
         auto issue_tab = [&](uint32_t base, const ExtBatch &bt) -> bool {
@@ -1074,7 +1078,8 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
         ExtBatch cur_b = get_batch(e0);
         ExtBatch nxt_b = get_batch(e0 + kExtBatch);
         int g_cur = ROWS_EARLY ? 0 : (int)((cur_b.kr[0] & 0xffffu) >> 6);  // (what was loaded earlier: 0)
-        if (!ROWS_EARLY) issue_rows(g_cur);
+        if constexpr (!ROWS_EARLY) issue_rows(g_cur);
+        else if constexpr (SWIGLU) issue_up(g_cur);
         issue_tab(t_cur, cur_b);
         bool nxt_direct = true;
         if (e0 + kExtBatch < e1) nxt_direct = issue_tab(t_nxt, nxt_b);
@@ -1122,7 +1127,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
                         for (int mi = 0; mi < MI16; ++mi) {
                             if (on16(mi)) {
                                 const int row = wm * WM + mi * 16 + r16;
-                                uint4 v = __builtin_bit_cast(uint4, lds_frag(smem + xa, row, c0));
+                                uint4 v = __builtin_bit_cast(uint4, lds_frag(smem + xa_w, row, c0));
                                 const bool in = row >= lo && row < hi;
                                 v.x = in ? v.x : 0u;
                                 v.y = in ? v.y : 0u;
@@ -1377,7 +1382,8 @@ __device__ __forceinline__ void skinny_store(const SkinnyArgs &p, const SkinnyIt
         uint2 o;
         o.x = pack_bf16(v[0] * p.bf_mult, v[1] * p.bf_mult);
         o.y = pack_bf16(v[2] * p.bf_mult, v[3] * p.bf_mult);
-        *reinterpret_cast<uint2 *>(bf_row + q) = o;
+        // (bf_up: the second sibling's half of the ranks, a multiple of 16, goes to the second half of the row)
+        *reinterpret_cast<uint2 *>(bf_row + (p.bf_up > 0 && 2 * q >= rank ? q - (rank >> 1) + p.bf_up : q)) = o;
     }
 }
 
@@ -2123,10 +2129,11 @@ static hipError_t launch_gemm_t(const GemmArgs &a, hipStream_t st)
     // four waves, 2 x 2
     constexpr int NT = 256;
     // two stages (or the ring's); some tiles keep the rows' area of the extension behind them
-    constexpr int stage_bytes = (RS ? RS : 2) * (BM + BN) * 128 + ((!SIBS && rows_early(BM, BN, RS)) ? BM * 128 : 0);
+    // (SwiGLU: an area for the up activations too, which on 256x256 tiles lies in the first stage)
+    constexpr int stage_bytes = (RS ? RS : 2) * (BM + BN) * 128 + ((SWIGLU || (!SIBS && rows_early(BM, BN, RS))) ? BM * 128 : 0);
     constexpr int epi_bytes = BM * BN * 2 + BM * 2 * 16;  // per wave (BM/2) rows of (BN/2) * 2 + 16 bytes
     constexpr int smem = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
-    static_assert(RS || BM * BN != 128 * 128 || smem == kSmallTileLds, "what grad_lds assumes");
+    static_assert(RS || SWIGLU || BM * BN != 128 * 128 || smem == kSmallTileLds, "what grad_lds assumes");
     static_assert(smem <= 160 * 1024, "LDS of a CU");
     static_assert(!SWIGLU || smem >= BM * (BN / 2) * 4, "the up halves of all rows pass through LDS as fp32");
     auto kern = gemm_lora_kernel<BM, BN, 2, 2, KM, false, SWIGLU, false, SIBS, RS>;

@@ -236,6 +236,49 @@ def test_swiglu_epilogue(tile):
     _run_swiglu(c, tile, keep_pre=False)
 
 
+@pytest.mark.parametrize("tile", [binding.TILE_256x256, binding.TILE_128x128])
+def test_swiglu_steps_reach_both_siblings_ranks(tile):
+    # ranks above 64 (the rows' areas are loaded again for the second group) beside narrow ones in the same tiles, a
+    # contraction shorter than two K tiles, the widest ranks a context takes (2 x 128)
+    c = SiblingCase(88, (256, 256), [80, 128, 16, 112], LENS, ADS, TRN, scale=0.3)
+    _run_swiglu(c, tile)
+    c = SiblingCase(64, (512, 512), [128, 64, 48], [3, 1, 60, 64, 129], [1, 2, 0, 1, 0], [0, 0, 1, 0, 0], scale=0.3)
+    _run_swiglu(c, tile, keep_pre=False)
+
+
+def test_swiglu_forward_and_sibling_backward_share_a_plan():
+    import torch
+
+    c = SiblingCase(320, (512, 512), [16, 32, 48, 64], LENS, ADS, TRN, scale=0.3)
+    ctx = binding.Context(c.T, len(c.seg_adapter), len(c.ranks), 128, 1024)
+    x, W, dy = to_dev(c.x, "bf16"), to_dev(c.W, "bf16"), to_dev(c.dy, "bf16")
+    A, B = [to_dev(a, "bf16") for a in c.A], [to_dev(b, "bf16") for b in c.B]
+    seg = (c.ranks, c.seg_start, c.seg_adapter, c.seg_is_train, c.scale)
+    y = [torch.empty((c.T, 512), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    flat = torch.empty((c.T, 1024), dtype=torch.bfloat16, device="cuda")
+    hs = torch.empty((c.T, 128), dtype=torch.float32, device="cuda")
+    dx = torch.empty((c.T, 320), dtype=torch.bfloat16, device="cuda")
+    dA, dB = [torch.empty(a.shape, device="cuda") for a in c.A], [torch.empty(b.shape, device="cuda") for b in c.B]
+    act = dict(activation=binding.ACT_SWIGLU)
+    ctx.collm_lora_siblings_fwd(c.d_outs, x, W, A, B, *seg, y[0], hs, **act)
+    modes = []
+    ctx.collm_lora_siblings_bwd(c.d_outs, x, W, A, B, *seg, dy, hs, dx, dA, dB)
+    modes.append(ctx.plan_stats()["mode"])
+    ctx.collm_lora_siblings_fwd(c.d_outs, x, W, A, B, *seg, flat)
+    ctx.collm_lora_siblings_fwd(c.d_outs, x, W, A, B, *seg, y[1], hs, **act)
+    modes.append(ctx.plan_stats()["mode"])
+    torch.cuda.synchronize()
+    assert modes == [3, 0]  # (gradient pointers put in; nothing new)
+    assert torch.equal(y[0], y[1])
+    y_ref, _ = oracle.lora_siblings_fwd(c.x, c.W, c.A, c.B, c.d_outs, c.tok_adapter, c.scale)
+    dx_ref, dA_ref, dB_ref = oracle.lora_siblings_bwd(c.x, c.W, c.A, c.B, c.d_outs, c.tok_adapter, c.tok_train, c.scale, c.dy)
+    tr = c.tok_train != 0
+    errs = [maxrel(to_host(flat), y_ref), maxrel(to_host(y[1]), oracle.swiglu(y_ref)), maxrel(to_host(dx)[tr], dx_ref[tr])]
+    errs += [maxrel(to_host(g[a]), r[a]) for g, r in ((dA, dA_ref), (dB, dB_ref)) for a in range(4) if r[a] is not None]
+    ctx.close()
+    assert max(errs) <= TOL["bf16"], errs
+
+
 def test_swiglu_epilogue_large_tiles_and_tail():
     # 2300 rows x (2 x 3840) columns: whole rounds of 256x256 tiles, then 128x128 tiles over the last rows
     lens = [700, 1, 1, 500, 300, 1, 600, 197]
