@@ -428,8 +428,12 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
     };
     hipError_t e = hipSuccess;
     if (t.tile == kTile128x128 && t.tail_tiles_m == 0 && try_split(t.big_tiles_m, 0, rows, e)) return e;
-    if (t.tail_cols > 0 && !swiglu) {
-        // whole rounds of large tiles over the first columns, small tiles over the other columns of all rows
+    // Whole rounds of large tiles over the first columns, small tiles over the other columns of all rows.  With the SwiGLU epilogue only
+    // where the last round counts: after three rounds and a half the blocks' different speeds have smoothed the rounds out (training
+    // rows also keep their pre-activations).  Forward call, one launch / two, by tiles / 256: 1.1 .. 1.5 0.85 .. 0.99, 2.1 .. 2.5 0.91 .. 0.99,
+    // 3.1 .. 3.3 0.93 .. 1.01, 3.5 0.97 .. 1.03, beyond 0.95 .. 1.05 (4096 rows 4096 -> 2 x 2560, rank 64 232 / 209 us, -> 2 x 9216 586 / 599).
+    const int big_tiles = t.big_tiles_m * ((cols + 255) / 256);
+    if (t.tail_cols > 0 && (!swiglu || big_tiles < 256 * 7 / 2)) {
         const int tn_big = (cols + 255) / 256 - t.tail_cols;
         g.tiles_n = tn_big;
         e = swiglu ? launch_gemm_swiglu(g, kTile256x256, st) : launch_gemm(g, kTile256x256, b_kmajor, st);

@@ -257,7 +257,7 @@ def test_swiglu_forward_and_sibling_backward_share_a_plan():
     y = [torch.empty((c.T, 512), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
     flat = torch.empty((c.T, 1024), dtype=torch.bfloat16, device="cuda")
     hs = torch.empty((c.T, 128), dtype=torch.float32, device="cuda")
-    dx = torch.empty((c.T, 320), dtype=torch.bfloat16, device="cuda")
+    dx = torch.zeros((c.T, 320), dtype=torch.bfloat16, device="cuda")
     dA, dB = [torch.empty(a.shape, device="cuda") for a in c.A], [torch.empty(b.shape, device="cuda") for b in c.B]
     act = dict(activation=binding.ACT_SWIGLU)
     ctx.collm_lora_siblings_fwd(c.d_outs, x, W, A, B, *seg, y[0], hs, **act)
@@ -285,6 +285,12 @@ def test_swiglu_epilogue_large_tiles_and_tail():
     ads = [0, 1, 2, 1, -1, 0, 2, 2]
     c = SiblingCase(64, (3840, 3840), [16, 32, 16], lens, ads, [1, 0, 0, 1, 0, 0, 1, 0], scale=0.5)
     _run_swiglu(c)
+
+
+def test_swiglu_epilogue_columns_in_small_tiles():
+    # 264 tiles of 256x256: one whole round over the first columns, the last two tile columns as 128x128 tiles of 64 outputs
+    assert binding.host_tiling(1000, 2 * 8448, 72, False) == (binding.TILE_256x256, 4, 0, 2)
+    _run_swiglu(SiblingCase(72, (8448, 8448), [16, 80, 32], [300, 1, 250, 200, 1, 248], [0, 1, 2, 1, -1, 0], [1, 0, 0, 1, 0, 0], scale=0.3))
 
 
 def test_swiglu_backward_kernel_and_chain():
