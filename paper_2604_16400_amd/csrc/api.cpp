@@ -101,6 +101,8 @@ struct collm_ctx {
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_dh = nullptr, ev_join = nullptr;
 
+    PlanPatch patch{};  // new table addresses that the call's first rank-wide pass puts in (blocks > 0)
+
     // host cost of the plan of the last compute call (collm_debug_plan_stats)
     float plan_build_us = 0.f, plan_upload_us = 0.f;
     int plan_mode = 0;       // 0: reused as it is, 1: built anew, 2: table addresses replaced, 3: gradient pointers only
@@ -567,20 +569,9 @@ void patch_tables(collm_ctx *c, int N, const void *const *A, const void *const *
     patch(L.train.off_ext_half, L.train.ext_adapter_half, A);
 }
 
-// Copy ints [lo, hi) of the host plan to the device plan through a pinned staging slot.
-int upload(collm_ctx *c, size_t lo, size_t hi, hipStream_t st)
+// Takes the next pinned staging slot and a sequence number for it; waits until the GPU has copied what the slot held.
+int take_slot(collm_ctx *c, int *slot, uint32_t *seq)
 {
-    if (hi <= lo) return COLLM_OK;
-    const auto t0 = std::chrono::steady_clock::now();
-    if (c->static_scratch) {
-        // no pinned staging exists: the words travel inside the arguments of a few small kernels
-        const size_t lo4 = lo & ~(size_t)3, hi4 = std::min((hi + 3) & ~(size_t)3, c->plan.size());
-        HIP_TRY(launch_plan_words(c->plan.data() + lo4, c->d_plan + lo4, hi4 - lo4, st));
-        c->last_stream = st;
-        c->plan_upload_us += std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - t0).count();
-        c->plan_bytes_up += (int)((hi4 - lo4) * sizeof(int32_t));
-        return COLLM_OK;
-    }
     const int sl = c->slot;
     c->slot = (c->slot + 1) % kSlots;
     if (c->stage_seq[sl] != 0) {
@@ -595,15 +586,71 @@ int upload(collm_ctx *c, size_t lo, size_t hi, hipStream_t st)
             std::this_thread::yield();
         }
     }
+    *slot = sl;
+    *seq = ++c->seq == 0 ? ++c->seq : c->seq;
+    return COLLM_OK;
+}
+
+// Copy ints [lo, hi) of the host plan to the device plan through a pinned staging slot.
+int upload(collm_ctx *c, size_t lo, size_t hi, hipStream_t st)
+{
+    if (hi <= lo) return COLLM_OK;
+    const auto t0 = std::chrono::steady_clock::now();
     // rounded outwards to 16 bytes (the plan vector is padded to a multiple of 64 ints)
     const size_t lo4 = lo & ~(size_t)3, hi4 = std::min((hi + 3) & ~(size_t)3, c->plan.size());
-    std::memcpy(c->h_stage[sl] + lo4, c->plan.data() + lo4, (hi4 - lo4) * sizeof(int32_t));
-    const uint32_t seq = ++c->seq == 0 ? ++c->seq : c->seq;
-    HIP_TRY(launch_plan_copy(c->h_stage_dev[sl], c->d_plan, lo4, hi4 - lo4, c->d_copy_counter, c->h_done_dev, seq, st));
-    c->stage_seq[sl] = seq;
+    if (c->static_scratch) {
+        // no pinned staging exists: the words travel inside the arguments of a few small kernels
+        HIP_TRY(launch_plan_words(c->plan.data() + lo4, c->d_plan + lo4, hi4 - lo4, st));
+    } else {
+        int sl = 0;
+        uint32_t seq = 0;
+        const int rc = take_slot(c, &sl, &seq);
+        if (rc != COLLM_OK) return rc;
+        std::memcpy(c->h_stage[sl] + lo4, c->plan.data() + lo4, (hi4 - lo4) * sizeof(int32_t));
+        HIP_TRY(launch_plan_copy(c->h_stage_dev[sl], c->d_plan, lo4, hi4 - lo4, c->d_copy_counter, c->h_done_dev, seq, st));
+        c->stage_seq[sl] = seq;
+    }
     c->last_stream = st;
     c->plan_upload_us += std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - t0).count();
     c->plan_bytes_up += (int)((hi4 - lo4) * sizeof(int32_t));
+    return COLLM_OK;
+}
+
+// Leaves the plan's table addresses (patch_tables) to the call's first rank-wide pass (PlanPatch).  tab: the tables
+// which that pass reads.
+int stage_patch(collm_ctx *c, const void *const *tab, int n_adapters)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    int sl = 0;
+    uint32_t seq = 0;
+    const int rc = take_slot(c, &sl, &seq);
+    if (rc != COLLM_OK) return rc;
+    const PlanLayout &L = c->L;
+    PlanPatch &q = c->patch;
+    int n16 = 0;
+    auto part = [&](int i, int32_t off, size_t ints) {
+        const size_t lo4 = (size_t)off & ~(size_t)3, hi4 = ints ? std::min(((size_t)off + ints + 3) & ~(size_t)3, c->plan.size()) : lo4;
+        std::memcpy(c->h_stage[sl] + lo4, c->plan.data() + lo4, (hi4 - lo4) * sizeof(int32_t));
+        q.lo[i] = (int32_t)(lo4 / 4);
+        q.n[i] = (int32_t)((hi4 - lo4) / 4);
+        n16 += q.n[i];
+    };
+    constexpr size_t kStepInts = sizeof(ExtStep) / sizeof(int32_t);
+    part(0, L.off_A_ptr, (size_t)(L.off_dB_ptr - L.off_A_ptr) + 2 * (size_t)std::max(n_adapters, 1));
+    part(1, L.all.off_ext, L.all.ext_adapter.size() * kStepInts);
+    part(2, L.all.off_ext_half, L.all.ext_adapter_half.size() * kStepInts);
+    part(3, L.train.off_ext, L.train.ext_adapter.size() * kStepInts);
+    part(4, L.train.off_ext_half, L.train.ext_adapter_half.size() * kStepInts);
+    q.src = c->h_stage_dev[sl];
+    q.dst = c->d_plan;
+    q.counter = c->d_copy_counter;
+    q.done_host = c->h_done_dev;
+    q.seq = seq;
+    q.blocks = std::max(1, std::min(16, (n16 + 511) / 512));
+    for (int a = 0; a < n_adapters; ++a) q.tab[a] = (uint64_t)(uintptr_t)tab[a];
+    c->stage_seq[sl] = seq;
+    c->plan_upload_us += std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - t0).count();
+    c->plan_bytes_up += n16 * 16;
     return COLLM_OK;
 }
 
@@ -671,6 +718,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
         rq.wide_min_rows_all = wide_all;
         rq.wide_min_rows_train = wide_train;
         c->plan_valid = false;
+        c->patch.blocks = 0;
         int rc = build_plan(rq, c->plan, c->L);
         if (rc != COLLM_OK) return rc;
         if ((size_t)c->L.total_ints > c->plan_cap) {
@@ -701,6 +749,15 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     } else if (dA || dB || upload_all) {
         // same batch as the plan on the device: at most the pointer tables are new
         const int N = s->n_adapters;
+        // (a forward call begins with a rank-wide pass that can carry them, unless no row has an adapter; a backward call may
+        // begin with gradients on the second stream)
+        bool carry = upload_all && fwd && !f32 && !c->static_scratch && N <= kPatchTables && c->L.all.n_items + c->L.all.n_wide > 0;
+        if (carry) {
+            // (a call recorded into a graph uploads all of the plan: at a replay the device may hold another batch's)
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            HIP_TRY(hipStreamIsCapturing(st, &capture));
+            carry = capture == hipStreamCaptureStatusNone;
+        }
         bool changed = false;
         for (int a = 0; a < N; ++a) {
             const uint64_t va = dA ? (uint64_t)(uintptr_t)dA[a] : 0, vb = dB ? (uint64_t)(uintptr_t)dB[a] : 0;
@@ -709,7 +766,10 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
             std::memcpy(c->plan.data() + c->L.off_dA_ptr + 2 * a, &va, 8);
             std::memcpy(c->plan.data() + c->L.off_dB_ptr + 2 * a, &vb, 8);
         }
-        if (upload_all) {
+        if (carry) {
+            const int rc = stage_patch(c, A, N);
+            if (rc != COLLM_OK) return rc;
+        } else if (upload_all) {
             int rc = upload(c, 0, c->L.total_ints, st);
             if (rc != COLLM_OK) return rc;
         } else if (changed) {
@@ -745,6 +805,13 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
                const SliceSums *sums = nullptr, int bf_up = 0)
 {
     if (R.n_items == 0 && R.n_wide == 0) return COLLM_OK;
+    // (taken by the pass's first kernel; behind it the plan is whole)
+    PlanPatch patch;
+    patch.blocks = 0;
+    if (c->patch.blocks > 0) {
+        patch = c->patch;
+        c->patch.blocks = 0;
+    }
     SkinnyArgs a{};
     // The weight of the GEMM that follows, fetched into the last-level cache by extra blocks of this pass (one per
     // compute unit) - if the weight is small (a GEMM of so few K tiles per block cannot hide the memory's latency:
@@ -854,10 +921,11 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
         ns = std::max<long>(ns, 1);
         g.k_per_split = round_up((int)((K + ns - 1) / ns), 64);
         n_wsplit = (K + g.k_per_split - 1) / g.k_per_split;
-        HIP_TRY(launch_wide(g, R.n_wide, rpad, n_wsplit, t_kmajor, st));
+        HIP_TRY(launch_wide(g, R.n_wide, rpad, n_wsplit, t_kmajor, st, patch.blocks > 0 ? &patch : nullptr));
+        patch.blocks = 0;
     }
     if (R.n_items > 0)
-        HIP_TRY(launch_skinny(a, R.n_items, rpad, R.item_rows / kSkinnyRows, n_split, t_kmajor, st));
+        HIP_TRY(launch_skinny(a, R.n_items, rpad, R.item_rows / kSkinnyRows, n_split, t_kmajor, st, patch.blocks > 0 ? &patch : nullptr));
     // (the sums of the two kinds of items lie in different rows of the workspace)
     HIP_TRY(launch_skinny_finish(a, reinterpret_cast<const SkinnyItem *>(c->d_plan + R.off_wide), R.n_wide, n_wsplit,
                                  n_split > 1 ? R.n_items : 0, R.item_rows / kSkinnyRows, n_split, st));
@@ -1325,7 +1393,10 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     rc = run_skinny(c, s, L.all, x, s->d_in, L.off_A_ptr, tr, h_save, c->max_rank, c->max_rank, 1, 1.0f,
                     c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, L.all, s->n_tokens, s->d_out, s->d_in, tr, P <= 1, P > 1)) ? W : nullptr,
                     (uint64_t)s->d_in * s->d_out * 2, nullptr, swiglu ? L.rpad / 2 : 0);
-    if (rc != COLLM_OK) return rc;
+    if (rc != COLLM_OK) {
+        c->plan_valid = false;  // (the pass may not have put in the addresses it was to carry)
+        return rc;
+    }
 
     GemmArgs g{};
     g.a = x;

@@ -30,6 +30,24 @@ extern thread_local LaunchEvents g_launch_events;
 
 enum { kTile256x256 = 0, kTile256x128 = 1, kTile128x128 = 2, kTile128x192 = 3, kTile256x192 = 4 };  // GEMM tile shapes (rows x columns of the output)
 
+// New adapter tables for a plan that the device holds already (same batch, another layer or projection), carried by the first
+// rank-wide pass of a call instead of a kernel of its own in front of it: `blocks` extra blocks of the pass copy the parts of the
+// plan that hold table addresses from pinned host memory, for the kernels behind the pass, while the pass itself finds its tables
+// in its arguments.  A stack of four 4096 -> 11008 projections over 64 decode tokens 225.5 /
+// 213.0 us, forward and backward through four 4096 -> 4096 over 2048 tokens 662 / 642.
+constexpr int kPatchTables = 128;  // adapters whose table addresses travel as arguments (1 KiB of 4)
+constexpr int kPatchParts = 5;     // the pointer tables, the extension steps of both row orders (two tile sizes each)
+struct PlanPatch {
+    const int32_t *src;  // pinned
+    int32_t *dst;
+    int32_t lo[kPatchParts], n[kPatchParts];  // in units of 16 bytes
+    int *counter;        // as launch_plan_copy
+    uint32_t *done_host;
+    uint32_t seq;
+    int blocks;          // 0: no patch
+    uint64_t tab[kPatchTables];
+};
+
 // out[tok(m)][n] = sum_k a[tok(m)][k] * b(k, n)  +  sum over the row tile's extension steps
 struct GemmArgs {
     const void *a;      // rows gathered through row_tok, K contiguous
@@ -191,7 +209,7 @@ hipError_t launch_gemm_finish(const GemmArgs &a, int n_split, hipStream_t st);
 hipError_t launch_gemm_swiglu(const GemmArgs &a, int tile_cfg, hipStream_t st);
 // a, lda, K, a_bytes, row_tok and the fields of the rank-wide pass; everything else is ignored.  Items hold up
 // to kWideRows rows; ranks must be multiples of 8.  The caller adds the slices with launch_skinny_finish.
-hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st);
+hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st, const PlanPatch *patch = nullptr);
 // adds the K slices of n_wide tiled items (`wide`, wide_split slices) and of n_items others (a.items, row_tiles = 1 or 2 groups
 // of 16 rows each, n_split slices) and does the pass's stores
 hipError_t launch_skinny_finish(const SkinnyArgs &a, const SkinnyItem *wide, int n_wide, int wide_split, int n_items, int row_tiles, int n_split,
@@ -200,7 +218,7 @@ int gemm_tile_rows(int tile_cfg);
 int gemm_tile_cols(int tile_cfg);
 // items hold up to 16 * row_tiles rows (row_tiles <= skinny_max_row_tiles(rpad)); n_split slices of K
 hipError_t launch_skinny(const SkinnyArgs &a, int n_items, int rpad, int row_tiles, int n_split, bool t_kmajor,
-                         hipStream_t st);
+                         hipStream_t st, const PlanPatch *patch = nullptr);
 int skinny_max_row_tiles(int rpad);
 int skinny_waves(int rpad);  // waves of a block, which split the block's K slice
 int skinny_chunk(int rpad);  // K values a wave fetches at a time

@@ -256,6 +256,52 @@ __device__ __forceinline__ void warm_cache(const void *base, uint64_t bytes, int
     if (fold == 0x9e3779b9u && bytes == 1) *reinterpret_cast<volatile uint32_t *>(const_cast<void *>(base)) = fold;
 }
 
+// Block `blk` of patch.blocks copies its share of the plan's new parts; the block that finishes last publishes the
+// sequence number, as in plan_copy_kernel.
+__device__ __forceinline__ void patch_plan(const PlanPatch &q, int blk, int tid, int n_thr)
+{
+    const int4 *__restrict__ src = reinterpret_cast<const int4 *>(q.src);
+    int4 *__restrict__ dst = reinterpret_cast<int4 *>(q.dst);
+#pragma unroll
+    for (int part = 0; part < kPatchParts; ++part)
+        for (int i = blk * n_thr + tid; i < q.n[part]; i += q.blocks * n_thr) dst[q.lo[part] + i] = src[q.lo[part] + i];
+    __syncthreads();  // every load of this block has returned: its stores have been issued
+    if (tid == 0) {
+        const int old = atomicAdd(q.counter, 1);
+        if (old == q.blocks - 1) {
+            *q.counter = 0;
+            *reinterpret_cast<volatile uint32_t *>(q.done_host) = q.seq;
+            __threadfence_system();
+        }
+    }
+}
+
+// Arguments of the passes that carry a patch: kernels of their own, as 1 KiB more of arguments makes every launch dearer
+// (three of them in a call of eight decode tokens: 20.0 / 20.3 us).
+struct WideArgs : GemmArgs {
+    PlanPatch patch;
+};
+struct SkinnyPassArgs : SkinnyArgs {
+    PlanPatch patch;
+};
+template <typename Args> constexpr bool kHasPatch = std::is_same_v<Args, WideArgs> || std::is_same_v<Args, SkinnyPassArgs>;
+template <typename Args>
+__device__ __forceinline__ int patch_blocks(const Args &p)
+{
+    if constexpr (kHasPatch<Args>) return p.patch.blocks;
+    else return 0;
+}
+// address of an adapter's table: out of the arguments while the plan's own list is being replaced
+template <typename Args>
+__device__ __forceinline__ const uint8_t *pass_table(const Args &p, int adapter)
+{
+    uint64_t v;
+    if constexpr (kHasPatch<Args>) v = p.patch.tab[adapter];
+    else v = p.tab[adapter];
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);  // (one adapter per block)
+}
+
 constexpr int kRingStages = 4;  // of the 128x128 tile run by one block per CU
 // whether the rows' area of the extension has a place of its own behind the stages
 constexpr bool rows_early(int bm, int bn, int rs) { return rs ? rs == 2 : bm * bn == 256 * 256; }
@@ -289,8 +335,8 @@ constexpr int kWideStages = 4;
 constexpr int wide_stages(bool t_kmajor) { return t_kmajor ? kWideStages : 2; }
 // RS: 0, or the number of LDS stages of a ring in which the loads of RS - 1 tiles are in flight (one block per CU).
 template <int BM, int BN, int WGM, int WGN, bool B_KMAJOR, bool PARTIAL = false, bool SWIGLU = false, bool SPLITK = false,
-          bool SIBS = false, int RS = 0>
-__global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN == 128 * 128) ? 2 : 1) gemm_lora_kernel(GemmArgs p)
+          bool SIBS = false, int RS = 0, typename Args = GemmArgs>
+__global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN == 128 * 128) ? 2 : 1) gemm_lora_kernel(Args p)
 {
     constexpr int NST = RS ? RS : 2;
     static_assert(RS == 0 || (!PARTIAL && !SIBS), "ring of stages: plain tiles");
@@ -332,8 +378,12 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
     uint32_t a_bytes = p.a_bytes, b_bytes = p.b_bytes, ldb = (uint32_t)p.ldb;
     if constexpr (PARTIAL) {
         if (blockIdx.x >= (unsigned)p.n_items) {
-            // a warm-up block: its share of the next GEMM's weight, read once and dropped
-            if (blockIdx.y == 0 && blockIdx.z == 0) warm_cache(p.warm_base, p.warm_bytes, blockIdx.x - p.n_items, p.warm_blocks, tid, NT);
+            if (blockIdx.y != 0 || blockIdx.z != 0) return;
+            // a block that puts in new table addresses, or a warm-up block: its share of the next GEMM's weight, read once and dropped
+            const int extra = blockIdx.x - p.n_items - patch_blocks(p);
+            if constexpr (kHasPatch<Args>)
+                if (extra < 0) patch_plan(p.patch, blockIdx.x - p.n_items, tid, NT);
+            if (extra >= 0) warm_cache(p.warm_base, p.warm_bytes, extra, p.warm_blocks, tid, NT);
             return;
         }
         // consecutive items mostly belong to one adapter; blocks go round-robin to the 8 XCDs, so give every XCD a
@@ -354,7 +404,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
         const uint32_t b_skip = B_KMAJOR ? (uint32_t)(k_begin + p.tab_off) * 2u : (uint32_t)k_begin * ldb * 2u;
         a_base = reinterpret_cast<const uint8_t *>(p.a) + a_skip;
         a_bytes = p.a_bytes - a_skip;
-        b_base = reinterpret_cast<const uint8_t *>(p.tab[it.adapter]) + b_skip;
+        b_base = pass_table(p, it.adapter) + b_skip;
         b_bytes = B_KMAJOR ? (uint32_t)N * ldb * 2u - b_skip : (uint32_t)K * ldb * 2u;
     } else {
         tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, p.band_m, tile_m, tile_n);
@@ -1399,8 +1449,8 @@ struct SkinnyCfg {
     static constexpr int RED_LD = RP + 4;                             // floats
 };
 
-template <int RP, bool T_KMAJOR, int RT>
-__global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyArgs p)
+template <int RP, bool T_KMAJOR, int RT, typename Args>
+__global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(Args p)
 {
     using C = SkinnyCfg<RP>;
     constexpr int KW = C::KW, STEPS = C::STEPS, CHK = C::CHK, NB = C::NB;
@@ -1412,8 +1462,12 @@ __global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyAr
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (blockIdx.x >= (unsigned)p.n_items) {
-        // a warm-up block: its share of the next GEMM's weight, read once and dropped
-        if (blockIdx.y == 0) warm_cache(p.warm_base, p.warm_bytes, blockIdx.x - p.n_items, p.warm_blocks, tid, KW * 64);
+        if (blockIdx.y != 0) return;
+        // a block that puts in new table addresses, or a warm-up block: its share of the next GEMM's weight, read once and dropped
+        const int extra = blockIdx.x - p.n_items - patch_blocks(p);
+        if constexpr (kHasPatch<Args>)
+            if (extra < 0) patch_plan(p.patch, blockIdx.x - p.n_items, tid, KW * 64);
+        if (extra >= 0) warm_cache(p.warm_base, p.warm_bytes, extra, p.warm_blocks, tid, KW * 64);
         return;
     }
     // (the item is the same for the whole block: kept in scalar registers)
@@ -1433,7 +1487,7 @@ __global__ void __launch_bounds__(SkinnyCfg<RP>::KW * 64) skinny_kernel(SkinnyAr
     const int k_hi = (k_lo + per) < K ? (k_lo + per) : K;
 
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.in, p.in_bytes);
-    const __amdgpu_buffer_rsrc_t rt = make_rsrc(reinterpret_cast<const void *>(p.tab[it.adapter]),
+    const __amdgpu_buffer_rsrc_t rt = make_rsrc(pass_table(p, it.adapter),
                                                 T_KMAJOR ? (uint32_t)rank * tld * 2u : (uint32_t)rank * (uint32_t)K * 2u);
     uint32_t xoff[RT];
 #pragma unroll
@@ -2186,17 +2240,13 @@ hipError_t launch_gemm(const GemmArgs &a, int tile_cfg, bool b_kmajor, hipStream
     }
 }
 
-hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st)
+hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st, const PlanPatch *patch)
 {
     static_assert(kWideRows == 128, "the rank-wide pass runs 128x128 tiles");
     if (n_items <= 0) return hipSuccess;
     if (n_split < 1 || !a.part || !a.items || !a.tab || a.k_per_split % 64 != 0) return hipErrorInvalidValue;
     const int smem = wide_stages(t_kmajor) * (128 + 128) * 128;
-    GemmArgs b = a;
-    b.n_items = n_items;
-    if (!b.warm_base || b.warm_bytes < 16) b.warm_blocks = 0;
-    const dim3 grid(n_items + b.warm_blocks, (rpad + 127) / 128, n_split);
-    auto launch = [&](auto kern) -> hipError_t {
+    auto launch = [&](auto kern, auto b) -> hipError_t {
         static bool attr_done = false;
         if (!attr_done) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -2204,11 +2254,22 @@ hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bo
             if (e != hipSuccess) return e;
             attr_done = true;
         }
-        COLLM_LAUNCH(kern, grid, dim3(512), smem, st, b);
+        static_cast<GemmArgs &>(b) = a;
+        b.n_items = n_items;
+        if (!b.warm_base || b.warm_bytes < 16) b.warm_blocks = 0;
+        int extra = b.warm_blocks;
+        if constexpr (kHasPatch<decltype(b)>) {
+            b.patch = *patch;
+            extra += patch->blocks;
+        }
+        COLLM_LAUNCH(kern, dim3(n_items + extra, (rpad + 127) / 128, n_split), dim3(512), smem, st, b);
         return hipGetLastError();
     };
     // eight waves, 32 rows x 64 rank columns each (two per SIMD): the loop is bound by what a wave has to issue
-    return t_kmajor ? launch(gemm_lora_kernel<128, 128, 4, 2, true, true>) : launch(gemm_lora_kernel<128, 128, 4, 2, false, true>);
+    if (patch)
+        return t_kmajor ? launch(gemm_lora_kernel<128, 128, 4, 2, true, true, false, false, false, 0, WideArgs>, WideArgs())
+                        : launch(gemm_lora_kernel<128, 128, 4, 2, false, true, false, false, false, 0, WideArgs>, WideArgs());
+    return t_kmajor ? launch(gemm_lora_kernel<128, 128, 4, 2, true, true>, GemmArgs()) : launch(gemm_lora_kernel<128, 128, 4, 2, false, true>, GemmArgs());
 }
 
 hipError_t launch_skinny_finish(const SkinnyArgs &a, const SkinnyItem *wide, int n_wide, int wide_split, int n_items, int row_tiles, int n_split,
@@ -2288,12 +2349,12 @@ int gemm_tile_cols(int tile_cfg)
     return tile_cfg == kTile256x256 ? 256 : (tile_cfg == kTile128x192 || tile_cfg == kTile256x192 ? 192 : 128);
 }
 
-template <int RP, bool KM, int RT>
-static hipError_t launch_skinny_t(const SkinnyArgs &a, int n_items, int n_split, hipStream_t st)
+template <int RP, bool KM, int RT, typename Args>
+static hipError_t launch_skinny_a(const SkinnyArgs &a, int n_items, int n_split, hipStream_t st, const PlanPatch *patch)
 {
     using C = SkinnyCfg<RP>;
     constexpr int smem = C::KW * 16 * RT * C::RED_LD * 4 + (KM ? 0 : C::KW * C::STAGE_BYTES);
-    auto kern = skinny_kernel<RP, KM, RT>;
+    auto kern = skinny_kernel<RP, KM, RT, Args>;
     static bool attr_done = false;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -2301,21 +2362,34 @@ static hipError_t launch_skinny_t(const SkinnyArgs &a, int n_items, int n_split,
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    SkinnyArgs b = a;
+    Args b;
+    static_cast<SkinnyArgs &>(b) = a;
     b.n_items = n_items;
     if (!b.warm_base || b.warm_bytes < 16) b.warm_blocks = 0;
-    COLLM_LAUNCH(kern, dim3(n_items + b.warm_blocks, n_split), dim3(C::KW * 64), smem, st, b);
+    int extra = b.warm_blocks;
+    if constexpr (kHasPatch<Args>) {
+        b.patch = *patch;
+        extra += patch->blocks;
+    }
+    COLLM_LAUNCH(kern, dim3(n_items + extra, n_split), dim3(C::KW * 64), smem, st, b);
     return hipGetLastError();
 }
 
+template <int RP, bool KM, int RT>
+static hipError_t launch_skinny_t(const SkinnyArgs &a, int n_items, int n_split, hipStream_t st, const PlanPatch *patch)
+{
+    return patch ? launch_skinny_a<RP, KM, RT, SkinnyPassArgs>(a, n_items, n_split, st, patch)
+                 : launch_skinny_a<RP, KM, RT, SkinnyArgs>(a, n_items, n_split, st, nullptr);
+}
+
 template <int RP, bool KM>
-static hipError_t launch_skinny_rt(const SkinnyArgs &a, int n_items, int row_tiles, int n_split, hipStream_t st)
+static hipError_t launch_skinny_rt(const SkinnyArgs &a, int n_items, int row_tiles, int n_split, hipStream_t st, const PlanPatch *patch)
 {
     constexpr int RTMAX = SkinnyCfg<RP>::RTMAX;
     if (row_tiles > RTMAX) return hipErrorInvalidValue;
     if constexpr (RTMAX >= 2)
-        if (row_tiles > 1) return launch_skinny_t<RP, KM, 2>(a, n_items, n_split, st);
-    return launch_skinny_t<RP, KM, 1>(a, n_items, n_split, st);
+        if (row_tiles > 1) return launch_skinny_t<RP, KM, 2>(a, n_items, n_split, st, patch);
+    return launch_skinny_t<RP, KM, 1>(a, n_items, n_split, st, patch);
 }
 
 int skinny_max_row_tiles(int rpad) { return rpad <= 128 ? 2 : 1; }
@@ -2330,13 +2404,13 @@ int skinny_depth(int rpad, int row_tiles)
 }
 
 hipError_t launch_skinny(const SkinnyArgs &a, int n_items, int rpad, int row_tiles, int n_split, bool t_kmajor,
-                         hipStream_t st)
+                         hipStream_t st, const PlanPatch *patch)
 {
     if (n_items <= 0) return hipSuccess;
     if (n_split < 1 || (n_split > 1 && !a.part)) return hipErrorInvalidValue;
 #define COLLM_SK(RP) \
-    return t_kmajor ? launch_skinny_rt<RP, true>(a, n_items, row_tiles, n_split, st) \
-                    : launch_skinny_rt<RP, false>(a, n_items, row_tiles, n_split, st)
+    return t_kmajor ? launch_skinny_rt<RP, true>(a, n_items, row_tiles, n_split, st, patch) \
+                    : launch_skinny_rt<RP, false>(a, n_items, row_tiles, n_split, st, patch)
     if (rpad <= 16) { COLLM_SK(16); }
     if (rpad <= 32) { COLLM_SK(32); }
     if (rpad <= 64) { COLLM_SK(64); }

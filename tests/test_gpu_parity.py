@@ -674,6 +674,76 @@ def test_same_batch_other_adapter_tables_reuses_the_plan():
         ctx.close()
 
 
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("ranks,lens,ads,wide,n_adapters", [
+    ([16, 8, 12], [40, 1, 300, 9], [0, 1, 2, -1], None, 3),             # row items only
+    ([64, 16, 128], [200, 1, 37, 130], [0, 1, 2, 0], None, 3),          # the tiled pass only
+    ([64, 12, 100], [200, 1, 37, 130], [0, 1, 2, 1], 64, 3),            # both kinds of items
+    ([8], [70, 9], [-1, -1], None, 1),                                  # no row has an adapter: nothing carries the addresses
+    ([16] * 128, [60, 1, 90], [127, 3, 64], None, 128),                 # as many adapters as a pass carries
+    ([16] * 129, [60, 1, 90], [128, 3, 64], None, 129),                 # one more
+])
+def test_new_table_addresses_ride_on_the_first_pass(ranks, lens, ads, wide, n_adapters, transposed):
+    # the same batch through three sets of tables in turn, in calls queued without a wait; backward calls in between use what
+    # the forward call before them put in (gradients on), or put in their own
+    trn = [1 if a >= 0 and i != 1 else 0 for i, a in enumerate(ads)]
+    ws = [_adhoc("bf16", 200, 264, ranks, lens, ads, trn, scale=0.5, seed=20 + k) for k in range(3)]
+    ctx = make_ctx(ws[0])
+    if wide is not None:
+        ctx.set_wide_pass(wide)
+    layers = [DeviceLayer(w, wl.make_tensors(w), ctx, transposed=transposed) for w in ws]
+    modes = []
+    for _ in range(2):
+        for l in layers:
+            l.fwd()
+            modes.append(ctx.plan_stats()["mode"])
+        for l in (layers[2], layers[0], layers[1]):
+            l.bwd()
+        for _ in range(7):  # more uploads than staging slots
+            for l in layers:
+                l.fwd()
+    assert modes == [1, 2, 2, 2, 2, 2]
+    for l in layers:
+        check_full(l, TOL["bf16"])
+    ctx.close()
+
+
+def test_recorded_calls_with_new_tables_upload_the_whole_plan():
+    # Two layers recorded on the stream they were warmed up on (only the tables are new then).  A recorded call uploads all of
+    # the plan.  Eager work between the replays goes through another context: a replay puts the recorded batch's plan on the
+    # device, of which the context it was recorded from does not learn.
+    import torch
+
+    lens, ads, trn = [60, 1, 90, 33], [0, 1, 2, 1], [1, 0, 0, 1]
+    ws = [_adhoc("bf16", 200, 264, [16, 8, 64], lens, ads, trn, scale=0.5, seed=30 + k) for k in range(2)]
+    ctx, ctx2 = make_ctx(ws[0]), make_ctx(ws[0])
+    a, b = [DeviceLayer(w, wl.make_tensors(w), ctx) for w in ws]
+    o = DeviceLayer(ws[0], wl.make_tensors(ws[0]), ctx2)
+    torch.cuda.synchronize()
+    st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(st):
+        a.fwd()
+        whole = ctx.plan_stats()["bytes"]
+        b.fwd()
+        assert ctx.plan_stats()["mode"] == 2 and ctx.plan_stats()["bytes"] < whole
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=st):
+        for l in (a, b):
+            l.fwd()
+            assert ctx.plan_stats()["mode"] == 2 and ctx.plan_stats()["bytes"] == whole
+    ref = [l.y.clone() for l in (a, b)]
+    for _ in range(3):
+        for l in (a, b):
+            l.y.fill_(float("nan"))
+        o.fwd()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(a.y, ref[0]) and torch.equal(b.y, ref[1])
+    ctx.close()
+    ctx2.close()
+
+
 def test_weight_fetch_beside_the_rank_wide_passes():
     # A small weight is read once by extra blocks of the rank-wide pass that runs before each GEMM (the pass must
     # stream fewer bytes than the weight).  Those blocks compute nothing: results are as the oracle's, on the
