@@ -43,6 +43,7 @@ int hip_fail(hipError_t e, const char *what)
 constexpr int kSlots = 16;             // pinned staging ring: the host may run this many uploads ahead
 constexpr uint64_t kWarmMaxBytes = (uint64_t)40 << 20;  // largest weight a rank-wide pass fetches ahead of its GEMM
 constexpr int kMaxProfile = 16;
+constexpr int64_t kDualMinBytes = (int64_t)192 << 20;  // training rows of dy from which dh and dB come from one pass (bwd_impl)
 
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
@@ -655,10 +656,13 @@ int stage_patch(collm_ctx *c, const void *const *tab, int n_adapters)
 }
 
 // Build (or reuse) the plan of this batch and put it on the device.
+// pass_tab: null, or the call begins with a rank-wide pass over these tables, which can carry new addresses (run_skinny takes
+// c->patch).  out_args: the call's kernels get the gradient buffers as arguments, not through the plan.
 int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const void *const *B,
                  const int32_t *rank, const int32_t *seg_start, const int32_t *seg_adapter,
                  const uint8_t *seg_is_train, float *const *dA, float *const *dB, bool allow_reuse,
-                 hipStream_t st, bool fwd, const int32_t *rank_ext_all = nullptr, int n_sib = 1, bool swiglu = false)
+                 hipStream_t st, bool fwd, const void *const *pass_tab, bool out_args, const int32_t *rank_ext_all = nullptr,
+                 int n_sib = 1, bool swiglu = false)
 {
     const bool f32 = s->dtype == COLLM_F32;
     int n_train = 0;
@@ -749,9 +753,9 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     } else if (dA || dB || upload_all) {
         // same batch as the plan on the device: at most the pointer tables are new
         const int N = s->n_adapters;
-        // (a forward call begins with a rank-wide pass that can carry them, unless no row has an adapter; a backward call may
-        // begin with gradients on the second stream)
-        bool carry = upload_all && fwd && !f32 && !c->static_scratch && N <= kPatchTables && c->L.all.n_items + c->L.all.n_wide > 0;
+        // (no row has an adapter: nothing runs)
+        const RowOrderLayout &R = fwd ? c->L.all : c->L.train;
+        bool carry = upload_all && pass_tab && !f32 && !c->static_scratch && N <= kPatchTables && R.n_items + R.n_wide > 0;
         if (carry) {
             // (a call recorded into a graph uploads all of the plan: at a replay the device may hold another batch's)
             hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -759,7 +763,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
             carry = capture == hipStreamCaptureStatusNone;
         }
         bool changed = false;
-        for (int a = 0; a < N; ++a) {
+        for (int a = 0; a < (out_args ? 0 : N); ++a) {
             const uint64_t va = dA ? (uint64_t)(uintptr_t)dA[a] : 0, vb = dB ? (uint64_t)(uintptr_t)dB[a] : 0;
             changed |= std::memcmp(c->plan.data() + c->L.off_dA_ptr + 2 * a, &va, 8) != 0;
             changed |= std::memcmp(c->plan.data() + c->L.off_dB_ptr + 2 * a, &vb, 8) != 0;
@@ -767,7 +771,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
             std::memcpy(c->plan.data() + c->L.off_dB_ptr + 2 * a, &vb, 8);
         }
         if (carry) {
-            const int rc = stage_patch(c, A, N);
+            const int rc = stage_patch(c, pass_tab, N);
             if (rc != COLLM_OK) return rc;
         } else if (upload_all) {
             int rc = upload(c, 0, c->L.total_ints, st);
@@ -781,6 +785,16 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     c->last_stream = st;
     return COLLM_OK;
 }
+
+// A call that ends without having launched the pass that was to carry new addresses leaves a plan that is not whole.
+struct PatchGuard {
+    collm_ctx *c;
+    ~PatchGuard()
+    {
+        if (c->patch.blocks > 0) c->plan_valid = false;
+        c->patch.blocks = 0;
+    }
+};
 
 // A rank-wide pass restricted to one of several sibling projections that lie side by side in the columns of
 // dy and of the K-major tables: columns col0 .. col0 + K of rows of length ld.
@@ -805,13 +819,8 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
                const SliceSums *sums = nullptr, int bf_up = 0)
 {
     if (R.n_items == 0 && R.n_wide == 0) return COLLM_OK;
-    // (taken by the pass's first kernel; behind it the plan is whole)
-    PlanPatch patch;
-    patch.blocks = 0;
-    if (c->patch.blocks > 0) {
-        patch = c->patch;
-        c->patch.blocks = 0;
-    }
+    // (taken by the call's first pass's first kernel; behind it the plan is whole)
+    const PlanPatch *patch = c->patch.blocks > 0 ? &c->patch : nullptr;
     SkinnyArgs a{};
     // The weight of the GEMM that follows, fetched into the last-level cache by extra blocks of this pass (one per
     // compute unit) - if the weight is small (a GEMM of so few K tiles per block cannot hide the memory's latency:
@@ -921,11 +930,14 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
         ns = std::max<long>(ns, 1);
         g.k_per_split = round_up((int)((K + ns - 1) / ns), 64);
         n_wsplit = (K + g.k_per_split - 1) / g.k_per_split;
-        HIP_TRY(launch_wide(g, R.n_wide, rpad, n_wsplit, t_kmajor, st, patch.blocks > 0 ? &patch : nullptr));
-        patch.blocks = 0;
+        HIP_TRY(launch_wide(g, R.n_wide, rpad, n_wsplit, t_kmajor, st, patch));
+        c->patch.blocks = 0;
+        patch = nullptr;
     }
-    if (R.n_items > 0)
-        HIP_TRY(launch_skinny(a, R.n_items, rpad, R.item_rows / kSkinnyRows, n_split, t_kmajor, st, patch.blocks > 0 ? &patch : nullptr));
+    if (R.n_items > 0) {
+        HIP_TRY(launch_skinny(a, R.n_items, rpad, R.item_rows / kSkinnyRows, n_split, t_kmajor, st, patch));
+        c->patch.blocks = 0;
+    }
     // (the sums of the two kinds of items lie in different rows of the workspace)
     HIP_TRY(launch_skinny_finish(a, reinterpret_cast<const SkinnyItem *>(c->d_plan + R.off_wide), R.n_wide, n_wsplit,
                                  n_split > 1 ? R.n_items : 0, R.item_rows / kSkinnyRows, n_split, st));
@@ -1377,9 +1389,10 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(c->device));
     c->n_prof = 0;
+    const PatchGuard guard{c};
     {
         Prof prof(c, st, "plan_copy");
-        rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, nullptr, nullptr, true, st, true,
+        rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, nullptr, nullptr, true, st, true, A, false,
                           P > 1 ? rank1 : nullptr, P, swiglu);
     }
     if (rc != COLLM_OK) return rc;
@@ -1393,10 +1406,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     rc = run_skinny(c, s, L.all, x, s->d_in, L.off_A_ptr, tr, h_save, c->max_rank, c->max_rank, 1, 1.0f,
                     c->d_hs, s->scale, "shrink", st, nullptr, !f32 && (swiglu || warm_pays(c, L.all, s->n_tokens, s->d_out, s->d_in, tr, P <= 1, P > 1)) ? W : nullptr,
                     (uint64_t)s->d_in * s->d_out * 2, nullptr, swiglu ? L.rpad / 2 : 0);
-    if (rc != COLLM_OK) {
-        c->plan_valid = false;  // (the pass may not have put in the addresses it was to carry)
-        return rc;
-    }
+    if (rc != COLLM_OK) return rc;
 
     GemmArgs g{};
     g.a = x;
@@ -1495,11 +1505,16 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     rc = check_common(c, s, x, W, A, B, rank, seg_start, seg_adapter, seg_is_train);
     if (rc != COLLM_OK) return rc;
     if ((dA == nullptr) != (dB == nullptr)) return COLLM_E_NULL;
-    int n_train = 0;
+    int n_train = 0, n_trained = 0;  // (trained adapters are counted up to kGradOuts + 1)
+    int32_t trained[kGradOuts];
     for (int k = 0; k < s->n_segments; ++k) {
         if (!seg_is_train[k] || seg_start[k + 1] == seg_start[k]) continue;
         n_train += seg_start[k + 1] - seg_start[k];
         const int a = seg_adapter[k];
+        if (n_trained <= kGradOuts && std::find(trained, trained + n_trained, a) == trained + n_trained) {
+            if (n_trained < kGradOuts) trained[n_trained] = a;
+            ++n_trained;
+        }
         if (dA) {
             if (!dA[a] || !dB[a]) return COLLM_E_ADAPTER;
             if (!aligned16(dA[a]) || !aligned16(dB[a])) return COLLM_E_ALIGN;
@@ -1511,9 +1526,16 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(c->device));
     c->n_prof = 0;
+    // Few gradient buffers travel as arguments of the gradient kernels, which then need nothing that an upload of this call puts into
+    // the plan (the pass over dy that gives dh and dB at once, for narrow ranks, looks them up there): new adapter tables
+    // ride on the rank-wide pass that the call begins with, beside dB on the second stream.  Four 4096 -> 4096 projections, 2048 tokens, 1792 of
+    // them training, forward and backward: 634 us with the backward calls' upload in front, 610 without.
+    const bool may_dual = P == 1 && s->layout == COLLM_LAYOUT_IN_OUT && c->dual_pass != 0 && (c->dual_pass == 1 || (int64_t)n_train * s->d_out * 2 >= kDualMinBytes);
+    const bool out_args = dA && s->dtype == COLLM_BF16 && n_trained <= kGradOuts && !may_dual;
+    const PatchGuard guard{c};
     {
         Prof prof(c, st, "plan_copy");
-        rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, dA, dB, true, st, false,
+        rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, dA, dB, true, st, false, dA && !out_args ? nullptr : (!h_save && dA ? A : B), out_args,
                           P > 1 ? rank1 : nullptr, P);
     }
     if (rc != COLLM_OK) return rc;
@@ -1547,6 +1569,12 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     ga.row_tok = c->d_plan + L.train.off_row_tok;
     ga.items = reinterpret_cast<const GradItem *>(c->d_plan + L.off_grad);
     ga.accumulate = accumulate ? 1 : 0;
+    auto set_outs = [&](float *const *g) {
+        if (!out_args || L.n_grad > kGradOuts) return;
+        ga.n_out = L.n_grad;
+        const GradItem *items = reinterpret_cast<const GradItem *>(c->plan.data() + L.off_grad);
+        for (int k = 0; k < L.n_grad; ++k) ga.out[k] = (uint64_t)(uintptr_t)g[items[k].adapter];
+    };
     if (overlap && dx && !f32) {
         const int tile = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, c->gemm_split != 1, one_round, c->tile_steps_train).tile;
         ga.beside_gemm = tile == kTile128x128 ? 1 : 0;
@@ -1561,7 +1589,6 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // no gain for the step (the two passes run side by side on two streams and the second reader finds dy in the
     // cache); on 8192 x 1024 (34 against 10 + 15) and 1792 x 4096 (28 against 14 + 10) the partial sums and the two
     // kernels that add them cost more than the second read.
-    constexpr int64_t kDualMinBytes = (int64_t)192 << 20;
     DualArgs du{};
     bool dual = false;
     if (!f32 && !tr && P == 1 && dA && c->dual_pass != 0 && L.rpad == kKStep && L.train.n_wide == 0 && L.n_grad > 0 &&
@@ -1655,6 +1682,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
             }
         }
         ga.out_tab = reinterpret_cast<const uint64_t *>(c->d_plan + L.off_dB_ptr);
+        set_outs(dB);
         ga.out_transposed = tr ? 1 : 0;
         {
             Prof prof(c, gs, "grad_dB");
@@ -1721,6 +1749,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
             ga.ld_small_bf = L.rpad;
         }
         ga.out_tab = reinterpret_cast<const uint64_t *>(c->d_plan + L.off_dA_ptr);
+        set_outs(dA);
         ga.out_transposed = tr ? 0 : 1;
         {
             Prof prof(c, gs, "grad_dA");

@@ -137,6 +137,7 @@ struct SkinnyArgs {
     int warm_blocks, n_items;
 };
 
+constexpr int kGradOuts = 16;  // trained adapters whose gradient buffers travel as arguments
 // out_a(q, n) = sum_t small[t][q] * big[tok(t)][n] over one adapter's training rows
 struct GradArgs {
     const void *big;          // [T][N] gathered through row_tok
@@ -152,6 +153,10 @@ struct GradArgs {
     const int32_t *row_tok;   // training row order
     const GradItem *items;    // one per trained adapter
     const uint64_t *out_tab;  // adapter -> fp32 output
+    // bf16 kernels: or (n_out > 0) the outputs of the items, in their order.  A call's few gradient buffers need no upload
+    // in front of its kernels then, and its new adapter tables can ride on a rank-wide pass (PlanPatch).
+    int n_out;
+    uint64_t out[kGradOuts];
     int out_transposed;       // 0: out[q][n] (row length N); 1: out[n][q] (row length rank)
     int accumulate;
     int beside_gemm;          // launch_grad: a GEMM of 128x128 tiles may start on another stream while this runs (see grad_lds)

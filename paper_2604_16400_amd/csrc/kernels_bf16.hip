@@ -1923,7 +1923,7 @@ __global__ void __launch_bounds__(GradCfg<RP>::KW * 64) grad_kernel(GradArgs p)
                 red[(wave * RP + mb * 16 + kg * 4 + j) * C::RED_LD + nb * 16 + l16] = acc[mb][nb][j];
     __syncthreads();
 
-    float *out = reinterpret_cast<float *>(p.out_tab[it.adapter]);
+    float *out = reinterpret_cast<float *>(p.n_out > 0 ? p.out[blockIdx.y] : p.out_tab[it.adapter]);
     const int qn = (rank - q0) < RP ? (rank - q0) : RP;  // rank indices of this slice
     if (qn <= 0) return;
     for (int idx = tid; idx < 64 * qn; idx += KW * 64) {

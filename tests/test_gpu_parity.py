@@ -674,6 +674,7 @@ def test_same_batch_other_adapter_tables_reuses_the_plan():
         ctx.close()
 
 
+@pytest.mark.parametrize("grad_streams", [0, 1])
 @pytest.mark.parametrize("transposed", [False, True])
 @pytest.mark.parametrize("ranks,lens,ads,wide,n_adapters", [
     ([16, 8, 12], [40, 1, 300, 9], [0, 1, 2, -1], None, 3),             # row items only
@@ -682,13 +683,18 @@ def test_same_batch_other_adapter_tables_reuses_the_plan():
     ([8], [70, 9], [-1, -1], None, 1),                                  # no row has an adapter: nothing carries the addresses
     ([16] * 128, [60, 1, 90], [127, 3, 64], None, 128),                 # as many adapters as a pass carries
     ([16] * 129, [60, 1, 90], [128, 3, 64], None, 129),                 # one more
+    ([16] * 20, [9] * 16 + [1], list(range(16)) + [18], None, 20),      # 16 and ...
+    ([16] * 20, [9] * 18, list(range(18)), None, 20),                   # 17 trained adapters: as arguments, through the plan
 ])
-def test_new_table_addresses_ride_on_the_first_pass(ranks, lens, ads, wide, n_adapters, transposed):
+def test_new_table_addresses_ride_on_the_first_pass(ranks, lens, ads, wide, n_adapters, transposed, grad_streams):
     # the same batch through three sets of tables in turn, in calls queued without a wait; backward calls in between use what
     # the forward call before them put in (gradients on), or put in their own
-    trn = [1 if a >= 0 and i != 1 else 0 for i, a in enumerate(ads)]
+    trn = [1 if a >= 0 and lens[i] > 1 else 0 for i, a in enumerate(ads)]
+    if len(ads) == 18:
+        trn[17] = 0
     ws = [_adhoc("bf16", 200, 264, ranks, lens, ads, trn, scale=0.5, seed=20 + k) for k in range(3)]
     ctx = make_ctx(ws[0])
+    ctx.set_grad_streams(grad_streams)
     if wide is not None:
         ctx.set_wide_pass(wide)
     layers = [DeviceLayer(w, wl.make_tensors(w), ctx, transposed=transposed) for w in ws]
@@ -699,6 +705,8 @@ def test_new_table_addresses_ride_on_the_first_pass(ranks, lens, ads, wide, n_ad
             modes.append(ctx.plan_stats()["mode"])
         for l in (layers[2], layers[0], layers[1]):
             l.bwd()
+            l.bwd(h_save=False)  # (begins with the pass over x)
+            l.bwd(dab=False)
         for _ in range(7):  # more uploads than staging slots
             for l in layers:
                 l.fwd()
