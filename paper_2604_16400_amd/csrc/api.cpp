@@ -379,6 +379,17 @@ bool grads_alone(int n_train, int d_in, int d_out, bool f32, int rpad)
     return bytes <= (f32 ? 8 * MiB : (rpad <= 16 ? 5 * MiB : (rpad <= 32 ? 2 * MiB : 0)));
 }
 
+// Whether dB starts behind the dh pass, with dA, instead of beside it: the caller's stream then has one point less at which it hands
+// over to the second one (5 us of idle time each), and the dX GEMM alone has to cover both gradients.  So not where they are long against
+// it: ranks above 32, a dimension so narrow that dX is short for its bytes, many columns of dy for few of x.  Backward call, beside
+// the dh pass / behind it, us: 1792 rows 4096 -> 4096 rank 16 81.7 / 79.5, 7000 rows 240 / 216, 2048 rows 5120 -> 5120 126 / 118, 575 rows 8192 -> 6368
+// rank 32 120 / 115; geometric mean over 30 shapes inside these limits 0.965, 0.82 .. 1.03.  Outside: 230 rows 2568 -> 18432 rank 8
+// 63 / 69, 4683 rows 1536 -> 4096 rank 16 90 / 92, 3500 rows 4096 -> 4096 rank 64 139 / 152, 276 rows 8448 -> 3328 rank 128 92 / 108.
+bool fork_behind_dh(int rpad, int d_in, int d_out)
+{
+    return rpad <= 32 && (int64_t)d_in * d_out >= (int64_t)1700 * ((int64_t)d_in + d_out) && d_out <= 3 * (int64_t)d_in;
+}
+
 // Whether the dX GEMM of a backward call may take the tiles that fill a CU's LDS and one round of CUs (pick_tiling): not
 // where the gradient kernels run beside it on the second stream, as a CU that holds such a tile has no room for their blocks.
 // Backward call, us, with the two sizes only / all of them: 1792 rows 4096 -> 4096 86 / 88, 901 rows 4104 -> 11008 172 / 180.
@@ -1647,12 +1658,13 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         if (rc != COLLM_OK) return rc;
         HIP_TRY(launch_dual_sum(du, st));
     }
-    if (dA && !dual) {
-        if (overlap) {
+    // dB_a = s h^T dy
+    const bool late = overlap && !dual && dx && P == 1 && fork_behind_dh(L.rpad, s->d_in, s->d_out);
+    auto launch_dB = [&]() -> int {
+        if (overlap && !late) {
             HIP_TRY(hipEventRecord(c->ev_fork, st));
             HIP_TRY(hipStreamWaitEvent(c->side, c->ev_fork, 0));
         }
-        // dB_a = s h^T dy
         ga.big = dy;
         ga.ld_big = s->d_out;
         ga.big_bytes = (uint32_t)((int64_t)s->n_tokens * s->d_out * esz);
@@ -1705,6 +1717,11 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
                 }
             }
         }
+        return COLLM_OK;
+    };
+    if (dA && !dual && !late) {
+        rc = launch_dB();
+        if (rc != COLLM_OK) return rc;
     }
 
     // dh = s dy B_a^T: fp32 for dA, element type for the dX GEMM's extra K-steps
@@ -1734,6 +1751,10 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         if (overlap) {
             HIP_TRY(hipEventRecord(c->ev_dh, st));
             HIP_TRY(hipStreamWaitEvent(c->side, c->ev_dh, 0));
+        }
+        if (late) {
+            rc = launch_dB();
+            if (rc != COLLM_OK) return rc;
         }
         // dA_a = x^T dh
         ga.big = x;

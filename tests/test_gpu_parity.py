@@ -497,6 +497,18 @@ def test_adapter_gradients_on_either_stream(dtype, ranks, transposed, grad_strea
         layer.ctx.close()
 
 
+@pytest.mark.parametrize("h_save", [True, False])
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("d_in,d_out,ranks", [
+    (3400, 3400, [16, 8]), (2272, 6816, [32, 20]),   # dB starts behind the dh pass, with dA: at the limits, and
+    (3392, 3400, [16, 8]), (2272, 6824, [32, 20]),   # beside it: one step beyond them
+    (3400, 3400, [16, 40]),
+])
+def test_adapter_gradients_started_behind_the_dh_pass(d_in, d_out, ranks, transposed, h_save):
+    w = _adhoc("bf16", d_in, d_out, ranks, [3, 50, 1, 38], [0, 1, 0, 0], [0, 1, 0, 1], scale=0.5)
+    _run_full(w, transposed=transposed, grad_streams=1, h_save=h_save)
+
+
 @pytest.mark.parametrize("transposed", [False, True])
 def test_many_extension_steps_in_one_row_tile(transposed):
     # Twelve adapters of ranks 128 and 256 with 20 rows each share one 256-row tile: 144 extension steps in four
