@@ -383,11 +383,19 @@ bool grads_alone(int n_train, int d_in, int d_out, bool f32, int rpad)
 // over to the second one (5 us of idle time each), and the dX GEMM alone has to cover both gradients.  So not where they are long against
 // it: ranks above 32, a dimension so narrow that dX is short for its bytes, many columns of dy for few of x.  Backward call, beside
 // the dh pass / behind it, us: 1792 rows 4096 -> 4096 rank 16 81.7 / 79.5, 7000 rows 240 / 216, 2048 rows 5120 -> 5120 126 / 118, 575 rows 8192 -> 6368
-// rank 32 120 / 115; geometric mean over 30 shapes inside these limits 0.965, 0.82 .. 1.03.  Outside: 230 rows 2568 -> 18432 rank 8
-// 63 / 69, 4683 rows 1536 -> 4096 rank 16 90 / 92, 3500 rows 4096 -> 4096 rank 64 139 / 152, 276 rows 8448 -> 3328 rank 128 92 / 108.
+// rank 32 120 / 115, 3000 rows 8192 -> 16384 862 / 700; 30 shapes inside these limits 0.965 (geometric mean), 0.82 .. 1.03.  Outside: 230 rows
+// 2568 -> 18432 rank 8 63 / 69, 4683 rows 1536 -> 4096 rank 16 90 / 92, 3500 rows 4096 -> 4096 rank 64 139 / 152, 276 rows 8448 -> 3328 rank 128 92 / 108.
 bool fork_behind_dh(int rpad, int d_in, int d_out)
 {
     return rpad <= 32 && (int64_t)d_in * d_out >= (int64_t)1700 * ((int64_t)d_in + d_out) && d_out <= 3 * (int64_t)d_in;
+}
+
+// ... nor where 256x256 tiles of dX make whole rounds (or all but a tenth of one): no CU is then free for the gradients before its end.
+// 4096 rows 8192 -> 8192 rank 16 431 / 439 us, 4000 rows 4096 -> 4096 rank 32 147 / 152, 12000 rows rank 16 363 / 375.
+bool whole_rounds(int rows, int cols)
+{
+    const int last = (int)((int64_t)(round_up(rows, 256) / 256) * ((cols + 255) / 256) % 256);
+    return last == 0 || last > 230;
 }
 
 // Whether the dX GEMM of a backward call may take the tiles that fill a CU's LDS and one round of CUs (pick_tiling): not
@@ -1586,9 +1594,11 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         const GradItem *items = reinterpret_cast<const GradItem *>(c->plan.data() + L.off_grad);
         for (int k = 0; k < L.n_grad; ++k) ga.out[k] = (uint64_t)(uintptr_t)g[items[k].adapter];
     };
+    bool dx_even = false;  // the dX GEMM leaves no CU free
     if (overlap && dx && !f32) {
         const int tile = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, c->gemm_split != 1, one_round, c->tile_steps_train).tile;
         ga.beside_gemm = tile == kTile128x128 ? 1 : 0;
+        dx_even = tile == kTile256x256 && whole_rounds(n_train, s->d_in);
     }
 
     // Narrow ranks (all at most 16), tables as [rank][d_out]: dh and dB_a both come from ONE pass over the training
@@ -1659,7 +1669,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         HIP_TRY(launch_dual_sum(du, st));
     }
     // dB_a = s h^T dy
-    const bool late = overlap && !dual && dx && P == 1 && fork_behind_dh(L.rpad, s->d_in, s->d_out);
+    const bool late = overlap && !dual && dx && P == 1 && !dx_even && fork_behind_dh(L.rpad, s->d_in, s->d_out);
     auto launch_dB = [&]() -> int {
         if (overlap && !late) {
             HIP_TRY(hipEventRecord(c->ev_fork, st));
