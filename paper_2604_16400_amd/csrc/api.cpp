@@ -80,6 +80,9 @@ struct collm_ctx {
     std::vector<int32_t> plan;
     PlanLayout L;
     bool plan_valid = false;
+    // A call of this context has been recorded into a graph.  A replay puts the recorded call's plan on the device and nothing tells the host,
+    // so from then on every call uploads all of its plan (the host's copy of a known batch is still reused).
+    bool recorded = false;
     // what the cached plan was built from
     collm_shape key_shape{};
     int key_bm_all = 0, key_bm_train = 0;
@@ -611,15 +614,15 @@ int take_slot(collm_ctx *c, int *slot, uint32_t *seq)
     return COLLM_OK;
 }
 
-// Copy ints [lo, hi) of the host plan to the device plan through a pinned staging slot.
-int upload(collm_ctx *c, size_t lo, size_t hi, hipStream_t st)
+// Copy ints [lo, hi) of the host plan to the device plan: through a pinned staging slot, or (no pinned staging exists, or a recorded
+// call, whose slot later uploads would overwrite before a replay reads it) inside the arguments of a few small kernels.
+int upload(collm_ctx *c, size_t lo, size_t hi, hipStream_t st, bool recording)
 {
     if (hi <= lo) return COLLM_OK;
     const auto t0 = std::chrono::steady_clock::now();
     // rounded outwards to 16 bytes (the plan vector is padded to a multiple of 64 ints)
     const size_t lo4 = lo & ~(size_t)3, hi4 = std::min((hi + 3) & ~(size_t)3, c->plan.size());
-    if (c->static_scratch) {
-        // no pinned staging exists: the words travel inside the arguments of a few small kernels
+    if (c->static_scratch || recording) {
         HIP_TRY(launch_plan_words(c->plan.data() + lo4, c->d_plan + lo4, hi4 - lo4, st));
     } else {
         int sl = 0;
@@ -684,6 +687,13 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
                  int n_sib = 1, bool swiglu = false)
 {
     const bool f32 = s->dtype == COLLM_F32;
+    bool recording = false;
+    if (st) {  // (the default stream cannot be recorded)
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(st, &capture));
+        recording = capture != hipStreamCaptureStatusNone;
+        c->recorded = c->recorded || recording;
+    }
     int n_train = 0;
     for (int k = 0; k < s->n_segments; ++k)
         if (seg_is_train[k]) n_train += seg_start[k + 1] - seg_start[k];
@@ -710,7 +720,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     // than the one the plan was uploaded on builds it again, since nothing orders the two streams.
     const bool reuse = allow_reuse && st == c->last_stream && n_sib == c->key_nsib &&
                        same_key(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, bm_all, bm_train, wide, fwd);
-    bool upload_all = false;
+    bool new_tables = false;
     c->plan_build_us = c->plan_upload_us = 0.f;
     c->plan_mode = c->plan_bytes_up = 0;
     const auto t_plan = std::chrono::steady_clock::now();
@@ -720,7 +730,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     };
     if (reuse && !same_tables(c, s->n_adapters, A, B)) {
         patch_tables(c, s->n_adapters, A, B);
-        upload_all = true;
+        new_tables = true;
         built(2);
     }
     if (!reuse) {
@@ -749,7 +759,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
             return COLLM_E_SHAPE;
         }
         built(1);
-        rc = upload(c, 0, c->L.total_ints, st);
+        rc = upload(c, 0, c->L.total_ints, st, recording);
         if (rc != COLLM_OK) return rc;
         // remember what this plan was built from
         const int S = s->n_segments, N = s->n_adapters;
@@ -769,18 +779,12 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
             c->key_B[a] = (uint64_t)(uintptr_t)B[a];
         }
         c->plan_valid = true;
-    } else if (dA || dB || upload_all) {
+    } else if (dA || dB || new_tables || c->recorded) {
         // same batch as the plan on the device: at most the pointer tables are new
         const int N = s->n_adapters;
         // (no row has an adapter: nothing runs)
         const RowOrderLayout &R = fwd ? c->L.all : c->L.train;
-        bool carry = upload_all && pass_tab && !f32 && !c->static_scratch && N <= kPatchTables && R.n_items + R.n_wide > 0;
-        if (carry) {
-            // (a call recorded into a graph uploads all of the plan: at a replay the device may hold another batch's)
-            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-            HIP_TRY(hipStreamIsCapturing(st, &capture));
-            carry = capture == hipStreamCaptureStatusNone;
-        }
+        const bool carry = new_tables && pass_tab && !f32 && !c->static_scratch && !c->recorded && N <= kPatchTables && R.n_items + R.n_wide > 0;
         bool changed = false;
         for (int a = 0; a < (out_args ? 0 : N); ++a) {
             const uint64_t va = dA ? (uint64_t)(uintptr_t)dA[a] : 0, vb = dB ? (uint64_t)(uintptr_t)dB[a] : 0;
@@ -792,12 +796,12 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
         if (carry) {
             const int rc = stage_patch(c, pass_tab, N);
             if (rc != COLLM_OK) return rc;
-        } else if (upload_all) {
-            int rc = upload(c, 0, c->L.total_ints, st);
+        } else if (new_tables || c->recorded) {
+            int rc = upload(c, 0, c->L.total_ints, st, recording);
             if (rc != COLLM_OK) return rc;
         } else if (changed) {
             c->plan_mode = 3;
-            int rc = upload(c, c->L.off_dA_ptr, (size_t)c->L.off_dB_ptr + 2 * (size_t)std::max(N, 1), st);
+            int rc = upload(c, c->L.off_dA_ptr, (size_t)c->L.off_dB_ptr + 2 * (size_t)std::max(N, 1), st, recording);
             if (rc != COLLM_OK) return rc;
         }
     }

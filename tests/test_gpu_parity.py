@@ -728,40 +728,61 @@ def test_new_table_addresses_ride_on_the_first_pass(ranks, lens, ads, wide, n_ad
     ctx.close()
 
 
-def test_recorded_calls_with_new_tables_upload_the_whole_plan():
-    # Two layers recorded on the stream they were warmed up on (only the tables are new then).  A recorded call uploads all of
-    # the plan.  Eager work between the replays goes through another context: a replay puts the recorded batch's plan on the
-    # device, of which the context it was recorded from does not learn.
+@pytest.mark.parametrize("grad_streams", [0, 1])
+def test_recorded_and_eager_calls_share_a_context(grad_streams):
+    # Two layers, forward and backward, recorded on the stream they were warmed up on.  Between the replays the same context serves
+    # eager calls of a larger batch and of the recorded one with other tables, more of them than there are staging slots: a replay brings
+    # its own plan, and the eager calls behind it upload theirs.
     import torch
 
-    lens, ads, trn = [60, 1, 90, 33], [0, 1, 2, 1], [1, 0, 0, 1]
-    ws = [_adhoc("bf16", 200, 264, [16, 8, 64], lens, ads, trn, scale=0.5, seed=30 + k) for k in range(2)]
-    ctx, ctx2 = make_ctx(ws[0]), make_ctx(ws[0])
-    a, b = [DeviceLayer(w, wl.make_tensors(w), ctx) for w in ws]
-    o = DeviceLayer(ws[0], wl.make_tensors(ws[0]), ctx2)
+    ranks = [16, 8, 64]
+    ws = [_adhoc("bf16", 200, 264, ranks, [60, 1, 90, 33], [0, 1, 2, 1], [1, 0, 0, 1], scale=0.5, seed=30 + k) for k in range(3)]
+    big = [_adhoc("bf16", 200, 264, ranks, [300, 70, 1, 140], [2, 0, 1, 0], [0, 1, 0, 1], scale=0.5, seed=40 + k) for k in range(2)]
+    ctx = make_ctx(big[0])
+    ctx.set_grad_streams(grad_streams)
+    a, b, other = [DeviceLayer(w, wl.make_tensors(w), ctx) for w in ws]
+    eager = [DeviceLayer(w, wl.make_tensors(w), ctx) for w in big] + [other]
     torch.cuda.synchronize()
     st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
     with torch.cuda.stream(st):
         a.fwd()
         whole = ctx.plan_stats()["bytes"]
+        a.bwd()
         b.fwd()
         assert ctx.plan_stats()["mode"] == 2 and ctx.plan_stats()["bytes"] < whole
+        b.bwd()
     torch.cuda.synchronize()
     with torch.cuda.graph(g, stream=st):
         for l in (a, b):
-            l.fwd()
-            assert ctx.plan_stats()["mode"] == 2 and ctx.plan_stats()["bytes"] == whole
-    ref = [l.y.clone() for l in (a, b)]
-    for _ in range(3):
+            for call in (l.fwd, l.bwd):
+                call()
+                assert ctx.plan_stats()["bytes"] == whole
+    def outputs(l):
+        train = torch.from_numpy(l.tok_train != 0).cuda()
+        return [l.y, l.dx[train], l.h_save[train]] + [t for k, t in enumerate(l.dA + l.dB) if not torch.isnan(t).all()]
+    def spoil(l):
+        for t in [l.y, l.dx, l.h_save] + l.dA + l.dB:
+            t.fill_(float("nan"))
+    ref = [[t.clone() for t in outputs(l)] for l in (a, b)]
+    assert all(torch.isfinite(t).all() for r in ref for t in r)
+    for rep in range(4):
         for l in (a, b):
-            l.y.fill_(float("nan"))
-        o.fwd()
+            spoil(l)
         torch.cuda.synchronize()
-        g.replay()
+        with torch.cuda.stream(st):
+            g.replay()
+            for l in eager * 3:
+                l.fwd()
+                l.bwd()
+            g.replay()
         torch.cuda.synchronize()
-        assert torch.equal(a.y, ref[0]) and torch.equal(b.y, ref[1])
+        for l, r in zip((a, b), ref):
+            got = outputs(l)
+            assert len(got) == len(r) and all(torch.equal(x, y) for x, y in zip(got, r)), rep
+        for l in eager:
+            check_full(l, TOL["bf16"])
+            spoil(l)
     ctx.close()
-    ctx2.close()
 
 
 def test_weight_fetch_beside_the_rank_wide_passes():

@@ -1,0 +1,172 @@
+"""What a call puts on the device and launches, checked on the CPU: the library runs against a HIP runtime that launches nothing
+(fake_hip.cpp) in a process of its own, one per scenario (`python test_host_calls.py <library of the runtime> <scenario> <arguments>`)."""
+from __future__ import annotations
+
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="session")
+def run(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--cuda-host-only", "-std=c++17", "-O1", "-w", "-fPIC",
+                    "-shared", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2604_16400_amd", "csrc"),
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", so], check=True, capture_output=True, text=True)
+
+    def go(scenario, *args):
+        r = subprocess.run([sys.executable, os.path.abspath(__file__), so, scenario, *map(str, args)], capture_output=True, text=True,
+                           timeout=120)
+        assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
+
+    return go
+
+
+@pytest.mark.parametrize("dtype,n_adapters", [("bf16", 3), ("bf16", 130), ("f32", 3)])  # 130: more than a pass carries
+@pytest.mark.parametrize("call", ["fwd", "bwd"])
+def test_eager_calls_behind_a_replay_find_their_own_plan(run, call, dtype, n_adapters):
+    run("behind_a_replay", call, dtype, n_adapters)
+
+
+@pytest.mark.parametrize("call", ["fwd", "bwd"])
+def test_a_replay_brings_its_own_plan(run, call):
+    run("replay", call)
+
+
+def test_calls_without_a_context_upload_when_recorded_and_ever_after(run):
+    run("noalloc")
+
+
+# ---------------------------------------------------------------------------------------------------------------------------
+# the process of a scenario
+
+STREAM = 0x5000
+
+
+class Batch:
+    """A batch, and its calls through a context; adapters' tables and gradients by layer."""
+
+    def __init__(self, w, ctx, lens, ads, trn, ranks, d_in=256, d_out=512, dtype="bf16", layout=0):
+        self.w, self.lib, self.ctx = w, w.lib, ctx
+        self.T, S, self.N = sum(lens), len(lens), len(ranks)
+        arr = lambda t, v: (t * max(len(v), 1))(*v)
+        starts = [sum(lens[:k]) for k in range(S + 1)]
+        self.seg = (arr(ctypes.c_int32, ranks), arr(ctypes.c_int32, starts), arr(ctypes.c_int32, ads), arr(ctypes.c_uint8, trn))
+        self.shape = w.binding.collm_shape(d_in, d_out, self.T, S, self.N, 1 if dtype == "bf16" else 0, 1.0, layout)
+        self.tok = [k for k in range(S) for _ in range(lens[k])]
+
+    def _tab(self, layer, kind):
+        return (ctypes.c_void_p * self.N)(*[0x100000000 * (1 + layer) + 0x10000000 * kind + 0x1000 * a for a in range(self.N)])
+
+    def fwd(self, layer=0, stream=STREAM):
+        return self.lib.collm_lora_linear_fwd(self.ctx, ctypes.byref(self.shape), 0x10000, 0x20000, self._tab(layer, 0), self._tab(layer, 1),
+                                              *self.seg, 0x30000, 0x40000, stream)
+
+    def bwd(self, layer=0, stream=STREAM, dx=0x60000, grads=0):
+        g = (self._tab(grads, 2), self._tab(grads, 3)) if grads is not None else (None, None)
+        return self.lib.collm_lora_linear_bwd(self.ctx, ctypes.byref(self.shape), 0x10000, 0x20000, self._tab(layer, 0), self._tab(layer, 1),
+                                              *self.seg, 0x50000, 0x40000, dx, *g, 0, stream)
+
+    def on_device(self):
+        """Whether the plan on the device is of this batch (it begins with the segment of every token)."""
+        return self.w.fake.fake_plan()[: self.T] == self.tok
+
+
+class World:
+    def __init__(self, so):
+        self.fake = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
+        self.fake.fake_log.restype = ctypes.c_char_p
+        self.fake.fake_plan.restype = ctypes.POINTER(ctypes.c_int32)
+        self.fake.fake_capture.argtypes = [ctypes.c_void_p, ctypes.c_int]
+        self.fake.fake_fail_launch.argtypes = [ctypes.c_char_p]
+        sys.modules["torch"] = None  # (nothing else binds to this runtime)
+        sys.path.insert(0, ROOT)
+        from paper_2604_16400_amd import binding
+
+        self.binding, self.lib = binding, binding.load_library(build_if_missing=False)
+
+    def context(self, max_tokens=2048, max_segments=64, max_adapters=200, max_rank=128, max_d=16384):
+        self.fake.fake_new_plan()
+        h = ctypes.c_void_p()
+        assert self.lib.collm_ctx_create(ctypes.byref(h), 0, max_tokens, max_segments, max_adapters, max_rank, max_d) == 0
+        self.launches()
+        return h
+
+    def batches(self, ctx, dtype="bf16", n_adapters=3):
+        ranks = [8, 16, 8] + [16] * (n_adapters - 3)
+        return [Batch(self, ctx, lens, [0, 1, 2, -1], [1, 0, 1, 0], ranks, dtype=dtype)
+                for lens in ([40, 3, 50, 9], [30, 20, 60, 7], [11, 90, 33, 1])]
+
+    def launches(self):
+        """[(kernel, grid, LDS bytes, LDS bytes asked for by the attribute)] since the last call of this function"""
+        out = []
+        for line in self.fake.fake_log().decode().splitlines():
+            f = line.split("\t")
+            out.append((f[0], tuple(map(int, f[1].split())), int(f[2]), int(f[3])) if len(f) == 4 else (line, (), 0, 0))
+        return out
+
+    def stats(self, ctx):
+        b, u, n, m = ctypes.c_float(), ctypes.c_float(), ctypes.c_int32(), ctypes.c_int32()
+        assert self.lib.collm_debug_plan_stats(ctx, ctypes.byref(b), ctypes.byref(u), ctypes.byref(n), ctypes.byref(m)) == 0
+        return m.value, n.value
+
+    def record(self, *calls):
+        self.fake.fake_capture(STREAM, 1)
+        for c in calls:
+            assert c() == 0
+        self.fake.fake_capture(STREAM, 0)
+
+
+def behind_a_replay(w, call, dtype, n_adapters):
+    for forms in ([0, 0], [0, 1]):  # the eager calls' layers: nothing new, other tables
+        ctx = w.context()
+        x, y, _ = w.batches(ctx, dtype, int(n_adapters))
+        go = lambda b, layer: (b.fwd if call == "fwd" else b.bwd)(layer)
+        w.record(lambda: go(x, 0))
+        assert go(y, forms[0]) == 0 and y.on_device()
+        w.fake.fake_replay()
+        assert x.on_device()
+        for layer in forms + forms:
+            assert go(y, layer) == 0 and y.on_device(), (forms, layer)
+            assert w.stats(ctx)[1] > 4 * 3 * y.T  # all of it
+            w.fake.fake_replay()
+            assert x.on_device()
+        w.lib.collm_ctx_destroy(ctx)
+
+
+def replay(w, call):
+    ctx = w.context()
+    x, y, z = w.batches(ctx)
+    go = lambda b, layer=0: (b.fwd if call == "fwd" else b.bwd)(layer)
+    assert go(x) == 0  # (warmed up: nothing is new when it is recorded)
+    w.record(lambda: go(x), lambda: go(x, 1))
+    for k in range(40):  # more uploads than staging slots
+        b = (y, z)[k % 2]
+        assert go(b, k % 3) == 0 and b.on_device()
+    for _ in range(3):
+        w.fake.fake_replay()
+        assert x.on_device()
+        assert go(y) == 0 and y.on_device()
+
+
+def noalloc(w):
+    x, y, _ = w.batches(None)
+    def go(b, layer=0):
+        assert w.lib.collm_lora_linear_fwd_noalloc(0, ctypes.byref(b.shape), 0x10000, 0x20000, b._tab(layer, 0), b._tab(layer, 1), *b.seg,
+                                                   0x30000, None, STREAM) == 0
+        return sum("plan_words" in l[0] for l in w.launches())
+    assert go(x) > 0 and go(x) == 0
+    w.fake.fake_capture(STREAM, 1)
+    assert go(x) > 0
+    w.fake.fake_capture(STREAM, 0)
+    assert go(x) > 0 and go(x) > 0
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[2]](World(sys.argv[1]), *sys.argv[3:])

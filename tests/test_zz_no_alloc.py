@@ -76,3 +76,37 @@ def test_noalloc_rejects_sizes_beyond_its_workspace():
     assert e.value.status == -5
     torch.cuda.synchronize()
     assert torch.isnan(y).all()
+
+
+def test_noalloc_calls_recorded_and_eager_in_turn():
+    import torch
+
+    def call(seed, lens, ads):
+        w = wl.make_adhoc("noalloc_graph", "bf16", 256, 328, [16, 40], lens, ads, [0] * len(lens), scale=0.5, seed=seed)
+        t = wl.make_tensors(w)
+        x, W = to_dev(t.x, "bf16"), to_dev(t.W, "bf16")
+        A, B = [to_dev(a, "bf16") for a in t.A], [to_dev(b, "bf16") for b in t.B]
+        y = torch.full((w.n_tokens, 328), float("nan"), dtype=torch.bfloat16, device="cuda")
+        return y, lambda: binding.collm_lora_linear_fwd_noalloc(x, W, A, B, w.ranks, w.seg_start, w.seg_adapter, w.seg_is_train, w.scale, y)
+
+    (y0, f0), (y1, f1) = call(3, [1, 1, 50, 7], [0, 1, 1, -1]), call(4, [200, 3, 1], [1, 0, 1])
+    st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        f1()
+        f0()
+    torch.cuda.synchronize()
+    ref = y0.clone(), y1.clone()
+    with torch.cuda.graph(g, stream=st):
+        f0()
+    for _ in range(3):
+        y0.fill_(float("nan"))
+        y1.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(st):
+            f1()
+            g.replay()
+            y1.fill_(float("nan"))
+            f1()
+        torch.cuda.synchronize()
+        assert torch.equal(y0, ref[0]) and torch.equal(y1, ref[1])
