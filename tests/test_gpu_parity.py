@@ -728,6 +728,42 @@ def test_new_table_addresses_ride_on_the_first_pass(ranks, lens, ads, wide, n_ad
     ctx.close()
 
 
+def test_recorded_calls_with_new_tables_upload_the_whole_plan():
+    # Two layers recorded on the stream they were warmed up on (only the tables are new then).  A recorded call uploads all of
+    # the plan.  Eager work between the replays goes through another context: a replay puts the recorded batch's plan on the
+    # device, of which the context it was recorded from does not learn.
+    import torch
+
+    lens, ads, trn = [60, 1, 90, 33], [0, 1, 2, 1], [1, 0, 0, 1]
+    ws = [_adhoc("bf16", 200, 264, [16, 8, 64], lens, ads, trn, scale=0.5, seed=30 + k) for k in range(2)]
+    ctx, ctx2 = make_ctx(ws[0]), make_ctx(ws[0])
+    a, b = [DeviceLayer(w, wl.make_tensors(w), ctx) for w in ws]
+    o = DeviceLayer(ws[0], wl.make_tensors(ws[0]), ctx2)
+    torch.cuda.synchronize()
+    st, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(st):
+        a.fwd()
+        whole = ctx.plan_stats()["bytes"]
+        b.fwd()
+        assert ctx.plan_stats()["mode"] == 2 and ctx.plan_stats()["bytes"] < whole
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=st):
+        for l in (a, b):
+            l.fwd()
+            assert ctx.plan_stats()["mode"] == 2 and ctx.plan_stats()["bytes"] == whole
+    ref = [l.y.clone() for l in (a, b)]
+    for _ in range(3):
+        for l in (a, b):
+            l.y.fill_(float("nan"))
+        o.fwd()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(a.y, ref[0]) and torch.equal(b.y, ref[1])
+    ctx.close()
+    ctx2.close()
+
+
 @pytest.mark.parametrize("grad_streams", [0, 1])
 def test_recorded_and_eager_calls_share_a_context(grad_streams):
     # Two layers, forward and backward, recorded on the stream they were warmed up on.  Between the replays the same context serves
