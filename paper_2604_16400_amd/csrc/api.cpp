@@ -728,6 +728,8 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
         c->plan_mode = mode;
         c->plan_build_us = std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - t_plan).count();
     };
+    // (until what is new has been sent the device's plan is not the host's: a call that fails in between leaves no plan to reuse)
+    c->plan_valid = false;
     if (reuse && !same_tables(c, s->n_adapters, A, B)) {
         patch_tables(c, s->n_adapters, A, B);
         new_tables = true;
@@ -750,8 +752,6 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
         rq.max_row_tiles = f32 ? 1 : skinny_max_row_tiles(round_up(rmax, kKStep));
         rq.wide_min_rows_all = wide_all;
         rq.wide_min_rows_train = wide_train;
-        c->plan_valid = false;
-        c->patch.blocks = 0;
         int rc = build_plan(rq, c->plan, c->L);
         if (rc != COLLM_OK) return rc;
         if ((size_t)c->L.total_ints > c->plan_cap) {
@@ -778,7 +778,6 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
             c->key_A[a] = (uint64_t)(uintptr_t)A[a];
             c->key_B[a] = (uint64_t)(uintptr_t)B[a];
         }
-        c->plan_valid = true;
     } else if (dA || dB || new_tables || c->recorded) {
         // same batch as the plan on the device: at most the pointer tables are new
         const int N = s->n_adapters;
@@ -805,6 +804,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
             if (rc != COLLM_OK) return rc;
         }
     }
+    c->plan_valid = true;
     c->last_stream = st;
     return COLLM_OK;
 }

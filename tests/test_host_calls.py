@@ -43,6 +43,13 @@ def test_calls_without_a_context_upload_when_recorded_and_ever_after(run):
     run("noalloc")
 
 
+@pytest.mark.parametrize("dtype,n_adapters,call,fail", [
+    ("f32", 3, "fwd", "plan_copy_kernel"), ("bf16", 130, "fwd", "plan_copy_kernel"), ("f32", 3, "bwd", "plan_copy_kernel"),
+    ("bf16", 3, "fwd", "SkinnyPassArgs"), ("bf16", 3, "bwd", "SkinnyPassArgs"), ("bf16", 3, "fwd", "query"), ("bf16", 3, "bwd", "query")])
+def test_a_call_behind_a_failed_upload_uploads(run, dtype, n_adapters, call, fail):
+    run("failed_upload", dtype, n_adapters, call, fail)
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -166,6 +173,22 @@ def noalloc(w):
     assert go(x) > 0
     w.fake.fake_capture(STREAM, 0)
     assert go(x) > 0 and go(x) > 0
+
+
+def failed_upload(w, dtype, n_adapters, call, fail):
+    ctx = w.context()
+    b = w.batches(ctx, dtype, int(n_adapters))[0]
+    go = lambda layer: (b.fwd if call == "fwd" else b.bwd)(layer)
+    assert go(0) == 0
+    w.launches()
+    w.fake.fake_fail_query(1) if fail == "query" else w.fake.fake_fail_launch(fail.encode())
+    assert go(1) == -8
+    w.fake.fake_fail_query(0)
+    w.launches()
+    assert go(1) == 0
+    assert any("plan_copy" in l[0] or "PassArgs" in l[0] for l in w.launches()), "computed with the tables of the call before"
+    assert go(1) == 0
+    assert not any("plan_copy" in l[0] or "PassArgs" in l[0] for l in w.launches())
 
 
 if __name__ == "__main__":
