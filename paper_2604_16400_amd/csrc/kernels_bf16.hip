@@ -2177,6 +2177,18 @@ void host_tile_order(int tiles_m, int tiles_n, int band, int32_t *tm, int32_t *t
     }
 }
 
+// Asks once for the most LDS that launches of KERN take.  (By kernel, not by its type: kernels of one signature differ in LDS.)
+template <auto KERN>
+static hipError_t allow_lds(int bytes)
+{
+    static bool done = false;
+    if (done) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    done = e == hipSuccess;
+    return e;
+}
+template <auto KERN> struct Kernel { static constexpr auto fn = KERN; };  // a kernel as an argument that keeps its identity
+
 template <int BM, int BN, bool KM, bool SWIGLU = false, bool SIBS = false, int RS = 0>
 static hipError_t launch_gemm_t(const GemmArgs &a, hipStream_t st)
 {
@@ -2190,14 +2202,9 @@ static hipError_t launch_gemm_t(const GemmArgs &a, hipStream_t st)
     static_assert(RS || SWIGLU || BM * BN != 128 * 128 || smem == kSmallTileLds, "what grad_lds assumes");
     static_assert(smem <= 160 * 1024, "LDS of a CU");
     static_assert(!SWIGLU || smem >= BM * (BN / 2) * 4, "the up halves of all rows pass through LDS as fp32");
-    auto kern = gemm_lora_kernel<BM, BN, 2, 2, KM, false, SWIGLU, false, SIBS, RS>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
+    constexpr auto kern = gemm_lora_kernel<BM, BN, 2, 2, KM, false, SWIGLU, false, SIBS, RS>;
+    const hipError_t e = allow_lds<kern>(smem);
+    if (e != hipSuccess) return e;
     const int grid = a.tiles_m * a.tiles_n;
     if (grid <= 0) return hipSuccess;
     GemmArgs b = a;
@@ -2246,14 +2253,10 @@ hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bo
     if (n_items <= 0) return hipSuccess;
     if (n_split < 1 || !a.part || !a.items || !a.tab || a.k_per_split % 64 != 0) return hipErrorInvalidValue;
     const int smem = wide_stages(t_kmajor) * (128 + 128) * 128;
-    auto launch = [&](auto kern, auto b) -> hipError_t {
-        static bool attr_done = false;
-        if (!attr_done) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-            if (e != hipSuccess) return e;
-            attr_done = true;
-        }
+    auto launch = [&](auto k, auto b) -> hipError_t {
+        constexpr auto kern = decltype(k)::fn;
+        const hipError_t e = allow_lds<kern>(smem);
+        if (e != hipSuccess) return e;
         static_cast<GemmArgs &>(b) = a;
         b.n_items = n_items;
         if (!b.warm_base || b.warm_bytes < 16) b.warm_blocks = 0;
@@ -2267,9 +2270,10 @@ hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bo
     };
     // eight waves, 32 rows x 64 rank columns each (two per SIMD): the loop is bound by what a wave has to issue
     if (patch)
-        return t_kmajor ? launch(gemm_lora_kernel<128, 128, 4, 2, true, true, false, false, false, 0, WideArgs>, WideArgs())
-                        : launch(gemm_lora_kernel<128, 128, 4, 2, false, true, false, false, false, 0, WideArgs>, WideArgs());
-    return t_kmajor ? launch(gemm_lora_kernel<128, 128, 4, 2, true, true>, GemmArgs()) : launch(gemm_lora_kernel<128, 128, 4, 2, false, true>, GemmArgs());
+        return t_kmajor ? launch(Kernel<gemm_lora_kernel<128, 128, 4, 2, true, true, false, false, false, 0, WideArgs>>(), WideArgs())
+                        : launch(Kernel<gemm_lora_kernel<128, 128, 4, 2, false, true, false, false, false, 0, WideArgs>>(), WideArgs());
+    return t_kmajor ? launch(Kernel<gemm_lora_kernel<128, 128, 4, 2, true, true>>(), GemmArgs())
+                    : launch(Kernel<gemm_lora_kernel<128, 128, 4, 2, false, true>>(), GemmArgs());
 }
 
 hipError_t launch_skinny_finish(const SkinnyArgs &a, const SkinnyItem *wide, int n_wide, int wide_split, int n_items, int row_tiles, int n_split,
@@ -2305,23 +2309,19 @@ hipError_t launch_gemm_splitk(const GemmArgs &a, int n_split, bool b_kmajor, hip
     // one block per CU: the ring of four stages (see gemm_lora_kernel); more blocks: two stages, two blocks per CU
     const bool ring = a.one_per_cu && a.n_sib <= 1;
     const int smem = ring ? kRingStages * (128 + 128) * 128 : kSmallTileLds;
-    auto launch = [&](auto kern) -> hipError_t {
-        static bool attr_done = false;
-        if (!attr_done) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-            if (e != hipSuccess) return e;
-            attr_done = true;
-        }
+    auto launch = [&](auto k) -> hipError_t {
+        constexpr auto kern = decltype(k)::fn;
+        const hipError_t e = allow_lds<kern>(smem);
+        if (e != hipSuccess) return e;
         COLLM_LAUNCH(kern, dim3(tiles, n_split), dim3(256), smem, st, a);
         return hipGetLastError();
     };
-    if (a.n_sib > 1) return b_kmajor ? hipErrorInvalidValue : launch(gemm_lora_kernel<128, 128, 2, 2, false, false, false, true, true>);
+    if (a.n_sib > 1) return b_kmajor ? hipErrorInvalidValue : launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, false, false, false, true, true>>());
     if (ring)
-        return b_kmajor ? launch(gemm_lora_kernel<128, 128, 2, 2, true, false, false, true, false, kRingStages>)
-                        : launch(gemm_lora_kernel<128, 128, 2, 2, false, false, false, true, false, kRingStages>);
-    return b_kmajor ? launch(gemm_lora_kernel<128, 128, 2, 2, true, false, false, true>)
-                    : launch(gemm_lora_kernel<128, 128, 2, 2, false, false, false, true>);
+        return b_kmajor ? launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, true, false, false, true, false, kRingStages>>())
+                        : launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, false, false, false, true, false, kRingStages>>());
+    return b_kmajor ? launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, true, false, false, true>>())
+                    : launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, false, false, false, true>>());
 }
 
 hipError_t launch_gemm_finish(const GemmArgs &a, int n_split, hipStream_t st)
@@ -2354,14 +2354,9 @@ static hipError_t launch_skinny_a(const SkinnyArgs &a, int n_items, int n_split,
 {
     using C = SkinnyCfg<RP>;
     constexpr int smem = C::KW * 16 * RT * C::RED_LD * 4 + (KM ? 0 : C::KW * C::STAGE_BYTES);
-    auto kern = skinny_kernel<RP, KM, RT, Args>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
+    constexpr auto kern = skinny_kernel<RP, KM, RT, Args>;
+    const hipError_t e = allow_lds<kern>(smem);
+    if (e != hipSuccess) return e;
     Args b;
     static_cast<SkinnyArgs &>(b) = a;
     b.n_items = n_items;
@@ -2442,14 +2437,9 @@ template <int RP, bool SMALL_BF>
 static hipError_t launch_grad_t(const GradArgs &a, int n_grad, int rpad, hipStream_t st)
 {
     using C = GradCfg<RP>;
-    auto kern = grad_kernel<RP, SMALL_BF>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, grad_lds_bytes(C::SMEM, true));
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
+    constexpr auto kern = grad_kernel<RP, SMALL_BF>;
+    const hipError_t e = allow_lds<kern>(grad_lds_bytes(C::SMEM, true));
+    if (e != hipSuccess) return e;
     const dim3 grid((a.N + 63) / 64, n_grad, (rpad + RP - 1) / RP);
     COLLM_LAUNCH(kern, grid, dim3(C::KW * 64), grad_lds_bytes(C::SMEM, a.beside_gemm != 0), st, a);
     return hipGetLastError();
@@ -2461,13 +2451,8 @@ hipError_t launch_dual(const DualArgs &a, hipStream_t st)
     if (a.piece_rows < 32 || a.piece_rows % 32 || a.piece_rows > kDualMaxPieceRows || a.max_pieces < 1 || !a.part_dh ||
         !a.part_dB || a.part_ld < 16)
         return hipErrorInvalidValue;
-    static bool attr_done = false;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(dydual_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, DualCfg::SMEM);
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
+    const hipError_t e = allow_lds<dydual_kernel>(DualCfg::SMEM);
+    if (e != hipSuccess) return e;
     DualArgs b = a;
     if (!b.warm_base || b.warm_bytes < 16) b.warm_rows = 0;
     const dim3 grid((a.N + kDualCols - 1) / kDualCols, a.n_grad * a.max_pieces + b.warm_rows);

@@ -50,6 +50,10 @@ def test_a_call_behind_a_failed_upload_uploads(run, dtype, n_adapters, call, fai
     run("failed_upload", dtype, n_adapters, call, fail)
 
 
+def test_every_launch_has_asked_for_its_lds(run):
+    run("lds")
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -189,6 +193,24 @@ def failed_upload(w, dtype, n_adapters, call, fail):
     assert any("plan_copy" in l[0] or "PassArgs" in l[0] for l in w.launches()), "computed with the tables of the call before"
     assert go(1) == 0
     assert not any("plan_copy" in l[0] or "PassArgs" in l[0] for l in w.launches())
+
+
+def lds(w):
+    # kernels of one signature whose LDS differs, the one with less first: K slices on two stages, then in the ring; the tiled
+    # rank-wide pass over both layouts of the tables, with new addresses and without; the gradients beside GEMMs of both sizes
+    seen = set()
+    for d_in, d_out, T, rank, layout in [(4096, 11008, 64, 64, 0), (4096, 1024, 64, 64, 0), (4096, 1024, 64, 64, 1), (512, 512, 600, 64, 0),
+                                         (4096, 4096, 1000, 16, 0), (4096, 4096, 2000, 128, 1), (12288, 16384, 2048, 16, 0)]:
+        ctx = w.context()
+        b = Batch(w, ctx, [T - 8, 8], [0, 1], [1, 0], [rank, 8], d_in, d_out, layout=layout)
+        for layer in (0, 1):
+            assert b.fwd(layer) == 0 and b.bwd(layer) == 0
+        for name, grid, smem, asked in w.launches():
+            assert smem <= max(asked, 65536), (name, smem, asked)
+            seen.add((name.split("<", 1)[-1], smem))
+        w.lib.collm_ctx_destroy(ctx)
+    sliced = {(km, lds) for n, lds in seen for km in ("true", "false") if n.startswith(f"128, 128, 2, 2, {km}, false, false, true, false")}
+    assert sliced >= {("false", 65536), ("false", 131072), ("true", 131072)}, seen
 
 
 if __name__ == "__main__":
