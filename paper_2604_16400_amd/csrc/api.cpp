@@ -195,9 +195,11 @@ Tiling pick_tiling(int rows, int cols, int K, bool can_split, bool one_round, in
     }
     // Tiles between the two sizes, where one block per CU holds the whole GEMM (see the ring in gemm_lora_kernel): a first round
     // that large tiles fill badly and small ones overfill.  x = blocks / 256.  GEMM alone, weights from memory, geometric means over
-    // 12000 shapes (100 to 8192 rows, 1024 to 16384 wide), time against the choice between the two sizes: 128x192 instead of
-    // 257 .. 340 small tiles 0.88 .. 0.96; 256x128 instead of 340 .. 512 small tiles 0.92 .. 0.95; 256x192 instead of 257 .. 370
-    // large ones' worth of small tiles (200 .. 250 blocks) 0.92 .. 0.93.  Below 257 small tiles K slices or the ring on 128x128 tiles are better.
+    // 12000 shapes (100 to 8192 rows, 1024 to 16384 wide), time against the choice between the two sizes: 128x192 0.88 .. 0.96,
+    // 256x128 0.92 .. 0.95, 256x192 0.92 .. 0.93.  Whole forward calls, weights from memory, 60 shapes each (128 to 4096 rows): 128x192 (259 to 385
+    // small tiles) 0.86 (0.68 .. 1.04), 256x128 (377 to 512) 0.89 (0.75 .. 1.02), 256x192 (518 to 744) 0.93 (0.86 .. 1.04).  Where the weight stands
+    // in the last-level cache there is less to hide: 1003 rows 5120 -> 5120 117 / 86 us from memory, 79 / 78 from the cache.
+    // Below 257 small tiles K slices or the ring on 128x128 tiles are better.
     // Not where the extension is long (`steps` of a 128-row tile): one block alone on its CU waits for every batch of tables (about 2 us a
     // batch, 472 rows of 93 adapters of rank 128, K = 10320, 125 -> 160 us; 935 rows of 31 of rank 32, K = 2304, 53 -> 67).
     // Nor up to 341 small tiles of K >= 16384, which are cut into three slices (733 rows 25448 -> 5408 386 / 451).
@@ -240,8 +242,13 @@ bool ring_alone(const Tiling &t, int cols, int K, int steps)
 // Slices of K of a GEMM of few tiles run as at most one block per CU with the ring of four stages (three tiles of loads in flight per
 // CU instead of two, half the partial sums), or 0 where `two` slices on two blocks per CU are better.  GEMM with the kernel
 // that adds the slices against two blocks per CU with two stages, weights from memory, 10000 shapes (1 to 2048 rows, K =
-// 1024 to 28672, 1 to 64 adapters of rank 16 to 64): up to 16 tiles 0.88 .. 0.91, up to 32 0.91, up to 64 0.92, up to 85 0.94; from 86 tiles
-// on (two slices at most) 0.96 .. 1.3.  A slice keeps 192 K values (geometric mean 0.927; 256: 0.929, 512: 0.976).
+// 1024 to 28672, 1 to 64 adapters of rank 16 to 64): up to 16 tiles 0.88 .. 0.91, up to 32 0.91, up to 64 0.92, up to 85 0.94.  From 86 to 128
+// tiles (two slices) it would be 0.96 .. 1.3 for every contraction; where the comparison below takes it, whole forward calls of 150 shapes
+// measured 0.94 (0.84 .. 1.03).  A slice keeps 192 K values (geometric mean 0.927; 256: 0.929, 512: 0.976).
+//  - Also for dX beside the gradient kernels on the second stream, although a CU that holds such a block has no room for theirs: whole
+//    backward calls, 950 shapes (64 to 1500 rows, 512 to 8192 <- 1024 to 16384): 0.979 (0.88 .. 1.18); level only where ranks up to 16 meet a
+//    weight below 8 MB (65 shapes, 1.003), by no line that separates the shapes that lose (695 rows 2568 <- 2712 57 / 48 us) from those that gain
+//    (948 rows 1472 <- 2080 39 / 44).
 //  - A block alone on its CU takes 0.48 us a K tile, one of two 0.90; a slice's sums are written and read once more (about 8 TB/s).  The rule
 //    compares these: a long contraction is better cut for the blocks that exist (714 rows, 72 tiles, K = 26112: three
 //    slices on 216 CUs 124 us, seven on two blocks per CU 109).
@@ -401,8 +408,9 @@ bool whole_rounds(int rows, int cols)
     return last == 0 || last > 230;
 }
 
-// Whether the dX GEMM of a backward call may take the tiles that fill a CU's LDS and one round of CUs (pick_tiling): not
-// where the gradient kernels run beside it on the second stream, as a CU that holds such a tile has no room for their blocks.
+// Whether the dX GEMM of a backward call may take the tiles that fill a CU's LDS and one round of CUs, uncut (pick_tiling, ring_alone):
+// not where the gradient kernels run beside it on the second stream, as a CU that holds such a tile has no room for their blocks.  (K slices
+// in the ring are shorter and take it all the same, slices_one_per_cu.)
 // Backward call, us, with the two sizes only / all of them: 1792 rows 4096 -> 4096 86 / 88, 901 rows 4104 -> 11008 172 / 180.
 bool dx_one_round(const collm_ctx *c, int n_train, int d_in, int d_out, bool f32, int rpad)
 {

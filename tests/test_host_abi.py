@@ -321,7 +321,11 @@ def test_gemm_slices_count_the_extension_steps(tiles_m, tiles_n, K, steps, want)
     (8, 4096, 1016, 0, (binding.TILE_128x128, 1, 1)),                      # one block per CU, not cut
     (64, 11008, 4096, 64, (binding.TILE_128x128, 5, 0)),                   # 86 tiles: five slices on two blocks per CU
     (64, 4096, 4096, 64, (binding.TILE_128x128, 8, 1)), (64, 4096, 4096, 65, (binding.TILE_128x128, 8, 0)),     # the steps outweigh K
-    (714, 1536, 26112, 0, (binding.TILE_128x128, 7, 0)), (714, 1536, 4096, 0, (binding.TILE_128x128, 3, 1))])  # long contractions
+    (714, 1536, 26112, 0, (binding.TILE_128x128, 7, 0)), (714, 1536, 4096, 0, (binding.TILE_128x128, 3, 1)),  # long contractions
+    (64, 10880, 4096, 0, (binding.TILE_128x128, 3, 1)), (64, 11008, 4096, 0, (binding.TILE_128x128, 5, 0)),     # 85 and 86 tiles,
+    (64, 11008, 3072, 0, (binding.TILE_128x128, 2, 1)), (64, 16384, 4096, 0, (binding.TILE_128x128, 2, 1)),     # 86 and 128 tiles: two
+    (512, 4096, 4096, 0, (binding.TILE_128x128, 2, 1)), (64, 16512, 4096, 0, (binding.TILE_128x128, 3, 0)),     # slices; 129 tiles
+    (64, 16384, 10240, 0, (binding.TILE_128x128, 4, 0))])
 def test_plain_gemm_choice_at_the_lines_of_the_rule(rows, cols, K, steps, want):
     assert binding.host_plain_gemm(rows, cols, K, steps=steps) == want
 

@@ -54,6 +54,15 @@ def test_every_launch_has_asked_for_its_lds(run):
     run("lds")
 
 
+@pytest.mark.parametrize("rows,d_in,d_out,streams,want", [
+    (512, 4096, 4096, 1, "128, 128 sliced 4"), (512, 4096, 4096, 0, "128, 128 sliced 4"),  # K slices in the ring on either stream
+    (640, 2048, 4096, 1, "128, 128 sliced 4"), (640, 2560, 10240, 1, "128, 128 sliced 0"),
+    (1792, 4096, 4096, 1, "128, 128 whole 0"), (1792, 4096, 4096, 0, "256, 128 whole 3"),  # tiles for one round not beside gradients
+    (256, 16384, 1016, 1, "128, 128 whole 0"), (256, 16384, 1016, 0, "128, 128 whole 4")])  # ... nor the ring uncut
+def test_the_dx_gemm_beside_gradient_kernels(run, rows, d_in, d_out, streams, want):
+    run("dx_gemm", rows, d_in, d_out, streams, want)
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -211,6 +220,15 @@ def lds(w):
         w.lib.collm_ctx_destroy(ctx)
     sliced = {(km, lds) for n, lds in seen for km in ("true", "false") if n.startswith(f"128, 128, 2, 2, {km}, false, false, true, false")}
     assert sliced >= {("false", 65536), ("false", 131072), ("true", 131072)}, seen
+
+
+def dx_gemm(w, rows, d_in, d_out, streams, want):
+    ctx = w.context()
+    w.lib.collm_debug_set_grad_streams(ctx, int(streams))
+    assert Batch(w, ctx, [int(rows)], [0], [1], [16], int(d_in), int(d_out)).bwd() == 0
+    gemms = [l[0].split("<", 1)[1].split(", ") for l in w.launches() if "gemm_lora_kernel" in l[0]]
+    gemms = [f"{a[0]}, {a[1]} {'sliced' if a[7] == 'true' else 'whole'} {a[9]}" for a in gemms if a[5] == "false"]
+    assert gemms == [want], gemms
 
 
 if __name__ == "__main__":
