@@ -510,6 +510,26 @@ def test_adapter_gradients_started_behind_the_dh_pass(d_in, d_out, ranks, transp
 
 
 @pytest.mark.parametrize("transposed", [False, True])
+def test_new_tables_where_the_gradients_start_behind_the_dh_pass(transposed):
+    # the pass that carries the addresses is the one over x (h recomputed) or the one over dy; dB and dA follow on the second stream
+    ws = [_adhoc("bf16", 3400, 3400, [16, 8], [3, 50, 1, 38], [0, 1, 0, 0], [0, 1, 0, 1], scale=0.5, seed=60 + k) for k in range(2)]
+    ctx = make_ctx(ws[0])
+    ctx.set_grad_streams(1)
+    a, b = [DeviceLayer(w, wl.make_tensors(w), ctx, transposed=transposed) for w in ws]
+    a.fwd()
+    b.fwd()
+    for h_save in (False, True):
+        for l in (a, b, a, b):
+            for t in [l.dx] + l.dA + l.dB:
+                t.fill_(float("nan"))
+            l.bwd(h_save=h_save)
+            assert ctx.plan_stats()["mode"] == 2
+        for l in (a, b):
+            check_full(l, TOL["bf16"])
+    ctx.close()
+
+
+@pytest.mark.parametrize("transposed", [False, True])
 def test_many_extension_steps_in_one_row_tile(transposed):
     # Twelve adapters of ranks 128 and 256 with 20 rows each share one 256-row tile: 144 extension steps in four
     # groups of 64 rank indices, more than the 64 step records a kernel keeps in registers (the later batches come

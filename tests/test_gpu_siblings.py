@@ -279,6 +279,54 @@ def test_swiglu_forward_and_sibling_backward_share_a_plan():
     assert max(errs) <= TOL["bf16"], errs
 
 
+@pytest.mark.parametrize("grad_streams", [0, 1])
+@pytest.mark.parametrize("d_outs,swiglu", [((256, 512, 136), False), ((256, 256), True)])
+@pytest.mark.parametrize("ranks", [[16, 8, 8, 16], [64, 16, 48, 64]])  # row items only; the tiled pass
+def test_sibling_calls_with_new_tables_carry_their_addresses(ranks, d_outs, swiglu, grad_streams):
+    # one batch through three sets of tables in turn, in calls queued without a wait: the passes over dy read the carried tables from a
+    # sibling's column on, and only the first of them carries
+    import torch
+
+    if swiglu:
+        ranks = [max(r, 16) for r in ranks]
+    cases = [SiblingCase(200, d_outs, ranks, LENS, ADS, TRN, scale=0.3, seed=50 + k) for k in range(3)]
+    c0, P, D = cases[0], len(d_outs), sum(d_outs)
+    wide, max_rank = d_outs[0] if swiglu else D, P * max(ranks)
+    ctx = binding.Context(c0.T, len(c0.seg_adapter), len(ranks), max_rank, max(200, D))
+    ctx.set_grad_streams(grad_streams)
+    seg = (c0.ranks, c0.seg_start, c0.seg_adapter, c0.seg_is_train, c0.scale)
+    act = dict(activation=binding.ACT_SWIGLU) if swiglu else {}
+    nan = lambda *s, **k: torch.full(s, float("nan"), device="cuda", **k)
+    L = []
+    for c in cases:
+        up = lambda a: to_dev(a, "bf16")
+        L.append(dict(x=up(c.x), W=up(c.W), dy=up(c.dy), A=[up(a) for a in c.A], B=[up(b) for b in c.B], hs=nan(c.T, max_rank),
+                      y=nan(c.T, wide, dtype=torch.bfloat16), dx=[nan(c.T, 200, dtype=torch.bfloat16) for _ in range(2)],
+                      dA=[[nan(*a.shape) for a in c.A] for _ in range(2)], dB=[[nan(*b.shape) for b in c.B] for _ in range(2)]))
+    modes = []
+    for _ in range(2):
+        for l in L:
+            ctx.collm_lora_siblings_fwd(d_outs, l["x"], l["W"], l["A"], l["B"], *seg, l["y"], l["hs"], **act)
+            modes.append(ctx.plan_stats())
+        for l in (L[0], L[2], L[1]):
+            for k, hs in enumerate((None, l["hs"])):  # (the first begins with the pass over x and carries, the second finds its tables there)
+                ctx.collm_lora_siblings_bwd(d_outs, l["x"], l["W"], l["A"], l["B"], *seg, l["dy"], hs, l["dx"][k], l["dA"][k], l["dB"][k])
+                modes.append(ctx.plan_stats())
+    torch.cuda.synchronize()
+    assert [m["mode"] for m in modes] == [1, 2, 2, 2, 0, 2, 0, 2, 0] + [2, 2, 2, 2, 0, 2, 0, 2, 0]
+    assert all(m["bytes"] < modes[0]["bytes"] for m in modes[1:])
+    tr = c0.tok_train != 0
+    for c, l in zip(cases, L):
+        y_ref, _ = oracle.lora_siblings_fwd(c.x, c.W, c.A, c.B, c.d_outs, c.tok_adapter, c.scale)
+        dx_ref, dA_ref, dB_ref = oracle.lora_siblings_bwd(c.x, c.W, c.A, c.B, c.d_outs, c.tok_adapter, c.tok_train, c.scale, c.dy)
+        errs = [maxrel(to_host(l["y"]), oracle.swiglu(y_ref) if swiglu else y_ref)]
+        for k in range(2):
+            errs += [maxrel(to_host(l["dx"][k])[tr], dx_ref[tr])]
+            errs += [maxrel(to_host(g[a]), r[a]) for g, r in ((l["dA"][k], dA_ref), (l["dB"][k], dB_ref)) for a in range(4) if r[a] is not None]
+        assert max(errs) <= TOL["bf16"], errs
+    ctx.close()
+
+
 def test_swiglu_epilogue_large_tiles_and_tail():
     # 2300 rows x (2 x 3840) columns: whole rounds of 256x256 tiles, then 128x128 tiles over the last rows
     lens = [700, 1, 1, 500, 300, 1, 600, 197]
