@@ -35,13 +35,14 @@
  *     = the default stream) and return.  Host arrays are copied before the call returns and
  *     may be reused at once.  One context serves one stream at a time; calls on the same
  *     context must not overlap on different streams, and a context is not thread-safe.
- *   - Calls may be recorded into a HIP graph; the graph must not outlive the context.  A recorded
- *     call carries all of its plan in the arguments of its kernels (one kernel for each 3.5 KiB), and
- *     a replay uses the context's workspace and device plan as an eager call does, on its stream
- *     and in its turn.  Eager calls of the same context between replays are legal.  As nothing tells
- *     the host of a replay, a context of which a call has been recorded uploads the plan of
- *     every later call, also where it would otherwise find its batch on the device: give recorded
- *     calls a context of their own where eager calls should not pay for that.
+ *   - Calls may be recorded into a HIP graph; the graph must not outlive the context.  A replay uses
+ *     the context's workspace and device plan as an eager call does, on its stream and in its
+ *     turn; eager calls of the same context between replays are legal.  A recorded call keeps its
+ *     plan in pinned memory of the context (64 MiB in all, released with the context; beyond that
+ *     the plan travels in the arguments of small kernels, 3.5 KiB each).  As nothing tells the
+ *     host of a replay, a context of which a call has been recorded uploads the plan of
+ *     every later eager call, also where it would otherwise find its batch on the device: give
+ *     recorded calls a context of their own where eager calls should not pay for that.
  *   - Every call returns a status: COLLM_OK (0) or a negative error.  All validation is done
  *     on the host before anything is launched; on an error no output buffer is touched.
  *   - d_in and d_out must be multiples of 8 (bf16) or 4 (fp32); x, dy and W must each stay
@@ -181,7 +182,7 @@ int collm_lora_linear_bwd(collm_ctx *ctx, const collm_shape *shape, const void *
  * Beyond them: COLLM_E_SHAPE (COLLM_E_RANK for a rank), collm_last_error() names the limits, nothing is launched.
  * All calls on one GPU share that GPU's array: a call must not overlap in time with another call of this entry
  * point on the same GPU (other stream or other thread); calls on one stream are ordered and safe, replays of
- * recorded ones among them (after the first recorded call every call uploads its plan, as with a context).
+ * recorded ones among them (after the first recorded call every eager call uploads its plan, as with a context).
  */
 int collm_lora_linear_fwd_noalloc(int device, const collm_shape *shape, const void *x, const void *W,
                                   const void *const *A, const void *const *B, const int32_t *rank,
@@ -385,7 +386,8 @@ int collm_device_info(int device, int32_t *compute_units, int32_t *clock_khz, in
  * Debug/profiling, HOST only: what the plan of the context's last compute call cost on the host.
  * *mode = 0: the plan on the device was reused as it is; 1: built anew from the segment table; 2: same
  * batch, other adapter tables (their addresses replaced in place); 3: only the dA/dB pointer tables were new.
- * (From the context's first recorded call on, all of the plan is sent in every case.)
+ * (From the context's first recorded call on, eager calls and the first call of a capture send all of the plan in
+ * every case.)
  * *build_us: host time spent building or patching; *upload_us: host time spent copying it into pinned
  * staging and enqueueing the copy kernel; *bytes: bytes sent to the device.
  */

@@ -42,6 +42,7 @@ int hip_fail(hipError_t e, const char *what)
 
 constexpr int kSlots = 16;             // pinned staging ring: the host may run this many uploads ahead
 constexpr uint64_t kWarmMaxBytes = (uint64_t)40 << 20;  // largest weight a rank-wide pass fetches ahead of its GEMM
+constexpr size_t kRecordBytes = (size_t)64 << 20, kRecordBlock = (size_t)1 << 20;  // pinned plans of recorded calls, in all and at a time
 constexpr int kMaxProfile = 16;
 constexpr int64_t kDualMinBytes = (int64_t)192 << 20;  // training rows of dy from which dh and dB come from one pass (bwd_impl)
 
@@ -49,6 +50,12 @@ inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
+
+// pinned memory with plans of recorded calls, which replays read; ints
+struct RecordBlock {
+    int32_t *host = nullptr, *dev = nullptr;
+    size_t size = 0, used = 0;
+};
 
 struct collm_ctx {
     int device = 0;
@@ -62,7 +69,7 @@ struct collm_ctx {
     int32_t *h_stage_dev[kSlots] = {};  // the same memory as the GPU addresses it
     uint32_t stage_seq[kSlots] = {};    // sequence number of the upload that last used the slot (0: none)
     uint32_t seq = 0;                   // uploads issued so far
-    uint32_t *h_done = nullptr;         // pinned word: sequence number of the last finished upload
+    uint32_t *h_done = nullptr;         // pinned words: sequence number of the last finished upload; what copies of recorded plans store, unread
     uint32_t *h_done_dev = nullptr;
     int *d_copy_counter = nullptr;
     void *d_zeros = nullptr;  // 256 bytes of zeros for masked 16-byte loads
@@ -81,8 +88,12 @@ struct collm_ctx {
     PlanLayout L;
     bool plan_valid = false;
     // A call of this context has been recorded into a graph.  A replay puts the recorded call's plan on the device and nothing tells the host,
-    // so from then on every call uploads all of its plan (the host's copy of a known batch is still reused).
+    // so from then on every eager call uploads all of its plan (the host's copy of a known batch is still reused), and so does the first
+    // recorded call of a capture; the calls behind it in that capture follow it in every replay too, and find its plan.
     bool recorded = false;
+    unsigned long long capture_id = 0;  // the capture that the last call was recorded in (0: it was eager)
+    std::vector<RecordBlock> record_blocks;
+    size_t record_bytes = 0;
     // what the cached plan was built from
     collm_shape key_shape{};
     int key_bm_all = 0, key_bm_train = 0;
@@ -622,15 +633,49 @@ int take_slot(collm_ctx *c, int *slot, uint32_t *seq)
     return COLLM_OK;
 }
 
-// Copy ints [lo, hi) of the host plan to the device plan: through a pinned staging slot, or (no pinned staging exists, or a recorded
-// call, whose slot later uploads would overwrite before a replay reads it) inside the arguments of a few small kernels.
+// Keeps `n` ints (a multiple of 4) of a plan for the replays of the call that is being recorded: their address as the device sees it, or null where
+// the context's room for that is used up.  They stay until the context is destroyed (the library does not learn when a graph is).
+const int32_t *keep_recorded(collm_ctx *c, const int32_t *src, size_t n)
+{
+    if (c->static_scratch) return nullptr;  // (allocates nothing)
+    if (c->record_blocks.empty() || c->record_blocks.back().size - c->record_blocks.back().used < n) {
+        const size_t bytes = std::max(n * sizeof(int32_t), kRecordBlock);
+        if (c->record_bytes + bytes > kRecordBytes) return nullptr;
+        RecordBlock b;
+        b.size = bytes / sizeof(int32_t);
+        c->record_blocks.reserve(c->record_blocks.size() + 1);
+        // (the allocation is no part of what is being captured)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return nullptr;
+        const bool ok = hipHostMalloc((void **)&b.host, bytes, hipHostMallocMapped) == hipSuccess &&
+                        hipHostGetDevicePointer((void **)&b.dev, b.host, 0) == hipSuccess;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!ok) {
+            (void)hipGetLastError();
+            if (b.host) (void)hipHostFree(b.host);
+            return nullptr;
+        }
+        c->record_blocks.push_back(b);
+        c->record_bytes += bytes;
+    }
+    RecordBlock &b = c->record_blocks.back();
+    std::memcpy(b.host + b.used, src, n * sizeof(int32_t));
+    b.used += n;
+    return b.dev + b.used - n;
+}
+
+// Copy ints [lo, hi) of the host plan to the device plan: through a pinned staging slot; for a call that is being recorded from pinned memory
+// that no later upload overwrites; where there is none of either inside the arguments of a few small kernels.
 int upload(collm_ctx *c, size_t lo, size_t hi, hipStream_t st, bool recording)
 {
     if (hi <= lo) return COLLM_OK;
     const auto t0 = std::chrono::steady_clock::now();
     // rounded outwards to 16 bytes (the plan vector is padded to a multiple of 64 ints)
     const size_t lo4 = lo & ~(size_t)3, hi4 = std::min((hi + 3) & ~(size_t)3, c->plan.size());
-    if (c->static_scratch || recording) {
+    const int32_t *kept = recording ? keep_recorded(c, c->plan.data() + lo4, hi4 - lo4) : nullptr;
+    if (kept) {
+        HIP_TRY(launch_plan_copy(kept, c->d_plan + lo4, 0, hi4 - lo4, c->d_copy_counter, c->h_done_dev + 1, 0, st));
+    } else if (c->static_scratch || recording) {
         HIP_TRY(launch_plan_words(c->plan.data() + lo4, c->d_plan + lo4, hi4 - lo4, st));
     } else {
         int sl = 0;
@@ -696,12 +741,17 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
 {
     const bool f32 = s->dtype == COLLM_F32;
     bool recording = false;
+    unsigned long long capture_id = 0;
     if (st) {  // (the default stream cannot be recorded)
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         HIP_TRY(hipStreamIsCapturing(st, &capture));
         recording = capture != hipStreamCaptureStatusNone;
-        c->recorded = c->recorded || recording;
+        if (recording) HIP_TRY(hipStreamGetCaptureInfo(st, &capture, &capture_id));
     }
+    // whether the device holds the host's plan when this call's kernels run
+    const bool known = recording ? capture_id != 0 && capture_id == c->capture_id : !c->recorded;
+    c->recorded = c->recorded || recording;
+    c->capture_id = capture_id;
     int n_train = 0;
     for (int k = 0; k < s->n_segments; ++k)
         if (seg_is_train[k]) n_train += seg_start[k + 1] - seg_start[k];
@@ -786,12 +836,12 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
             c->key_A[a] = (uint64_t)(uintptr_t)A[a];
             c->key_B[a] = (uint64_t)(uintptr_t)B[a];
         }
-    } else if (dA || dB || new_tables || c->recorded) {
-        // same batch as the plan on the device: at most the pointer tables are new
+    } else if (dA || dB || new_tables || !known) {
+        // same batch as the host's plan: at most the pointer tables are new
         const int N = s->n_adapters;
         // (no row has an adapter: nothing runs)
         const RowOrderLayout &R = fwd ? c->L.all : c->L.train;
-        const bool carry = new_tables && pass_tab && !f32 && !c->static_scratch && !c->recorded && N <= kPatchTables && R.n_items + R.n_wide > 0;
+        const bool carry = new_tables && pass_tab && !f32 && !c->static_scratch && known && !recording && N <= kPatchTables && R.n_items + R.n_wide > 0;
         bool changed = false;
         for (int a = 0; a < (out_args ? 0 : N); ++a) {
             const uint64_t va = dA ? (uint64_t)(uintptr_t)dA[a] : 0, vb = dB ? (uint64_t)(uintptr_t)dB[a] : 0;
@@ -803,7 +853,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
         if (carry) {
             const int rc = stage_patch(c, pass_tab, N);
             if (rc != COLLM_OK) return rc;
-        } else if (new_tables || c->recorded) {
+        } else if (new_tables || !known) {
             int rc = upload(c, 0, c->L.total_ints, st, recording);
             if (rc != COLLM_OK) return rc;
         } else if (changed) {
@@ -1194,6 +1244,7 @@ int collm_ctx_destroy(collm_ctx *c)
     for (int i = 0; i < kSlots; ++i) {
         if (c->h_stage[i]) (void)hipHostFree(c->h_stage[i]);
     }
+    for (const RecordBlock &b : c->record_blocks) (void)hipHostFree(b.host);
     if (c->h_done) (void)hipHostFree(c->h_done);
     if (c->side) (void)hipStreamDestroy(c->side);
     for (hipEvent_t e : {c->ev_fork, c->ev_dh, c->ev_join})

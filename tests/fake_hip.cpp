@@ -33,7 +33,8 @@ std::set<hipStream_t> g_capturing;
 std::vector<Launch> g_graph;
 std::string g_log, g_fail;
 hipError_t g_error = hipSuccess;
-bool g_fail_query = false;
+bool g_fail_query = false, g_relaxed = false;
+unsigned long long g_capture_id = 0;
 const int32_t *g_plan = nullptr;  // where the first upload went: the block of the plan on the device
 struct { dim3 grid, block; size_t smem; hipStream_t st; } g_call;
 
@@ -113,7 +114,12 @@ void *zeroed(size_t n)
 extern "C" {
 
 // what the tests use
-void fake_capture(void *st, int on) { on ? (void)g_capturing.insert((hipStream_t)st) : (void)g_capturing.erase((hipStream_t)st); }
+void fake_capture(void *st, int on)
+{
+    if (on && g_capturing.empty()) ++g_capture_id;
+    on ? (void)g_capturing.insert((hipStream_t)st) : (void)g_capturing.erase((hipStream_t)st);
+}
+void fake_new_graph() { g_graph.clear(); }
 void fake_replay() { for (const Launch &l : g_graph) carry_out(l); }
 void fake_fail_launch(const char *part) { g_fail = part; }
 void fake_fail_query(int on) { g_fail_query = on; }
@@ -176,8 +182,25 @@ hipError_t hipStreamIsCapturing(hipStream_t st, hipStreamCaptureStatus *s)
     *s = g_capturing.count(st) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-hipError_t hipMalloc(void **p, size_t n) { return *p = zeroed(n), hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return *p = zeroed(n), hipSuccess; }
+hipError_t hipStreamGetCaptureInfo(hipStream_t st, hipStreamCaptureStatus *s, unsigned long long *id)
+{
+    *id = g_capture_id;
+    return hipStreamIsCapturing(st, s);
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *mode)
+{
+    const hipStreamCaptureMode old = g_relaxed ? hipStreamCaptureModeRelaxed : hipStreamCaptureModeGlobal;
+    g_relaxed = *mode == hipStreamCaptureModeRelaxed;
+    *mode = old;
+    return hipSuccess;
+}
+hipError_t allocate(void **p, size_t n)
+{
+    if (!g_capturing.empty() && !g_relaxed) return hipErrorStreamCaptureUnsupported;
+    return *p = zeroed(n), hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n) { return allocate(p, n); }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return allocate(p, n); }
 hipError_t hipFree(void *p) { return std::free(p), hipSuccess; }
 hipError_t hipHostFree(void *p) { return std::free(p), hipSuccess; }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { return *d = h, hipSuccess; }

@@ -808,11 +808,14 @@ def test_recorded_and_eager_calls_share_a_context(grad_streams):
         assert ctx.plan_stats()["mode"] == 2 and ctx.plan_stats()["bytes"] < whole
         b.bwd()
     torch.cuda.synchronize()
-    with torch.cuda.graph(g, stream=st):
-        for l in (a, b):
-            for call in (l.fwd, l.bwd):
-                call()
-                assert ctx.plan_stats()["bytes"] == whole
+    sent, g2 = [], torch.cuda.CUDAGraph()
+    for graph in (g, g2):  # (the second is captured right behind the first: it must bring its own plan all the same)
+        with torch.cuda.graph(graph, stream=st):
+            for l in (a, b) if graph is g else (b,):
+                for call in (l.fwd, l.bwd):
+                    call()
+                    sent.append(ctx.plan_stats()["bytes"])
+    assert sent == [whole, 0, whole, 0, whole, 0]
     def outputs(l):
         train = torch.from_numpy(l.tok_train != 0).cuda()
         return [l.y, l.dx[train], l.h_save[train]] + [t for k, t in enumerate(l.dA + l.dB) if not torch.isnan(t).all()]
@@ -830,7 +833,11 @@ def test_recorded_and_eager_calls_share_a_context(grad_streams):
             for l in eager * 3:
                 l.fwd()
                 l.bwd()
-            g.replay()
+            if rep % 2:
+                g.replay()
+            else:
+                spoil(b)
+                g2.replay()
         torch.cuda.synchronize()
         for l, r in zip((a, b), ref):
             got = outputs(l)

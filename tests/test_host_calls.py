@@ -39,6 +39,10 @@ def test_a_replay_brings_its_own_plan(run, call):
     run("replay", call)
 
 
+def test_plans_of_recorded_calls_beyond_the_room_for_them(run):
+    run("many_recorded")
+
+
 def test_calls_without_a_context_upload_when_recorded_and_ever_after(run):
     run("noalloc")
 
@@ -113,6 +117,7 @@ class World:
 
     def context(self, max_tokens=2048, max_segments=64, max_adapters=200, max_rank=128, max_d=16384):
         self.fake.fake_new_plan()
+        self.fake.fake_new_graph()
         h = ctypes.c_void_p()
         assert self.lib.collm_ctx_create(ctypes.byref(h), 0, max_tokens, max_segments, max_adapters, max_rank, max_d) == 0
         self.launches()
@@ -165,7 +170,13 @@ def replay(w, call):
     x, y, z = w.batches(ctx)
     go = lambda b, layer=0: (b.fwd if call == "fwd" else b.bwd)(layer)
     assert go(x) == 0  # (warmed up: nothing is new when it is recorded)
-    w.record(lambda: go(x), lambda: go(x, 1))
+    whole, sent = w.stats(ctx)[1], []
+    def note(b, layer):
+        r = go(b, layer)
+        sent.append(w.stats(ctx)[1])
+        return r
+    w.record(lambda: note(x, 0), lambda: note(x, 0), lambda: note(x, 1))
+    assert sent == [whole, 0, whole]  # the second finds what the first brings, whatever ran between the replays
     for k in range(40):  # more uploads than staging slots
         b = (y, z)[k % 2]
         assert go(b, k % 3) == 0 and b.on_device()
@@ -173,6 +184,38 @@ def replay(w, call):
         w.fake.fake_replay()
         assert x.on_device()
         assert go(y) == 0 and y.on_device()
+    # two captures in a row: a graph brings its own plan, as the other need not have run before it
+    w.fake.fake_new_graph()
+    w.record(lambda: note(x, 1))
+    w.fake.fake_new_graph()
+    w.record(lambda: note(x, 1), lambda: note(x, 1))
+    assert sent[3:] == [whole, whole, 0]
+    # an eager call on another stream while one is captured
+    w.fake.fake_new_graph()
+    w.fake.fake_capture(STREAM, 1)
+    assert note(x, 0) == 0 and (y.fwd if call == "fwd" else y.bwd)(0, STREAM + 1) == 0 and note(x, 0) == 0
+    w.fake.fake_capture(STREAM, 0)
+    assert sent[6:] == [whole, whole]
+    w.fake.fake_replay()
+    assert x.on_device()
+
+
+def many_recorded(w):
+    # 2048 tokens, recorded with new tables until the room for kept plans is used up: the rest travel in kernel arguments
+    ctx = w.context()
+    x = Batch(w, ctx, [2000, 48], [0, 1], [1, 0], [16, 8])
+    w.fake.fake_capture(STREAM, 1)
+    kinds = []
+    for k in range(2 * (64 << 20) // 40000):
+        assert x.fwd(k % 2) == 0
+        names = [l[0] for l in w.launches()]
+        kinds.append("words" if any("plan_words" in n for n in names) else "copy" if any("plan_copy" in n for n in names) else "none")
+    w.fake.fake_capture(STREAM, 0)
+    kept = kinds.index("words")
+    assert set(kinds[:kept]) == {"copy"} and set(kinds[kept:]) == {"words"}
+    assert 0.9 * (64 << 20) < kept * w.stats(ctx)[1] <= 64 << 20
+    w.fake.fake_replay()
+    assert x.on_device()
 
 
 def noalloc(w):
