@@ -1116,6 +1116,7 @@ int scratch_context(int device, hipStream_t st, collm_ctx **out)
         c->workspace_bytes = (int64_t)kScratchBytes;
         // host vectors at their largest size, so that later calls do not grow them
         c->plan.reserve(c->plan_cap);
+        c->rows_of.reserve(2 * kScratchMaxAdapters);
         c->key_seg_start.reserve(kScratchMaxSegments + 1);
         c->key_seg_adapter.reserve(kScratchMaxSegments);
         c->key_seg_train.reserve(kScratchMaxSegments);
