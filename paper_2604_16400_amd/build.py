@@ -14,8 +14,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcollm_lora.so")
 # the Python binding's argument marshalling (CPython extension), named after the interpreter it is built for
 MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
-SOURCES = ["api.cpp", "planner.cpp", "kernels_bf16.hip", "kernels_f32.hip", "kernels_adapter.hip"]
-HEADERS = ["plan.h", "planner.h", "kernels.h"]
+SOURCES = ["api.cpp", "planner.cpp", "kernels_bf16.hip", "kernels_decode.hip", "kernels_f32.hip", "kernels_adapter.hip"]
+HEADERS = ["plan.h", "planner.h", "kernels.h", "bf16_device.h"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-mcode-object-version=5",

@@ -428,6 +428,28 @@ bool dx_one_round(const collm_ctx *c, int n_train, int d_in, int d_out, bool f32
     return c->grad_streams >= 0 ? c->grad_streams == 0 : grads_alone(n_train, d_in, d_out, f32, rpad);
 }
 
+// Whether a call runs as the two kernels of kernels_decode.hip.
+bool decode_sized(const collm_ctx *c, const collm_shape *s, const int32_t *rank, const int32_t *seg_start, const uint8_t *seg_is_train, int n_sib, bool swiglu)
+{
+    const int T = s->n_tokens;
+    if (s->dtype != COLLM_BF16 || n_sib > 1 || swiglu || T < 1 || T > kDecodeRows) return false;
+    if (c->tile_fwd >= 0 || c->gemm_split >= 0 || c->wide_min_rows >= 0) return false;
+    // (64 rows of [N][K] weights are a quarter slower to read, which the longest contractions do not get back, us the general path / this: 28672 -> 4096 70.9 / 72.6,
+    // 50 rows 24576 -> 6144 93.6 / 94.5, 20000 -> 4096 58.0 / 55.0)
+    const bool tr = s->layout == COLLM_LAYOUT_OUT_IN;
+    if (tr && T > 32 && s->d_in > 20480) return false;
+    for (int k = 0; k < s->n_segments; ++k)
+        if (seg_is_train[k] && seg_start[k + 1] > seg_start[k]) return false;
+    int rmax = 1;
+    for (int a = 0; a < s->n_adapters; ++a) {
+        // (16-byte loads of parts of a table's rows: [rank] rows of B_a in one layout, 64 of more than 64 columns of A_a in the other)
+        if (rank[a] % 8 != 0 && (tr || rank[a] > kDecodeRankCols)) return false;
+        rmax = std::max(rmax, rank[a]);
+    }
+    // (at least one slice of each kind fits the workspace)
+    return (int64_t)T * s->d_out + (int64_t)round_up(T, 16) * round_up(rmax, kKStep) <= (int64_t)c->part_bytes / 4;
+}
+
 // One GEMM over the row order `R`: a single launch, or whole rounds of large tiles followed by
 // small tiles over the remaining rows.
 hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows, int cols, int forced_tile,
@@ -737,7 +759,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
                  const int32_t *rank, const int32_t *seg_start, const int32_t *seg_adapter,
                  const uint8_t *seg_is_train, float *const *dA, float *const *dB, bool allow_reuse,
                  hipStream_t st, bool fwd, const void *const *pass_tab, bool out_args, const int32_t *rank_ext_all = nullptr,
-                 int n_sib = 1, bool swiglu = false)
+                 int n_sib = 1, bool swiglu = false, bool decode = false)
 {
     const bool f32 = s->dtype == COLLM_F32;
     bool recording = false;
@@ -769,7 +791,7 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     // Narrow ranks waste its 128 columns of matrix work; measured, it still pays for the dh pass (tables
     // with K contiguous) from rank 32 up.  Encoded as all-rows threshold + 65536 * training-rows threshold.
     const int rpad_max = round_up(rmax, kKStep);
-    const int wide_all = f32 ? 0 : (c->wide_min_rows >= 0 ? c->wide_min_rows : (rpad_max >= 64 ? 1 : 0));
+    const int wide_all = f32 || decode ? 0 : (c->wide_min_rows >= 0 ? c->wide_min_rows : (rpad_max >= 64 ? 1 : 0));
     const int wide_train = f32 ? 0 : (c->wide_min_rows >= 0 ? c->wide_min_rows : (rpad_max >= 32 ? 1 : 0));
     const int wide = wide_all + 65536 * wide_train;
 
@@ -1025,6 +1047,87 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
     return COLLM_OK;
 }
 
+
+// How the first kernel of a decode-sized call is cut: slices of K of each of the weight's strips, and of each of the shrink's `items`.  A block fills
+// a CU, and what is left over for a second round costs nearly as much as a first (64 rows of 4096 -> 11008, 56 items: two slices of 86 strips 27 us,
+// three 38), so the two kinds share the CUs: `h` slices of the shrink leave n slices of the strips, and the h is taken whose longer side is
+// shorter.  A wave's round of 64 values takes 1.45 .. 2.2 us by the number of rows, a quarter more with [N][K] weights, unless the weight's bytes
+// take longer; a chunk of the shrink's 64 values 0.4 us for ranks up to 16, else 1.3.  Whole calls, the general path / this, us: 8 rows 4096 -> 4096 24 / 17, 64 rows of 29 adapters
+// 4096 -> 11008 50 / 40 ([N][K]: 52 / 48), 64 rows 8192 -> 28672 122 / 116, 12 rows 1000 -> 28672 47 / 21, 64 rows 1024 -> 4096 30 / 20.
+struct DecodeCut {
+    int n_slices, k_per_slice, h_slices;
+};
+DecodeCut decode_cut(int T, int N, int K, bool kmajor, int rpad, int items, int cus, int64_t room)
+{
+    const int strips = (N + kDecodeCols - 1) / kDecodeCols;
+    const int64_t rows_h = (int64_t)round_up(T, 16) * rpad, rows_y = (int64_t)T * N;  // floats of a slice
+    const double round_us = (T <= 16 ? 1.45 : (T <= 32 ? 1.8 : 2.2)) * (kmajor ? 1.25 : 1.0), chunk_us = rpad <= 16 ? 0.4 : 1.3;
+    const double stream_us = (double)K * N * 2 / 5.0e6;
+    DecodeCut best{1, 0, 1};
+    double best_us = 1e30;
+    for (int h = 1; h <= 8 && (h == 1 || (items > 0 && h * 512 <= K && h * items < cus && h * rows_h + rows_y <= room)); ++h) {
+        long n = std::max(1, (cus - h * items) / strips);
+        n = std::max(1L, std::min<long>({n, (long)K / 512, (long)((room - h * rows_h) / rows_y)}));
+        const double base = std::max(stream_us, round_us * ((K + 256 * n - 1) / (256 * n))), shrink = items > 0 ? chunk_us * ((K + 256 * h - 1) / (256 * h)) : 0.0;
+        const double us = (strips * n + h * items <= cus ? std::max(base, shrink) : base + shrink) + (double)n * rows_y * 8 / 4.0e6;
+        if (us < best_us) {
+            best = {(int)n, 0, h};
+            best_us = us;
+        }
+    }
+    best.k_per_slice = round_up((K + best.n_slices - 1) / best.n_slices, 64);
+    best.n_slices = (K + best.k_per_slice - 1) / best.k_per_slice;
+    return best;
+}
+
+// The two kernels of a decode-sized inference call.
+int run_decode(collm_ctx *c, const collm_shape *s, const void *x, const void *W, const void *const *B, void *y, hipStream_t st)
+{
+    const PlanLayout &L = c->L;
+    const RowOrderLayout &R = L.all;
+    const bool tr = s->layout == COLLM_LAYOUT_OUT_IN;
+    const int T = s->n_tokens, N = s->d_out, K = s->d_in;
+    const int strips = (N + kDecodeCols - 1) / kDecodeCols, rows_h = round_up(T, 16);
+    const int h_cols = L.rpad <= 16 ? 1 : (L.rpad + kDecodeRankCols - 1) / kDecodeRankCols;
+    const DecodeCut cut = decode_cut(T, N, K, tr, L.rpad, R.n_items * h_cols, std::max(c->n_cus, 1), (int64_t)c->part_bytes / 4);
+    const int n_slices = cut.n_slices;
+    SkinnyArgs a{};
+    a.in = x;
+    a.ld_in = s->d_in;
+    a.in_bytes = (uint32_t)((int64_t)s->n_tokens * s->d_in * 2);
+    a.K = s->d_in;
+    a.tab = reinterpret_cast<const uint64_t *>(c->d_plan + L.off_A_ptr);
+    a.items = reinterpret_cast<const SkinnyItem *>(c->d_plan + R.off_items);
+    a.n_items = R.n_items;
+    a.row_tok = c->d_plan + R.off_row_tok;
+    DecodeFinishArgs d;
+    d.w = W;
+    d.ldw = tr ? s->d_in : s->d_out;
+    d.w_bytes = (uint32_t)((int64_t)s->d_in * s->d_out * 2);
+    d.N = s->d_out;
+    d.y = y;
+    d.n_rows = s->n_tokens;
+    d.part = c->d_part;
+    d.strips = strips;
+    d.n_slices = n_slices;
+    d.k_per_slice = cut.k_per_slice;
+    d.h_slices = cut.h_slices;
+    d.h_cols = h_cols;
+    d.scale = s->scale;
+    d.n_base = R.n_base;
+    const SkinnyItem *items = reinterpret_cast<const SkinnyItem *>(c->plan.data() + R.off_items);
+    for (int i = 0; i < R.n_items; ++i)
+        d.items[i] = {(uint32_t)items[i].row_lo | (uint32_t)items[i].n_rows << 16, (uint32_t)items[i].rank, (uint64_t)(uintptr_t)B[items[i].adapter]};
+    // the shrink's sums behind those of the slices
+    a.part = c->d_part + (int64_t)n_slices * T * N;
+    a.part_rows = rows_h;
+    a.part_ld = L.rpad;
+    Prof prof(c, st, "decode");
+    HIP_TRY(launch_decode_base(a, d, L.rpad, tr, st, c->patch.blocks > 0 ? &c->patch : nullptr));
+    c->patch.blocks = 0;
+    HIP_TRY(launch_decode_finish(a, d, tr, st));
+    return COLLM_OK;
+}
 
 // Sibling projections (several projections of the same x side by side in the columns of W, y and dy).  Checks
 // the description and fills c->sum_rank with the ranks summed over the siblings, which is what the rank-wide
@@ -1473,14 +1576,16 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     HIP_TRY(hipSetDevice(c->device));
     c->n_prof = 0;
     const PatchGuard guard{c};
+    const bool decode = decode_sized(c, s, rank, seg_start, seg_is_train, P, swiglu);
     {
         Prof prof(c, st, "plan_copy");
         rc = prepare_plan(c, s, A, B, rank, seg_start, seg_adapter, seg_is_train, nullptr, nullptr, true, st, true, A, false,
-                          P > 1 ? rank1 : nullptr, P, swiglu);
+                          P > 1 ? rank1 : nullptr, P, swiglu, decode);
     }
     if (rc != COLLM_OK) return rc;
     const PlanLayout &L = c->L;
     const bool f32 = s->dtype == COLLM_F32;
+    if (decode) return run_decode(c, s, x, W, B, y, st);
 
     // shrink: h = x A_a (fp32), kept as s*h in the element type for the GEMM's extra K-steps
     // COLLM_LAYOUT_OUT_IN: every table is the transpose, so each pass takes the kernel variant its

@@ -231,6 +231,34 @@ int skinny_depth(int rpad, int row_tiles);  // chunks a wave keeps in flight
 hipError_t launch_grad(const GradArgs &a, int n_grad, int rpad, hipStream_t st);
 int grad_lds(int rpad, bool beside_gemm);  // bytes of LDS a block of launch_grad asks for
 constexpr int kSmallTileLds = 2 * (128 + 128) * 128;  // bytes of LDS of a 128x128 GEMM block (two stages); two such blocks run on a CU
+// A decode-sized inference call in two kernels (kernels_decode.hip): y = x W + (s h) B_a for up to kDecodeRows rows, ranks up to
+// kDecodeRank.  The shrink's arguments (x, tables, items of 16 rows, where its sums go) are a SkinnyArgs.
+constexpr int kDecodeRows = 64, kDecodeRank = kMaxRank, kDecodeCols = 128, kDecodeRankCols = 64;
+struct DecodeArgs {
+    const void *w;            // [K][N] or, K-major, [N][K]; row length ldw
+    int64_t ldw;
+    uint32_t w_bytes;
+    int N;
+    void *y;                  // [tokens][N]
+    int n_rows;               // rows of the row order, one per token
+    float *part;              // sums of the K slices [slice][n_rows][N]
+    int strips, n_slices, k_per_slice;  // k_per_slice: a multiple of 64
+    int h_slices, h_cols;     // K slices of the shrink, blocks of kDecodeRankCols columns that the widest rank takes
+    float scale;
+    int n_base;               // rows without an adapter, the first of the order
+};
+// The items travel as arguments of the second kernel: looked up in the plan they are two trips to memory before the first of a table's loads.
+struct DecodeItem {
+    uint32_t rows;            // first row | number of rows << 16
+    uint32_t rank;
+    uint64_t tab;             // B_a
+};
+struct DecodeFinishArgs : DecodeArgs {
+    DecodeItem items[kDecodeRows];
+};
+hipError_t launch_decode_base(const SkinnyArgs &a, const DecodeArgs &d, int rpad, bool kmajor, hipStream_t st, const PlanPatch *patch);
+hipError_t launch_decode_finish(const SkinnyArgs &a, const DecodeFinishArgs &d, bool kmajor, hipStream_t st);
+
 // dst[t][q] = bf16(mult * src[row_tok[t]][q]) for n_rows rows and ld_dst (multiple of 8) columns; columns from
 // src_cols on are zero
 hipError_t launch_pack_rows(const float *src, int64_t ld_src, int src_cols, const int32_t *row_tok, int n_rows,

@@ -52,6 +52,7 @@ struct GradItem {
 // Offsets (in int32 units) into the plan block, and counts.  Host-side description.
 struct RowOrderLayout {
     int32_t n_rows = 0, n_rows_pad = 0;
+    int32_t n_base = 0;           // rows without an adapter: the first of the order
     int32_t off_row_tok = 0;      // [n_rows_pad] token index or -1
     int32_t off_row_adapter = 0;  // [n_rows_pad] adapter or -1
     int32_t n_items = 0, off_items = 0;  // SkinnyItem[n_items]

@@ -78,6 +78,7 @@ void build_row_order(Builder &b, RowOrderLayout &L, const std::vector<int32_t> &
     // is one run (what the gradient items need), larger adapters first.
     std::vector<int32_t> count(n_adapters + 1, 0);  // [0]: base-only rows
     for (int i = 0; i < n; ++i) count[tok_adapter[tokens[i]] + 1]++;
+    L.n_base = count[0];
     struct Run {
         int32_t adapter, lo, len;
     };
