@@ -914,12 +914,12 @@ struct SliceSums {
     int part_rows, part_ld, n_slices;
 };
 
-// One skinny pass over a row order.
+// One skinny pass over a row order.  beside (fp32): gradients that run in the same launch.
 int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, const void *in, int K,
                int32_t off_tab, bool t_kmajor, float *f32_out, int64_t f32_ld, int f32_cols,
                int f32_by_token, float f32_mult, void *bf_out, float bf_mult, const char *name,
                hipStream_t st, const SiblingPass *sp = nullptr, const void *warm = nullptr, uint64_t warm_bytes = 0,
-               const SliceSums *sums = nullptr, int bf_up = 0)
+               const SliceSums *sums = nullptr, int bf_up = 0, const GradArgs *beside = nullptr)
 {
     if (R.n_items == 0 && R.n_wide == 0) return COLLM_OK;
     // (taken by the call's first pass's first kernel; behind it the plan is whole)
@@ -998,7 +998,8 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
     }
     Prof prof(c, st, name);
     if (s->dtype == COLLM_F32) {
-        HIP_TRY(launch_skinny_f32(a, R.n_items, t_kmajor, st));
+        a.n_items = R.n_items;
+        HIP_TRY(beside ? launch_dh_dB_f32(a, *beside, rpad, t_kmajor, st) : launch_skinny_f32(a, R.n_items, t_kmajor, st));
         return COLLM_OK;
     }
     int n_wsplit = 1;
@@ -1751,11 +1752,14 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     const bool alone = c->grad_streams >= 0 ? c->grad_streams == 0 : grads_alone(n_train, s->d_in, s->d_out, f32, L.rpad);
     const bool overlap = dA && !alone && !c->profile;
     const bool one_round = dx_one_round(c, n_train, s->d_in, s->d_out, f32, L.rpad);
+    // fp32 on one stream: dB beside dh, dA beside dX
+    const bool pair = f32 && dA && alone && !c->profile && pair_f32(L.rpad, s->d_in, s->d_out);
     hipStream_t gs = overlap ? c->side : st;
     GradArgs ga{};
     const int64_t esz = f32 ? 4 : 2;
     ga.row_tok = c->d_plan + L.train.off_row_tok;
     ga.items = reinterpret_cast<const GradItem *>(c->d_plan + L.off_grad);
+    ga.n_items = L.n_grad;
     ga.accumulate = accumulate ? 1 : 0;
     auto set_outs = [&](float *const *g) {
         if (!out_args || L.n_grad > kGradOuts) return;
@@ -1875,7 +1879,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         ga.out_tab = reinterpret_cast<const uint64_t *>(c->d_plan + L.off_dB_ptr);
         set_outs(dB);
         ga.out_transposed = tr ? 1 : 0;
-        {
+        if (!pair) {
             Prof prof(c, gs, "grad_dB");
             if (f32) {
                 HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, gs));
@@ -1909,7 +1913,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     } else if (P == 1) {
         rc = run_skinny(c, s, L.train, dy, s->d_out, L.off_B_ptr, !tr, c->d_dh32, L.rpad, L.rpad, 0, s->scale,
                         c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, L.train, n_train, s->d_in, s->d_out, !tr, one_round, false) ? W : nullptr,
-                        (uint64_t)s->d_in * s->d_out * 2);
+                        (uint64_t)s->d_in * s->d_out * 2, nullptr, 0, pair ? &ga : nullptr);
         if (rc != COLLM_OK) return rc;
     } else {
         // one pass per sibling over its columns of dy and of the tables, each writing its columns of dh
@@ -1951,7 +1955,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         ga.out_tab = reinterpret_cast<const uint64_t *>(c->d_plan + L.off_dA_ptr);
         set_outs(dA);
         ga.out_transposed = tr ? 0 : 1;
-        {
+        if (!pair) {
             Prof prof(c, gs, "grad_dA");
             if (f32) HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, gs));
             else HIP_TRY(launch_grad(ga, L.n_grad, L.rpad, gs));
@@ -1983,11 +1987,18 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         Prof prof(c, st, "gemm_dx");
         if (f32) {
             g.n_rows = n_train;
-            HIP_TRY(launch_gemm_f32(g, !tr, st));
+            // (a caller's dx in the place of its x: dA reads x first)
+            if (pair && dx != x && gemm_f32_short_blocks(g)) {
+                HIP_TRY(launch_dx_dA_f32(g, ga, L.rpad, !tr, st));
+            } else {
+                if (pair) HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, st));
+                HIP_TRY(launch_gemm_f32(g, !tr, st));
+            }
         } else {
             HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, one_round, st));
         }
     }
+    if (pair && !dx) HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, st));
     if (overlap) HIP_TRY(hipStreamWaitEvent(st, c->ev_join, 0));
     return COLLM_OK;
 }

@@ -152,6 +152,7 @@ struct GradArgs {
     int ld_small_bf;          // already scaled, zeros from the rank up to the next multiple of 16 (fp32 one unused)
     const int32_t *row_tok;   // training row order
     const GradItem *items;    // one per trained adapter
+    int n_items;              // (launch_dh_dB_f32, launch_dx_dA_f32)
     const uint64_t *out_tab;  // adapter -> fp32 output
     // bf16 kernels: or (n_out > 0) the outputs of the items, in their order.  A call's few gradient buffers need no upload
     // in front of its kernels then, and its new adapter tables can ride on a rank-wide pass (PlanPatch).
@@ -315,6 +316,11 @@ hipError_t launch_adamw(const AdamWArgs &a, bool bf16, hipStream_t st);
 // fp32 element type: same argument blocks, fp32 MFMAs (16x16x4)
 hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st);  // a.n_rows: rows of the order
 hipError_t launch_skinny_f32(const SkinnyArgs &a, int n_items, bool t_kmajor, hipStream_t st);
+// dh beside dB, dX beside dA, where no table is beyond 32-bit offsets (pair_f32) and the GEMM runs on blocks of 16 rows (gemm_f32_short_blocks)
+bool pair_f32(int rpad, int d_in, int d_out);
+bool gemm_f32_short_blocks(const GemmArgs &a);
+hipError_t launch_dh_dB_f32(const SkinnyArgs &s, const GradArgs &g, int rpad, bool t_kmajor, hipStream_t st);
+hipError_t launch_dx_dA_f32(const GemmArgs &m, const GradArgs &g, int rpad, bool b_kmajor, hipStream_t st);
 hipError_t launch_grad_f32(const GradArgs &a, int n_grad, int rpad, hipStream_t st);
 
 }  // namespace collm

@@ -64,15 +64,22 @@ static bool table_is_big(int rank, int d) { return (int64_t)rank * d * 4 > 0x7ff
 // One block = 16 RT rows x 64 columns; its KW waves split K (and the extension steps) between them.  Column i of
 // 16-column block c is n0 + 4 i + c: a lane's four columns are then consecutive both where it loads the second
 // operand ([K][N]) and where it stores.
+template <int RT, int KW> constexpr int kF32GemmRed = KW * 16 * RT * (64 + 4);  // floats of LDS
 template <bool B_KMAJOR, int RT, int KW, bool BIG>
-__global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
+__device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by, float *red)
 {
     using idx_t = std::conditional_t<BIG, uint64_t, uint32_t>;
     constexpr int ROWS = 16 * RT, LD = 64 + 4;
-    __shared__ __align__(16) float red[KW * ROWS * LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
-    const int n0 = blockIdx.x * 64, m0 = blockIdx.y * ROWS;
+    const int n0 = bx * 64, m0 = by * ROWS;
+    const int tile = m0 / kF32Tile, in_tile = m0 - tile * kF32Tile;
+    const int e0 = p.ext_off[tile], e1 = p.ext_off[tile + 1];
+    // the tokens this thread stores to in the end
+    constexpr int OUTS = ROWS * 16 / (KW * 64) > 0 ? ROWS * 16 / (KW * 64) : 1;
+    int tok_out[OUTS];
+#pragma unroll
+    for (int i = 0; i < OUTS; ++i) tok_out[i] = ((tid + i * KW * 64) >> 4) < ROWS ? p.row_tok[m0 + ((tid + i * KW * 64) >> 4)] : -1;
     const int K = p.K, N = p.N;
     const int n = n0 + 4 * l16;  // first of this lane's four columns (N is a multiple of 4)
     const __amdgpu_buffer_rsrc_t ra = f32_rsrc(p.a, 0x7fffffffu), rb = f32_rsrc(p.b, 0x7fffffffu);
@@ -93,22 +100,72 @@ __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
     const int k_lo = wave * per, k_hi = (k_lo + per) < K ? (k_lo + per) : K;
     // 16 K values per step (this lane: k + 4 kg .. + 3), U steps of loads in flight
     constexpr int U = RT == 1 ? 4 : 2;
-    for (int k0 = k_lo; k0 < k_hi; k0 += 16 * U) {
-        floatx4 xa[U][RT], wb[U][4];
+    floatx4 xa[U][RT], wb[U][4];
+    auto load = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = k0 + u * 16 + kg * 4;
-            const bool on = k < k_hi;
-#pragma unroll
-            for (int t = 0; t < RT; ++t) xa[u][t] = f32_load4(ra, on && aoff[t] != kF32Oob ? aoff[t] + (uint32_t)k * 4u : kF32Oob);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 // [K][N]: K value k + j, columns n .. n + 3; [N][K]: column n + j, K values k .. k + 3
                 const uint32_t off = B_KMAJOR ? ((uint32_t)(n + j) * (uint32_t)p.ldb + (uint32_t)k) * 4u
                                               : ((uint32_t)(k + j) * (uint32_t)p.ldb + (uint32_t)n) * 4u;
-                wb[u][j] = f32_load4(rb, on && n < N ? off : kF32Oob);
+                wb[u][j] = f32_load4(rb, k < k_hi && n < N ? off : kF32Oob);
             }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * 16 + kg * 4;
+#pragma unroll
+            for (int t = 0; t < RT; ++t) xa[u][t] = f32_load4(ra, k < k_hi && aoff[t] != kF32Oob ? aoff[t] + (uint32_t)k * 4u : kF32Oob);
+        }
+    };
+    load(k_lo);
+
+    // Low-rank extension: one step = 16 rank indices of one adapter's table against the rows of its run.  A wave's first step is asked for
+    // behind its first operands, not behind the contraction: what a small call takes is a chain of trips to memory.
+    const float *__restrict__ Hs = reinterpret_cast<const float *>(p.hs);
+    struct Step {
+        int row_lo, row_hi;
+        floatx4 tb[4], hv[RT];
+    };
+    auto load_step = [&](int e, Step &s) {
+        const ExtStep st = p.ext[e];
+        const int koff = (int)(st.koff_rank & 0xffffu), rk = (int)(st.koff_rank >> 16);
+        s.row_lo = (int)(st.rows & 0xffffu) - in_tile;
+        s.row_hi = (int)(st.rows >> 16) - in_tile;
+        if (rk == 0 || s.row_hi <= 0 || s.row_lo >= ROWS) {
+            s.row_hi = 0;
+            return;
+        }
+        const uint32_t tab_bytes = (uint32_t)rk * (uint32_t)(B_KMAJOR ? N : p.ext_ld) * 4u;
+        const float *tab = reinterpret_cast<const float *>(st.tab);
+        const __amdgpu_buffer_rsrc_t rt = f32_rsrc(tab, tab_bytes);
+        const int q = koff + kg * 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (B_KMAJOR) {
+                // table rows are output columns, `rank` long: any rank, so element by element
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    s.tb[j][i] = table1<BIG>(tab, rt, n < N && q + i < rk, (idx_t)(n + j) * (idx_t)rk + (idx_t)(q + i));
+            } else {
+                s.tb[j] = table4<BIG>(tab, rt, n < N && q + j < rk, (idx_t)(q + j) * (idx_t)p.ext_ld + (idx_t)n);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            // (zeros lie behind the rank, up to the row's padded length)
+            const int r = t * 16 + l16;
+            s.hv[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (r >= s.row_lo && r < s.row_hi) s.hv[t] = *reinterpret_cast<const floatx4 *>(Hs + (int64_t)(m0 + r) * p.hs_ld + q);
+        }
+    };
+    Step s;
+    s.row_hi = 0;
+    if (e0 + wave < e1) load_step(e0 + wave, s);
+
+    for (int k0 = k_lo; k0 < k_hi;) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -118,56 +175,31 @@ __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
 #pragma unroll
                     for (int t = 0; t < RT; ++t)
                         acc[t][c] = mfma_f32(B_KMAJOR ? wb[u][c][e] : wb[u][e][c], xa[u][t][e], acc[t][c]);
+        k0 += 16 * U;
+        if (k0 < k_hi) load(k0);
     }
 
-    // Low-rank extension: one step = 16 rank indices of one adapter's table against the rows of its run.  The
-    // products of a step are summed apart and added to the rows of the run only, so that a table's infinities
+    // The products of a step are summed apart and added to the rows of the run only, so that a table's infinities
     // and NaNs stay out of other adapters' rows.
-    const float *__restrict__ Hs = reinterpret_cast<const float *>(p.hs);
-    const int tile = m0 / kF32Tile, in_tile = m0 - tile * kF32Tile;
-    const int e0 = p.ext_off[tile], e1 = p.ext_off[tile + 1];
-    for (int e = e0 + wave; e < e1; e += KW) {
-        const ExtStep st = p.ext[e];
-        const int koff = (int)(st.koff_rank & 0xffffu), rk = (int)(st.koff_rank >> 16);
-        const int row_lo = (int)(st.rows & 0xffffu) - in_tile, row_hi = (int)(st.rows >> 16) - in_tile;
-        if (rk == 0 || row_hi <= 0 || row_lo >= ROWS) continue;
-        const uint32_t tab_bytes = (uint32_t)rk * (uint32_t)(B_KMAJOR ? N : p.ext_ld) * 4u;
-        const float *tab = reinterpret_cast<const float *>(st.tab);
-        const __amdgpu_buffer_rsrc_t rt = f32_rsrc(tab, tab_bytes);
-        const int q = koff + kg * 4;
-        floatx4 tb[4], hv[RT];
+    for (int e = e0 + wave; e < e1;) {
+        if (s.row_hi > 0) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if constexpr (B_KMAJOR) {
-                // table rows are output columns, `rank` long: any rank, so element by element
+            for (int t = 0; t < RT; ++t) {
+                floatx4 add[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) add[c] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    tb[j][i] = table1<BIG>(tab, rt, n < N && q + i < rk, (idx_t)(n + j) * (idx_t)rk + (idx_t)(q + i));
-            } else {
-                tb[j] = table4<BIG>(tab, rt, n < N && q + j < rk, (idx_t)(q + j) * (idx_t)p.ext_ld + (idx_t)n);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) add[c] = mfma_f32(B_KMAJOR ? s.tb[c][i] : s.tb[i][c], s.hv[t][i], add[c]);
+                const int r = t * 16 + l16;
+                if (r >= s.row_lo && r < s.row_hi)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[t][c] += add[c];
             }
         }
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            // (zeros lie behind the rank, up to the row's padded length)
-            const int r = t * 16 + l16;
-            hv[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-            if (r >= row_lo && r < row_hi) hv[t] = *reinterpret_cast<const floatx4 *>(Hs + (int64_t)(m0 + r) * p.hs_ld + q);
-        }
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            floatx4 add[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) add[c] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) add[c] = mfma_f32(B_KMAJOR ? tb[c][i] : tb[i][c], hv[t][i], add[c]);
-            const int r = t * 16 + l16;
-            if (r >= row_lo && r < row_hi)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[t][c] += add[c];
-        }
+        e += KW;
+        if (e < e1) load_step(e, s);
     }
 
     // lane holds row l16 and, in register j of block c, column 16 kg + 4 j + c
@@ -179,9 +211,9 @@ __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
                 floatx4{acc[t][0][j], acc[t][1][j], acc[t][2][j], acc[t][3][j]};
     __syncthreads();
     float *__restrict__ Out = reinterpret_cast<float *>(p.out);
-    for (int idx = tid; idx < ROWS * 16; idx += KW * 64) {
-        const int r = idx >> 4, c = (idx & 15) * 4;
-        const int tok = p.row_tok[m0 + r];
+#pragma unroll
+    for (int i = 0; i < OUTS; ++i) {
+        const int idx = tid + i * KW * 64, r = idx >> 4, c = (idx & 15) * 4, tok = tok_out[i];
         if (tok < 0 || n0 + c >= N) continue;
         floatx4 sum = *reinterpret_cast<const floatx4 *>(red + r * LD + c);
 #pragma unroll
@@ -190,20 +222,34 @@ __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
     }
 }
 
+template <bool B_KMAJOR, int RT, int KW, bool BIG>
+__global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
+{
+    __shared__ __align__(16) float red[kF32GemmRed<RT, KW>];
+    gemm_f32_block<B_KMAJOR, RT, KW, BIG>(p, blockIdx.x, blockIdx.y, red);
+}
+
 // out[m][q] = sum_k in[tok(m)][k] table_a(k, q): one block = one item (up to 16 rows of one adapter) x 16 columns of
 // the output row (blockIdx.y; columns beyond the rank are cleared); its eight waves split K.
 constexpr int kF32SkinnyWaves = 8;
+constexpr int kF32SkinnyRed = kF32SkinnyWaves * 16 * (16 + 4);
 template <bool T_KMAJOR, bool BIG>
-__global__ void __launch_bounds__(kF32SkinnyWaves * 64) skinny_f32_kernel(SkinnyArgs p)
+__device__ __forceinline__ void skinny_f32_block(const SkinnyArgs &p, int item, int by, float *red)
 {
     using idx_t = std::conditional_t<BIG, uint64_t, uint32_t>;
     constexpr int KW = kF32SkinnyWaves, LD = 16 + 4;
-    __shared__ __align__(16) float red[KW * 16 * LD];
-    const SkinnyItem it = p.items[blockIdx.x];
+    const SkinnyItem it = p.items[item];
     const int rank = it.rank, K = p.K;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, kg = lane >> 4;
-    const int q0 = blockIdx.y * 16, q = q0 + l16;
+    const int q0 = by * 16, q = q0 + l16;
+    // the row this thread stores to in the end, and where
+    const int m = tid >> 4, qo = q0 + (tid & 15), row = it.row_lo + m;
+    float *f32_row = nullptr;
+    if (p.f32_out && m < it.n_rows && qo < p.f32_cols) {
+        const int tok = p.f32_by_token ? p.row_tok[row] : row;
+        if (!p.f32_by_token || p.tok_train[tok]) f32_row = p.f32_out + (int64_t)tok * p.f32_ld;
+    }
     floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
     if (q0 < rank) {
         const __amdgpu_buffer_rsrc_t rx = f32_rsrc(p.in, p.in_bytes);
@@ -238,39 +284,37 @@ __global__ void __launch_bounds__(kF32SkinnyWaves * 64) skinny_f32_kernel(Skinny
     // lane holds row l16, columns 4 kg ..
     *reinterpret_cast<floatx4 *>(red + (wave * 16 + l16) * LD + kg * 4) = acc;
     __syncthreads();
-    if (tid >= 256) return;
-    const int m = tid >> 4, qo = q0 + (tid & 15);
-    if (m >= it.n_rows) return;
+    if (m >= it.n_rows) return;  // (the second half of the threads: m is 16 and more)
     float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < KW; ++w) sum += red[(w * 16 + m) * LD + (tid & 15)];
     if (qo >= rank) sum = 0.f;
-    const int row = it.row_lo + m;
-    const int tok = p.row_tok[row];
-    if (p.f32_out && qo < p.f32_cols) {
-        if (p.f32_by_token) {
-            if (p.tok_train[tok]) p.f32_out[(int64_t)tok * p.f32_ld + qo] = sum * p.f32_mult;
-        } else {
-            p.f32_out[(int64_t)row * p.f32_ld + qo] = sum * p.f32_mult;
-        }
-    }
+    if (f32_row) f32_row[qo] = sum * p.f32_mult;
     if (p.bf_out && qo < p.bf_ld) reinterpret_cast<float *>(p.bf_out)[(int64_t)row * p.bf_ld + qo] = sum * p.bf_mult;
+}
+
+template <bool T_KMAJOR, bool BIG>
+__global__ void __launch_bounds__(kF32SkinnyWaves * 64) skinny_f32_kernel(SkinnyArgs p)
+{
+    __shared__ __align__(16) float red[kF32SkinnyRed];
+    skinny_f32_block<T_KMAJOR, BIG>(p, blockIdx.x, blockIdx.y, red);
 }
 
 // out_a(q, n) = sum_t small[t][q] big[tok(t)][n] over the adapter's rows t: one block = one trained adapter x 64 columns
 // x 16 rank indices (blockIdx.z); its eight waves split the rows.  Column i of block c is n0 + 4 i + c, as above.
 constexpr int kF32GradWaves = 8;
-__global__ void __launch_bounds__(kF32GradWaves * 64) grad_f32_kernel(GradArgs p)
+constexpr int kF32GradRed = kF32GradWaves * 16 * (64 + 4);
+__device__ __forceinline__ void grad_f32_block(const GradArgs &p, int bx, int by, int bz, float *red)
 {
     constexpr int KW = kF32GradWaves, LD = 64 + 4;
-    __shared__ __align__(16) float red[KW * 16 * LD];
-    const GradItem it = p.items[blockIdx.y];
+    const GradItem it = p.items[by];
     const int N = p.N, rank = it.rank;
-    const int q0 = blockIdx.z * 16;
+    const int q0 = bz * 16;
     if (q0 >= rank) return;
+    float *out = reinterpret_cast<float *>(p.out_tab[it.adapter]);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, kg = lane >> 4;
-    const int n0 = blockIdx.x * 64, n = n0 + 4 * l16, q = q0 + l16;
+    const int n0 = bx * 64, n = n0 + 4 * l16, q = q0 + l16;
     const __amdgpu_buffer_rsrc_t rb = f32_rsrc(p.big, p.big_bytes);
     const float *__restrict__ Small = p.small_;
     const int n_rows = it.row_hi - it.row_lo;
@@ -306,7 +350,6 @@ __global__ void __launch_bounds__(kF32GradWaves * 64) grad_f32_kernel(GradArgs p
     for (int j = 0; j < 4; ++j)
         *reinterpret_cast<floatx4 *>(red + (wave * 16 + l16) * LD + kg * 16 + j * 4) = floatx4{acc[0][j], acc[1][j], acc[2][j], acc[3][j]};
     __syncthreads();
-    float *out = reinterpret_cast<float *>(p.out_tab[it.adapter]);
     const int qn = rank - q0 < 16 ? rank - q0 : 16;
     for (int idx = tid; idx < 64 * qn; idx += KW * 64) {
         // (consecutive threads write consecutive addresses in either layout)
@@ -318,6 +361,37 @@ __global__ void __launch_bounds__(kF32GradWaves * 64) grad_f32_kernel(GradArgs p
         float *dst = p.out_transposed ? out + (int64_t)(n0 + c) * rank + q0 + qi : out + (int64_t)(q0 + qi) * N + n0 + c;
         *dst = p.accumulate ? (*dst + sum) : sum;
     }
+}
+
+__global__ void __launch_bounds__(kF32GradWaves * 64) grad_f32_kernel(GradArgs p)
+{
+    __shared__ __align__(16) float red[kF32GradRed];
+    grad_f32_block(p, blockIdx.x, blockIdx.y, blockIdx.z, red);
+}
+
+// Two passes of a small backward call that do not depend on each other as one launch (a pass is a chain of a few trips to memory on a part of the
+// CUs): dh beside dB, dX beside dA.
+__device__ __forceinline__ void grad_f32_blocks(const GradArgs &g, int b, float *red)
+{
+    const int cols = (g.N + 63) / 64;
+    grad_f32_block(g, b % cols, b / cols % g.n_items, b / cols / g.n_items, red);
+}
+template <bool T_KMAJOR>
+__global__ void __launch_bounds__(512) dh_dB_f32_kernel(SkinnyArgs s, GradArgs g)
+{
+    static_assert(kF32SkinnyWaves == 8 && kF32GradWaves == 8, "one block size");
+    __shared__ __align__(16) float red[std::max(kF32SkinnyRed, kF32GradRed)];
+    const int b = blockIdx.x, first = s.n_items * ((s.bf_ld + 15) / 16);
+    if (b < first) skinny_f32_block<T_KMAJOR, false>(s, b % s.n_items, b / s.n_items, red);
+    else grad_f32_blocks(g, b - first, red);
+}
+template <bool B_KMAJOR>
+__global__ void __launch_bounds__(512) dx_dA_f32_kernel(GemmArgs m, GradArgs g)
+{
+    __shared__ __align__(16) float red[std::max(kF32GemmRed<1, 8>, kF32GradRed)];
+    const int b = blockIdx.x, cols = (m.N + 63) / 64, first = cols * ((m.n_rows + 15) / 16);
+    if (b < first) gemm_f32_block<B_KMAJOR, 1, 8, false>(m, b % cols, b / cols, red);
+    else grad_f32_blocks(g, b - first, red);
 }
 
 // Plan upload: the host builds the plan in pinned, device-visible memory and this kernel
@@ -415,7 +489,7 @@ hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
     if (a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) {  // (hs_ld: at least the largest rank)
         if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, true>, 32, 256);
         else launch(gemm_f32_kernel<false, 2, 4, true>, 32, 256);
-    } else if ((int64_t)cols * ((rows + 15) / 16) < 512) {
+    } else if (gemm_f32_short_blocks(a)) {
         if (b_kmajor) launch(gemm_f32_kernel<true, 1, 8, false>, 16, 512);
         else launch(gemm_f32_kernel<false, 1, 8, false>, 16, 512);
     } else {
@@ -423,6 +497,11 @@ hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
         else launch(gemm_f32_kernel<false, 2, 4, false>, 32, 256);
     }
     return hipGetLastError();
+}
+
+bool gemm_f32_short_blocks(const GemmArgs &a)
+{
+    return !(a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) && (int64_t)((a.N + 63) / 64) * ((a.n_rows + 15) / 16) < 512;
 }
 
 hipError_t launch_skinny_f32(const SkinnyArgs &a, int n_items, bool t_kmajor, hipStream_t st)
@@ -442,6 +521,25 @@ hipError_t launch_grad_f32(const GradArgs &a, int n_grad, int rpad, hipStream_t 
 {
     if (n_grad <= 0 || a.N <= 0) return hipSuccess;
     COLLM_LAUNCH(grad_f32_kernel, dim3((a.N + 63) / 64, n_grad, (rpad + 15) / 16), dim3(kF32GradWaves * 64), 0, st, a);
+    return hipGetLastError();
+}
+
+// (whoever calls these has looked at gemm_f32_short_blocks and pair_f32)
+bool pair_f32(int rpad, int d_in, int d_out) { return !table_is_big(rpad, std::max(d_in, d_out)); }
+hipError_t launch_dh_dB_f32(const SkinnyArgs &s, const GradArgs &g, int rpad, bool t_kmajor, hipStream_t st)
+{
+    const int blocks = s.n_items * ((s.bf_ld + 15) / 16) + (g.N + 63) / 64 * g.n_items * ((rpad + 15) / 16);
+    if (blocks <= 0) return hipSuccess;
+    if (t_kmajor) COLLM_LAUNCH(dh_dB_f32_kernel<true>, dim3(blocks), dim3(512), 0, st, s, g);
+    else COLLM_LAUNCH(dh_dB_f32_kernel<false>, dim3(blocks), dim3(512), 0, st, s, g);
+    return hipGetLastError();
+}
+hipError_t launch_dx_dA_f32(const GemmArgs &m, const GradArgs &g, int rpad, bool b_kmajor, hipStream_t st)
+{
+    const int blocks = (m.N + 63) / 64 * ((m.n_rows + 15) / 16) + (g.N + 63) / 64 * g.n_items * ((rpad + 15) / 16);
+    if (blocks <= 0) return hipSuccess;
+    if (b_kmajor) COLLM_LAUNCH(dx_dA_f32_kernel<true>, dim3(blocks), dim3(512), 0, st, m, g);
+    else COLLM_LAUNCH(dx_dA_f32_kernel<false>, dim3(blocks), dim3(512), 0, st, m, g);
     return hipGetLastError();
 }
 
