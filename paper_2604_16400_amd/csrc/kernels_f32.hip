@@ -7,8 +7,9 @@
 // does the multiplying because its operands come straight from memory: lane l supplies one K value
 // (group l / 16) of row or column l % 16, so a lane that loads four consecutive K values feeds four of them.
 // Measured on 256 -> 256, 64 tokens, rank 8 (us; before: one thread per output of the narrow passes with a serial sum,
-// 64 x 64 LDS tiles): GEMM 35 -> 6.3 (forward), 34 -> 7.6 (dX), rank-wide passes 22 -> 4.5, gradients 20 -> 4.2; the
-// shorter chains also halve the distance from the 64-bit result (3.3e-7 -> 1.4e-7).
+// 64 x 64 LDS tiles): rank-wide passes 22 -> 4.5, gradients 20 -> 4.2, GEMM 35 -> 6.3 on 64 columns a block, on 16 (launch_gemm_f32) less again:
+// the step 27.9 -> 15.5 with the passes that run side by side (dh_dB_f32_kernel); the shorter chains also halve the distance from the 64-bit
+// result (3.3e-7 -> 1.4e-7).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -38,6 +39,14 @@ __device__ __forceinline__ float f32_load1(__amdgpu_buffer_rsrc_t r, uint32_t of
 {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
+template <int NC>
+__device__ __forceinline__ auto f32_load(__amdgpu_buffer_rsrc_t r, uint32_t off)  // NC consecutive values
+{
+    typedef float cols_t __attribute__((ext_vector_type(NC)));
+    if constexpr (NC == 4) return __builtin_bit_cast(cols_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    else if constexpr (NC == 2) return __builtin_bit_cast(cols_t, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    else return __builtin_bit_cast(cols_t, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
 __device__ __forceinline__ floatx4 mfma_f32(float a, float b, floatx4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -57,31 +66,39 @@ __device__ __forceinline__ float table1(const float *tab, __amdgpu_buffer_rsrc_t
     if constexpr (BIG) return on ? tab[i] : 0.f;
     else return f32_load1(rt, on ? i * 4u : kF32Oob);
 }
+template <bool BIG, int NC, typename I>
+__device__ __forceinline__ auto table_cols(const float *tab, __amdgpu_buffer_rsrc_t rt, bool on, I i)  // NC of them
+{
+    typedef float cols_t __attribute__((ext_vector_type(NC)));
+    if constexpr (BIG) return on ? *reinterpret_cast<const cols_t *>(tab + i) : cols_t{};
+    else return f32_load<NC>(rt, on ? i * 4u : kF32Oob);
+}
 static bool table_is_big(int rank, int d) { return (int64_t)rank * d * 4 > 0x7fffffff; }
 
 // y[tok(m)][n] = sum_k a[tok(m)][k] b(k, n) + sum_q hs[m][q] table_a(q, n)
 //
-// One block = 16 RT rows x 64 columns; its KW waves split K (and the extension steps) between them.  Column i of
-// 16-column block c is n0 + 4 i + c: a lane's four columns are then consecutive both where it loads the second
+// One block = 16 RT rows x 16 NC columns; its KW waves split K (and the extension steps) between them.  Column i of
+// 16-column block c is n0 + NC i + c: a lane's NC columns are then consecutive both where it loads the second
 // operand ([K][N]) and where it stores.
-template <int RT, int KW> constexpr int kF32GemmRed = KW * 16 * RT * (64 + 4);  // floats of LDS
-template <bool B_KMAJOR, int RT, int KW, bool BIG>
+template <int RT, int KW, int NC> constexpr int kF32GemmRed = KW * 16 * RT * (16 * NC + 4);  // floats of LDS
+template <bool B_KMAJOR, int RT, int KW, bool BIG, int NC>
 __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by, float *red)
 {
     using idx_t = std::conditional_t<BIG, uint64_t, uint32_t>;
-    constexpr int ROWS = 16 * RT, LD = 64 + 4;
+    constexpr int ROWS = 16 * RT, COLS = 16 * NC, LD = COLS + 4, QUADS = ROWS * COLS / 4;
+    typedef float cols_t __attribute__((ext_vector_type(NC)));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
-    const int n0 = bx * 64, m0 = by * ROWS;
+    const int n0 = bx * COLS, m0 = by * ROWS;
     const int tile = m0 / kF32Tile, in_tile = m0 - tile * kF32Tile;
     const int e0 = p.ext_off[tile], e1 = p.ext_off[tile + 1];
     // the tokens this thread stores to in the end
-    constexpr int OUTS = ROWS * 16 / (KW * 64) > 0 ? ROWS * 16 / (KW * 64) : 1;
+    constexpr int OUTS = QUADS / (KW * 64) > 0 ? QUADS / (KW * 64) : 1;
     int tok_out[OUTS];
 #pragma unroll
-    for (int i = 0; i < OUTS; ++i) tok_out[i] = ((tid + i * KW * 64) >> 4) < ROWS ? p.row_tok[m0 + ((tid + i * KW * 64) >> 4)] : -1;
+    for (int i = 0; i < OUTS; ++i) tok_out[i] = tid + i * KW * 64 < QUADS ? p.row_tok[m0 + (tid + i * KW * 64) / (COLS / 4)] : -1;
     const int K = p.K, N = p.N;
-    const int n = n0 + 4 * l16;  // first of this lane's four columns (N is a multiple of 4)
+    const int n = n0 + NC * l16;  // first of this lane's columns (N is a multiple of 4)
     const __amdgpu_buffer_rsrc_t ra = f32_rsrc(p.a, 0x7fffffffu), rb = f32_rsrc(p.b, 0x7fffffffu);
 
     uint32_t aoff[RT];
@@ -90,27 +107,28 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
         const int tok = p.row_tok[m0 + t * 16 + l16];
         aoff[t] = tok >= 0 ? (uint32_t)tok * (uint32_t)p.lda * 4u : kF32Oob;
     }
-    floatx4 acc[RT][4];
+    floatx4 acc[RT][NC];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[t][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < NC; ++c) acc[t][c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const int per = (((K + KW - 1) / KW) + 15) & ~15;
     const int k_lo = wave * per, k_hi = (k_lo + per) < K ? (k_lo + per) : K;
     // 16 K values per step (this lane: k + 4 kg .. + 3), U steps of loads in flight
     constexpr int U = RT == 1 ? 4 : 2;
-    floatx4 xa[U][RT], wb[U][4];
+    floatx4 xa[U][RT];
+    std::conditional_t<B_KMAJOR, floatx4, cols_t> wb[U][B_KMAJOR ? NC : 4];
     auto load = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = k0 + u * 16 + kg * 4;
+            // [K][N]: K value k + j, columns n ..; [N][K]: column n + j, K values k .. k + 3
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                // [K][N]: K value k + j, columns n .. n + 3; [N][K]: column n + j, K values k .. k + 3
-                const uint32_t off = B_KMAJOR ? ((uint32_t)(n + j) * (uint32_t)p.ldb + (uint32_t)k) * 4u
-                                              : ((uint32_t)(k + j) * (uint32_t)p.ldb + (uint32_t)n) * 4u;
-                wb[u][j] = f32_load4(rb, k < k_hi && n < N ? off : kF32Oob);
+            for (int j = 0; j < (B_KMAJOR ? NC : 4); ++j) {
+                const bool on = k < k_hi && n + (B_KMAJOR ? j : 0) < N;
+                if constexpr (B_KMAJOR) wb[u][j] = f32_load4(rb, on ? ((uint32_t)(n + j) * (uint32_t)p.ldb + (uint32_t)k) * 4u : kF32Oob);
+                else wb[u][j] = f32_load<NC>(rb, on ? ((uint32_t)(k + j) * (uint32_t)p.ldb + (uint32_t)n) * 4u : kF32Oob);
             }
         }
 #pragma unroll
@@ -127,7 +145,8 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
     const float *__restrict__ Hs = reinterpret_cast<const float *>(p.hs);
     struct Step {
         int row_lo, row_hi;
-        floatx4 tb[4], hv[RT];
+        std::conditional_t<B_KMAJOR, floatx4, cols_t> tb[B_KMAJOR ? NC : 4];
+        floatx4 hv[RT];
     };
     auto load_step = [&](int e, Step &s) {
         const ExtStep st = p.ext[e];
@@ -143,14 +162,14 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
         const __amdgpu_buffer_rsrc_t rt = f32_rsrc(tab, tab_bytes);
         const int q = koff + kg * 4;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < (B_KMAJOR ? NC : 4); ++j) {
             if constexpr (B_KMAJOR) {
                 // table rows are output columns, `rank` long: any rank, so element by element
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    s.tb[j][i] = table1<BIG>(tab, rt, n < N && q + i < rk, (idx_t)(n + j) * (idx_t)rk + (idx_t)(q + i));
+                    s.tb[j][i] = table1<BIG>(tab, rt, n + j < N && q + i < rk, (idx_t)(n + j) * (idx_t)rk + (idx_t)(q + i));
             } else {
-                s.tb[j] = table4<BIG>(tab, rt, n < N && q + j < rk, (idx_t)(q + j) * (idx_t)p.ext_ld + (idx_t)n);
+                s.tb[j] = table_cols<BIG, NC>(tab, rt, n < N && q + j < rk, (idx_t)(q + j) * (idx_t)p.ext_ld + (idx_t)n);
             }
         }
 #pragma unroll
@@ -167,14 +186,18 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
 
     for (int k0 = k_lo; k0 < k_hi;) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            if (k0 + 16 * u >= k_hi) break;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
+                for (int c = 0; c < NC; ++c)
 #pragma unroll
-                    for (int t = 0; t < RT; ++t)
-                        acc[t][c] = mfma_f32(B_KMAJOR ? wb[u][c][e] : wb[u][e][c], xa[u][t][e], acc[t][c]);
+                    for (int t = 0; t < RT; ++t) {
+                        if constexpr (B_KMAJOR) acc[t][c] = mfma_f32(wb[u][c][e], xa[u][t][e], acc[t][c]);
+                        else acc[t][c] = mfma_f32(wb[u][e][c], xa[u][t][e], acc[t][c]);
+                    }
+        }
         k0 += 16 * U;
         if (k0 < k_hi) load(k0);
     }
@@ -185,35 +208,41 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
         if (s.row_hi > 0) {
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
-                floatx4 add[4];
+                floatx4 add[NC];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) add[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+                for (int c = 0; c < NC; ++c) add[c] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) add[c] = mfma_f32(B_KMAJOR ? s.tb[c][i] : s.tb[i][c], s.hv[t][i], add[c]);
+                    for (int c = 0; c < NC; ++c) {
+                        if constexpr (B_KMAJOR) add[c] = mfma_f32(s.tb[c][i], s.hv[t][i], add[c]);
+                        else add[c] = mfma_f32(s.tb[i][c], s.hv[t][i], add[c]);
+                    }
                 const int r = t * 16 + l16;
                 if (r >= s.row_lo && r < s.row_hi)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) acc[t][c] += add[c];
+                    for (int c = 0; c < NC; ++c) acc[t][c] += add[c];
             }
         }
         e += KW;
         if (e < e1) load_step(e, s);
     }
 
-    // lane holds row l16 and, in register j of block c, column 16 kg + 4 j + c
+    // lane holds row l16 and, in register j of block c, column NC (4 kg + j) + c
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            *reinterpret_cast<floatx4 *>(red + (wave * ROWS + t * 16 + l16) * LD + kg * 16 + j * 4) =
-                floatx4{acc[t][0][j], acc[t][1][j], acc[t][2][j], acc[t][3][j]};
+        for (int i = 0; i < NC; ++i) {
+            floatx4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[t][(4 * i + e) % NC][(4 * i + e) / NC];
+            *reinterpret_cast<floatx4 *>(red + (wave * ROWS + t * 16 + l16) * LD + kg * 4 * NC + i * 4) = v;
+        }
     __syncthreads();
     float *__restrict__ Out = reinterpret_cast<float *>(p.out);
 #pragma unroll
     for (int i = 0; i < OUTS; ++i) {
-        const int idx = tid + i * KW * 64, r = idx >> 4, c = (idx & 15) * 4, tok = tok_out[i];
+        const int idx = tid + i * KW * 64, r = idx / (COLS / 4), c = idx % (COLS / 4) * 4, tok = tok_out[i];
         if (tok < 0 || n0 + c >= N) continue;
         floatx4 sum = *reinterpret_cast<const floatx4 *>(red + r * LD + c);
 #pragma unroll
@@ -222,11 +251,11 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
     }
 }
 
-template <bool B_KMAJOR, int RT, int KW, bool BIG>
+template <bool B_KMAJOR, int RT, int KW, bool BIG, int NC>
 __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
 {
-    __shared__ __align__(16) float red[kF32GemmRed<RT, KW>];
-    gemm_f32_block<B_KMAJOR, RT, KW, BIG>(p, blockIdx.x, blockIdx.y, red);
+    __shared__ __align__(16) float red[kF32GemmRed<RT, KW, NC>];
+    gemm_f32_block<B_KMAJOR, RT, KW, BIG, NC>(p, blockIdx.x, blockIdx.y, red);
 }
 
 // out[m][q] = sum_k in[tok(m)][k] table_a(k, q): one block = one item (up to 16 rows of one adapter) x 16 columns of
@@ -385,12 +414,12 @@ __global__ void __launch_bounds__(512) dh_dB_f32_kernel(SkinnyArgs s, GradArgs g
     if (b < first) skinny_f32_block<T_KMAJOR, false>(s, b % s.n_items, b / s.n_items, red);
     else grad_f32_blocks(g, b - first, red);
 }
-template <bool B_KMAJOR>
+template <bool B_KMAJOR, int NC>
 __global__ void __launch_bounds__(512) dx_dA_f32_kernel(GemmArgs m, GradArgs g)
 {
-    __shared__ __align__(16) float red[std::max(kF32GemmRed<1, 8>, kF32GradRed)];
-    const int b = blockIdx.x, cols = (m.N + 63) / 64, first = cols * ((m.n_rows + 15) / 16);
-    if (b < first) gemm_f32_block<B_KMAJOR, 1, 8, false>(m, b % cols, b / cols, red);
+    __shared__ __align__(16) float red[std::max(kF32GemmRed<1, 8, NC>, kF32GradRed)];
+    const int b = blockIdx.x, cols = (m.N + 16 * NC - 1) / (16 * NC), first = cols * ((m.n_rows + 15) / 16);
+    if (b < first) gemm_f32_block<B_KMAJOR, 1, 8, false, NC>(m, b % cols, b / cols, red);
     else grad_f32_blocks(g, b - first, red);
 }
 
@@ -464,6 +493,23 @@ hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t st)
     return hipGetLastError();
 }
 
+// Blocks of 16 rows and eight waves, of as few columns as pays: the smaller a block, the fewer products in its waves' chains and the more CUs at work, but
+// the more often the rows and the weight are read.  By blocks of 16 rows x 64 columns; whole step (forward and backward call) with 16 / 32 / 64 columns / 32 rows and four
+// waves a block, us:
+//   16 blocks, K 256 15.5 / 17.0 / 19.4 / 27;  64, K 1024 21.0 / 24.7 / 31.4 / 41.9;  128, K 1024 25.6 / 24.9 / 30.9 / 41.4;  200, K 512 21.1 / 21.6 / 23.4 / 31.2;  256, K 1024
+//   31.4 / 29.1 / 31.4 / 42.0;  512, K 512 29.9 / 30.4 / 32.5 / 37.3, K 1024 40.3 / 38.6 / 38.1 / 42.4;  1000, K 512 42.2 / 38.6 / 37.9 / 40.3, K 1024 60.2 / 57.2 / 53.0 / 54.5
+static int64_t blocks_16x64(const GemmArgs &a) { return (int64_t)((a.N + 63) / 64) * ((a.n_rows + 15) / 16); }
+bool gemm_f32_short_blocks(const GemmArgs &a)
+{
+    return !(a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) && blocks_16x64(a) < 1024;
+}
+static int short_block_cols(const GemmArgs &a)  // in sixteens
+{
+    const int64_t blocks = blocks_16x64(a);
+    if (blocks >= 768) return 4;
+    return a.K <= 512 || blocks * a.K < 131072 ? 1 : 2;
+}
+
 hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
 {
     // (row blocks are the grid's second dimension, which holds 65536: more rows than that go in several launches)
@@ -479,29 +525,26 @@ hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
         const hipError_t e = launch_gemm_f32(first, b_kmajor, st);
         return e == hipSuccess ? launch_gemm_f32(rest, b_kmajor, st) : e;
     }
-    const int cols = (a.N + 63) / 64, rows = a.n_rows;  // (the row order is padded to a multiple of 256 rows)
-    if (cols <= 0 || rows <= 0) return hipSuccess;
-    // 16 rows and eight waves per block while those blocks leave CUs without a second one; then 32 rows and four waves
-    // (half the reads of the second operand)
-    auto launch = [&](auto kern, int block_rows, int threads) {
-        COLLM_LAUNCH(kern, dim3(cols, (rows + block_rows - 1) / block_rows), dim3(threads), 0, st, a);
+    const int rows = a.n_rows;  // (the row order is padded to a multiple of 256 rows)
+    if (a.N <= 0 || rows <= 0) return hipSuccess;
+    // (then 32 rows and four waves: half the reads of the second operand)
+    auto launch = [&](auto kern, int block_rows, int block_cols, int threads) {
+        COLLM_LAUNCH(kern, dim3((a.N + block_cols - 1) / block_cols, (rows + block_rows - 1) / block_rows), dim3(threads), 0, st, a);
     };
     if (a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) {  // (hs_ld: at least the largest rank)
-        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, true>, 32, 256);
-        else launch(gemm_f32_kernel<false, 2, 4, true>, 32, 256);
+        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, true, 4>, 32, 64, 256);
+        else launch(gemm_f32_kernel<false, 2, 4, true, 4>, 32, 64, 256);
     } else if (gemm_f32_short_blocks(a)) {
-        if (b_kmajor) launch(gemm_f32_kernel<true, 1, 8, false>, 16, 512);
-        else launch(gemm_f32_kernel<false, 1, 8, false>, 16, 512);
+        switch (short_block_cols(a)) {
+        case 1: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 1>, 16, 16, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 1>, 16, 16, 512); break;
+        case 2: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 2>, 16, 32, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 2>, 16, 32, 512); break;
+        default: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 4>, 16, 64, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 4>, 16, 64, 512); break;
+        }
     } else {
-        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, false>, 32, 256);
-        else launch(gemm_f32_kernel<false, 2, 4, false>, 32, 256);
+        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, false, 4>, 32, 64, 256);
+        else launch(gemm_f32_kernel<false, 2, 4, false, 4>, 32, 64, 256);
     }
     return hipGetLastError();
-}
-
-bool gemm_f32_short_blocks(const GemmArgs &a)
-{
-    return !(a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) && (int64_t)((a.N + 63) / 64) * ((a.n_rows + 15) / 16) < 512;
 }
 
 hipError_t launch_skinny_f32(const SkinnyArgs &a, int n_items, bool t_kmajor, hipStream_t st)
@@ -536,10 +579,15 @@ hipError_t launch_dh_dB_f32(const SkinnyArgs &s, const GradArgs &g, int rpad, bo
 }
 hipError_t launch_dx_dA_f32(const GemmArgs &m, const GradArgs &g, int rpad, bool b_kmajor, hipStream_t st)
 {
-    const int blocks = (m.N + 63) / 64 * ((m.n_rows + 15) / 16) + (g.N + 63) / 64 * g.n_items * ((rpad + 15) / 16);
+    const int nc = short_block_cols(m);
+    const int blocks = (m.N + 16 * nc - 1) / (16 * nc) * ((m.n_rows + 15) / 16) + (g.N + 63) / 64 * g.n_items * ((rpad + 15) / 16);
     if (blocks <= 0) return hipSuccess;
-    if (b_kmajor) COLLM_LAUNCH(dx_dA_f32_kernel<true>, dim3(blocks), dim3(512), 0, st, m, g);
-    else COLLM_LAUNCH(dx_dA_f32_kernel<false>, dim3(blocks), dim3(512), 0, st, m, g);
+    auto launch = [&](auto kern) { COLLM_LAUNCH(kern, dim3(blocks), dim3(512), 0, st, m, g); };
+    switch (nc) {
+    case 1: launch(b_kmajor ? dx_dA_f32_kernel<true, 1> : dx_dA_f32_kernel<false, 1>); break;
+    case 2: launch(b_kmajor ? dx_dA_f32_kernel<true, 2> : dx_dA_f32_kernel<false, 2>); break;
+    default: launch(b_kmajor ? dx_dA_f32_kernel<true, 4> : dx_dA_f32_kernel<false, 4>); break;
+    }
     return hipGetLastError();
 }
 
