@@ -119,6 +119,31 @@ __device__ __forceinline__ const uint8_t *pass_table(const Args &p, int adapter)
     return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);  // (one adapter per block)
 }
 
+__device__ __forceinline__ uint32_t word(const uint4 &v, int i) { return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)); }
+
+// Operands of K-contiguous rows.  An MFMA wants 16 rows x 32 values (lane l: row l % 16, values 8 (l / 16) ..), of which a load would
+// touch half of 16 cache lines; two loads of 8 rows x 64 values touch 8 whole lines each: load 0 takes rows 0 .. 7 (lanes l % 16 < 8:
+// values 8 (l / 16) .., the others 32 more), load 1 rows 8 .. 15 the other way round.  Then the operand of the first 32 values is in place, half
+// of the lanes in each load, and that of the second 32 is the other halves, 8 lanes further in each row of 16.
+// (Reading 90 MB of [11008][4096], 344 blocks: 26 us by half lines, 19.7 by whole ones.)
+struct RowPair {
+    uint4 v[2];
+};
+__device__ __forceinline__ uint32_t pair_row(int load, int l16) { return (uint32_t)(8 * load + (l16 & 7)); }
+__device__ __forceinline__ uint32_t pair_k(int load, int l16, int g) { return (uint32_t)(8 * g + (((l16 >> 3) ^ load) << 5)); }
+__device__ __forceinline__ void pair_operands(const RowPair &p, int l16, bf16x8 &first, bf16x8 &second)
+{
+    u32x4 a, b;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t x = word(p.v[0], i), y = word(p.v[1], i);
+        a[i] = l16 < 8 ? x : y;
+        b[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)(l16 < 8 ? y : x), 0x128, 0xf, 0xf, true);  // row_ror:8
+    }
+    first = __builtin_bit_cast(bf16x8, a);
+    second = __builtin_bit_cast(bf16x8, b);
+}
+
 // =========================================================================================
 // skinny: out[m][q] = sum_k in[tok(m)][k] * table_a(k, q)     (rank-wide output, HBM-bound)
 //
@@ -134,60 +159,69 @@ __device__ __forceinline__ const uint8_t *pass_table(const Args &p, int adapter)
 // a second, small kernel adds the slices in slice order (fixed order, no float atomics, and no
 // fences inside a kernel: on this GPU a device-wide fence writes back and invalidates the L2).
 // =========================================================================================
-// Results of four rank indices q .. q + 3 of row m of an item: the fp32 copy (token-indexed h_save
-// or row-indexed workspace) and the scaled copy in the element type.
-__device__ __forceinline__ void skinny_store(const SkinnyArgs &p, const SkinnyItem it, int m, int q, floatx4 sum)
+// Where a row's results go: its row of the fp32 copy (token-indexed h_save, training rows only, or row-indexed workspace).  Loads that depend on
+// each other: asked for before the sums that they wait for (a row's token, then its flag).
+__device__ __forceinline__ float *skinny_f32_row(const SkinnyArgs &p, int row)
 {
-    const int row = it.row_lo + m;
+    if (!p.f32_out) return nullptr;
+    if (!p.f32_by_token) return p.f32_out + (int64_t)row * p.f32_ld;
     const int tok = p.row_tok[row];
-    float *f32_row = nullptr;
-    if (p.f32_out) {
-        if (p.f32_by_token) {
-            if (p.tok_train[tok]) f32_row = p.f32_out + (int64_t)tok * p.f32_ld;
-        } else {
-            f32_row = p.f32_out + (int64_t)row * p.f32_ld;
-        }
-    }
-    uint16_t *bf_row = p.bf_out ? reinterpret_cast<uint16_t *>(p.bf_out) + (int64_t)row * p.bf_ld : nullptr;
-    if (p.n_sib > 1) {
+    return p.tok_train[tok] ? p.f32_out + (int64_t)tok * p.f32_ld : nullptr;
+}
+// Results of four rank indices q .. q + 3 of a row whose adapter has rank `it_rank`: the fp32 copy and the scaled copy in the element type.
+// (The arguments it needs are read once, at its start: read where they are used, they went through scratch memory, a trip for each at the end of a pass.)
+__device__ __forceinline__ void skinny_store(const SkinnyArgs &p, float *f32_row, int row, int it_rank, int q, floatx4 sum)
+{
+    const float f32_mult = p.f32_mult, bf_mult = p.bf_mult;
+    const int n_sib = p.n_sib, sib = p.sib, f32_cols = p.f32_cols, bf_ld = p.bf_ld, bf_up = p.bf_up;
+    uint16_t *bf_row = p.bf_out ? reinterpret_cast<uint16_t *>(p.bf_out) + (int64_t)row * bf_ld : nullptr;
+    asm volatile("" ::: "memory");
+    if (n_sib > 1) {
         // one sibling's columns of the row (ranks are multiples of 8 here); the last sibling clears the rest
-        const int rank = it.rank / p.n_sib, co = p.sib * rank;
+        const int rank = it_rank / n_sib, co = sib * rank;
         if (q < rank) {
             if (f32_row)
-                *reinterpret_cast<floatx4 *>(f32_row + co + q) = sum * p.f32_mult;
+                *reinterpret_cast<floatx4 *>(f32_row + co + q) = sum * f32_mult;
             if (bf_row) {
                 uint2 o;
-                o.x = pack_bf16(sum[0] * p.bf_mult, sum[1] * p.bf_mult);
-                o.y = pack_bf16(sum[2] * p.bf_mult, sum[3] * p.bf_mult);
+                o.x = pack_bf16(sum[0] * bf_mult, sum[1] * bf_mult);
+                o.y = pack_bf16(sum[2] * bf_mult, sum[3] * bf_mult);
                 *reinterpret_cast<uint2 *>(bf_row + co + q) = o;
             }
         }
-        if (q == 0 && p.sib == p.n_sib - 1) {
+        if (q == 0 && sib == n_sib - 1) {
             if (f32_row)
-                for (int z = it.rank; z < p.f32_cols; ++z) f32_row[z] = 0.f;
+                for (int z = it_rank; z < f32_cols; ++z) f32_row[z] = 0.f;
             if (bf_row)
-                for (int z = it.rank; z < p.bf_ld; ++z) bf_row[z] = 0;
+                for (int z = it_rank; z < bf_ld; ++z) bf_row[z] = 0;
         }
         return;
     }
-    const int rank = it.rank, rp = (rank + 15) & ~15;
-    float v[4];
+    const int rank = it_rank, rp = (rank + 15) & ~15;
+    floatx4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = (q + e < rank) ? sum[e] : 0.f;
     if (f32_row) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (q + e < p.f32_cols) f32_row[q + e] = v[e] * p.f32_mult;
+        const floatx4 f = v * f32_mult;
         // zero fill beyond the padded rank (h_save rows are max_rank wide)
-        if (q + 4 == rp)
-            for (int z = rp; z < p.f32_cols; ++z) f32_row[z] = 0.f;
+        if (((f32_cols | (int)p.f32_ld) & 3) == 0) {
+            if (q < f32_cols) *reinterpret_cast<floatx4 *>(f32_row + q) = f;
+            if (q + 4 == rp)
+                for (int z = rp; z < f32_cols; z += 4) *reinterpret_cast<floatx4 *>(f32_row + z) = floatx4{0.f, 0.f, 0.f, 0.f};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (q + e < f32_cols) f32_row[q + e] = f[e];
+            if (q + 4 == rp)
+                for (int z = rp; z < f32_cols; ++z) f32_row[z] = 0.f;
+        }
     }
     if (bf_row) {
         uint2 o;
-        o.x = pack_bf16(v[0] * p.bf_mult, v[1] * p.bf_mult);
-        o.y = pack_bf16(v[2] * p.bf_mult, v[3] * p.bf_mult);
+        o.x = pack_bf16(v[0] * bf_mult, v[1] * bf_mult);
+        o.y = pack_bf16(v[2] * bf_mult, v[3] * bf_mult);
         // (bf_up: the second sibling's half of the ranks, a multiple of 16, goes to the second half of the row)
-        *reinterpret_cast<uint2 *>(bf_row + (p.bf_up > 0 && 2 * q >= rank ? q - (rank >> 1) + p.bf_up : q)) = o;
+        *reinterpret_cast<uint2 *>(bf_row + (bf_up > 0 && 2 * q >= rank ? q - (rank >> 1) + bf_up : q)) = o;
     }
 }
 
@@ -226,14 +260,14 @@ __device__ __forceinline__ void skinny_item(const Args &p, int item, int split, 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // (the item is the same for the whole block: kept in scalar registers)
     const SkinnyItem *ip = p.items + item;
-    const SkinnyItem it = {__builtin_amdgcn_readfirstlane(ip->adapter), __builtin_amdgcn_readfirstlane(ip->row_lo),
-                           __builtin_amdgcn_readfirstlane(ip->n_rows), __builtin_amdgcn_readfirstlane(ip->rank)};
-    const int K = p.K, rank = p.n_sib > 1 ? it.rank / p.n_sib : it.rank;
+    const int adapter = __builtin_amdgcn_readfirstlane(ip->adapter), row_lo = __builtin_amdgcn_readfirstlane(ip->row_lo);
+    const int item_rows = __builtin_amdgcn_readfirstlane(ip->n_rows), it_rank = __builtin_amdgcn_readfirstlane(ip->rank);
+    const int K = p.K, rank = p.n_sib > 1 ? it_rank / p.n_sib : it_rank;
     if (COLS && q_base >= rank) return;
     const int width = COLS && rank - q_base > RP ? RP : rank - (COLS ? q_base : 0);  // columns of this block
     const int rp = (width + 15) & ~15;
     const int l16 = lane & 15, kg = lane >> 4;
-    const int n_rt = (it.n_rows + 15) >> 4;  // row tiles of this item
+    const int n_rt = (item_rows + 15) >> 4;  // row tiles of this item
     const uint32_t tld = T_KMAJOR && p.tab_ld ? (uint32_t)p.tab_ld : (uint32_t)K, toff = T_KMAJOR ? (uint32_t)p.tab_off : 0u;
 
     // K range of this wave: the slices of the blocks, cut again into the ranges of their waves
@@ -242,17 +276,24 @@ __device__ __forceinline__ void skinny_item(const Args &p, int item, int split, 
     const int k_hi = (k_lo + per) < K ? (k_lo + per) : K;
 
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.in, p.in_bytes);
-    const __amdgpu_buffer_rsrc_t rt = make_rsrc(pass_table(p, it.adapter),
+    const __amdgpu_buffer_rsrc_t rt = make_rsrc(pass_table(p, adapter),
                                                 T_KMAJOR ? (uint32_t)rank * tld * 2u : (uint32_t)rank * (uint32_t)K * 2u);
-    uint32_t xoff[RT];
+    // chunks of 64 values by whole cache lines (RowPair)
+    constexpr bool PAIR = STEPS == 2;
+    uint32_t xoff[RT][STEPS];
 #pragma unroll
-    for (int t = 0; t < RT; ++t) {
-        xoff[t] = kOob;
-        if (t * 16 + l16 < it.n_rows) {
-            const int tok = p.row_tok[it.row_lo + t * 16 + l16];
-            if (tok >= 0) xoff[t] = (uint32_t)tok * (uint32_t)p.ld_in * 2u + kg * 16u;
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            const int r = t * 16 + (PAIR ? (int)pair_row(s, l16) : l16);
+            xoff[t][s] = kOob;
+            if (r < item_rows) {
+                const int tok = p.row_tok[row_lo + r];
+                if (tok >= 0) xoff[t][s] = (uint32_t)tok * (uint32_t)p.ld_in * 2u + (PAIR ? pair_k(s, l16, kg) : kg * 8u) * 2u;
+            }
         }
-    }
+    // first value of the chunk that this lane takes in load s
+    auto lane_k = [&](int s) { return PAIR ? (int)pair_k(s, l16, kg) : s * 32 + kg * 8; };
 
     // D chunks are in flight per wave (a ring of register sets): the pass is bound by memory latency.
     // Four where the registers of a chunk are few enough to keep four waves per SIMD, else two.
@@ -262,10 +303,7 @@ __device__ __forceinline__ void skinny_item(const Args &p, int item, int split, 
 #pragma unroll
         for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int s = 0; s < STEPS; ++s) {
-                const int k = k0 + s * 32;
-                xreg[buf][t][s] = buf16(rx, (k + kg * 8 < k_hi) ? xoff[t] + (uint32_t)k * 2u : kOob);
-            }
+            for (int s = 0; s < STEPS; ++s) xreg[buf][t][s] = buf16(rx, k0 + lane_k(s) < k_hi ? xoff[t][s] + (uint32_t)k0 * 2u : kOob);
     };
 
     // K-major table: operand registers straight from memory
@@ -274,10 +312,10 @@ __device__ __forceinline__ void skinny_item(const Args &p, int item, int split, 
         if constexpr (T_KMAJOR) {
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
-                const int k = k0 + s * 32 + kg * 8;
+                const int k = k0 + lane_k(s);
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    const int q = (COLS ? q_base : 0) + nb * 16 + l16;
+                    const int q = (COLS ? q_base : 0) + nb * 16 + (PAIR ? (int)pair_row(s, l16) : l16);
                     treg[buf][s * NB + nb] =
                         buf16(rt, (q < rank && k < k_hi) ? ((uint32_t)q * tld + toff + (uint32_t)k) * 2u : kOob);
                 }
@@ -356,6 +394,12 @@ __device__ __forceinline__ void skinny_item(const Args &p, int item, int split, 
         }
     };
 
+    // (a thread's sums are all of one row)
+    static_assert(KW * 64 % ROWS == 0, "a block's threads go over whole columns");
+    float *f32_row = nullptr;
+    if constexpr (!SUMS) {
+        if (n_split == 1 && (int)(tid % ROWS) < item_rows && tid < ROWS * (RP / 4)) f32_row = skinny_f32_row(p, row_lo + tid % ROWS);
+    }
     floatx4 acc[RT][NB];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
@@ -375,25 +419,28 @@ __device__ __forceinline__ void skinny_item(const Args &p, int item, int split, 
             for (int d = 0; d < D; ++d) {
                 const int k0 = kb + d * CHK;  // chunks beyond the wave's range were loaded as zeros
                 store_t_nmajor(d);
+                bf16x8 xf[RT][STEPS];
 #pragma unroll
-                for (int s = 0; s < STEPS; ++s) {
+                for (int t = 0; t < RT; ++t) {
+                    if constexpr (PAIR) pair_operands(RowPair{{xreg[d][t][0], xreg[d][t][1]}}, l16, xf[t][0], xf[t][1]);
+                    else xf[t][0] = __builtin_bit_cast(bf16x8, xreg[d][t][0]);
+                }
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        if (nb * 16 < rp) {
-                            bf16x8 tf;
-                            if constexpr (T_KMAJOR) {
-                                tf = __builtin_bit_cast(bf16x8, treg[d][s * NB + nb]);
-                            } else {
-                                const uint8_t *src = stage + (s * 32 + kg * 8 + (l16 >> 2)) * C::PITCH +
-                                                     (nb * 16 + (l16 & 3) * 4) * 2;
+                for (int nb = 0; nb < NB; ++nb) {
+                    if (nb * 16 < rp) {
+                        bf16x8 tf[STEPS];
+                        if constexpr (T_KMAJOR && PAIR) pair_operands(RowPair{{treg[d][nb], treg[d][NB + nb]}}, l16, tf[0], tf[1]);
+                        else if constexpr (T_KMAJOR) tf[0] = __builtin_bit_cast(bf16x8, treg[d][nb]);
+#pragma unroll
+                        for (int s = 0; s < STEPS; ++s) {
+                            if constexpr (!T_KMAJOR) {
+                                const uint8_t *src = stage + (s * 32 + kg * 8 + (l16 >> 2)) * C::PITCH + (nb * 16 + (l16 & 3) * 4) * 2;
                                 const bf16x4 lo = lds_tr(src), hi = lds_tr(src + 4 * C::PITCH);
-                                tf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                                tf[s] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                             }
 #pragma unroll
                             for (int t = 0; t < RT; ++t)
-                                if (t < n_rt)
-                                    acc[t][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                        tf, __builtin_bit_cast(bf16x8, xreg[d][t][s]), acc[t][nb], 0, 0, 0);
+                                if (t < n_rt) acc[t][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf[s], xf[t][s], acc[t][nb], 0, 0, 0);
                         }
                     }
                 }
@@ -425,14 +472,14 @@ __device__ __forceinline__ void skinny_item(const Args &p, int item, int split, 
     const int n_quads = ROWS * (RP / 4);
     for (int idx = tid; idx < n_quads; idx += KW * 64) {
         const int m = idx % ROWS, q = (idx / ROWS) * 4;
-        if (m >= it.n_rows || q >= rp) continue;
+        if (m >= item_rows || q >= rp) continue;
         floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < KW; ++w) sum += *reinterpret_cast<const floatx4 *>(red + (w * ROWS + m) * C::RED_LD + q);
         if (SUMS || n_split > 1)
-            *reinterpret_cast<floatx4 *>(p.part + ((int64_t)split * p.part_rows + it.row_lo + m) * p.part_ld + (COLS ? q_base : 0) + q) = sum;
+            *reinterpret_cast<floatx4 *>(p.part + ((int64_t)split * p.part_rows + row_lo + m) * p.part_ld + (COLS ? q_base : 0) + q) = sum;
         else
-            skinny_store(p, it, m, q, sum);
+            skinny_store(p, f32_row, row_lo + m, it_rank, q, sum);
     }
 }
 

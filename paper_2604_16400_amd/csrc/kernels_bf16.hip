@@ -1298,8 +1298,9 @@ __global__ void __launch_bounds__(256) skinny_finish_kernel(SkinnyArgs p, const 
     const int m_lo = tile * 16, m_hi = it.n_rows < m_lo + 16 ? it.n_rows : m_lo + 16;
     for (int idx = threadIdx.x; idx < (m_hi - m_lo) * nq; idx += 256) {
         const int m = m_lo + idx / nq, q = (idx % nq) * 4;
+        float *f32_row = skinny_f32_row(p, it.row_lo + m);
         const floatx4 sum = sum_slices(p.part + (int64_t)(it.row_lo + m) * p.part_ld + q, (int64_t)p.part_rows * p.part_ld, n_split);
-        skinny_store(p, it, m, q, sum);
+        skinny_store(p, f32_row, it.row_lo + m, it.rank, q, sum);
     }
 }
 

@@ -20,31 +20,6 @@ __device__ __forceinline__ uint4 buf16s(__amdgpu_buffer_rsrc_t r, uint32_t off, 
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-__device__ __forceinline__ uint32_t word(const uint4 &v, int i) { return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)); }
-
-// Operands of K-contiguous rows.  An MFMA wants 16 rows x 32 values (lane l: row l % 16, values 8 (l / 16) ..), of which a load would
-// touch half of 16 cache lines; two loads of 8 rows x 64 values touch 8 whole lines each: load 0 takes rows 0 .. 7 (lanes l % 16 < 8:
-// values 8 (l / 16) .., the others 32 more), load 1 rows 8 .. 15 the other way round.  Then the operand of the first 32 values is in place, half
-// of the lanes in each load, and that of the second 32 is the other halves, 8 lanes further in each row of 16.
-// (Reading 90 MB of [11008][4096], 344 blocks: 26 us by half lines, 19.7 by whole ones.)
-struct RowPair {
-    uint4 v[2];
-};
-__device__ __forceinline__ uint32_t pair_row(int load, int l16) { return (uint32_t)(8 * load + (l16 & 7)); }
-__device__ __forceinline__ uint32_t pair_k(int load, int l16, int g) { return (uint32_t)(8 * g + (((l16 >> 3) ^ load) << 5)); }
-__device__ __forceinline__ void pair_operands(const RowPair &p, int l16, bf16x8 &first, bf16x8 &second)
-{
-    u32x4 a, b;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t x = word(p.v[0], i), y = word(p.v[1], i);
-        a[i] = l16 < 8 ? x : y;
-        b[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)(l16 < 8 ? y : x), 0x128, 0xf, 0xf, true);  // row_ror:8
-    }
-    first = __builtin_bit_cast(bf16x8, a);
-    second = __builtin_bit_cast(bf16x8, b);
-}
-
 // Operand of MFMA j of 32 contraction values by 128 columns of a [contraction][column] matrix, out of a lane's eight 16-byte loads: the lane has
 // values 8 (l / 16) .. by columns 8 (l % 16) ..  MFMA j takes column j of every lane, its column i is column 8 i + j, and the operand is put
 // together in registers: half a dword of each of two loads at a time, 32 v_perm for eight MFMAs.  (No LDS: neither a copy nor a transposing read.)
