@@ -964,13 +964,19 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
     a.bf_ld = c->L.rpad;
     a.bf_mult = bf_mult;
     a.bf_up = bf_up;
-    // A wave keeps `depth` chunks of K in flight and so needs K / (waves * chunk * depth) round trips to
-    // memory; cutting K into slices across blocks shortens that chain at the price of a second kernel that
-    // adds the slices (about 6 us with its launch).  Cut only when the chain is longer than about six round
-    // trips and the items alone give fewer than 8 waves per CU (with more, the pass is bound by bandwidth and
-    // more, shorter blocks only scatter the stream), up to that many waves or down to about three trips, as
-    // long as a wave keeps one chunk and the partial sums stay well below the bytes streamed (and inside the
+    // A wave keeps `depth` chunks of K in flight and so needs K / (waves * chunk * depth) round trips to memory; cutting K into
+    // slices across blocks shortens that chain at the price of a second kernel that adds the slices (about 4 us with its launch).
+    // Slices at all: as long as a wave keeps one chunk and the partial sums stay well below the bytes streamed (and inside the
     // workspace).
+    //  - Chains of more than six round trips are cut where the items alone give fewer than 8 waves per CU (with more, the pass is
+    //    bound by bandwidth and more, shorter blocks only scatter the stream), up to that many waves or down to about three trips.
+    //  - Shorter ones, of blocks of eight waves (ranks to 32), are cut in four where that gives at most one block per CU, else in
+    //    two on the same condition, if at least two round trips go away.  Forward call uncut / cut, us: rank 16, 128 rows
+    //    5120 -> 5120 37.9 / 35.7, 500 rows 8192 -> 2048 [N][K] 52.1 / 45.0, 1003 rows 11008 -> 4096 142 / 136, 1003 rows
+    //    8192 -> 4096 109.4 / 108.1; rank 24, 300 rows 7000 -> 504 40.2 / 31.1; forward and backward, 512 rows 5120 133.1 / 129.9,
+    //    1200 rows 8192 292 / 287.  Outside: one trip less of three (1003 rows 5120, two slices) 76.7 / 77.3; 2048 -> 8192 49.6 /
+    //    52; more blocks than CUs, 2000 rows 8192 207 / 211, 5120 rank 32 124.6 / 127; blocks of four waves, rank 40, 300 rows
+    //    2560 -> 2560 77.0 / 80.8 with the backward.
     int n_split = 1;
     if (s->dtype == COLLM_BF16) {
         const int kw = skinny_waves(rpad);
@@ -981,8 +987,12 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
         lim = std::min<long>(lim, K / (4L * rpad));
         lim = std::min<long>(lim, K / ((long)skinny_chunk(rpad) * kw));
         const long waves = (long)R.n_items * kw;
-        if (trips > 6 && waves > 0 && waves < 2048)
+        if (trips > 6 && waves > 0 && waves < 2048) {
             n_split = (int)std::max<long>(1, std::min<long>({lim, (2048 + waves - 1) / waves, (trips + 2) / 3}));
+        } else if (kw == 8) {
+            const long n = std::min<long>(waves <= 512 ? 4 : (waves <= 1024 ? 2 : 1), lim);
+            if (n > 1 && trips - (trips + n - 1) / n >= 2) n_split = (int)n;
+        }
     }
     a.part = c->d_part;
     a.part_rows = c->rows_cap;
