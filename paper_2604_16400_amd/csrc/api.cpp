@@ -141,6 +141,7 @@ struct Tiling {
     int big_tiles_m;
     int tail_tiles_m;
     int tail_cols = 0;
+    int slices = 1;  // 256x256 tiles, no tail: K slices (large_slices)
 };
 
 constexpr int kSplitBlocks = 512;  // 128x128 tiles that run at once: two per CU
@@ -328,6 +329,48 @@ long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, b
     return two;
 }
 
+// K slices of 256x256 tiles, one block per CU in one round, or 0 where 128x128 tiles (at most 256 of them, in slices of their own on two
+// blocks per CU) are the better ones.  For the same products a CU moves twice the bytes from L2 to LDS with two blocks of 128x128 tiles, and that
+// path, not the matrix pipes, is their limit; but a block of 256x256 starts and ends longer, its slices are more and their sums too, and rows and
+// columns that do not exist cost up to four times as much.  Times (us a K tile of a block, sums read and written per us, fixed) fitted to 63
+// forward calls of 128 to 3600 rows, weights from memory; the margin is what separates all that lost from all that gained.
+// GEMM with its sums inside whole calls, us, 128x128 / 256x256: 512 rows 22016 -> 5856 237 / 147 and 204 / 157 (backward), 1024 rows 4096 <- 22016 with the
+// gradients beside it 214 / 160, 768 rows 9216 -> 4272 93 / 80, 2048 rows 22016 -> 1280 175 / 144, 256 rows 24832 -> 8792 199 / 144; outside the
+// line 384 rows 15616 -> 10752 154 / 167, 599 rows 6912 -> 3840 56 / 66, 833 rows 12800 -> 1792 63 / 70, 896 rows 27136 -> 1024 level.
+long large_slices(int64_t part_bytes, int rows, int cols, int K, bool b_kmajor, int steps)
+{
+    const int tiles_m = (rows + 127) / 128;
+    const long tiles = (long)((rows + 255) / 256) * ((cols + 255) / 256), small_tiles = (long)tiles_m * ((cols + 127) / 128);
+    const int64_t slice_bytes = (int64_t)rows * cols * 4;
+    const long n = tiles > 0 ? std::min<long>({kSplitBlocks / 2 / tiles, (long)(part_bytes / slice_bytes), K / 512L}) : 0;
+    // (not where the extension is long, as in slices_one_per_cu)
+    if (n < 2 || small_tiles > kSplitBlocks / 2 || (int64_t)steps * 64 > K) return 0;
+    bool alone = false;
+    const long small = gemm_slices(-1, part_bytes, tiles_m, cols, K, b_kmajor, steps * tiles_m, &alone);
+    if (alone) return 0;
+    auto ktiles = [&](long slices) { return (double)((K + 64 * slices - 1) / (64 * slices)); };
+    const double mb = slice_bytes / 1e6;
+    const double large_us = 2.2 * ktiles(n) + 0.44 * mb * n + 8.0, small_us = 1.35 * ktiles(small) + 0.62 * mb * (small > 1 ? small : 0);
+    return large_us < small_us ? n : 0;
+}
+
+// pick_tiling, or 256x256 tiles in slices of K (plain: no siblings side by side, no SwiGLU epilogue).
+Tiling choose_tiling(int gemm_split, int64_t part_bytes, int rows, int cols, int K, bool b_kmajor, bool plain, bool can_split, bool one_round, int steps)
+{
+    Tiling t = pick_tiling(rows, cols, K, can_split, one_round, steps);
+    if (!plain || !can_split || gemm_split >= 0 || t.tile != kTile128x128 || t.tail_tiles_m > 0) return t;
+    const long n = large_slices(part_bytes, rows, cols, K, b_kmajor, steps);
+    if (n >= 2) {
+        t = Tiling{kTile256x256, (rows + 255) / 256, 0};
+        t.slices = (int)n;
+    }
+    return t;
+}
+Tiling choose_tiling(const collm_ctx *c, int rows, int cols, int K, bool b_kmajor, bool plain, bool can_split, bool one_round, int steps)
+{
+    return choose_tiling(c->gemm_split, (int64_t)c->part_bytes, rows, cols, K, b_kmajor, plain, can_split, one_round, steps);
+}
+
 // Low-rank K-steps that a 128-row tile of the batch has on average, over all rows and over the training rows: an adapter reaches
 // into about rows / 128 + 1 tiles.  (The tile choice needs it before the plan, whose steps depend on the tiles, is built.)
 void count_steps(collm_ctx *c, const collm_shape *s, const int32_t *rank, const int32_t *seg_start, const int32_t *seg_adapter,
@@ -376,7 +419,8 @@ bool warm_pays(const collm_ctx *c, const RowOrderLayout &R, int rows, int cols, 
     constexpr int64_t kWarmSlicedMaxBytes = (int64_t)8 << 20;
     if ((int64_t)cols * K * 2 <= kWarmSlicedMaxBytes) return true;
     const bool can_split = c->gemm_split != 1;
-    const Tiling t = pick_tiling(rows, cols, K, can_split, one_round, tile_steps(c, R));
+    const Tiling t = choose_tiling(c, rows, cols, K, b_kmajor, !siblings, can_split, one_round, tile_steps(c, R));
+    if (t.slices > 1) return false;
     if (t.tile != kTile256x256 && t.tile != kTile128x128) return false;
     bool alone = false;
     if (one_round && ring_alone(t, cols, K, tile_steps(c, R))) return false;
@@ -413,9 +457,9 @@ bool fork_behind_dh(int rpad, int d_in, int d_out)
 
 // ... nor where 256x256 tiles of dX make whole rounds (or all but a tenth of one): no CU is then free for the gradients before its end.
 // 4096 rows 8192 -> 8192 rank 16 431 / 439 us, 4000 rows 4096 -> 4096 rank 32 147 / 152, 12000 rows rank 16 363 / 375.
-bool whole_rounds(int rows, int cols)
+bool whole_rounds(int rows, int cols, int slices)
 {
-    const int last = (int)((int64_t)(round_up(rows, 256) / 256) * ((cols + 255) / 256) % 256);
+    const int last = (int)((int64_t)(round_up(rows, 256) / 256) * ((cols + 255) / 256) * slices % 256);
     return last == 0 || last > 230;
 }
 
@@ -464,7 +508,7 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
     // (the tiles between the two sizes are plain ones: a forced one stands for the size of the same height elsewhere)
     if (forced_tile >= 0 && (swiglu || g.n_sib > 1)) forced_tile = gemm_tile_rows(forced_tile) == 256 ? kTile256x256 : kTile128x128;
     const Tiling t = forced_tile >= 0 ? Tiling{forced_tile, R.n_rows_pad / gemm_tile_rows(forced_tile), 0}
-                                      : pick_tiling(rows, cols, g.K, can_split, one_round, tile_steps(c, R));
+                                      : choose_tiling(c, rows, cols, g.K, b_kmajor, !swiglu && g.n_sib <= 1, can_split, one_round, tile_steps(c, R));
     g.tile_m_base = 0;
     g.tiles_m = t.big_tiles_m;
     g.ext_off = c->d_plan + R.off_ext_off;
@@ -488,10 +532,24 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         gs.one_per_cu = alone;
         gs.row_base = row_base;
         gs.n_rows = n_rows_here;
-        err = launch_gemm_splitk(gs, n_split, b_kmajor, st);
+        err = launch_gemm_splitk(gs, kTile128x128, n_split, b_kmajor, st);
         if (err == hipSuccess) err = launch_gemm_finish(gs, n_split, st);
         return true;
     };
+    if (t.slices > 1) {
+        GemmArgs gs = g;
+        gs.tiles_n = (cols + 255) / 256;
+        gs.k_per_split = round_up((g.K + t.slices - 1) / t.slices, 64);
+        const int n_split = (g.K + gs.k_per_split - 1) / gs.k_per_split;
+        gs.part = c->d_part;
+        gs.part_rows = rows;
+        gs.part_ld = cols;
+        gs.row_base = 0;
+        gs.n_rows = rows;
+        if (R.bm != 256 || (int64_t)n_split * rows * cols * 4 > (int64_t)c->part_bytes) return hipErrorInvalidValue;
+        const hipError_t err = launch_gemm_splitk(gs, kTile256x256, n_split, b_kmajor, st);
+        return err == hipSuccess ? launch_gemm_finish(gs, n_split, st) : err;
+    }
     hipError_t e = hipSuccess;
     if (t.tile == kTile128x128 && t.tail_tiles_m == 0 && try_split(t.big_tiles_m, 0, rows, e)) return e;
     // Whole rounds of large tiles over the first columns, small tiles over the other columns of all rows.  With the SwiGLU epilogue only
@@ -777,13 +835,13 @@ int prepare_plan(collm_ctx *c, const collm_shape *s, const void *const *A, const
     int n_train = 0;
     for (int k = 0; k < s->n_segments; ++k)
         if (seg_is_train[k]) n_train += seg_start[k + 1] - seg_start[k];
-    const bool can_split = !f32 && c->gemm_split != 1;
+    const bool can_split = !f32 && c->gemm_split != 1, tr = s->layout == COLLM_LAYOUT_OUT_IN;
     count_steps(c, s, rank, seg_start, seg_adapter, seg_is_train);
-    const int tile_fwd = c->tile_fwd >= 0 ? c->tile_fwd : pick_tiling(s->n_tokens, s->d_out, s->d_in, can_split && !swiglu, n_sib <= 1, c->tile_steps_all).tile;
+    const int tile_fwd = c->tile_fwd >= 0 ? c->tile_fwd : choose_tiling(c, s->n_tokens, s->d_out, s->d_in, tr, !swiglu && n_sib <= 1, can_split && !swiglu, n_sib <= 1, c->tile_steps_all).tile;
     int rmax = 1;
     for (int a = 0; a < s->n_adapters; ++a) rmax = std::max(rmax, rank[a]);
     const bool one_round_dx = dx_one_round(c, n_train, s->d_in, s->d_out, f32, round_up(rmax, kKStep));
-    const int tile_bwd = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, can_split, one_round_dx, c->tile_steps_train).tile;
+    const int tile_bwd = c->tile_bwd >= 0 ? c->tile_bwd : choose_tiling(c, n_train, s->d_in, s->d_out, !tr, true, can_split, one_round_dx, c->tile_steps_train).tile;
     const int bm_all = f32 ? 64 : gemm_tile_rows(tile_fwd);
     const int bm_train = f32 ? 64 : gemm_tile_rows(tile_bwd);
     // All rows of an adapter take the tiled rank-wide pass when ranks reach 64: there an adapter's table
@@ -1416,10 +1474,10 @@ int collm_debug_host_plain_gemm(int rows, int cols, int K, int b_kmajor, int ste
 {
     if (!tile || !slices || !one_per_cu) return COLLM_E_NULL;
     if (rows <= 0 || cols <= 0 || K <= 0 || steps < 0 || workspace_bytes < 0) return COLLM_E_SHAPE;
-    const Tiling t = pick_tiling(rows, cols, K, true, true, (int)((steps + (rows + 127) / 128 - 1) / ((rows + 127) / 128)));
+    const Tiling t = choose_tiling(-1, workspace_bytes, rows, cols, K, b_kmajor != 0, true, true, true, (int)((steps + (rows + 127) / 128 - 1) / ((rows + 127) / 128)));
     *tile = t.tile;
-    *slices = 1;
-    *one_per_cu = 0;
+    *slices = t.slices;
+    *one_per_cu = t.slices > 1;
     if (t.tile == kTile128x128 && t.tail_tiles_m == 0) {
         bool alone = false;
         *slices = (int32_t)std::max(1L, gemm_slices(-1, workspace_bytes, t.big_tiles_m, cols, K, b_kmajor != 0, steps, &alone));
@@ -1779,9 +1837,10 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     };
     bool dx_even = false;  // the dX GEMM leaves no CU free
     if (overlap && dx && !f32) {
-        const int tile = c->tile_bwd >= 0 ? c->tile_bwd : pick_tiling(n_train, s->d_in, s->d_out, c->gemm_split != 1, one_round, c->tile_steps_train).tile;
-        ga.beside_gemm = tile == kTile128x128 ? 1 : 0;
-        dx_even = tile == kTile256x256 && whole_rounds(n_train, s->d_in);
+        const Tiling t = c->tile_bwd >= 0 ? Tiling{c->tile_bwd, 0, 0}
+                                          : choose_tiling(c, n_train, s->d_in, s->d_out, !tr, true, c->gemm_split != 1, one_round, c->tile_steps_train);
+        ga.beside_gemm = t.tile == kTile128x128 ? 1 : 0;
+        dx_even = t.tile == kTile256x256 && whole_rounds(n_train, s->d_in, t.slices);
     }
 
     // Narrow ranks (all at most 16), tables as [rank][d_out]: dh and dB_a both come from ONE pass over the training

@@ -91,7 +91,7 @@ struct GemmArgs {
     int part_rows, part_ld;
     int k_per_split;          // multiple of 64
     int n_rows, row_base;     // launch_gemm_splitk: the launch covers rows row_base .. row_base + n_rows of the row order
-                              // (row_base = 128 tile_m_base); part row = row - row_base
+                              // (row_base = rows of a tile times tile_m_base); part row = row - row_base
     int part_n_sib;           // as SkinnyArgs::n_sib (0 or 1: ranks as the items give them)
     int64_t tab_ld, tab_off;  // as SkinnyArgs
     // launch_wide: warm-up of the GEMM that follows, as in SkinnyArgs (extra blocks behind the n_items items)
@@ -206,10 +206,10 @@ hipError_t launch_dual_sum(const DualArgs &a, hipStream_t st);
 void host_tile_order(int tiles_m, int tiles_n, int band, int32_t *tm, int32_t *tn);
 int gemm_band_rows(int tile_rows, int K, int tiles_m);
 hipError_t launch_gemm(const GemmArgs &a, int tile_cfg, bool b_kmajor, hipStream_t st);
-// The GEMM with K cut into n_split slices of k_per_split (128x128 tiles): fp32 sums of slice s for row r of the row order at
+// The GEMM with K cut into n_split slices of k_per_split (128x128 or 256x256 tiles): fp32 sums of slice s for row r of the row order at
 // part[(s * part_rows + r) * part_ld + n] (part_ld >= N, a multiple of 4), then launch_gemm_finish adds the slices, rounds
 // and scatters the rows through row_tok.
-hipError_t launch_gemm_splitk(const GemmArgs &a, int n_split, bool b_kmajor, hipStream_t st);
+hipError_t launch_gemm_splitk(const GemmArgs &a, int tile_cfg, int n_split, bool b_kmajor, hipStream_t st);
 hipError_t launch_gemm_finish(const GemmArgs &a, int n_split, hipStream_t st);
 // tile_cfg kTile256x256 or kTile128x128; tiles_n counts tiles of half as many output columns as the tile has
 hipError_t launch_gemm_swiglu(const GemmArgs &a, int tile_cfg, hipStream_t st);

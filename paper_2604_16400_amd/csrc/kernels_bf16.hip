@@ -1886,14 +1886,19 @@ __global__ void __launch_bounds__(256) gemm_finish_kernel(GemmArgs p, int n_spli
     *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(p.out) + (int64_t)tok * p.ldo + n) = v;
 }
 
-hipError_t launch_gemm_splitk(const GemmArgs &a, int n_split, bool b_kmajor, hipStream_t st)
+constexpr int kLargeTileLds = 2 * (256 + 256) * 128 + 256 * 128;  // two stages and the rows' area of the extension
+
+hipError_t launch_gemm_splitk(const GemmArgs &a, int tile_cfg, int n_split, bool b_kmajor, hipStream_t st)
 {
     if (n_split < 1 || !a.part || a.k_per_split % 64 != 0 || a.part_ld < a.N || a.part_ld % 4 != 0) return hipErrorInvalidValue;
     const int tiles = a.tiles_m * a.tiles_n;
     if (tiles <= 0) return hipSuccess;
-    // one block per CU: the ring of four stages (see gemm_lora_kernel); more blocks: two stages, two blocks per CU
+    // 256x256 tiles (see large_slices in api.cpp); 128x128, one block per CU: the ring of four stages (see gemm_lora_kernel); more
+    // blocks: two stages, two blocks per CU
     const bool ring = a.one_per_cu && a.n_sib <= 1;
-    const int smem = ring ? kRingStages * (128 + 128) * 128 : kSmallTileLds;
+    const bool large = tile_cfg == kTile256x256;
+    if ((!large && tile_cfg != kTile128x128) || (large && a.n_sib > 1)) return hipErrorInvalidValue;
+    const int smem = large ? kLargeTileLds : (ring ? kRingStages * (128 + 128) * 128 : kSmallTileLds);
     auto launch = [&](auto k) -> hipError_t {
         constexpr auto kern = decltype(k)::fn;
         const hipError_t e = allow_lds<kern>(smem);
@@ -1902,6 +1907,9 @@ hipError_t launch_gemm_splitk(const GemmArgs &a, int n_split, bool b_kmajor, hip
         return hipGetLastError();
     };
     if (a.n_sib > 1) return b_kmajor ? hipErrorInvalidValue : launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, false, false, false, true, true>>());
+    if (large)
+        return b_kmajor ? launch(Kernel<gemm_lora_kernel<256, 256, 2, 2, true, false, false, true>>())
+                        : launch(Kernel<gemm_lora_kernel<256, 256, 2, 2, false, false, false, true>>());
     if (ring)
         return b_kmajor ? launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, true, false, false, true, false, kRingStages>>())
                         : launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, false, false, false, true, false, kRingStages>>());
