@@ -102,6 +102,21 @@ struct SkinnyPassArgs : SkinnyArgs {
     PlanPatch patch;
 };
 template <typename Args> constexpr bool kHasPatch = std::is_same_v<Args, WideArgs> || std::is_same_v<Args, SkinnyPassArgs>;
+// The tiled pass with the 16-row items (of ranks up to RP) in blocks of the same launch, mixed_cols columns of blocks behind its own.
+template <int RP, typename Pass>
+struct MixedArgs : GemmArgs {
+    static constexpr int kRp = RP;
+    Pass pass;
+    int mixed_split, mixed_cols;
+};
+template <typename Args> constexpr bool kMixed = false;
+template <int RP, typename Pass> constexpr bool kMixed<MixedArgs<RP, Pass>> = true;
+template <typename Args>
+__device__ __forceinline__ const auto &pass_args(const Args &p)  // what knows the tables and the patch
+{
+    if constexpr (kMixed<Args>) return p.pass;
+    else return p;
+}
 template <typename Args>
 __device__ __forceinline__ int patch_blocks(const Args &p)
 {

@@ -215,7 +215,11 @@ hipError_t launch_gemm_finish(const GemmArgs &a, int n_split, hipStream_t st);
 hipError_t launch_gemm_swiglu(const GemmArgs &a, int tile_cfg, hipStream_t st);
 // a, lda, K, a_bytes, row_tok and the fields of the rank-wide pass; everything else is ignored.  Items hold up
 // to kWideRows rows; ranks must be multiples of 8.  The caller adds the slices with launch_skinny_finish.
-hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st, const PlanPatch *patch = nullptr);
+// mixed: null, or 16-row items of ranks up to mixed_rank (at most kMixedRank), in mixed_split slices of K, that run in blocks of the same launch
+// (16-row items, sums to mixed->part whatever the number of slices).
+constexpr int kMixedRank = 64;
+hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st, const PlanPatch *patch = nullptr,
+                       const SkinnyArgs *mixed = nullptr, int mixed_rank = 0, int mixed_split = 1);
 // adds the K slices of n_wide tiled items (`wide`, wide_split slices) and of n_items others (a.items, row_tiles = 1 or 2 groups
 // of 16 rows each, n_split slices) and does the pass's stores
 hipError_t launch_skinny_finish(const SkinnyArgs &a, const SkinnyItem *wide, int n_wide, int wide_split, int n_items, int row_tiles, int n_split,

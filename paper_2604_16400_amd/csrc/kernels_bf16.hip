@@ -242,6 +242,7 @@ constexpr bool rows_early(int bm, int bn, int rs) { return rs ? rs == 2 : bm * b
 // (about 800 cycles from L2 or beyond): with tables as they lie in memory ([K][rank], transposing reads) two
 // blocks per CU whose phases interleave, two stages each, beat one block with four; with K-major tables
 // (fewer, cheaper fragment reads) the four stages do.
+// (With the 16-row items in the same launch, whose registers leave one block per CU, four in both.)
 constexpr int kWideStages = 4;
 constexpr int wide_stages(bool t_kmajor) { return t_kmajor ? kWideStages : 2; }
 // RS: 0, or the number of LDS stages of a ring in which the loads of RS - 1 tiles are in flight (one block per CU).
@@ -289,11 +290,22 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
     uint32_t a_bytes = p.a_bytes, b_bytes = p.b_bytes, ldb = (uint32_t)p.ldb;
     if constexpr (PARTIAL) {
         if (blockIdx.x >= (unsigned)p.n_items) {
-            if (blockIdx.y != 0 || blockIdx.z != 0) return;
+            if (blockIdx.y != 0) return;
+            int col = (int)blockIdx.x - p.n_items;
+            if constexpr (kMixed<Args>) {
+                const int e = col * (int)gridDim.z + (int)blockIdx.z, n = p.pass.n_items;
+                if (col < p.mixed_cols) {
+                    if (e < n * p.mixed_split) skinny_item<Args::kRp, B_KMAJOR, 1, NT / 64, true>(p.pass, e % n, e / n, p.mixed_split, smem);
+                    return;
+                }
+                col -= p.mixed_cols;
+            }
+            if (blockIdx.z != 0) return;
             // a block that puts in new table addresses, or a warm-up block: its share of the next GEMM's weight, read once and dropped
-            const int extra = blockIdx.x - p.n_items - patch_blocks(p);
-            if constexpr (kHasPatch<Args>)
-                if (extra < 0) patch_plan(p.patch, blockIdx.x - p.n_items, tid, NT);
+            const auto &pa = pass_args(p);
+            const int extra = col - patch_blocks(pa);
+            if constexpr (kHasPatch<std::decay_t<decltype(pa)>>)
+                if (extra < 0) patch_plan(pa.patch, col, tid, NT);
             if (extra >= 0) warm_cache(p.warm_base, p.warm_bytes, extra, p.warm_blocks, tid, NT);
             return;
         }
@@ -315,7 +327,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
         const uint32_t b_skip = B_KMAJOR ? (uint32_t)(k_begin + p.tab_off) * 2u : (uint32_t)k_begin * ldb * 2u;
         a_base = reinterpret_cast<const uint8_t *>(p.a) + a_skip;
         a_bytes = p.a_bytes - a_skip;
-        b_base = pass_table(p, it.adapter) + b_skip;
+        b_base = pass_table(pass_args(p), it.adapter) + b_skip;
         b_bytes = B_KMAJOR ? (uint32_t)N * ldb * 2u - b_skip : (uint32_t)K * ldb * 2u;
     } else {
         if constexpr (SPLITK) {
@@ -730,7 +742,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
         // stages of [rows tile | table tile]; the loads of kWideStages - 1 tiles are in flight while one is multiplied.
         // One barrier per tile: before it every wave has received its own loads of tile kc, after it all of the tile
         // is in LDS and every wave is done with tile kc - 1, whose stage the loads of tile kc + kWideStages - 1 may fill.
-        constexpr int NS = wide_stages(B_KMAJOR);
+        constexpr int NS = wide_stages(B_KMAJOR || kMixed<Args>);
         static_assert((NS - 2) * ND <= 63, "outstanding loads must fit the counter");
         auto issue_tile = [&](int kc) {
             const uint32_t base = lds_wave + (uint32_t)(kc % NS) * STAGE;
@@ -1832,33 +1844,45 @@ hipError_t launch_gemm(const GemmArgs &a, int tile_cfg, bool b_kmajor, hipStream
     }
 }
 
-hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st, const PlanPatch *patch)
+hipError_t launch_wide(const GemmArgs &a, int n_items, int rpad, int n_split, bool t_kmajor, hipStream_t st, const PlanPatch *patch,
+                       const SkinnyArgs *mixed, int mixed_rank, int mixed_split)
 {
     static_assert(kWideRows == 128, "the rank-wide pass runs 128x128 tiles");
     if (n_items <= 0) return hipSuccess;
     if (n_split < 1 || !a.part || !a.items || !a.tab || a.k_per_split % 64 != 0) return hipErrorInvalidValue;
-    const int smem = wide_stages(t_kmajor) * (128 + 128) * 128;
-    auto launch = [&](auto k, auto b) -> hipError_t {
-        constexpr auto kern = decltype(k)::fn;
+    if (mixed && (mixed_split < 1 || mixed_rank > kMixedRank || mixed->n_items < 1 || !mixed->part)) return hipErrorInvalidValue;
+    // eight waves, 32 rows x 64 rank columns each (two per SIMD): the loop is bound by what a wave has to issue
+    auto launch = [&](auto km, auto b) -> hipError_t {
+        using Args = decltype(b);
+        constexpr bool KM = decltype(km)::value;
+        constexpr auto kern = gemm_lora_kernel<128, 128, 4, 2, KM, true, false, false, false, 0, Args>;
+        constexpr int smem = wide_stages(KM || kMixed<Args>) * (128 + 128) * 128;
+        if constexpr (kMixed<Args>) static_assert(skinny_lds<Args::kRp, KM, 1, 8, true>() <= smem, "the items' LDS");
         const hipError_t e = allow_lds<kern>(smem);
         if (e != hipSuccess) return e;
         static_cast<GemmArgs &>(b) = a;
         b.n_items = n_items;
         if (!b.warm_base || b.warm_bytes < 16) b.warm_blocks = 0;
         int extra = b.warm_blocks;
-        if constexpr (kHasPatch<decltype(b)>) {
+        if constexpr (kMixed<Args>) {
+            static_cast<SkinnyArgs &>(b.pass) = *mixed;
+            b.mixed_split = mixed_split;
+            b.mixed_cols = (mixed->n_items * mixed_split + n_split - 1) / n_split;
+            extra += b.mixed_cols;
+            if constexpr (kHasPatch<decltype(b.pass)>) b.pass.patch = *patch;
+        } else if constexpr (kHasPatch<Args>) {
             b.patch = *patch;
-            extra += patch->blocks;
         }
+        if (patch) extra += patch->blocks;
         COLLM_LAUNCH(kern, dim3(n_items + extra, (rpad + 127) / 128, n_split), dim3(512), smem, st, b);
         return hipGetLastError();
     };
-    // eight waves, 32 rows x 64 rank columns each (two per SIMD): the loop is bound by what a wave has to issue
-    if (patch)
-        return t_kmajor ? launch(Kernel<gemm_lora_kernel<128, 128, 4, 2, true, true, false, false, false, 0, WideArgs>>(), WideArgs())
-                        : launch(Kernel<gemm_lora_kernel<128, 128, 4, 2, false, true, false, false, false, 0, WideArgs>>(), WideArgs());
-    return t_kmajor ? launch(Kernel<gemm_lora_kernel<128, 128, 4, 2, true, true>>(), GemmArgs())
-                    : launch(Kernel<gemm_lora_kernel<128, 128, 4, 2, false, true>>(), GemmArgs());
+    auto by_args = [&](auto km) -> hipError_t {
+        if (!mixed) return patch ? launch(km, WideArgs()) : launch(km, GemmArgs());
+        if (mixed_rank <= 32) return patch ? launch(km, MixedArgs<32, SkinnyPassArgs>()) : launch(km, MixedArgs<32, SkinnyArgs>());
+        return patch ? launch(km, MixedArgs<kMixedRank, SkinnyPassArgs>()) : launch(km, MixedArgs<kMixedRank, SkinnyArgs>());
+    };
+    return t_kmajor ? by_args(std::true_type()) : by_args(std::false_type());
 }
 
 hipError_t launch_skinny_finish(const SkinnyArgs &a, const SkinnyItem *wide, int n_wide, int wide_split, int n_items, int row_tiles, int n_split,

@@ -57,6 +57,7 @@ struct RowOrderLayout {
     int32_t off_row_adapter = 0;  // [n_rows_pad] adapter or -1
     int32_t n_items = 0, off_items = 0;  // SkinnyItem[n_items]
     int32_t item_rows = kSkinnyRows;     // most rows an item holds (16 or 32)
+    int32_t item_rank = 1;               // largest rank of an item
     int32_t n_wide = 0, off_wide = 0;    // SkinnyItem[n_wide] of up to kWideRows rows: long runs, taken by the tiled pass
     int32_t bm = 0, n_tiles_m = 0;       // GEMM row tile the extension tables were built for
     int32_t off_ext_off = 0;             // [n_tiles_m + 1]

@@ -173,6 +173,7 @@ void build_row_order(Builder &b, RowOrderLayout &L, const std::vector<int32_t> &
             items.push_back({a, r, std::min(L.item_rows, hi - r), rank[a]});
     }
     L.n_items = (int)items.size();
+    for (const SkinnyItem &it : items) L.item_rank = std::max(L.item_rank, it.rank);
     L.off_items = b.alloc(items.size() * 4 + 4);
     if (!items.empty())
         std::memcpy(b.blk.data() + L.off_items, items.data(), items.size() * sizeof(SkinnyItem));
