@@ -351,7 +351,7 @@ int collm_debug_set_tiles(collm_ctx *ctx, int fwd_tile, int bwd_tile);
 int collm_debug_set_gemm_split(collm_ctx *ctx, int n_slices);
 
 /*
- * Debug/tuning: where the adapter gradients of a backward call run.  -1: let the library choose; 0: on the caller's
+ * Debug/tuning: where the adapter gradients of a backward call run.  -1: let the library choose (also: in blocks of the dX GEMM's launch); 0: on the caller's
  * stream, one kernel after the other; 1: on the context's second stream, beside dh and the dX GEMM.  Affects only speed.
  */
 int collm_debug_set_grad_streams(collm_ctx *ctx, int mode);

@@ -494,10 +494,36 @@ bool decode_sized(const collm_ctx *c, const collm_shape *s, const int32_t *rank,
     return (int64_t)T * s->d_out + (int64_t)round_up(T, 16) * round_up(rmax, kKStep) <= (int64_t)c->part_bytes / 4;
 }
 
+// Gradients that run in blocks of the dX GEMM's launch (launch_gemm_grads).
+struct GradsBeside {
+    GradArgs dB, dA;
+    int n_grad, rpad;
+    bool done = false;
+};
+
+// Whether they do: one launch saves the two points at which the caller's stream hands over to the second one (5 us of idle time each) and the
+// kernel that packs h, but the gradients' blocks are half as wide and share the CUs with the GEMM's, so only where all of the GEMM's blocks run at
+// once and the gradients end before them in the places they leave.  A K tile of a GEMM block takes 0.9 us, a chunk of 128 rows of a gradient block
+// 1.2.  Passes (forward and backward), two streams / one launch, us: four layers 4096 -> 4096, 2048 tokens, rank 16 603 / 580; 740 tokens
+// 5632 -> 2528 rank 32 448 / 406, 2147 tokens 7424 -> 1792 151 / 138, 1148 tokens 6496 -> 3072 rank 64 700 / 660; 45 batches 1.009, none slower.  Where
+// the comparison is missed by up to 2.5 as many lose as gain (1096 -> 4864 rank 64 256 / 277, 13072 -> 2360 294 / 280).
+bool grads_in_gemm(const collm_ctx *c, int n_train, int d_in, int d_out, bool b_kmajor, int rpad)
+{
+    if (c->grad_streams >= 0 || c->tile_bwd >= 0 || c->gemm_split >= 0 || rpad > kGemmGradRank) return false;
+    const Tiling t = choose_tiling(c, n_train, d_in, d_out, b_kmajor, true, true, false, c->tile_steps_train);
+    if (t.tile != kTile128x128 || t.tail_tiles_m > 0) return false;
+    bool alone = false;
+    const long n = std::max(1L, gemm_slices(c, c->L.train, 0, t.big_tiles_m, d_in, d_out, b_kmajor, &alone));
+    if (n > 1 && alone) return false;
+    const long gemm = (long)t.big_tiles_m * ((d_in + 127) / 128) * n, grads = (long)c->L.n_grad * ((d_in + 63) / 64 + (d_out + 63) / 64);
+    const double gemm_us = 0.9 * ((d_out + 64 * n - 1) / (64 * n)), grad_us = 5.0 + 1.2 * ((c->L.max_grad_rows + 127) / 128);
+    return gemm < kSplitBlocks && grads * grad_us <= gemm_us * (kSplitBlocks - gemm);
+}
+
 // One GEMM over the row order `R`: a single launch, or whole rounds of large tiles followed by
 // small tiles over the remaining rows.
 hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows, int cols, int forced_tile,
-                    bool b_kmajor, bool one_round, hipStream_t st, bool swiglu = false)
+                    bool b_kmajor, bool one_round, hipStream_t st, bool swiglu = false, GradsBeside *beside = nullptr)
 {
     // SwiGLU epilogue: `cols` counts gate and up columns; a tile holds half as many output columns as it is wide
     auto launch = [&](int tile) {
@@ -532,7 +558,12 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         gs.one_per_cu = alone;
         gs.row_base = row_base;
         gs.n_rows = n_rows_here;
-        err = launch_gemm_splitk(gs, kTile128x128, n_split, b_kmajor, st);
+        if (beside && whole && !alone) {
+            err = launch_gemm_grads(gs, n_split, b_kmajor, beside->dB, beside->dA, beside->n_grad, beside->rpad, st);
+            beside->done = true;
+        } else {
+            err = launch_gemm_splitk(gs, kTile128x128, n_split, b_kmajor, st);
+        }
         if (err == hipSuccess) err = launch_gemm_finish(gs, n_split, st);
         return true;
     };
@@ -568,6 +599,11 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         g.ext_off = c->d_plan + R.off_ext_off_half;
         g.ext = reinterpret_cast<const ExtStep *>(c->d_plan + R.off_ext_half);
         return swiglu ? launch_gemm_swiglu(g, kTile128x128, st) : launch_gemm(g, kTile128x128, b_kmajor, st);
+    }
+    if (beside && t.tile == kTile128x128 && t.tail_tiles_m == 0) {
+        g.tiles_n = (cols + 127) / 128;
+        beside->done = true;
+        return launch_gemm_grads(g, 1, b_kmajor, beside->dB, beside->dA, beside->n_grad, beside->rpad, st);
     }
     g.one_per_cu = one_round && forced_tile < 0 && ring_alone(t, cols, g.K, tile_steps(c, R));
     e = launch(t.tile);
@@ -1836,7 +1872,10 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // caller's stream again before the call returns.  (Serial when kernels are being timed.)
     // Small batches stay on the caller's stream (see grads_alone).
     const bool alone = c->grad_streams >= 0 ? c->grad_streams == 0 : grads_alone(n_train, s->d_in, s->d_out, f32, L.rpad);
-    const bool overlap = dA && !alone && !c->profile;
+    // Or in the dX GEMM's launch, where that leaves places free (grads_in_gemm).
+    const bool may_fuse = dA && dx && !alone && !c->profile && !f32 && P == 1 && !may_dual && dx != x && dx != dy && L.n_grad > 0;
+    const bool fused = may_fuse && grads_in_gemm(c, n_train, s->d_in, s->d_out, !tr, L.rpad);
+    const bool overlap = dA && !alone && !fused && !c->profile;
     const bool one_round = dx_one_round(c, n_train, s->d_in, s->d_out, f32, L.rpad);
     // fp32 on one stream: dB beside dh, dA beside dX
     const bool pair = f32 && dA && alone && !c->profile && pair_f32(L.rpad, s->d_in, s->d_out);
@@ -1928,6 +1967,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         if (rc != COLLM_OK) return rc;
         HIP_TRY(launch_dual_sum(du, st));
     }
+    GradsBeside beside{};
     // dB_a = s h^T dy
     const bool late = overlap && !dual && dx && P == 1 && !dx_even && fork_behind_dh(L.rpad, s->d_in, s->d_out);
     auto launch_dB = [&]() -> int {
@@ -1954,7 +1994,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
             // conversion in the kernel): left by the recomputing pass, or packed from h_save here.  The forward
             // call's copy of s h (all rows) in the same buffer is dead once that call's GEMM has run.
             // (small batches skip the packing kernel: their gradient kernel converts as it reads)
-            const bool pack = h_save && !(alone && P == 1);
+            const bool pack = h_save && !((alone || fused) && P == 1);
             if (pack)
                 HIP_TRY(launch_pack_rows(h_save, c->max_rank, c->max_rank, c->d_plan + L.train.off_row_tok,
                                          L.train.n_rows, s->scale, c->d_hs, L.rpad, gs));
@@ -1966,7 +2006,10 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         ga.out_tab = reinterpret_cast<const uint64_t *>(c->d_plan + L.off_dB_ptr);
         set_outs(dB);
         ga.out_transposed = tr ? 1 : 0;
-        if (!pair) {
+        if (fused) {
+            beside.dB = ga;
+            ga.small_bf = nullptr;
+        } else if (!pair) {
             Prof prof(c, gs, "grad_dB");
             if (f32) {
                 HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, gs));
@@ -2042,7 +2085,11 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         ga.out_tab = reinterpret_cast<const uint64_t *>(c->d_plan + L.off_dA_ptr);
         set_outs(dA);
         ga.out_transposed = tr ? 0 : 1;
-        if (!pair) {
+        if (fused) {
+            beside.dA = ga;
+            beside.n_grad = L.n_grad;
+            beside.rpad = L.rpad;
+        } else if (!pair) {
             Prof prof(c, gs, "grad_dA");
             if (f32) HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, gs));
             else HIP_TRY(launch_grad(ga, L.n_grad, L.rpad, gs));
@@ -2082,7 +2129,11 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
                 HIP_TRY(launch_gemm_f32(g, !tr, st));
             }
         } else {
-            HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, one_round, st));
+            HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, one_round, st, false, fused ? &beside : nullptr));
+            if (fused && !beside.done) {
+                HIP_TRY(launch_grad(beside.dB, L.n_grad, L.rpad, st));
+                HIP_TRY(launch_grad(beside.dA, L.n_grad, L.rpad, st));
+            }
         }
     }
     if (pair && !dx) HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, st));

@@ -211,6 +211,10 @@ hipError_t launch_gemm(const GemmArgs &a, int tile_cfg, bool b_kmajor, hipStream
 // and scatters the rows through row_tok.
 hipError_t launch_gemm_splitk(const GemmArgs &a, int tile_cfg, int n_split, bool b_kmajor, hipStream_t st);
 hipError_t launch_gemm_finish(const GemmArgs &a, int n_split, hipStream_t st);
+// The dX GEMM on 128x128 tiles, two blocks per CU, uncut or in n_split slices (as launch_gemm_splitk), with the gradients of n_grad adapters of ranks
+// up to rpad (at most kGemmGradRank) in blocks behind its own.
+constexpr int kGemmGradRank = 64;
+hipError_t launch_gemm_grads(const GemmArgs &a, int n_split, bool b_kmajor, const GradArgs &dB, const GradArgs &dA, int n_grad, int rpad, hipStream_t st);
 // tile_cfg kTile256x256 or kTile128x128; tiles_n counts tiles of half as many output columns as the tile has
 hipError_t launch_gemm_swiglu(const GemmArgs &a, int tile_cfg, hipStream_t st);
 // a, lda, K, a_bytes, row_tok and the fields of the rank-wide pass; everything else is ignored.  Items hold up

@@ -245,6 +245,19 @@ constexpr bool rows_early(int bm, int bn, int rs) { return rs ? rs == 2 : bm * b
 // (With the 16-row items in the same launch, whose registers leave one block per CU, four in both.)
 constexpr int kWideStages = 4;
 constexpr int wide_stages(bool t_kmajor) { return t_kmajor ? kWideStages : 2; }
+// The dX GEMM with the gradients dB_a and dA_a (ranks up to RP) in blocks of the same launch, behind its own: columns of blocks, the first at
+// a multiple of 8 blocks so that the GEMM's blocks keep their XCDs.
+template <int RP>
+struct GemmGradArgs : GemmArgs {
+    static constexpr int kRp = RP;
+    GradArgs dB, dA;
+    int dB_blocks, blocks;  // of dB, of both
+};
+template <typename Args> constexpr bool kWithGrads = false;
+template <int RP> constexpr bool kWithGrads<GemmGradArgs<RP>> = true;
+template <int RP, bool SMALL_BF, int KW>
+__device__ __forceinline__ void grad_block(const GradArgs &p, int col_block, int item, int rank_slice, uint8_t *smem);
+
 // RS: 0, or the number of LDS stages of a ring in which the loads of RS - 1 tiles are in flight (one block per CU).
 template <int BM, int BN, int WGM, int WGN, bool B_KMAJOR, bool PARTIAL = false, bool SWIGLU = false, bool SPLITK = false,
           bool SIBS = false, int RS = 0, typename Args = GemmArgs>
@@ -330,10 +343,29 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
         b_base = pass_table(pass_args(p), it.adapter) + b_skip;
         b_bytes = B_KMAJOR ? (uint32_t)N * ldb * 2u - b_skip : (uint32_t)K * ldb * 2u;
     } else {
+        int pid = SPLITK ? blockIdx.y * gridDim.x + blockIdx.x : blockIdx.x;
+        if constexpr (kWithGrads<Args>) {
+            const int tiles = p.tiles_m * p.tiles_n, pad = (tiles + 7) & ~7;
+            if ((int)blockIdx.x >= tiles) {
+                const int e = ((int)blockIdx.x - pad) * (int)gridDim.y + (int)blockIdx.y;
+                if ((int)blockIdx.x < pad || e >= p.blocks) return;
+                constexpr int RP = Args::kRp, KW = NT / 64;
+                if (e < p.dB_blocks) {
+                    const int cols = (p.dB.N + 63) >> 6;
+                    if (p.dB.small_bf) grad_block<RP, true, KW>(p.dB, e % cols, e / cols, 0, smem);
+                    else grad_block<RP, false, KW>(p.dB, e % cols, e / cols, 0, smem);
+                } else {
+                    const int f = e - p.dB_blocks, cols = (p.dA.N + 63) >> 6;
+                    grad_block<RP, true, KW>(p.dA, f % cols, f / cols, 0, smem);
+                }
+                return;
+            }
+            pid = (int)blockIdx.y * tiles + (int)blockIdx.x;
+        }
         if constexpr (SPLITK) {
-            slice_coords(blockIdx.y * gridDim.x + blockIdx.x, p.tiles_m, p.tiles_n, (int)gridDim.y, slice, tile_m, tile_n);
+            slice_coords(pid, p.tiles_m, p.tiles_n, (int)gridDim.y, slice, tile_m, tile_n);
         } else {
-            tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, p.band_m, tile_m, tile_n);
+            tile_coords(pid, p.tiles_m, p.tiles_n, p.band_m, tile_m, tile_n);
         }
         tile_m += p.tile_m_base;
         m0 = tile_m * BM;
@@ -1351,9 +1383,9 @@ __global__ void __launch_bounds__(256) skinny_finish_kernel(SkinnyArgs p, const 
 // token) is the slow index of both.  The partial sums of the waves meet in LDS in wave
 // order: fixed order, no atomics, one writer per output element.
 // =========================================================================================
-template <int RP>
+constexpr int grad_waves(int rp) { return rp <= 32 ? 8 : 4; }
+template <int RP, int KW = grad_waves(RP)>
 struct GradCfg {
-    static constexpr int KW = RP <= 32 ? 8 : 4;
     static constexpr int CHT = 32;                 // rows per chunk = one MFMA K step
     static constexpr int MB = RP / 16;
     static constexpr int BPITCH = 64 * 2 + 32;     // bytes
@@ -1366,22 +1398,21 @@ struct GradCfg {
     static constexpr int SROW = 64 * 4 / RP;       // rows advanced per piece index
 };
 
-template <int RP, bool SMALL_BF>
-__global__ void __launch_bounds__(GradCfg<RP>::KW * 64) grad_kernel(GradArgs p)
+template <int RP, bool SMALL_BF, int KW>
+__device__ __forceinline__ void grad_block(const GradArgs &p, int col_block, int item, int rank_slice, uint8_t *smem)
 {
-    using C = GradCfg<RP>;
-    constexpr int KW = C::KW, MB = C::MB, SV = SMALL_BF ? 1 : C::SV;
+    using C = GradCfg<RP, KW>;
+    constexpr int MB = C::MB, SV = SMALL_BF ? 1 : C::SV;
     constexpr int NP = RP / 16;   // 16-byte pieces of a bf16 `small` chunk per lane
     constexpr int PPR = RP / 8;   // pieces per row
-    extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint8_t *stage_b = smem + wave * C::STAGE_BYTES;
     uint8_t *stage_s = stage_b + C::CHT * C::BPITCH;
     float *red = reinterpret_cast<float *>(smem);
 
-    const int n0 = blockIdx.x * 64;
-    const GradItem it = p.items[blockIdx.y];
-    const int q0 = blockIdx.z * RP;
+    const int n0 = col_block * 64;
+    const GradItem it = p.items[item];
+    const int q0 = rank_slice * RP;
     const int rank = p.n_sib > 1 ? it.rank / p.n_sib : it.rank;
     const int N = p.N;
     const int l16 = lane & 15, kg = lane >> 4;
@@ -1530,7 +1561,7 @@ __global__ void __launch_bounds__(GradCfg<RP>::KW * 64) grad_kernel(GradArgs p)
                 red[(wave * RP + mb * 16 + kg * 4 + j) * C::RED_LD + nb * 16 + l16] = acc[mb][nb][j];
     __syncthreads();
 
-    float *out = reinterpret_cast<float *>(p.n_out > 0 ? p.out[blockIdx.y] : p.out_tab[it.adapter]);
+    float *out = reinterpret_cast<float *>(p.n_out > 0 ? p.out[item] : p.out_tab[it.adapter]);
     const int qn = (rank - q0) < RP ? (rank - q0) : RP;  // rank indices of this slice
     if (qn <= 0) return;
     for (int idx = tid; idx < 64 * qn; idx += KW * 64) {
@@ -1550,6 +1581,13 @@ __global__ void __launch_bounds__(GradCfg<RP>::KW * 64) grad_kernel(GradArgs p)
                                       : out + (int64_t)(q0 + q) * (p.ld_out ? p.ld_out : (int64_t)N) + p.out_off + n0 + n;
         *dst = p.accumulate ? (*dst + sum) : sum;
     }
+}
+
+template <int RP, bool SMALL_BF>
+__global__ void __launch_bounds__(grad_waves(RP) * 64) grad_kernel(GradArgs p)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    grad_block<RP, SMALL_BF, grad_waves(RP)>(p, blockIdx.x, blockIdx.y, blockIdx.z, smem);
 }
 
 // =========================================================================================
@@ -1941,6 +1979,34 @@ hipError_t launch_gemm_splitk(const GemmArgs &a, int tile_cfg, int n_split, bool
                     : launch(Kernel<gemm_lora_kernel<128, 128, 2, 2, false, false, false, true>>());
 }
 
+hipError_t launch_gemm_grads(const GemmArgs &a, int n_split, bool b_kmajor, const GradArgs &dB, const GradArgs &dA, int n_grad, int rpad, hipStream_t st)
+{
+    if (rpad > kGemmGradRank || n_grad < 1 || !dA.small_bf || dB.n_sib > 1 || dA.n_sib > 1 || a.n_sib > 1 || n_split < 1) return hipErrorInvalidValue;
+    if (n_split > 1 && (!a.part || a.k_per_split % 64 != 0 || a.part_ld < a.N || a.part_ld % 4 != 0)) return hipErrorInvalidValue;
+    const int tiles = a.tiles_m * a.tiles_n;
+    auto launch = [&](auto km, auto split, auto b) -> hipError_t {
+        using Args = decltype(b);
+        constexpr auto kern = gemm_lora_kernel<128, 128, 2, 2, decltype(km)::value, false, false, decltype(split)::value, false, 0, Args>;
+        constexpr int smem = kSmallTileLds > GradCfg<Args::kRp, 4>::SMEM ? kSmallTileLds : GradCfg<Args::kRp, 4>::SMEM;
+        static_assert(2 * smem <= 160 * 1024, "two blocks per CU");
+        const hipError_t e = allow_lds<kern>(smem);
+        if (e != hipSuccess) return e;
+        static_cast<GemmArgs &>(b) = a;
+        b.band_m = gemm_band_rows(128, a.K, a.tiles_m);
+        b.dB = dB;
+        b.dA = dA;
+        b.dB_blocks = n_grad * ((dB.N + 63) / 64);
+        b.blocks = b.dB_blocks + n_grad * ((dA.N + 63) / 64);
+        COLLM_LAUNCH(kern, dim3(((tiles + 7) & ~7) + (((b.blocks + n_split - 1) / n_split + 7) & ~7), n_split), dim3(256), smem, st, b);
+        return hipGetLastError();
+    };
+    auto by_rank = [&](auto km, auto split) -> hipError_t {
+        return rpad <= 16 ? launch(km, split, GemmGradArgs<16>()) : launch(km, split, GemmGradArgs<kGemmGradRank>());
+    };
+    auto by_split = [&](auto km) -> hipError_t { return n_split > 1 ? by_rank(km, std::true_type()) : by_rank(km, std::false_type()); };
+    return b_kmajor ? by_split(std::true_type()) : by_split(std::false_type());
+}
+
 hipError_t launch_gemm_finish(const GemmArgs &a, int n_split, hipStream_t st)
 {
     if (a.n_rows <= 0) return hipSuccess;
@@ -2058,7 +2124,7 @@ static hipError_t launch_grad_t(const GradArgs &a, int n_grad, int rpad, hipStre
     const hipError_t e = allow_lds<kern>(grad_lds_bytes(C::SMEM, true));
     if (e != hipSuccess) return e;
     const dim3 grid((a.N + 63) / 64, n_grad, (rpad + RP - 1) / RP);
-    COLLM_LAUNCH(kern, grid, dim3(C::KW * 64), grad_lds_bytes(C::SMEM, a.beside_gemm != 0), st, a);
+    COLLM_LAUNCH(kern, grid, dim3(grad_waves(RP) * 64), grad_lds_bytes(C::SMEM, a.beside_gemm != 0), st, a);
     return hipGetLastError();
 }
 
