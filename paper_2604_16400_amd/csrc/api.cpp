@@ -498,26 +498,49 @@ bool decode_sized(const collm_ctx *c, const collm_shape *s, const int32_t *rank,
 struct GradsBeside {
     GradArgs dB, dA;
     int n_grad, rpad;
+    int slices = 0;  // of K
     bool done = false;
 };
 
-// Whether they do: one launch saves the two points at which the caller's stream hands over to the second one (5 us of idle time each) and the
-// kernel that packs h, but the gradients' blocks are half as wide and share the CUs with the GEMM's, so only where all of the GEMM's blocks run at
-// once and the gradients end before them in the places they leave.  A K tile of a GEMM block takes 0.9 us, a chunk of 128 rows of a gradient block
-// 1.2.  Passes (forward and backward), two streams / one launch, us: four layers 4096 -> 4096, 2048 tokens, rank 16 603 / 580; 740 tokens
-// 5632 -> 2528 rank 32 448 / 406, 2147 tokens 7424 -> 1792 151 / 138, 1148 tokens 6496 -> 3072 rank 64 700 / 660; 45 batches 1.009, none slower.  Where
-// the comparison is missed by up to 2.5 as many lose as gain (1096 -> 4864 rank 64 256 / 277, 13072 -> 2360 294 / 280).
-bool grads_in_gemm(const collm_ctx *c, int n_train, int d_in, int d_out, bool b_kmajor, int rpad)
+// Slices of K of a dX GEMM with the gradients in its launch, or 0 where they have kernels of their own (serial: on the caller's stream).  One
+// launch saves the two points at which the caller's stream hands over to the second one (5 us of idle time each), or two kernels in a
+// chain, and the kernel that packs h; but the gradients' blocks are half as wide and share the CUs with the GEMM's.  A K tile of one of two
+// GEMM blocks on a CU takes 0.9 us (0.48 of one alone, which leaves no place for a gradient), a chunk of 128 rows of a gradient block 1.2; the
+// sums are written and read at 8 TB/s.
+//  - GEMM of two blocks per CU beside the second stream: where the gradients end before its blocks in the places they leave.  Passes (forward and
+//    backward), us: four layers 4096 -> 4096, 2048 tokens, rank 16 603 / 580; 740 tokens 5632 -> 2528 rank 32 448 / 406, 1148 tokens
+//    6496 -> 3072 rank 64 700 / 660; 45 batches 1.009, none slower.  Where they miss it by up to 2.5 as many lose as gain (1096 -> 4864 rank 64
+//    256 / 277, 13072 -> 2360 294 / 280).
+//  - GEMM of one block per CU, or a call on one stream: the number of slices at which GEMM and gradients end first, if it is at most 8 (one
+//    stream: 10) us behind the GEMM without them.  469 tokens 1056 -> 5496 rank 16 151 / 114, 733 tokens 1280 -> 2816 rank 64 357 / 289, 257 tokens
+//    2992 -> 4096 rank 64 347 / 312; on one stream 271 tokens 3072 -> 1208 445 / 365, 401 tokens 1536 -> 2304 rank 8 114 / 98, 712 tokens 1280 -> 1280
+//    rank 32 264 / 229; 36 batches 1.05 times as fast; at 10 us 1418 tokens 1792 -> 4136 rank 32 184 / 192, on one stream at 12 us 257
+//    tokens 12544 -> 6488 728 / 750.
+int grads_in_gemm(const collm_ctx *c, int n_train, int d_in, int d_out, bool b_kmajor, int rpad, bool serial)
 {
-    if (c->grad_streams >= 0 || c->tile_bwd >= 0 || c->gemm_split >= 0 || rpad > kGemmGradRank) return false;
+    if (c->grad_streams >= 0 || c->tile_bwd >= 0 || c->gemm_split >= 0 || rpad > kGemmGradRank || c->L.train.bm != 128) return 0;
     const Tiling t = choose_tiling(c, n_train, d_in, d_out, b_kmajor, true, true, false, c->tile_steps_train);
-    if (t.tile != kTile128x128 || t.tail_tiles_m > 0) return false;
+    if (t.tile != kTile128x128 || t.tail_tiles_m > 0) return 0;
     bool alone = false;
     const long n = std::max(1L, gemm_slices(c, c->L.train, 0, t.big_tiles_m, d_in, d_out, b_kmajor, &alone));
-    if (n > 1 && alone) return false;
-    const long gemm = (long)t.big_tiles_m * ((d_in + 127) / 128) * n, grads = (long)c->L.n_grad * ((d_in + 63) / 64 + (d_out + 63) / 64);
-    const double gemm_us = 0.9 * ((d_out + 64 * n - 1) / (64 * n)), grad_us = 5.0 + 1.2 * ((c->L.max_grad_rows + 127) / 128);
-    return gemm < kSplitBlocks && grads * grad_us <= gemm_us * (kSplitBlocks - gemm);
+    const long tiles = (long)t.big_tiles_m * ((d_in + 127) / 128), grads = (long)c->L.n_grad * ((d_in + 63) / 64 + (d_out + 63) / 64);
+    const double grad_us = grads * (5.0 + 1.2 * ((c->L.max_grad_rows + 127) / 128));
+    auto gemm_us = [&](long slices, double tile_us) { return tile_us * ((d_out + 64 * slices - 1) / (64 * slices)); };
+    if (!serial && !(n > 1 && alone)) return tiles * n < kSplitBlocks && grad_us <= gemm_us(n, 0.9) * (kSplitBlocks - tiles * n) ? (int)n : 0;
+    // (wider ranks' blocks have more sums to write)
+    const double grads_us = rpad <= 16 ? grad_us : grads * (8.0 + 1.8 * ((c->L.max_grad_rows + 127) / 128));
+    if (tiles > kSplitBlocks / 2) return 0;  // (on one stream the tiles between the two sizes are better)
+    const double sum_us = (double)t.big_tiles_m * 128 * d_in * 8 / 8e6;
+    double best_us = gemm_us(n, n == 1 || alone ? 0.48 : 0.9) + (n > 1 ? n * sum_us : 0.0) + (serial ? 10.0 : 8.0);
+    int best = 0;
+    for (long k = 1; k <= n && tiles * k < kSplitBlocks; ++k) {
+        const double us = std::max(gemm_us(k, 0.9), grads_us / (kSplitBlocks - tiles * k)) + (k > 1 ? k * sum_us : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best = (int)k;
+        }
+    }
+    return best;
 }
 
 // One GEMM over the row order `R`: a single launch, or whole rounds of large tiles followed by
@@ -545,7 +568,8 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         const int tiles_n = (cols + 127) / 128;
         const bool whole = !swiglu && g.n_sib <= 1 && row_base == 0 && t.tail_tiles_m == 0;
         bool alone = false;
-        const long want = gemm_slices(c, R, row_base / 128, tiles_m, cols, g.K, b_kmajor, whole ? &alone : nullptr);
+        const bool with_grads = beside && whole;
+        const long want = with_grads ? beside->slices : gemm_slices(c, R, row_base / 128, tiles_m, cols, g.K, b_kmajor, whole ? &alone : nullptr);
         if (want < 2) return false;
         GemmArgs gs = g;
         gs.tiles_m = tiles_m;
@@ -558,7 +582,7 @@ hipError_t run_gemm(collm_ctx *c, GemmArgs g, const RowOrderLayout &R, int rows,
         gs.one_per_cu = alone;
         gs.row_base = row_base;
         gs.n_rows = n_rows_here;
-        if (beside && whole && !alone) {
+        if (with_grads) {
             err = launch_gemm_grads(gs, n_split, b_kmajor, beside->dB, beside->dA, beside->n_grad, beside->rpad, st);
             beside->done = true;
         } else {
@@ -1873,8 +1897,10 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // Small batches stay on the caller's stream (see grads_alone).
     const bool alone = c->grad_streams >= 0 ? c->grad_streams == 0 : grads_alone(n_train, s->d_in, s->d_out, f32, L.rpad);
     // Or in the dX GEMM's launch, where that leaves places free (grads_in_gemm).
-    const bool may_fuse = dA && dx && !alone && !c->profile && !f32 && P == 1 && !may_dual && dx != x && dx != dy && L.n_grad > 0;
-    const bool fused = may_fuse && grads_in_gemm(c, n_train, s->d_in, s->d_out, !tr, L.rpad);
+    const bool may_fuse = dA && dx && !c->profile && !f32 && P == 1 && !may_dual && dx != x && dx != dy && L.n_grad > 0;
+    GradsBeside beside{};
+    beside.slices = may_fuse ? grads_in_gemm(c, n_train, s->d_in, s->d_out, !tr, L.rpad, alone) : 0;
+    const bool fused = beside.slices > 0;
     const bool overlap = dA && !alone && !fused && !c->profile;
     const bool one_round = dx_one_round(c, n_train, s->d_in, s->d_out, f32, L.rpad);
     // fp32 on one stream: dB beside dh, dA beside dX
@@ -1967,7 +1993,6 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         if (rc != COLLM_OK) return rc;
         HIP_TRY(launch_dual_sum(du, st));
     }
-    GradsBeside beside{};
     // dB_a = s h^T dy
     const bool late = overlap && !dual && dx && P == 1 && !dx_even && fork_behind_dh(L.rpad, s->d_in, s->d_out);
     auto launch_dB = [&]() -> int {
@@ -2129,7 +2154,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
                 HIP_TRY(launch_gemm_f32(g, !tr, st));
             }
         } else {
-            HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, one_round, st, false, fused ? &beside : nullptr));
+            HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, one_round && !fused, st, false, fused ? &beside : nullptr));
             if (fused && !beside.done) {
                 HIP_TRY(launch_grad(beside.dB, L.n_grad, L.rpad, st));
                 HIP_TRY(launch_grad(beside.dA, L.n_grad, L.rpad, st));

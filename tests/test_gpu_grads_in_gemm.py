@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("transposed", [False, True])
 @pytest.mark.parametrize("d_in,d_out,ranks,lens", [
-    (200, 392, [64], [129]), (72, 1000, [40, 12], [1, 31, 33, 160]), (1032, 264, [64, 3, 24], [200, 1, 64, 17]),
+    (200, 392, [64], [129]), (264, 136, [16], [257]), (1096, 2056, [16, 5], [65, 300]), (264, 136, [16], [257]), (1096, 2056, [16, 5], [65, 300]), (72, 1000, [40, 12], [1, 31, 33, 160]), (1032, 264, [64, 3, 24], [200, 1, 64, 17]),
     (136, 520, [48] * 19, [3] * 38)])  # (more trained adapters than travel as arguments)
 def test_small(d_in, d_out, ranks, lens, transposed):
     n = len(lens)
@@ -35,7 +35,7 @@ def test_small(d_in, d_out, ranks, lens, transposed):
 
 
 @pytest.mark.parametrize("transposed", [False, True])
-@pytest.mark.parametrize("rows,d_in,d_out,rank", [(1792, 4096, 1024, 16), (400, 5632, 2528, 32), (1000, 2056, 4104, 64), (130, 7000, 8200, 12)])
+@pytest.mark.parametrize("rows,d_in,d_out,rank", [(1792, 4096, 1024, 16), (400, 5632, 2528, 32), (1000, 2056, 4104, 64), (386, 1280, 2816, 64), (411, 1056, 5496, 16), (77, 3072, 1208, 16), (386, 1280, 2816, 64), (411, 1056, 5496, 16), (77, 3072, 1208, 16), (130, 7000, 8200, 12)])
 def test_large(rows, d_in, d_out, rank, transposed):
     g = torch.Generator(device="cuda").manual_seed(rows)
     rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda")
