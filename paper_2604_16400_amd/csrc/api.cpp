@@ -335,7 +335,7 @@ long gemm_slices(int forced, int64_t part_bytes, int tiles_m, int cols, int K, b
 // columns that do not exist cost up to four times as much.  Times (us a K tile of a block, sums read and written per us, fixed) fitted to 63
 // forward calls of 128 to 3600 rows, weights from memory; the margin is what separates all that lost from all that gained.
 // GEMM with its sums inside whole calls, us, 128x128 / 256x256: 512 rows 22016 -> 5856 237 / 147 and 204 / 157 (backward), 1024 rows 4096 <- 22016 with the
-// gradients beside it 214 / 160, 768 rows 9216 -> 4272 93 / 80, 2048 rows 22016 -> 1280 175 / 144, 256 rows 24832 -> 8792 199 / 144; outside the
+// gradients beside it 214 / 165, 768 rows 9216 -> 4272 93 / 80, 2048 rows 22016 -> 1280 175 / 144, 256 rows 24832 -> 8792 199 / 144; outside the
 // line 384 rows 15616 -> 10752 154 / 167, 599 rows 6912 -> 3840 56 / 66, 833 rows 12800 -> 1792 63 / 70, 896 rows 27136 -> 1024 level.
 long large_slices(int64_t part_bytes, int rows, int cols, int K, bool b_kmajor, int steps)
 {
