@@ -291,9 +291,9 @@ int collm_debug_host_gemm_slices(int tiles_m, int cols, int K, int b_kmajor, int
 /*
  * Debug, HOST only (no GPU): the same for a plain GEMM (one projection, forward or dX without gradient kernels beside it), which may
  * also take tiles between the two sizes: *tile = 0 (256x256), 1 (256x128), 2 (128x128), 3 (128x192) or 4 (256x192) for the
- * first rows; *slices of K and *one_per_cu (0/1: at most one block per CU, with a ring of LDS stages) of 128x128 tiles that
- * are the whole GEMM.  (dX beside gradient kernels: the two sizes; its 128x128 tiles take the same slices in the same way, and are
- * never one per CU uncut.)  steps: 16-wide low-rank K-steps of all the 128-row tiles.
+ * first rows; *slices of K and *one_per_cu (0/1: at most one block per CU) of 128x128 tiles (with a ring of LDS stages) or 256x256 tiles that
+ * are the whole GEMM.  (dX beside gradient kernels: the two sizes; its tiles take the same slices in the same way, 128x128 ones are
+ * never one per CU uncut, and with the gradients in the same launch two per CU.)  steps: 16-wide low-rank K-steps of all the 128-row tiles.
  */
 int collm_debug_host_plain_gemm(int rows, int cols, int K, int b_kmajor, int steps, int64_t workspace_bytes, int32_t *tile,
                                 int32_t *slices, int32_t *one_per_cu);
