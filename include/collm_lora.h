@@ -323,6 +323,15 @@ int collm_debug_host_tile_order(int tile_rows, int tiles_m, int tiles_n, int K, 
                                 int32_t *tile_m, int32_t *tile_n);
 
 /*
+ * Debug, HOST only (no GPU): the same for a dX GEMM on 128x128 tiles in n_slices slices of K with grad_blocks blocks of the adapter gradients in
+ * its launch (workgroups start in the order of their ids): for workgroup id 0, 1, .. the slice and the tile of the GEMM (all -1: none) and
+ * the block of the gradients (-1: none).  slice, tile_m, tile_n, grad: HOST, tiles_m * tiles_n * n_slices rounded up to a multiple of 8, plus
+ * grad_blocks, entries.  Returns that number or a negative status.
+ */
+int collm_debug_host_shared_order(int tiles_m, int tiles_n, int n_slices, int K, int grad_blocks, int32_t *slice, int32_t *tile_m,
+                                  int32_t *tile_n, int32_t *grad);
+
+/*
  * Debug, HOST only (no GPU): the order in which the plan lists the rows of a batch for the GEMM
  * over all rows (training_rows_only = 0) or over the training rows (1), and the number of
  * 16-wide low-rank K-steps every row tile of tile_rows (64, 128 or 256) rows carries.

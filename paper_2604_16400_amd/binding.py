@@ -124,6 +124,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.collm_debug_host_tile_order.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _i32p,
                                                 _i32p, _i32p]
     lib.collm_debug_host_tile_order.restype = ctypes.c_int
+    lib.collm_debug_host_shared_order.argtypes = [ctypes.c_int] * 5 + [_i32p] * 4
+    lib.collm_debug_host_shared_order.restype = ctypes.c_int
     lib.collm_debug_host_row_order.argtypes = [sp, _i32p, _i32p, _i32p, _u8p, ctypes.c_int, ctypes.c_int, _i32p, _i32p]
     lib.collm_debug_host_row_order.restype = ctypes.c_int
     lib.collm_debug_set_tiles.argtypes = [vp, ctypes.c_int, ctypes.c_int]
@@ -251,6 +253,17 @@ def host_tile_order(tile_rows: int, tiles_m: int, tiles_n: int, K: int, band: in
                                            tm.ctypes.data_as(_i32p), tn.ctypes.data_as(_i32p)),
            "collm_debug_host_tile_order")
     return used.value, tm, tn
+
+
+def host_shared_order(tiles_m: int, tiles_n: int, n_slices: int, K: int, grad_blocks: int):
+    """(slice, tile_m, tile_n, gradient block) of every workgroup id of a dX GEMM with the adapter gradients in its launch, -1 where it has none
+    (host logic, no GPU)."""
+    lib = load_library()
+    out = [np.full((tiles_m * tiles_n * n_slices + 7) // 8 * 8 + grad_blocks, -7, dtype=np.int32) for _ in range(4)]
+    n = lib.collm_debug_host_shared_order(tiles_m, tiles_n, n_slices, K, grad_blocks, *[o.ctypes.data_as(_i32p) for o in out])
+    _check(min(n, 0), "collm_debug_host_shared_order")
+    assert n == len(out[0])
+    return tuple(out)
 
 
 def host_row_order(rank, seg_start, seg_adapter, seg_is_train, tile_rows: int = 256, training_rows_only: bool = False):

@@ -1526,6 +1526,16 @@ int collm_debug_host_tile_order(int tile_rows, int tiles_m, int tiles_n, int K, 
     return COLLM_OK;
 }
 
+int collm_debug_host_shared_order(int tiles_m, int tiles_n, int n_slices, int K, int grad_blocks, int32_t *slice, int32_t *tile_m,
+                                  int32_t *tile_n, int32_t *grad)
+{
+    if (!slice || !tile_m || !tile_n || !grad) return COLLM_E_NULL;
+    if (tiles_m <= 0 || tiles_n <= 0 || n_slices < 1 || K <= 0 || grad_blocks < 0 ||
+        (int64_t)tiles_m * tiles_n * n_slices + grad_blocks > (1 << 24))
+        return COLLM_E_SHAPE;
+    return host_shared_order(tiles_m, tiles_n, n_slices, K, grad_blocks, slice, tile_m, tile_n, grad);
+}
+
 int collm_debug_host_tiling(int rows, int cols, int K, int can_split, int32_t *tile, int32_t *big_tiles_m,
                             int32_t *tail_tiles_m, int32_t *tail_cols)
 {

@@ -205,6 +205,9 @@ hipError_t launch_dual_sum(const DualArgs &a, hipStream_t st);
 // row tiles (0 = none), and the band the launchers choose for a tile height and contraction length (host only).
 void host_tile_order(int tiles_m, int tiles_n, int band, int32_t *tm, int32_t *tn);
 int gemm_band_rows(int tile_rows, int K, int tiles_m);
+// ... and of launch_gemm_grads: slice and tile of every workgroup id (-1: not the GEMM's) and its block of the gradients (-1: none); returns the
+// number of ids (host only)
+int host_shared_order(int tiles_m, int tiles_n, int n_slices, int K, int grad_blocks, int32_t *slice, int32_t *tm, int32_t *tn, int32_t *grad);
 hipError_t launch_gemm(const GemmArgs &a, int tile_cfg, bool b_kmajor, hipStream_t st);
 // The GEMM with K cut into n_split slices of k_per_split (128x128 or 256x256 tiles): fp32 sums of slice s for row r of the row order at
 // part[(s * part_rows + r) * part_ld + n] (part_ld >= N, a multiple of 4), then launch_gemm_finish adds the slices, rounds

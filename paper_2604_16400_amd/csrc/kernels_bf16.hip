@@ -234,7 +234,7 @@ constexpr bool rows_early(int bm, int bn, int rs) { return rs ? rs == 2 : bm * b
 // [rows][N = d_ff]; training rows also keep both pre-activations.
 // SIBS: sibling projections side by side in the columns; the low-rank extension then loads the rows' operand per
 // batch at the sibling's offset inside each adapter's ranks (see the extension below).
-// SPLITK: the GEMM itself with K cut into gridDim.y slices (few rows against a long contraction: too few tiles to
+// SPLITK: the GEMM itself with K cut into slices_of(p) slices (few rows against a long contraction: too few tiles to
 // fill the GPU).  A block takes one tile, one slice and its share of the tile's extension steps; the fp32
 // sums go to the workspace and gemm_finish_kernel adds the slices, rounds once and scatters the rows.
 // LDS stages of the PARTIAL loop (128x128 tiles: 32 KiB each).  The loop is bound by what a wave has to issue per
@@ -245,16 +245,27 @@ constexpr bool rows_early(int bm, int bn, int rs) { return rs ? rs == 2 : bm * b
 // (With the 16-row items in the same launch, whose registers leave one block per CU, four in both.)
 constexpr int kWideStages = 4;
 constexpr int wide_stages(bool t_kmajor) { return t_kmajor ? kWideStages : 2; }
-// The dX GEMM with the gradients dB_a and dA_a (ranks up to RP) in blocks of the same launch, behind its own: columns of blocks, the first at
-// a multiple of 8 blocks so that the GEMM's blocks keep their XCDs.
+// The dX GEMM with the gradients dB_a and dA_a (ranks up to RP) in blocks of the same launch: the GEMM's blocks of all slices first, as they are
+// without gradients (blocks start in the order of their ids, and an id's last three bits are its XCD), the gradients' from the next multiple of 8
+// on.  With a share of the gradients' blocks behind each slice's, as the rows of a two-dimensional grid, slices wait for gradients where the two
+// together exceed the places, and an XCD gets pieces of several slices: backward calls, that order / this one, us, 304 rows of four adapters 8776 <- 15176
+// rank 32 (207 tiles, 2 slices) 207 / 187, 70 rows of three 27120 <- 26288 414 / 388; 72 batches in 2 to 23 slices 1.07 times as fast (0.92 .. 1.33).
 template <int RP>
 struct GemmGradArgs : GemmArgs {
     static constexpr int kRp = RP;
     GradArgs dB, dA;
+    int n_slices;           // of K
     int dB_blocks, blocks;  // of dB, of both
 };
+__host__ __device__ constexpr int first_grad_block(int tiles, int n_slices) { return (tiles * n_slices + 7) & ~7; }
 template <typename Args> constexpr bool kWithGrads = false;
 template <int RP> constexpr bool kWithGrads<GemmGradArgs<RP>> = true;
+template <typename Args>
+__device__ __forceinline__ int slices_of(const Args &p)
+{
+    if constexpr (kWithGrads<Args>) return p.n_slices;
+    else return gridDim.y;
+}
 template <int RP, bool SMALL_BF, int KW>
 __device__ __forceinline__ void grad_block(const GradArgs &p, int col_block, int item, int rank_slice, uint8_t *smem);
 
@@ -297,7 +308,8 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WGM, wn = wave / WGM;
-    int tile_m, tile_n, slice = 0;
+    int tile_m, tile_n, slice = 0, n_slices = 1;
+    if constexpr (SPLITK) n_slices = slices_of(p);
     int m0, K, N, rows_in = BM;
     const void *a_base = p.a, *b_base = p.b;
     uint32_t a_bytes = p.a_bytes, b_bytes = p.b_bytes, ldb = (uint32_t)p.ldb;
@@ -343,12 +355,12 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
         b_base = pass_table(pass_args(p), it.adapter) + b_skip;
         b_bytes = B_KMAJOR ? (uint32_t)N * ldb * 2u - b_skip : (uint32_t)K * ldb * 2u;
     } else {
-        int pid = SPLITK ? blockIdx.y * gridDim.x + blockIdx.x : blockIdx.x;
+        const int pid = SPLITK && !kWithGrads<Args> ? blockIdx.y * gridDim.x + blockIdx.x : blockIdx.x;
         if constexpr (kWithGrads<Args>) {
-            const int tiles = p.tiles_m * p.tiles_n, pad = (tiles + 7) & ~7;
-            if ((int)blockIdx.x >= tiles) {
-                const int e = ((int)blockIdx.x - pad) * (int)gridDim.y + (int)blockIdx.y;
-                if ((int)blockIdx.x < pad || e >= p.blocks) return;
+            const int tiles = p.tiles_m * p.tiles_n;
+            if (pid >= tiles * p.n_slices) {
+                const int e = pid - first_grad_block(tiles, p.n_slices);
+                if (e < 0) return;
                 constexpr int RP = Args::kRp, KW = NT / 64;
                 if (e < p.dB_blocks) {
                     const int cols = (p.dB.N + 63) >> 6;
@@ -360,10 +372,9 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
                 }
                 return;
             }
-            pid = (int)blockIdx.y * tiles + (int)blockIdx.x;
         }
         if constexpr (SPLITK) {
-            slice_coords(pid, p.tiles_m, p.tiles_n, (int)gridDim.y, slice, tile_m, tile_n);
+            slice_coords(pid, p.tiles_m, p.tiles_n, n_slices, slice, tile_m, tile_n);
         } else {
             tile_coords(pid, p.tiles_m, p.tiles_n, p.band_m, tile_m, tile_n);
         }
@@ -420,8 +431,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64, (!PARTIAL && RS == 0 && BM * BN
     if constexpr (SPLITK) {
         // the slices share the tile's batches of extension steps: a decode batch of 64 adapters has more steps in its
         // one row tile than K tiles, and a slice that ran them all would finish last
-        const int batches = (e1 - e0 + kExtBatch - 1) / kExtBatch, n_sl = (int)gridDim.y, sl = slice;
-        const int lo = batches * sl / n_sl, hi = batches * (sl + 1) / n_sl;
+        const int batches = (e1 - e0 + kExtBatch - 1) / kExtBatch, lo = batches * slice / n_slices, hi = batches * (slice + 1) / n_slices;
         e1 = e1 < e0 + hi * kExtBatch ? e1 : e0 + hi * kExtBatch;
         e0 += lo * kExtBatch;
     }
@@ -1822,6 +1832,24 @@ void host_tile_order(int tiles_m, int tiles_n, int band, int32_t *tm, int32_t *t
     }
 }
 
+int host_shared_order(int tiles_m, int tiles_n, int n_slices, int K, int grad_blocks, int32_t *slice, int32_t *tm, int32_t *tn, int32_t *grad)
+{
+    const int gemm = tiles_m * tiles_n * n_slices, first = first_grad_block(tiles_m * tiles_n, n_slices);
+    for (int id = 0; id < first + grad_blocks; ++id) {
+        int s = -1, m = -1, n = -1;
+        if (id < gemm) {
+            s = 0;
+            if (n_slices > 1) slice_coords(id, tiles_m, tiles_n, n_slices, s, m, n);
+            else tile_coords(id, tiles_m, tiles_n, gemm_band_rows(128, K, tiles_m), m, n);
+        }
+        slice[id] = s;
+        tm[id] = m;
+        tn[id] = n;
+        grad[id] = id < first ? -1 : id - first;
+    }
+    return first + grad_blocks;
+}
+
 template <auto KERN> struct Kernel { static constexpr auto fn = KERN; };  // a kernel as an argument that keeps its identity
 
 template <int BM, int BN, bool KM, bool SWIGLU = false, bool SIBS = false, int RS = 0>
@@ -1995,9 +2023,10 @@ hipError_t launch_gemm_grads(const GemmArgs &a, int n_split, bool b_kmajor, cons
         b.band_m = gemm_band_rows(128, a.K, a.tiles_m);
         b.dB = dB;
         b.dA = dA;
+        b.n_slices = n_split;
         b.dB_blocks = n_grad * ((dB.N + 63) / 64);
         b.blocks = b.dB_blocks + n_grad * ((dA.N + 63) / 64);
-        COLLM_LAUNCH(kern, dim3(((tiles + 7) & ~7) + (((b.blocks + n_split - 1) / n_split + 7) & ~7), n_split), dim3(256), smem, st, b);
+        COLLM_LAUNCH(kern, dim3(first_grad_block(tiles, n_split) + b.blocks), dim3(256), smem, st, b);
         return hipGetLastError();
     };
     auto by_rank = [&](auto km, auto split) -> hipError_t {

@@ -235,6 +235,24 @@ def test_gemm_tile_order_visits_every_tile_once_and_keeps_bands_together():
 
 
 
+@pytest.mark.parametrize("tiles_m,tiles_n,n_slices", [(2, 30, 4), (1, 212, 2), (3, 11, 8), (1, 1, 3), (5, 13, 1), (40, 11, 1)])
+def test_gradients_in_the_gemm_s_launch_start_behind_all_of_its_slices(tiles_m, tiles_n, n_slices):
+    tiles, grads = tiles_m * tiles_n, 19
+    sl, tm, tn, gr = (a.astype(np.int64) for a in binding.host_shared_order(tiles_m, tiles_n, n_slices, 4096, grads))
+    gemm = tiles * n_slices
+    first = (gemm + 7) // 8 * 8
+    assert (gr[:first] == -1).all() and (gr[first:] == np.arange(grads)).all() and (sl[gemm:] == -1).all()
+    assert sorted((sl * tiles + tm * tiles_n + tn)[:gemm]) == list(range(gemm))  # every tile of every slice once
+    if n_slices == 1:
+        _, m, n = binding.host_tile_order(128, tiles_m, tiles_n, 4096)
+        assert (m == tm[:gemm]).all() and (n == tn[:gemm]).all()
+        return
+    # an XCD (the id's last three bits) has one run of the tiles of one slice after the other
+    run = [sl[x:gemm:8] * tiles + (tm[x:gemm:8] // 8) * 8 * tiles_n + tn[x:gemm:8] * np.minimum(8, tiles_m - tm[x:gemm:8] // 8 * 8) + tm[x:gemm:8] % 8
+           for x in range(8)]
+    assert (np.concatenate(run) == np.arange(gemm)).all()
+
+
 def test_marshalling_takes_the_plain_forms_and_leaves_the_rest():
     """The compiled marshalling calls the library for contiguous int32 / uint8 arrays and pointer tables (here it reports
     the missing context) and hands everything else back to the binding's general path."""

@@ -67,6 +67,11 @@ def test_the_dx_gemm_beside_gradient_kernels(run, rows, d_in, d_out, streams, wa
     run("dx_gemm", rows, d_in, d_out, streams, want)
 
 
+@pytest.mark.parametrize("rows,d_in,d_out,tiles,slices", [(247, 7384, 1792, 116, 2), (96, 4160, 1536, 33, 6), (1792, 4096, 4096, 448, 1)])
+def test_the_launch_of_the_dx_gemm_and_the_gradients(run, rows, d_in, d_out, tiles, slices):
+    run("shared_launch", rows, d_in, d_out, tiles, slices)
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -272,6 +277,15 @@ def dx_gemm(w, rows, d_in, d_out, streams, want):
     gemms = [l[0].split("<", 1)[1].split(", ") for l in w.launches() if "gemm_lora_kernel" in l[0]]
     gemms = [f"{a[0]}, {a[1]} {'sliced' if a[7] == 'true' else 'whole'} {a[9]}" for a in gemms if a[5] == "false"]
     assert gemms == [want], gemms
+
+
+def shared_launch(w, rows, d_in, d_out, tiles, slices):
+    # one dimension: workgroups start in the order of their ids, the GEMM's of every slice before the gradients'
+    ctx = w.context()
+    assert Batch(w, ctx, [int(rows)], [0], [1], [16], int(d_in), int(d_out)).bwd() == 0
+    got = [(l[0], l[1]) for l in w.launches() if "GemmGradArgs" in l[0]]
+    n = len(w.binding.host_shared_order(1, int(tiles), int(slices), int(d_out), -(-int(d_in) // 64) + -(-int(d_out) // 64))[0])
+    assert len(got) == 1 and got[0][1] == (n, 1, 1), (got, n)
 
 
 if __name__ == "__main__":
