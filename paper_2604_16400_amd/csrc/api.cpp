@@ -516,6 +516,11 @@ struct GradsBeside {
 //    2992 -> 4096 rank 64 347 / 312; on one stream 271 tokens 3072 -> 1208 445 / 365, 401 tokens 1536 -> 2304 rank 8 114 / 98, 712 tokens 1280 -> 1280
 //    rank 32 264 / 229; 36 batches 1.05 times as fast; at 10 us 1418 tokens 1792 -> 4136 rank 32 184 / 192, on one stream at 12 us 257
 //    tokens 12544 -> 6488 728 / 750.
+//  - Never where one block's rows take longer than all that: it walks the rows of its adapter in four waves, 1.3 us for 128 of them up to rank 16, 3.6
+//    beyond (64 rank columns whatever the rank), while the kernels of their own have eight waves up to rank 32 and start beside the dh pass.  Backward calls,
+//    two streams / one launch: one adapter of rank 32 with 6288 rows 784 <- 768 79 / 206, of rank 64 with 3381 rows 344 <- 536 92 / 124, of rank 16 with
+//    5995 rows 768 <- 472 72 / 75.  780 drawn calls of 100 to 9000 rows: level at nine chunks of 128 rows (rank 16: 37), or where the GEMM covers them two and
+//    a half times; 151 of them were more than 3 % slower in one launch, of the 573 inside this line 8 are (down to 0.885), those outside it 0.84.
 int grads_in_gemm(const collm_ctx *c, int n_train, int d_in, int d_out, bool b_kmajor, int rpad, bool serial)
 {
     if (c->grad_streams >= 0 || c->tile_bwd >= 0 || c->gemm_split >= 0 || rpad > kGemmGradRank || c->L.train.bm != 128) return 0;
@@ -523,12 +528,15 @@ int grads_in_gemm(const collm_ctx *c, int n_train, int d_in, int d_out, bool b_k
     if (t.tile != kTile128x128 || t.tail_tiles_m > 0) return 0;
     bool alone = false;
     const long n = std::max(1L, gemm_slices(c, c->L.train, 0, t.big_tiles_m, d_in, d_out, b_kmajor, &alone));
+    const int chunks = (c->L.max_grad_rows + 127) / 128;
     const long tiles = (long)t.big_tiles_m * ((d_in + 127) / 128), grads = (long)c->L.n_grad * ((d_in + 63) / 64 + (d_out + 63) / 64);
-    const double grad_us = grads * (5.0 + 1.2 * ((c->L.max_grad_rows + 127) / 128));
+    const double grad_us = grads * (5.0 + 1.2 * chunks);
     auto gemm_us = [&](long slices, double tile_us) { return tile_us * ((d_out + 64 * slices - 1) / (64 * slices)); };
+    const double block_us = rpad <= 16 ? 5.0 + 1.3 * chunks : 8.0 + 3.6 * chunks;
+    if (chunks > (rpad <= 16 ? 37 : 9) && block_us > 0.4 * gemm_us(n, 0.9)) return 0;
     if (!serial && !(n > 1 && alone)) return tiles * n < kSplitBlocks && grad_us <= gemm_us(n, 0.9) * (kSplitBlocks - tiles * n) ? (int)n : 0;
     // (wider ranks' blocks have more sums to write)
-    const double grads_us = rpad <= 16 ? grad_us : grads * (8.0 + 1.8 * ((c->L.max_grad_rows + 127) / 128));
+    const double grads_us = rpad <= 16 ? grad_us : grads * (8.0 + 1.8 * chunks);
     if (tiles > kSplitBlocks / 2) return 0;  // (on one stream the tiles between the two sizes are better)
     const double sum_us = (double)t.big_tiles_m * 128 * d_in * 8 / 8e6;
     double best_us = gemm_us(n, n == 1 || alone ? 0.48 : 0.9) + (n > 1 ? n * sum_us : 0.0) + (serial ? 10.0 : 8.0);

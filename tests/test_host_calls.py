@@ -72,6 +72,12 @@ def test_the_launch_of_the_dx_gemm_and_the_gradients(run, rows, d_in, d_out, til
     run("shared_launch", rows, d_in, d_out, tiles, slices)
 
 
+@pytest.mark.parametrize("rows,d_in,d_out,rank,want", [
+    (1152, 1024, 1024, 64, 1), (1153, 1024, 1024, 64, 0), (4736, 512, 1024, 16, 1), (4737, 512, 1024, 16, 0), (1300, 4864, 9216, 64, 1), (1300, 4864, 8192, 64, 0)])
+def test_gradients_of_many_rows_are_not_in_the_dx_gemm_s_launch(run, rows, d_in, d_out, rank, want):
+    run("many_rows", rows, d_in, d_out, rank, want)
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -286,6 +292,13 @@ def shared_launch(w, rows, d_in, d_out, tiles, slices):
     got = [(l[0], l[1]) for l in w.launches() if "GemmGradArgs" in l[0]]
     n = len(w.binding.host_shared_order(1, int(tiles), int(slices), int(d_out), -(-int(d_in) // 64) + -(-int(d_out) // 64))[0])
     assert len(got) == 1 and got[0][1] == (n, 1, 1), (got, n)
+
+
+def many_rows(w, rows, d_in, d_out, rank, want):
+    # one gradient block walks all rows of its adapter
+    ctx = w.context(max_tokens=8192)
+    assert Batch(w, ctx, [int(rows)], [0], [1], [int(rank)], int(d_in), int(d_out)).bwd() == 0
+    assert sum("GemmGradArgs" in l[0] for l in w.launches()) == int(want)
 
 
 if __name__ == "__main__":
