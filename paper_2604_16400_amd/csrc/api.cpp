@@ -1794,6 +1794,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         Prof prof(c, st, "gemm_fwd");
         if (f32) {
             g.n_rows = s->n_tokens;
+            g.tile_steps = L.all.n_ext / ((L.all.n_rows + 63) / 64);
             HIP_TRY(launch_gemm_f32(g, tr, st));
         } else {
             HIP_TRY(run_gemm(c, g, L.all, s->n_tokens, s->d_out, c->tile_fwd, tr, P <= 1, st, swiglu));
@@ -2164,8 +2165,9 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         Prof prof(c, st, "gemm_dx");
         if (f32) {
             g.n_rows = n_train;
+            g.tile_steps = L.train.n_ext / ((L.train.n_rows + 63) / 64);
             // (a caller's dx in the place of its x: dA reads x first)
-            if (pair && dx != x && gemm_f32_short_blocks(g)) {
+            if (pair && dx != x && gemm_f32_with_dA(g, !tr)) {
                 HIP_TRY(launch_dx_dA_f32(g, ga, L.rpad, !tr, st));
             } else {
                 if (pair) HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, st));

@@ -66,6 +66,7 @@ struct GemmArgs {
     const int32_t *row_tok;   // [tiles_m * BM]
     const int32_t *ext_off;   // [tiles_m + 1]
     const ExtStep *ext;
+    int tile_steps;           // fp32: extension steps of a row tile, on average
     const void *hs;           // low-rank activations of the rows, [rows][hs_ld], row order
     int hs_ld;
     uint32_t hs_bytes;        // size of hs
@@ -327,9 +328,9 @@ hipError_t launch_adamw(const AdamWArgs &a, bool bf16, hipStream_t st);
 // fp32 element type: same argument blocks, fp32 MFMAs (16x16x4)
 hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st);  // a.n_rows: rows of the order
 hipError_t launch_skinny_f32(const SkinnyArgs &a, int n_items, bool t_kmajor, hipStream_t st);
-// dh beside dB, dX beside dA, where no table is beyond 32-bit offsets (pair_f32) and the GEMM runs on blocks of 16 rows (gemm_f32_short_blocks)
+// dh beside dB, dX beside dA, where no table is beyond 32-bit offsets (pair_f32) and the GEMM's blocks have 16 rows (gemm_f32_with_dA)
 bool pair_f32(int rpad, int d_in, int d_out);
-bool gemm_f32_short_blocks(const GemmArgs &a);
+bool gemm_f32_with_dA(const GemmArgs &a, bool b_kmajor);
 hipError_t launch_dh_dB_f32(const SkinnyArgs &s, const GradArgs &g, int rpad, bool t_kmajor, hipStream_t st);
 hipError_t launch_dx_dA_f32(const GemmArgs &m, const GradArgs &g, int rpad, bool b_kmajor, hipStream_t st);
 hipError_t launch_grad_f32(const GradArgs &a, int n_grad, int rpad, hipStream_t st);

@@ -80,8 +80,12 @@ static bool table_is_big(int rank, int d) { return (int64_t)rank * d * 4 > 0x7ff
 // One block = 16 RT rows x 16 NC columns; its KW waves split K (and the extension steps) between them.  Column i of
 // 16-column block c is n0 + NC i + c: a lane's NC columns are then consecutive both where it loads the second
 // operand ([K][N]) and where it stores.
+// AHEAD: a wave asks for the operands of its next trip behind the products of this one, and for its first extension step before the first: shorter
+// chains where few blocks share a CU.  Else it asks at the start of a trip and multiplies what has come while the rest is on its way, which is
+// better with many: forward calls of 32-row blocks, us, ahead / not: 546 rows 1416 -> 3536 87 / 70, 912 rows 3948 -> 2916 [N][K] 328 / 275, 200 drawn
+// ones 1.12 (up to 256 blocks of 16 x 64), 1.09 (512), 1.00 (2048), 0.96.
 template <int RT, int KW, int NC> constexpr int kF32GemmRed = KW * 16 * RT * (16 * NC + 4);  // floats of LDS
-template <bool B_KMAJOR, int RT, int KW, bool BIG, int NC>
+template <bool B_KMAJOR, int RT, int KW, bool BIG, int NC, bool AHEAD>
 __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by, float *red)
 {
     using idx_t = std::conditional_t<BIG, uint64_t, uint32_t>;
@@ -119,26 +123,35 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
     constexpr int U = RT == 1 ? 4 : 2;
     floatx4 xa[U][RT];
     std::conditional_t<B_KMAJOR, floatx4, cols_t> wb[U][B_KMAJOR ? NC : 4];
+    auto load_w = [&](int k0, int u) {
+        const int k = k0 + u * 16 + kg * 4;
+        // [K][N]: K value k + j, columns n ..; [N][K]: column n + j, K values k .. k + 3
+#pragma unroll
+        for (int j = 0; j < (B_KMAJOR ? NC : 4); ++j) {
+            const bool on = k < k_hi && n + (B_KMAJOR ? j : 0) < N;
+            if constexpr (B_KMAJOR) wb[u][j] = f32_load4(rb, on ? ((uint32_t)(n + j) * (uint32_t)p.ldb + (uint32_t)k) * 4u : kF32Oob);
+            else wb[u][j] = f32_load<NC>(rb, on ? ((uint32_t)(k + j) * (uint32_t)p.ldb + (uint32_t)n) * 4u : kF32Oob);
+        }
+    };
+    auto load_x = [&](int k0, int u) {
+        const int k = k0 + u * 16 + kg * 4;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) xa[u][t] = f32_load4(ra, k < k_hi && aoff[t] != kF32Oob ? aoff[t] + (uint32_t)k * 4u : kF32Oob);
+    };
     auto load = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = k0 + u * 16 + kg * 4;
-            // [K][N]: K value k + j, columns n ..; [N][K]: column n + j, K values k .. k + 3
-#pragma unroll
-            for (int j = 0; j < (B_KMAJOR ? NC : 4); ++j) {
-                const bool on = k < k_hi && n + (B_KMAJOR ? j : 0) < N;
-                if constexpr (B_KMAJOR) wb[u][j] = f32_load4(rb, on ? ((uint32_t)(n + j) * (uint32_t)p.ldb + (uint32_t)k) * 4u : kF32Oob);
-                else wb[u][j] = f32_load<NC>(rb, on ? ((uint32_t)(k + j) * (uint32_t)p.ldb + (uint32_t)n) * 4u : kF32Oob);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = k0 + u * 16 + kg * 4;
-#pragma unroll
-            for (int t = 0; t < RT; ++t) xa[u][t] = f32_load4(ra, k < k_hi && aoff[t] != kF32Oob ? aoff[t] + (uint32_t)k * 4u : kF32Oob);
+            load_x(k0, u);
+            load_w(k0, u);
         }
     };
-    load(k_lo);
+    if constexpr (AHEAD) {
+        // (the rows' tokens are on their way while the weight is asked for)
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_w(k_lo, u);
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_x(k_lo, u);
+    }
 
     // Low-rank extension: one step = 16 rank indices of one adapter's table against the rows of its run.  A wave's first step is asked for
     // behind its first operands, not behind the contraction: what a small call takes is a chain of trips to memory.
@@ -185,9 +198,10 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
     if (e0 + wave < e1) load_step(e0 + wave, s);
 
     for (int k0 = k_lo; k0 < k_hi;) {
+        if constexpr (!AHEAD) load(k0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (k0 + 16 * u >= k_hi) break;
+            if (AHEAD && k0 + 16 * u >= k_hi) break;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -199,7 +213,7 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
                     }
         }
         k0 += 16 * U;
-        if (k0 < k_hi) load(k0);
+        if (AHEAD && k0 < k_hi) load(k0);
     }
 
     // The products of a step are summed apart and added to the rows of the run only, so that a table's infinities
@@ -251,11 +265,11 @@ __device__ __forceinline__ void gemm_f32_block(const GemmArgs &p, int bx, int by
     }
 }
 
-template <bool B_KMAJOR, int RT, int KW, bool BIG, int NC>
+template <bool B_KMAJOR, int RT, int KW, bool BIG, int NC, bool AHEAD = true>
 __global__ void __launch_bounds__(KW * 64) gemm_f32_kernel(GemmArgs p)
 {
     __shared__ __align__(16) float red[kF32GemmRed<RT, KW, NC>];
-    gemm_f32_block<B_KMAJOR, RT, KW, BIG, NC>(p, blockIdx.x, blockIdx.y, red);
+    gemm_f32_block<B_KMAJOR, RT, KW, BIG, NC, AHEAD>(p, blockIdx.x, blockIdx.y, red);
 }
 
 // out[m][q] = sum_k in[tok(m)][k] table_a(k, q): one block = one item (up to 16 rows of one adapter) x 16 columns of
@@ -419,7 +433,7 @@ __global__ void __launch_bounds__(512) dx_dA_f32_kernel(GemmArgs m, GradArgs g)
 {
     __shared__ __align__(16) float red[std::max(kF32GemmRed<1, 8, NC>, kF32GradRed)];
     const int b = blockIdx.x, cols = (m.N + 16 * NC - 1) / (16 * NC), first = cols * ((m.n_rows + 15) / 16);
-    if (b < first) gemm_f32_block<B_KMAJOR, 1, 8, false, NC>(m, b % cols, b / cols, red);
+    if (b < first) gemm_f32_block<B_KMAJOR, 1, 8, false, NC, true>(m, b % cols, b / cols, red);
     else grad_f32_blocks(g, b - first, red);
 }
 
@@ -493,22 +507,32 @@ hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t st)
     return hipGetLastError();
 }
 
-// Blocks of 16 rows and eight waves, of as few columns as pays: the smaller a block, the fewer products in its waves' chains and the more CUs at work, but
-// the more often the rows and the weight are read.  By blocks of 16 rows x 64 columns; whole step (forward and backward call) with 16 / 32 / 64 columns / 32 rows and four
-// waves a block, us:
-//   16 blocks, K 256 15.5 / 17.0 / 19.4 / 27;  64, K 1024 21.0 / 24.7 / 31.4 / 41.9;  128, K 1024 25.6 / 24.9 / 30.9 / 41.4;  200, K 512 21.1 / 21.6 / 23.4 / 31.2;  256, K 1024
-//   31.4 / 29.1 / 31.4 / 42.0;  512, K 512 29.9 / 30.4 / 32.5 / 37.3, K 1024 40.3 / 38.6 / 38.1 / 42.4;  1000, K 512 42.2 / 38.6 / 37.9 / 40.3, K 1024 60.2 / 57.2 / 53.0 / 54.5
+// Blocks of 16 rows and eight waves: a block's products are the shorter a chain the fewer columns it has, but the rows and the weight are read the more
+// often.  16 columns up to 64 blocks of 16 rows x 64 columns, up to 128 on a short contraction, else 32; 64 columns while that is one block per CU; beyond
+// a CU has two blocks to run one after the other, and 32 rows with four waves, which read the weight half as often, are better.  Forward calls by
+// number of 16 x 64 blocks, the time of the best over that of 16 / 32 / 64 columns / 32 rows, geometric means over 1100 drawn ones of few extension steps:
+//   to 64    K <= 512 1.00 / 0.96 / 0.90 / 0.84, longer 1.00 / 0.89 / 0.73 / 0.57
+//   to 128   K <= 512 0.99 / 0.98 / 0.93 / 0.84, longer 0.91 / 0.99 / 0.85 / 0.65
+//   to 256   K <= 512 0.95 / 0.96 / 0.98 / 0.91, longer 0.86 / 0.90 / 0.98 / 0.78
+//   to 512   K <= 512 0.90 / 0.91 / 0.89 / 1.00, longer 0.76 / 0.86 / 0.86 / 0.99;  beyond 0.6 .. 0.8 / 0.7 .. 0.8 / 0.7 .. 0.8 / 1.00
+// Extension steps (of a row tile) are trips to memory that the waves share, and a step costs by its columns, most with [N][rank] tables, which
+// are read element by element: 16 columns then up to 256 blocks (45 rows 772 -> 1352 of 14 adapters of rank 128 21.5 / 29.2 us with 16 / 32), with [N][rank]
+// tables up to 512 (more than six steps and K <= 512 1.00 / 0.92 / 0.85 / 0.85), with the other ones on many steps and a short contraction.
+// With dA in the same launch (dX of a backward call; its blocks have 16 rows) 32 columns are best up to 512 blocks of K <= 1024: 0.98, and 0.94 for
+// 32 rows and a launch of its own for dA; longer 0.89 and 0.95, more blocks 0.92 and 0.99.
 static int64_t blocks_16x64(const GemmArgs &a) { return (int64_t)((a.N + 63) / 64) * ((a.n_rows + 15) / 16); }
-bool gemm_f32_short_blocks(const GemmArgs &a)
-{
-    return !(a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) && blocks_16x64(a) < 1024;
-}
-static int short_block_cols(const GemmArgs &a)  // in sixteens
+static int short_block_cols(const GemmArgs &a, bool b_kmajor, bool with_dA)  // in sixteens; 0: 32 rows
 {
     const int64_t blocks = blocks_16x64(a);
-    if (blocks >= 768) return 4;
-    return a.K <= 512 || blocks * a.K < 131072 ? 1 : 2;
+    if (a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) return 0;
+    if (blocks <= 64) return 1;
+    if (blocks <= 128) return a.K <= 512 || a.tile_steps > (b_kmajor ? 6 : 16) ? 1 : 2;
+    if (blocks <= 256) return a.tile_steps > (b_kmajor ? 6 : 40) ? 1 : 4;
+    if (blocks > 512) return 0;
+    if (with_dA) return a.K <= 1024 ? 2 : 0;
+    return (b_kmajor || a.K <= 512) && a.tile_steps > (b_kmajor && a.K <= 512 ? 6 : 16) ? 1 : 0;
 }
+bool gemm_f32_with_dA(const GemmArgs &a, bool b_kmajor) { return short_block_cols(a, b_kmajor, true) > 0; }
 
 hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
 {
@@ -527,22 +551,21 @@ hipError_t launch_gemm_f32(const GemmArgs &a, bool b_kmajor, hipStream_t st)
     }
     const int rows = a.n_rows;  // (the row order is padded to a multiple of 256 rows)
     if (a.N <= 0 || rows <= 0) return hipSuccess;
-    // (then 32 rows and four waves: half the reads of the second operand)
     auto launch = [&](auto kern, int block_rows, int block_cols, int threads) {
         COLLM_LAUNCH(kern, dim3((a.N + block_cols - 1) / block_cols, (rows + block_rows - 1) / block_rows), dim3(threads), 0, st, a);
     };
     if (a.hs_ld > 0 && table_is_big(a.hs_ld, a.N)) {  // (hs_ld: at least the largest rank)
-        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, true, 4>, 32, 64, 256);
-        else launch(gemm_f32_kernel<false, 2, 4, true, 4>, 32, 64, 256);
-    } else if (gemm_f32_short_blocks(a)) {
-        switch (short_block_cols(a)) {
-        case 1: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 1>, 16, 16, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 1>, 16, 16, 512); break;
-        case 2: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 2>, 16, 32, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 2>, 16, 32, 512); break;
-        default: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 4>, 16, 64, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 4>, 16, 64, 512); break;
-        }
-    } else {
-        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, false, 4>, 32, 64, 256);
-        else launch(gemm_f32_kernel<false, 2, 4, false, 4>, 32, 64, 256);
+        if (b_kmajor) launch(gemm_f32_kernel<true, 2, 4, true, 4, false>, 32, 64, 256);
+        else launch(gemm_f32_kernel<false, 2, 4, true, 4, false>, 32, 64, 256);
+        return hipGetLastError();
+    }
+    switch (short_block_cols(a, b_kmajor, false)) {
+    case 1: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 1>, 16, 16, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 1>, 16, 16, 512); break;
+    case 2: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 2>, 16, 32, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 2>, 16, 32, 512); break;
+    case 4: b_kmajor ? launch(gemm_f32_kernel<true, 1, 8, false, 4>, 16, 64, 512) : launch(gemm_f32_kernel<false, 1, 8, false, 4>, 16, 64, 512); break;
+    default:
+        if (blocks_16x64(a) <= 1024 || a.K <= 512) b_kmajor ? launch(gemm_f32_kernel<true, 2, 4, false, 4>, 32, 64, 256) : launch(gemm_f32_kernel<false, 2, 4, false, 4>, 32, 64, 256);
+        else b_kmajor ? launch(gemm_f32_kernel<true, 2, 4, false, 4, false>, 32, 64, 256) : launch(gemm_f32_kernel<false, 2, 4, false, 4, false>, 32, 64, 256);
     }
     return hipGetLastError();
 }
@@ -567,7 +590,7 @@ hipError_t launch_grad_f32(const GradArgs &a, int n_grad, int rpad, hipStream_t 
     return hipGetLastError();
 }
 
-// (whoever calls these has looked at gemm_f32_short_blocks and pair_f32)
+// (whoever calls these has looked at gemm_f32_with_dA and pair_f32)
 bool pair_f32(int rpad, int d_in, int d_out) { return !table_is_big(rpad, std::max(d_in, d_out)); }
 hipError_t launch_dh_dB_f32(const SkinnyArgs &s, const GradArgs &g, int rpad, bool t_kmajor, hipStream_t st)
 {
@@ -579,7 +602,8 @@ hipError_t launch_dh_dB_f32(const SkinnyArgs &s, const GradArgs &g, int rpad, bo
 }
 hipError_t launch_dx_dA_f32(const GemmArgs &m, const GradArgs &g, int rpad, bool b_kmajor, hipStream_t st)
 {
-    const int nc = short_block_cols(m);
+    const int nc = short_block_cols(m, b_kmajor, true);
+    if (nc == 0) return hipErrorInvalidValue;
     const int blocks = (m.N + 16 * nc - 1) / (16 * nc) * ((m.n_rows + 15) / 16) + (g.N + 63) / 64 * g.n_items * ((rpad + 15) / 16);
     if (blocks <= 0) return hipSuccess;
     auto launch = [&](auto kern) { COLLM_LAUNCH(kern, dim3(blocks), dim3(512), 0, st, m, g); };

@@ -12,11 +12,14 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("transposed", [False, True])
 @pytest.mark.parametrize("d_in,d_out,lens", [
-    (520, 1028, [150, 31, 79]),    # forward 32 columns (289 blocks of 16 x 64, K 520), backward (K 1028) 16
-    (1028, 524, [33, 150, 279]),   # forward 32 columns, K no multiple of 16; backward 16
-    (68, 740, [700, 31, 369]),     # forward 64 columns (828 blocks), dX 16 of its 68
+    (520, 1028, [150, 31, 79]),    # forward 32 rows (289 blocks of 16 x 64), dX 64 columns (135), or 16 (K-major, steps)
+    (1028, 524, [33, 150, 279]),   # forward 32 rows, K no multiple of 16; dX of 312 rows 32 columns (340, K 524)
+    (68, 740, [700, 31, 369]),     # forward 32 rows (828 blocks), dX 64 columns of its 68
     (36, 1000, [700, 31, 369]),    # forward 32 rows (1104)
     (20, 12, [15, 1, 1]),          # a block wider than the output
+    (1036, 292, [33, 150, 71]),    # forward 32 columns (80, K 1036)
+    (1036, 516, [33, 150, 71]),    # forward 64 columns (144)
+    (524, 1100, [700, 31, 369]),   # forward 32 rows, loads not ahead (1242, K 524)
 ])
 def test_gemm_blocks(d_in, d_out, lens, transposed):
     w = wl.make_adhoc("f32", "f32", d_in, d_out, [5, 20, 16], lens, [0, 1, 2], [1, 0, 1], scale=0.5, seed=3)

@@ -78,6 +78,17 @@ def test_gradients_of_many_rows_are_not_in_the_dx_gemm_s_launch(run, rows, d_in,
     run("many_rows", rows, d_in, d_out, rank, want)
 
 
+@pytest.mark.parametrize("rows,d_in,d_out,layout,rank,n,fwd,dx", [
+    (64, 256, 1024, 0, 8, 1, "16x16", "16x16+dA"), (128, 1024, 512, 0, 8, 1, "16x16", "16x16+dA"),
+    (256, 1024, 512, 0, 8, 1, "16x32", "16x64+dA"), (256, 1024, 512, 0, 128, 16, "16x16", "16x16+dA"),  # steps
+    (512, 256, 512, 0, 8, 1, "16x64", "16x16+dA"), (512, 256, 512, 1, 64, 16, "16x16", "16x16+dA"),
+    (272, 1024, 1024, 0, 8, 1, "32x64", "16x32+dA"), (272, 2048, 1024, 0, 8, 1, "32x64", "32x64"),
+    (400, 512, 1024, 0, 64, 32, "16x16", "16x16+dA"), (400, 512, 1024, 1, 32, 32, "16x16", "16x64+dA"), (400, 1024, 1024, 1, 64, 32, "16x16", "16x32+dA"),
+    (1100, 1024, 1024, 0, 8, 1, "32x64 late", "32x64 late"), (1100, 512, 1024, 0, 8, 1, "32x64", "32x64")])
+def test_blocks_of_the_fp32_gemm(run, rows, d_in, d_out, layout, rank, n, fwd, dx):
+    run("f32_blocks", rows, d_in, d_out, layout, rank, n, fwd, dx)
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -299,6 +310,24 @@ def many_rows(w, rows, d_in, d_out, rank, want):
     ctx = w.context(max_tokens=8192)
     assert Batch(w, ctx, [int(rows)], [0], [1], [int(rank)], int(d_in), int(d_out)).bwd() == 0
     assert sum("GemmGradArgs" in l[0] for l in w.launches()) == int(want)
+
+
+def f32_blocks(w, rows, d_in, d_out, layout, rank, n, fwd, dx):
+    rows, n = int(rows), int(n)
+    ctx = w.context()
+    b = Batch(w, ctx, [rows // n + (k < rows % n) for k in range(n)], list(range(n)), [1] * n, [int(rank)] * n, int(d_in), int(d_out), "f32", int(layout))
+    def blocks():
+        for name, *_ in w.launches():
+            a = name.split("<", 1)[-1].rstrip(">").split(", ")
+            if "gemm_f32_kernel" in name:
+                return f"{16 * int(a[1])}x{16 * int(a[4])}{'' if a[5] == 'true' else ' late'}"
+            if "dx_dA_f32_kernel" in name:
+                return f"16x{16 * int(a[1])}+dA"
+    assert b.fwd() == 0
+    got = [blocks()]
+    assert b.bwd() == 0
+    got.append(blocks())
+    assert got == [fwd, dx], got
 
 
 if __name__ == "__main__":
