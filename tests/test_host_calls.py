@@ -89,6 +89,13 @@ def test_blocks_of_the_fp32_gemm(run, rows, d_in, d_out, layout, rank, n, fwd, d
     run("f32_blocks", rows, d_in, d_out, layout, rank, n, fwd, dx)
 
 
+@pytest.mark.parametrize("rows,d_in,d_out,layout,adapter,low,high", [
+    (8, 616, 13376, 1, -1, 0, 0), (8, 4096, 4096, 0, -1, 0, 0),  # no row with an adapter: the general path
+    (8, 4096, 4096, 0, 0, 32, 256)])
+def test_blocks_of_a_decode_sized_call(run, rows, d_in, d_out, layout, adapter, low, high):
+    run("decode_blocks", rows, d_in, d_out, layout, adapter, low, high)
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -328,6 +335,13 @@ def f32_blocks(w, rows, d_in, d_out, layout, rank, n, fwd, dx):
     assert b.bwd() == 0
     got.append(blocks())
     assert got == [fwd, dx], got
+
+
+def decode_blocks(w, rows, d_in, d_out, layout, adapter, low, high):
+    ctx = w.context(max_d=20000)
+    assert Batch(w, ctx, [int(rows)], [int(adapter)], [0], [16], int(d_in), int(d_out), layout=int(layout)).fwd() == 0
+    blocks = [l[1][0] for l in w.launches() if "decode_base_kernel" in l[0]]
+    assert int(low) <= sum(blocks) <= int(high) and len(blocks) == (int(high) > 0), blocks
 
 
 if __name__ == "__main__":
