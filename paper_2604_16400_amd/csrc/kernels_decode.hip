@@ -40,9 +40,14 @@ constexpr int red_bytes(int row_tiles) { return kWaves * row_tiles * 16 * kRedLd
 // from memory straight into operand registers, R rounds (16 KB each) per wave in flight: two, and one block per CU (128 KB in flight).
 // Tried: eight waves a block with half the rows each (every line of the weight asked for twice: 64 rows 8192 -> 28672 135 us instead of
 // 102), one round in flight and two blocks per CU (30 / 26), three rounds (registers spill; 38 / 34 for the call).
+// Every XCD (the block id's last three bits) takes one run of the strips of one slice after the other: the lines that two strips share (rows of the
+// weight that do not begin at a line) and the slice's share of x are then in one L2.  Calls, weights from memory, strips dealt out to the XCDs /
+// this: 12304 -> 6496 41 / 37 us, 9488 -> 21704 91 / 86; 28 of 20 million weights and more 1.05 (0.99 .. 1.15).
 template <int MT, int R, bool KM>
-__device__ __forceinline__ void base_block(const SkinnyArgs &p, const DecodeArgs &d, int pid, uint8_t *smem)
+__device__ __forceinline__ void base_block(const SkinnyArgs &p, const DecodeArgs &d, int blk, uint8_t *smem)
 {
+    const int total = d.strips * d.n_slices, per = total >> 3, rem = total & 7, xcd = blk & 7;
+    const int pid = xcd * per + (xcd < rem ? xcd : rem) + (blk >> 3);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const int strip = pid % d.strips, slice = pid / d.strips;
