@@ -1212,30 +1212,46 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
 
 
 // How the first kernel of a decode-sized call is cut: slices of K of each of the weight's strips, and of each of the shrink's `items`.  A block fills
-// a CU, and what is left over for a second round costs nearly as much as a first (64 rows of 4096 -> 11008, 56 items: two slices of 86 strips 27 us,
-// three 38), so the two kinds share the CUs: `h` slices of the shrink leave n slices of the strips, and the h is taken whose longer side is
-// shorter.  A wave's round of 64 values takes 1.45 .. 2.2 us by the number of rows, a quarter more with [N][K] weights, unless the weight's bytes
-// take longer; a chunk of the shrink's 64 values 0.4 us for ranks up to 16, else 1.3.  Whole calls, the general path / this, us: 8 rows 4096 -> 4096 24 / 17, 64 rows of 29 adapters
-// 4096 -> 11008 50 / 40 ([N][K]: 52 / 48), 64 rows 8192 -> 28672 122 / 116, 12 rows 1000 -> 28672 47 / 21, 64 rows 1024 -> 4096 30 / 20.
+// a CU, and the two kinds share the CUs.  Both numbers are taken by estimate (us):
+//  - a round of 256 values takes 1 .. 2.5 by the number of rows, a third more with [N][K] weights, and no less than the memory needs for what the
+//    blocks that run at once ask for (1.4 with a few, 2.7 with 256: 9656 -> 14256 in 112 blocks 84 us, in 224 55); a block 2 beside its rounds.
+//  - one round of blocks, or up to two where one would leave a quarter of the CUs idle (18312 -> 18120, 142 strips, 148 uncut, 126 in three slices: the
+//    second, partial round reads from memory beside the first); a slice keeps 192 values.
+//  - a block of the shrink 2 and a chunk of its 64 values 0.4 for ranks up to 16, else 1.3.
+//  - the second kernel: 0.8 a trip to memory (decode_sum_trips, of the largest item), or the sums' bytes (15104 -> 768, 34 rows: 31 us in 24 slices, 26 in ten).
+// No places are kept for the blocks that put in new table addresses (up to 16, short): four layers of 64 rows 4096 -> 11008 with tables of their own 167
+// us either way, and a call's sums must not depend on whether its tables are new.
+// 386 drawn calls of 1 to 64 rows, weights from memory: 0.98 of the best of the cuts tried; 260 others 1.32 times as fast as the general path (0.90 at
+// the least), 1.04 times as with slices for one round by chains and bytes alone.
 struct DecodeCut {
     int n_slices, k_per_slice, h_slices;
 };
-DecodeCut decode_cut(int T, int N, int K, bool kmajor, int rpad, int items, int cus, int64_t room)
+DecodeCut decode_cut(int T, int N, int K, bool kmajor, int rpad, int items, int item_rows, int cus, int64_t room)
 {
     const int strips = (N + kDecodeCols - 1) / kDecodeCols;
     const int64_t rows_h = (int64_t)round_up(T, 16) * rpad, rows_y = (int64_t)T * N;  // floats of a slice
-    const double round_us = (T <= 16 ? 1.45 : (T <= 32 ? 1.8 : 2.2)) * (kmajor ? 1.25 : 1.0), chunk_us = rpad <= 16 ? 0.4 : 1.3;
-    const double stream_us = (double)K * N * 2 / 5.0e6;
+    const double round_us = (T <= 16 ? 1.0 : (T <= 32 ? 1.6 : 2.5)) * (kmajor ? 1.3 : 1.0), chunk_us = rpad <= 16 ? 0.4 : 1.3;
     DecodeCut best{1, 0, 1};
-    double best_us = 1e30;
-    for (int h = 1; h <= 8 && (h == 1 || (items > 0 && h * 512 <= K && h * items < cus && h * rows_h + rows_y <= room)); ++h) {
-        long n = std::max(1, (cus - h * items) / strips);
-        n = std::max(1L, std::min<long>({n, (long)K / 512, (long)((room - h * rows_h) / rows_y)}));
-        const double base = std::max(stream_us, round_us * ((K + 256 * n - 1) / (256 * n))), shrink = items > 0 ? chunk_us * ((K + 256 * h - 1) / (256 * h)) : 0.0;
-        const double us = (strips * n + h * items <= cus ? std::max(base, shrink) : base + shrink) + (double)n * rows_y * 8 / 4.0e6;
-        if (us < best_us) {
-            best = {(int)n, 0, h};
-            best_us = us;
+    double best_us = 1e30, shrink[9];
+    long most[9];
+    int h_most = 0;
+    for (int h = 1; h <= 8 && (h == 1 || (items > 0 && h * 512 <= K && h * items < cus && h * rows_h + rows_y <= room)); h_most = h++) {
+        const long one = std::max(0L, (cus - (long)h * items) / strips);  // slices in one round
+        const long places = one * strips < cus * 3 / 4 ? 2L * cus / strips : one;
+        most[h] = std::max(1L, std::min<long>({places, (long)K / 192, (long)((room - h * rows_h) / rows_y)}));
+        shrink[h] = items > 0 ? 2.0 + chunk_us * ((K + 256 * h - 1) / (256 * h)) : 0.0;
+    }
+    for (long n = 1; n <= most[1]; n += n < 16 ? 1 : 4) {  // (the fewer slices of the shrink, the more there may be of the strips)
+        const long blocks = strips * n, rounds = (round_up((int)((K + n - 1) / n), 64) + 255) / 256;
+        auto at_once = [&](long b) { return b > 0 ? rounds * std::max(round_us, 1.4 + 0.005 * b) + 2.0 : 0.0; };
+        const double base = (blocks / cus) * at_once(cus) + at_once(blocks % cus);
+        const double sums = std::max((double)n * rows_y * 8 / 4.0e6, 0.8 * decode_sum_trips(item_rows, (int)n));
+        for (int h = 1; h <= h_most; ++h) {
+            const double us = (blocks + (long)h * items <= cus ? std::max(base, shrink[h]) : base + 0.7 * shrink[h]) + sums;
+            if (n <= most[h] && us < best_us) {
+                best = {(int)n, 0, h};
+                best_us = us;
+            }
         }
     }
     best.k_per_slice = round_up((K + best.n_slices - 1) / best.n_slices, 64);
@@ -1252,7 +1268,10 @@ int run_decode(collm_ctx *c, const collm_shape *s, const void *x, const void *W,
     const int T = s->n_tokens, N = s->d_out, K = s->d_in;
     const int strips = (N + kDecodeCols - 1) / kDecodeCols, rows_h = round_up(T, 16);
     const int h_cols = L.rpad <= 16 ? 1 : (L.rpad + kDecodeRankCols - 1) / kDecodeRankCols;
-    const DecodeCut cut = decode_cut(T, N, K, tr, L.rpad, R.n_items * h_cols, std::max(c->n_cus, 1), (int64_t)c->part_bytes / 4);
+    const SkinnyItem *items = reinterpret_cast<const SkinnyItem *>(c->plan.data() + R.off_items);
+    int item_rows = std::min(R.n_base, 16);
+    for (int i = 0; i < R.n_items; ++i) item_rows = std::max(item_rows, items[i].n_rows);
+    const DecodeCut cut = decode_cut(T, N, K, tr, L.rpad, R.n_items * h_cols, item_rows, std::max(c->n_cus, 1), (int64_t)c->part_bytes / 4);
     const int n_slices = cut.n_slices;
     SkinnyArgs a{};
     a.in = x;
@@ -1278,7 +1297,6 @@ int run_decode(collm_ctx *c, const collm_shape *s, const void *x, const void *W,
     d.h_cols = h_cols;
     d.scale = s->scale;
     d.n_base = R.n_base;
-    const SkinnyItem *items = reinterpret_cast<const SkinnyItem *>(c->plan.data() + R.off_items);
     for (int i = 0; i < R.n_items; ++i)
         d.items[i] = {(uint32_t)items[i].row_lo | (uint32_t)items[i].n_rows << 16, (uint32_t)items[i].rank, (uint64_t)(uintptr_t)B[items[i].adapter]};
     // the shrink's sums behind those of the slices

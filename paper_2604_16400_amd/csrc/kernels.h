@@ -269,6 +269,12 @@ struct DecodeItem {
 struct DecodeFinishArgs : DecodeArgs {
     DecodeItem items[kDecodeRows];
 };
+// trips to memory in which the second kernel's threads read the sums of `rows` rows (of an item)
+inline int decode_sum_trips(int rows, int n_slices)
+{
+    if (rows <= 4) return (rows + 1) / 2 * (n_slices / 8 + (n_slices % 8 >= 4) + n_slices % 4);
+    return (rows + 7) / 8 * ((n_slices + 1) / 2);
+}
 hipError_t launch_decode_base(const SkinnyArgs &a, const DecodeArgs &d, int rpad, bool kmajor, hipStream_t st, const PlanPatch *patch);
 hipError_t launch_decode_finish(const SkinnyArgs &a, const DecodeFinishArgs &d, bool kmajor, hipStream_t st);
 

@@ -260,8 +260,9 @@ __global__ void __launch_bounds__(256, 3) decode_finish_kernel(SkinnyArgs p, Dec
         for (int e = 0; e < 4; ++e) h[e] = q + e < rank ? h[e] * d.scale : 0.f;
         *reinterpret_cast<uint2 *>(lows + m * low_ld + q) = make_uint2(pack_bf16(h[0], h[1]), pack_bf16(h[2], h[3]));
     }
-    // (a thread's quads lie two rows apart; four of them, two slices each, are asked for at a time, or eight slices of one where there are many)
-    if (d.n_slices > 8) {
+    // (a thread's quads lie two rows apart; what counts is the number of trips: eight slices of one of its at most two quads are asked for at a time,
+    // or two slices of four; decode_sum_trips)
+    if (n_rows <= 4) {
         for (int idx = tid; idx < n_rows * (kFinishCols / 4); idx += 256) {
             const int m = idx / (kFinishCols / 4), q = (idx % (kFinishCols / 4)) * 4;
             if (cb + q < d.N) *reinterpret_cast<floatx4 *>(sums + m * kSumLd + q) = sum_slices(d.part + (int64_t)(row_lo + m) * d.N + cb + q, (int64_t)d.n_rows * d.N, d.n_slices);

@@ -78,6 +78,14 @@ def test_all_rows_on_the_base_weight(transposed):
 
 
 @pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("rows,ranks", [(1, [8]), (4, [16, 8]), (5, [16]), (13, [8, 16]), (64, [8] * 20)])
+def test_many_slices(rows, ranks, transposed):
+    # a narrow output: up to 32 slices, added eight at a time (items of up to four rows) or two at a time (more rows)
+    for d_in, d_out in ((12296, 264), (16384, 136)):
+        _check(rows, d_in, d_out, ranks, transposed, seed=rows + d_in, base=0.0 if rows < 8 else 0.2)
+
+
+@pytest.mark.parametrize("transposed", [False, True])
 def test_layers_in_turn_with_tables_of_their_own(transposed):
     # the batch's plan stays, new table addresses ride on the first kernel
     lens, ads = _batch(21, 5, 9)

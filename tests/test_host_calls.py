@@ -91,7 +91,9 @@ def test_blocks_of_the_fp32_gemm(run, rows, d_in, d_out, layout, rank, n, fwd, d
 
 @pytest.mark.parametrize("rows,d_in,d_out,layout,adapter,low,high", [
     (8, 616, 13376, 1, -1, 0, 0), (8, 4096, 4096, 0, -1, 0, 0),  # no row with an adapter: the general path
-    (8, 4096, 4096, 0, 0, 32, 256)])
+    (16, 9656, 14256, 0, 0, 2 * 112, 256),    # 112 strips: one slice leaves more than half of the CUs idle
+    (3, 18312, 16384, 0, 0, 2 * 128 + 1, 512),  # 128 strips and the shrink: one slice or a second, partial round
+    (34, 15104, 768, 0, 0, 6 * 6, 6 * 17 + 8 * 3), (64, 1024, 4096, 0, 0, 32, 256)])  # few blocks add the slices
 def test_blocks_of_a_decode_sized_call(run, rows, d_in, d_out, layout, adapter, low, high):
     run("decode_blocks", rows, d_in, d_out, layout, adapter, low, high)
 
