@@ -414,10 +414,13 @@ long gemm_slices(const collm_ctx *c, const RowOrderLayout &R, int first, int til
 // (33 MB: 4-5 us, of which the GEMM gives back 1-3).  Measured, whole forward call in us with / without the fetch,
 // 4096 -> 4096: 8 rows 32 / 29, 64 rows 36 / 32, 256 rows 47 / 44, 512 rows level, 1003 rows (one slice) 65 / 71;
 // 1024 -> 1024 (2 MB): 22 / 24 and 26 / 28.
-bool warm_pays(const collm_ctx *c, const RowOrderLayout &R, int rows, int cols, int K, bool b_kmajor, bool one_round, bool siblings)
+// grad_slices: 0, or the slices of a dX GEMM with the gradients in its launch, which has two blocks per CU whatever it would take alone.  Backward calls
+// whose GEMM alone would be cut or in the ring, weights from memory: 90 shapes 1.06 times as fast with the fetch (1.00 .. 1.12; 79 tokens 5600 <- 824 26 / 23 us).
+bool warm_pays(const collm_ctx *c, const RowOrderLayout &R, int rows, int cols, int K, bool b_kmajor, bool one_round, bool siblings, int grad_slices = 0)
 {
     constexpr int64_t kWarmSlicedMaxBytes = (int64_t)8 << 20;
     if ((int64_t)cols * K * 2 <= kWarmSlicedMaxBytes) return true;
+    if (grad_slices > 0) return grad_slices == 1;
     const bool can_split = c->gemm_split != 1;
     const Tiling t = choose_tiling(c, rows, cols, K, b_kmajor, !siblings, can_split, one_round, tile_steps(c, R));
     if (t.slices > 1) return false;
@@ -2112,7 +2115,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         // dh came out of the pass over dy above, together with dB
     } else if (P == 1) {
         rc = run_skinny(c, s, L.train, dy, s->d_out, L.off_B_ptr, !tr, c->d_dh32, L.rpad, L.rpad, 0, s->scale,
-                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, L.train, n_train, s->d_in, s->d_out, !tr, one_round, false) ? W : nullptr,
+                        c->d_dhs, s->scale, "dh", st, nullptr, !f32 && dx && warm_pays(c, L.train, n_train, s->d_in, s->d_out, !tr, one_round, false, beside.slices) ? W : nullptr,
                         (uint64_t)s->d_in * s->d_out * 2, nullptr, 0, pair ? &ga : nullptr);
         if (rc != COLLM_OK) return rc;
     } else {

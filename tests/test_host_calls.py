@@ -98,6 +98,13 @@ def test_blocks_of_a_decode_sized_call(run, rows, d_in, d_out, layout, adapter, 
     run("decode_blocks", rows, d_in, d_out, layout, adapter, low, high)
 
 
+@pytest.mark.parametrize("rows,d_in,d_out,rank,fetched", [
+    (52, 7392, 672, 8, 1), (39, 11184, 928, 32, 1),  # uncut with the gradients in the launch (alone it would be cut)
+    (96, 4160, 1536, 16, 0), (1792, 4096, 4096, 16, 1)])  # in slices; two streams' worth of tiles
+def test_the_dh_pass_fetches_the_weight_for_the_gemm_that_runs(run, rows, d_in, d_out, rank, fetched):
+    run("fetched_weight", rows, d_in, d_out, rank, fetched)
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -344,6 +351,16 @@ def decode_blocks(w, rows, d_in, d_out, layout, adapter, low, high):
     assert Batch(w, ctx, [int(rows)], [int(adapter)], [0], [16], int(d_in), int(d_out), layout=int(layout)).fwd() == 0
     blocks = [l[1][0] for l in w.launches() if "decode_base_kernel" in l[0]]
     assert int(low) <= sum(blocks) <= int(high) and len(blocks) == (int(high) > 0), blocks
+
+
+def fetched_weight(w, rows, d_in, d_out, rank, fetched):
+    # weights beyond 8 MiB; 256 blocks behind the items of the pass
+    ctx = w.context()
+    assert Batch(w, ctx, [int(rows)], [0], [1], [int(rank)], int(d_in), int(d_out)).bwd() == 0
+    l = w.launches()
+    gemm = [x for x in l if "GemmGradArgs" in x[0]]
+    dh = [x for x in l if "skinny_kernel" in x[0] or "gemm_lora_kernel<128, 128, 4, 2" in x[0]]
+    assert len(gemm) == 1 and len(dh) == 1 and (dh[0][1][0] >= 256) == bool(int(fetched)), l
 
 
 if __name__ == "__main__":
