@@ -47,6 +47,8 @@ constexpr int kMaxProfile = 16;
 constexpr int64_t kDualMinBytes = (int64_t)192 << 20;  // training rows of dy from which dh and dB come from one pass (bwd_impl)
 
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
+// whether n bytes at p and m bytes at q have none in common
+inline bool apart(const void *p, int64_t n, const void *q, int64_t m) { return (uintptr_t)p + n <= (uintptr_t)q || (uintptr_t)q + m <= (uintptr_t)p; }
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
@@ -1944,8 +1946,16 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     // caller's stream again before the call returns.  (Serial when kernels are being timed.)
     // Small batches stay on the caller's stream (see grads_alone).
     const bool alone = c->grad_streams >= 0 ? c->grad_streams == 0 : grads_alone(n_train, s->d_in, s->d_out, f32, L.rpad);
-    // Or in the dX GEMM's launch, where that leaves places free (grads_in_gemm).
-    const bool may_fuse = dA && dx && !c->profile && !f32 && P == 1 && !may_dual && dx != x && dx != dy && L.n_grad > 0;
+    // Or in the dX GEMM's launch, where that leaves places free (grads_in_gemm).  Not where a buffer that the launch writes lies in one that another part
+    // of it reads: a dx in the place of what the gradients read, a dA in that of h, which are behind them otherwise.
+    const int64_t T = s->n_tokens, esz = f32 ? 4 : 2;
+    bool own = dA && dx && apart(dx, T * s->d_in * esz, x, T * s->d_in * esz);
+    const bool dx_behind_dA = own;  // (fp32)
+    own = own && apart(dx, T * s->d_in * esz, dy, T * s->d_out * esz) && apart(dx, T * s->d_in * esz, h_save, h_save ? T * c->max_rank * 4 : 0);
+    for (int k = 0; own && h_save && k < s->n_segments; ++k)
+        if (seg_is_train[k] && seg_start[k + 1] > seg_start[k])
+            own = apart(dA[seg_adapter[k]], (int64_t)s->d_in * rank[seg_adapter[k]] * 4, h_save, T * c->max_rank * 4);
+    const bool may_fuse = own && !c->profile && !f32 && P == 1 && !may_dual && L.n_grad > 0;
     GradsBeside beside{};
     beside.slices = may_fuse ? grads_in_gemm(c, n_train, s->d_in, s->d_out, !tr, L.rpad, alone) : 0;
     const bool fused = beside.slices > 0;
@@ -1955,7 +1965,6 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     const bool pair = f32 && dA && alone && !c->profile && pair_f32(L.rpad, s->d_in, s->d_out);
     hipStream_t gs = overlap ? c->side : st;
     GradArgs ga{};
-    const int64_t esz = f32 ? 4 : 2;
     ga.row_tok = c->d_plan + L.train.off_row_tok;
     ga.items = reinterpret_cast<const GradItem *>(c->d_plan + L.off_grad);
     ga.n_items = L.n_grad;
@@ -2195,8 +2204,8 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
         if (f32) {
             g.n_rows = n_train;
             g.tile_steps = L.train.n_ext / ((L.train.n_rows + 63) / 64);
-            // (a caller's dx in the place of its x: dA reads x first)
-            if (pair && dx != x && gemm_f32_with_dA(g, !tr)) {
+            // (a caller's dx in the place of its x, or part of it: dA reads x first)
+            if (pair && dx_behind_dA && gemm_f32_with_dA(g, !tr)) {
                 HIP_TRY(launch_dx_dA_f32(g, ga, L.rpad, !tr, st));
             } else {
                 if (pair) HIP_TRY(launch_grad_f32(ga, L.n_grad, L.rpad, st));

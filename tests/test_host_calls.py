@@ -105,6 +105,11 @@ def test_the_dh_pass_fetches_the_weight_for_the_gemm_that_runs(run, rows, d_in, 
     run("fetched_weight", rows, d_in, d_out, rank, fetched)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_a_dx_in_the_place_of_what_the_gradients_read_comes_behind_them(run, dtype):
+    run("overlapping", dtype)
+
+
 # ---------------------------------------------------------------------------------------------------------------------------
 # the process of a scenario
 
@@ -130,10 +135,10 @@ class Batch:
         return self.lib.collm_lora_linear_fwd(self.ctx, ctypes.byref(self.shape), 0x10000, 0x20000, self._tab(layer, 0), self._tab(layer, 1),
                                               *self.seg, 0x30000, 0x40000, stream)
 
-    def bwd(self, layer=0, stream=STREAM, dx=0x60000, grads=0):
+    def bwd(self, layer=0, stream=STREAM, dx=0x60000000, grads=0, x=0x10000, dy=0x50000000, h=0x40000000):
         g = (self._tab(grads, 2), self._tab(grads, 3)) if grads is not None else (None, None)
-        return self.lib.collm_lora_linear_bwd(self.ctx, ctypes.byref(self.shape), 0x10000, 0x20000, self._tab(layer, 0), self._tab(layer, 1),
-                                              *self.seg, 0x50000, 0x40000, dx, *g, 0, stream)
+        return self.lib.collm_lora_linear_bwd(self.ctx, ctypes.byref(self.shape), x, 0x20000000, self._tab(layer, 0), self._tab(layer, 1),
+                                              *self.seg, dy, h, dx, *g, 0, stream)
 
     def on_device(self):
         """Whether the plan on the device is of this batch (it begins with the segment of every token)."""
@@ -361,6 +366,22 @@ def fetched_weight(w, rows, d_in, d_out, rank, fetched):
     gemm = [x for x in l if "GemmGradArgs" in x[0]]
     dh = [x for x in l if "skinny_kernel" in x[0] or "gemm_lora_kernel<128, 128, 4, 2" in x[0]]
     assert len(gemm) == 1 and len(dh) == 1 and (dh[0][1][0] >= 256) == bool(int(fetched)), l
+
+
+def overlapping(w, dtype):
+    ctx = w.context()
+    b = Batch(w, ctx, [100, 28], [0, 1], [1, 0], [16, 16], 256, 512, dtype)
+    e = 2 if dtype == "bf16" else 4
+    names = ("GemmGradArgs", "dx_dA_f32")
+    def shared(**where):
+        assert b.bwd(**where) == 0
+        return any(n in l[0] for l in w.launches() for n in names)
+    x, h, dy, dx = 0x10000, 0x40000000, 0x50000000, 128 * 256 * e  # (dx: bytes)
+    assert shared() and shared(dx=x + dx) and shared(x=x + dx, dx=x)  # beside one another
+    assert not shared(dx=x) and not shared(dx=x + dx - 16) and not shared(x=x + dx - 16, dx=x)
+    if dtype == "bf16":  # (fp32: dB has read them before)
+        assert not shared(dx=dy + 16) and not shared(dx=h + 128 * 128 * 4 - 16) and shared(dx=h + 128 * 128 * 4)
+        assert not shared(h=0x100000000 + 0x20000000) and shared(h=0x100000000 + 0x20000000 + 256 * 16 * 4)  # dA of adapter 0
 
 
 if __name__ == "__main__":
