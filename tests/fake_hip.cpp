@@ -19,6 +19,7 @@ namespace {
 // as in the kernel sources: passes that carry new table addresses, a chunk of a plan as an argument
 struct WideArgs : GemmArgs { PlanPatch patch; };
 struct SkinnyPassArgs : SkinnyArgs { PlanPatch patch; };
+struct MixedPassArgs : GemmArgs { SkinnyPassArgs pass; int mixed_split, mixed_cols; };  // (in the kernels' names: MixedArgs<.., SkinnyPassArgs>)
 struct PlanChunk { int32_t v[896]; };
 
 struct Launch {
@@ -56,7 +57,7 @@ Launch take(const std::string &name, void **args)
     if (has(name, "plan_copy_kernel")) rest = 5;
     if (has(name, "plan_words_kernel")) bytes = sizeof(PlanChunk), rest = 2;
     if (has(name, "WideArgs")) bytes = sizeof(WideArgs);
-    if (has(name, "SkinnyPassArgs")) bytes = sizeof(SkinnyPassArgs);
+    if (has(name, "SkinnyPassArgs")) bytes = has(name, "MixedArgs") ? sizeof(MixedPassArgs) : sizeof(SkinnyPassArgs);
     l.first.assign((unsigned char *)args[0], (unsigned char *)args[0] + bytes);
     for (int i = 0; i < rest; ++i) {
         l.rest[i] = 0;
@@ -78,6 +79,8 @@ void carry_out(const Launch &l)
         std::memcpy((void *)l.rest[0], a, 4 * (size_t)l.rest[1]);
     } else if (has(l.name, "WideArgs")) {
         copy_patch(reinterpret_cast<const WideArgs *>(a)->patch);
+    } else if (has(l.name, "MixedArgs") && has(l.name, "SkinnyPassArgs")) {
+        copy_patch(reinterpret_cast<const MixedPassArgs *>(a)->pass.patch);
     } else if (has(l.name, "SkinnyPassArgs")) {
         copy_patch(reinterpret_cast<const SkinnyPassArgs *>(a)->patch);
     }

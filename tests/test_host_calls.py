@@ -54,6 +54,14 @@ def test_a_call_behind_a_failed_upload_uploads(run, dtype, n_adapters, call, fai
     run("failed_upload", dtype, n_adapters, call, fail)
 
 
+@pytest.mark.parametrize("call", ["fwd", "bwd"])
+@pytest.mark.parametrize("kind,kernel", [("items", "skinny_kernel"), ("tiles", "WideArgs"), ("mixed", "MixedArgs"), ("decode", "decode_base")])
+def test_new_tables_carried_by_a_pass_leave_the_plan_of_a_whole_upload(run, kind, kernel, call):
+    if kind == "decode" and call == "bwd":
+        pytest.skip("inference only")
+    run("carried", kind, kernel, call)
+
+
 def test_every_launch_has_asked_for_its_lds(run):
     run("lds")
 
@@ -288,6 +296,37 @@ def failed_upload(w, dtype, n_adapters, call, fail):
     assert any("plan_copy" in l[0] or "PassArgs" in l[0] for l in w.launches()), "computed with the tables of the call before"
     assert go(1) == 0
     assert not any("plan_copy" in l[0] or "PassArgs" in l[0] for l in w.launches())
+
+
+def carried(w, kind, kernel, call):
+    # and a failed launch of the pass leaves no plan to reuse; a replay brings a plan of its own
+    ranks = {"items": [8, 16, 16], "tiles": [64, 64, 64], "mixed": [12, 64, 20], "decode": [8, 64, 16]}[kind]
+    lens, trn = ([1, 5, 9], [0, 0, 0]) if kind == "decode" else ([40, 33, 50], [1, 1, 1])
+    go = lambda b, layer: (b.fwd if call == "fwd" else b.bwd)(layer)
+    plans = []
+    for layers in ([0, 1], [1]):
+        ctx = w.context()
+        b = Batch(w, ctx, lens, [0, 1, 2], trn, ranks, 1024, 1024)
+        whole = 0
+        for layer in layers:
+            w.launches()
+            assert go(b, layer) == 0
+            whole = max(whole, w.stats(ctx)[1])
+        names = [l[0] for l in w.launches()]
+        if len(layers) == 2:
+            assert any(kernel in n and "PassArgs" in n or "WideArgs" in n and kernel == "WideArgs" for n in names) and not any("plan_copy" in n for n in names), names
+        plans.append(w.fake.fake_plan()[: whole // 4])
+    assert plans[0] == plans[1]
+    assert go(b, 0) == 0
+    w.fake.fake_fail_launch(b"WideArgs" if kernel == "WideArgs" else b"SkinnyPassArgs")
+    assert go(b, 1) == -8
+    w.launches()
+    assert go(b, 1) == 0 and any("plan_copy" in l[0] for l in w.launches()) and w.fake.fake_plan()[: whole // 4] == plans[0]
+    x, y = Batch(w, ctx, lens, [0, 1, 2], trn, ranks, 1024, 1024), Batch(w, ctx, lens, [2, 1, 0], trn, ranks, 1024, 1024)
+    w.record(lambda: go(x, 1))
+    assert go(y, 0) == 0
+    w.fake.fake_replay()
+    assert w.fake.fake_plan()[: whole // 4] == plans[0]
 
 
 def lds(w):
