@@ -403,6 +403,13 @@ int collm_device_info(int device, int32_t *compute_units, int32_t *clock_khz, in
 int collm_debug_plan_stats(const collm_ctx *ctx, float *build_us, float *upload_us, int32_t *bytes, int32_t *mode);
 
 /*
+ * Debug, HOST only: which kernels the context's last compute call ran (bf16).  *grad_slices: 0, or the number of slices of K of a dX GEMM with the
+ * adapter gradients in its launch (1: not cut); *mixed_passes: rank-wide passes that ran 128-row tiles and 16-row items in one launch;
+ * *pass_slices: the most slices of K of a rank-wide pass over 16-row items (0: there was none).
+ */
+int collm_debug_last_call(const collm_ctx *ctx, int32_t *grad_slices, int32_t *mixed_passes, int32_t *pass_slices);
+
+/*
  * Debug/profiling: duration in milliseconds of each pass (one kernel, or the few kernels of
  * a pass) launched by the context's last compute call, from the start of its first kernel to
  * the end of its last by the kernels' own time stamps (HIP events attached to the launches on

@@ -142,6 +142,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.collm_device_info.restype = ctypes.c_int
     lib.collm_debug_plan_stats.argtypes = [vp, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_float), _i32p, _i32p]
     lib.collm_debug_plan_stats.restype = ctypes.c_int
+    lib.collm_debug_last_call.argtypes = [vp, _i32p, _i32p, _i32p]
+    lib.collm_debug_last_call.restype = ctypes.c_int
     lib.collm_profile_enable.argtypes = [vp, ctypes.c_int]
     lib.collm_profile_enable.restype = ctypes.c_int
     lib.collm_profile_read.argtypes = [vp, ctypes.POINTER(ctypes.c_char_p), ctypes.POINTER(ctypes.c_float),
@@ -364,6 +366,12 @@ class Context:
         _check(self._lib.collm_debug_plan_stats(self._h, ctypes.byref(b), ctypes.byref(u), ctypes.byref(n),
                                                 ctypes.byref(m)), "collm_debug_plan_stats")
         return {"build_us": b.value, "upload_us": u.value, "bytes": n.value, "mode": m.value}
+
+    def last_call(self):
+        """Which kernels the last compute call ran: dict(grad_slices, mixed_passes, pass_slices)."""
+        v = [ctypes.c_int32(-9) for _ in range(3)]
+        _check(self._lib.collm_debug_last_call(self._h, *[ctypes.byref(x) for x in v]), "collm_debug_last_call")
+        return {"grad_slices": v[0].value, "mixed_passes": v[1].value, "pass_slices": v[2].value}
 
     def profile_enable(self, on: bool):
         _check(self._lib.collm_profile_enable(self._h, 1 if on else 0), "collm_profile_enable")

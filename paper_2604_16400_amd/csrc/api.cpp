@@ -125,6 +125,9 @@ struct collm_ctx {
     int plan_mode = 0;       // 0: reused as it is, 1: built anew, 2: table addresses replaced, 3: gradient pointers only
     int plan_bytes_up = 0;   // bytes the call sent to the device
 
+    // what the last compute call ran (collm_debug_last_call)
+    int ran_grad_slices = 0, ran_mixed = 0, ran_pass_slices = 0;
+
     bool profile = false;
     int n_prof = 0;
     const char *prof_name[kMaxProfile] = {};
@@ -1169,6 +1172,8 @@ int run_skinny(collm_ctx *c, const collm_shape *s, const RowOrderLayout &R, cons
         mixed = (K + n * per_trip - 1) / (n * per_trip) <= 6;
         if (mixed) n_split = (int)n;
     }
+    c->ran_mixed += mixed;
+    if (R.n_items > 0) c->ran_pass_slices = std::max(c->ran_pass_slices, n_split);
     if (R.n_wide > 0) {
         // Long runs: 128-row tiles through the GEMM machinery.  A block fills a CU (four LDS stages), so K is cut
         // so that at most one block per CU exists, as long as a slice keeps 512 K values and the partial sums fit
@@ -1723,6 +1728,15 @@ int collm_debug_plan_stats(const collm_ctx *c, float *build_us, float *upload_us
     return COLLM_OK;
 }
 
+int collm_debug_last_call(const collm_ctx *c, int32_t *grad_slices, int32_t *mixed_passes, int32_t *pass_slices)
+{
+    if (!c || !grad_slices || !mixed_passes || !pass_slices) return COLLM_E_NULL;
+    *grad_slices = c->ran_grad_slices;
+    *mixed_passes = c->ran_mixed;
+    *pass_slices = c->ran_pass_slices;
+    return COLLM_OK;
+}
+
 int collm_profile_enable(collm_ctx *c, int enable)
 {
     if (!c) return COLLM_E_NULL;
@@ -1771,6 +1785,7 @@ static int fwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(c->device));
     c->n_prof = 0;
+    c->ran_grad_slices = c->ran_mixed = c->ran_pass_slices = 0;
     const PatchGuard guard{c};
     const bool decode = decode_sized(c, s, rank, seg_start, seg_adapter, seg_is_train, P, swiglu);
     {
@@ -1911,6 +1926,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(c->device));
     c->n_prof = 0;
+    c->ran_grad_slices = c->ran_mixed = c->ran_pass_slices = 0;
     // Few gradient buffers travel as arguments of the gradient kernels, which then need nothing that an upload of this call puts into
     // the plan (the pass over dy that gives dh and dB at once, for narrow ranks, looks them up there): new adapter tables
     // ride on the rank-wide pass that the call begins with, beside dB on the second stream.  Four 4096 -> 4096 projections, 2048 tokens, 1792 of
@@ -2213,6 +2229,7 @@ static int bwd_impl(collm_ctx *c, const collm_shape *s, const collm_siblings *si
             }
         } else {
             HIP_TRY(run_gemm(c, g, L.train, n_train, s->d_in, c->tile_bwd, !tr, one_round && !fused, st, false, fused ? &beside : nullptr));
+            if (fused && beside.done) c->ran_grad_slices = beside.slices;
             if (fused && !beside.done) {
                 HIP_TRY(launch_grad(beside.dB, L.n_grad, L.rpad, st));
                 HIP_TRY(launch_grad(beside.dA, L.n_grad, L.rpad, st));

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("transposed", [False, True])
-@pytest.mark.parametrize("d_in,d_out,ranks,lens", [
-    (200, 392, [64], [129]), (264, 136, [16], [257]), (1096, 2056, [16, 5], [65, 300]), (264, 136, [16], [257]), (1096, 2056, [16, 5], [65, 300]), (72, 1000, [40, 12], [1, 31, 33, 160]), (1032, 264, [64, 3, 24], [200, 1, 64, 17]),
-    (136, 520, [48] * 19, [3] * 38)])  # (more trained adapters than travel as arguments)
-def test_small(d_in, d_out, ranks, lens, transposed):
+@pytest.mark.parametrize("d_in,d_out,ranks,lens,slices", [
+    (200, 392, [64], [129], 1), (264, 136, [16], [257], 1), (1096, 2056, [16, 5], [65, 300], 9), (72, 1000, [40, 12], [1, 31, 33, 160], 4),
+    (1032, 264, [64, 3, 24], [200, 1, 64, 17], 1), (264, 4104, [64, 24], [65, 30], 17),
+    (256, 1024, [16] * 20, [8] * 20, 4), (256, 1024, [24] * 20, [8] * 20, 2),  # more trained adapters than travel as arguments
+    (136, 520, [48] * 19, [3] * 38, 0)])  # too much work for the places
+def test_small(d_in, d_out, ranks, lens, slices, transposed):
     n = len(lens)
     w = wl.make_adhoc("beside", "bf16", d_in, d_out, ranks, lens + [5], [i % len(ranks) for i in range(n)] + [-1], [1] * n + [0], scale=0.7, seed=n)
     t = wl.make_tensors(w)
@@ -24,19 +26,23 @@ def test_small(d_in, d_out, ranks, lens, transposed):
     layer = DeviceLayer(w, t, ctx, transposed=transposed)
     layer.fwd(h_save=True)
     layer.bwd(h_save=True)
+    assert ctx.last_call()["grad_slices"] == slices
     check_full(layer, TOL["bf16"])
     once = [g.clone() for g in layer.dA + layer.dB]
     layer.bwd(h_save=True, accumulate=True)
     for g, o in zip(layer.dA + layer.dB, once):
         assert torch.equal(g, o + o)
     layer.bwd(h_save=False)
+    assert ctx.last_call()["grad_slices"] == slices
     check_full(layer, TOL["bf16"])
     ctx.close()
 
 
 @pytest.mark.parametrize("transposed", [False, True])
-@pytest.mark.parametrize("rows,d_in,d_out,rank", [(1792, 4096, 1024, 16), (400, 5632, 2528, 32), (1000, 2056, 4104, 64), (386, 1280, 2816, 64), (411, 1056, 5496, 16), (77, 3072, 1208, 16), (386, 1280, 2816, 64), (411, 1056, 5496, 16), (77, 3072, 1208, 16), (130, 7000, 8200, 12)])
-def test_large(rows, d_in, d_out, rank, transposed):
+@pytest.mark.parametrize("rows,d_in,d_out,rank,slices", [
+    (768, 6944, 1864, 16, 1), (726, 5368, 912, 32, 1), (400, 5632, 2528, 32, 2), (386, 1280, 2816, 64, 6), (411, 1056, 5496, 16, 7),
+    (77, 3072, 1208, 16, 5), (130, 7000, 8200, 12, 3), (1792, 4096, 1024, 16, 0), (1000, 2056, 4104, 64, 0)])
+def test_large(rows, d_in, d_out, rank, slices, transposed):
     g = torch.Generator(device="cuda").manual_seed(rows)
     rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda")
     st = (lambda a: a.t().contiguous()) if transposed else (lambda a: a)
@@ -61,6 +67,7 @@ def test_large(rows, d_in, d_out, rank, transposed):
         ctx.collm_lora_linear_bwd(x, st(W), [st(a) for a in A], [st(b) for b in B], *batch, dy, h, dx, dA, dB,
                                   layout=binding.LAYOUT_OUT_IN if transposed else binding.LAYOUT_IN_OUT)
         torch.cuda.synchronize()
+        assert ctx.last_call()["grad_slices"] == (slices if streams < 0 else 0)
         close = lambda got, ref: float((got.float() - ref).abs().max()) <= TOL["bf16"] * float(ref.abs().max())
         assert close(dx, want_dx)
         for a in (0, 1):

@@ -10,8 +10,8 @@ from gpu_util import TOL, DeviceLayer, check_full, make_ctx
 pytestmark = pytest.mark.gpu
 
 
-def _check(d_in, d_out, ranks, lens, transposed, seed):
-    """Forward, backward with h and without; new adapter tables on a known batch ride on the pass."""
+def _check(d_in, d_out, ranks, lens, transposed, seed, mixed=True):
+    """Forward, backward with h and without; new adapter tables on a known batch ride on the pass.  mixed: whether the kinds share a launch."""
     n = len(lens)
     w = wl.make_adhoc("mixed", "bf16", d_in, d_out, ranks, lens, [i % len(ranks) for i in range(n)], [(i // len(ranks)) % 2 for i in range(n)], scale=0.7, seed=seed)
     t = wl.make_tensors(w)
@@ -19,9 +19,12 @@ def _check(d_in, d_out, ranks, lens, transposed, seed):
     for _ in range(2):
         layer = DeviceLayer(w, t, ctx, transposed=transposed)  # (tables of their own)
         layer.fwd(h_save=True)
+        assert ctx.last_call()["mixed_passes"] == mixed
         layer.bwd(h_save=True)
+        assert ctx.last_call()["mixed_passes"] == mixed
         check_full(layer, TOL["bf16"], check_h=True)
     layer.bwd(h_save=False)
+    assert ctx.last_call()["mixed_passes"] == 2 * mixed
     check_full(layer, TOL["bf16"], check_h=True)
     ctx.close()
 
@@ -33,9 +36,9 @@ def test_lengths(K, transposed):
     _check(72, K, [36, 72, 3], [17, 33, 40, 1, 130, 7], transposed, seed=K + 1)
 
 
-@pytest.mark.parametrize("ranks", [[60, 128], [12, 200], [68, 64]])  # the last: too wide for the shared launch
-def test_ranks(ranks):
-    _check(1032, 2056, ranks, [20, 129, 1, 1, 35, 16], False, seed=ranks[0])
+@pytest.mark.parametrize("ranks,mixed", [([60, 128], True), ([12, 200], True), ([68, 64], False)])  # the last: too wide for the shared launch
+def test_ranks(ranks, mixed):
+    _check(1032, 2056, ranks, [20, 129, 1, 1, 35, 16], False, seed=ranks[0], mixed=mixed)
 
 
 @pytest.mark.parametrize("n12,n64", [(130, 2), (2, 70)])  # more 16-row items than half of the places; more tiled ones than places are left
