@@ -122,7 +122,9 @@ const char *collm_last_error(void);
  * Steps, all in the library's kernels: the host turns the segment table into a device plan
  * (token -> segment/adapter map, rows grouped by adapter, tile tables); a segmented shrink
  * computes h = x A[a] in fp32; one GEMM computes x W and adds scale * h B[a] as extra
- * K-steps before the single rounding of y.
+ * K-steps before the single rounding of y.  (bf16 batches of up to 64 tokens with adapters and without training
+ * segments, one projection: x W and x A[a] side by side in one kernel, fp32 sums in the workspace; a second one adds
+ * bf16(scale * h) B[a] and rounds.)
  *
  *   x            dev  [T, d_in]
  *   W            dev  [d_in, d_out]  (shapes of W, A, B as for COLLM_LAYOUT_IN_OUT; see collm_layout)
@@ -346,8 +348,8 @@ int collm_debug_host_row_order(const collm_shape *shape, const int32_t *rank, co
  * Debug/tuning: force the tile shape of the forward GEMM and of the dX GEMM
  * (0: 256x256, 1: 256x128, 2: 128x128, 3: 128x192, 4: 256x192 rows x columns of the output - 1, 3 and 4 stand for 0 or 2 of the
  * same height where several siblings or the SwiGLU epilogue are computed; -1: let the library choose from the
- * problem size; anything else: COLLM_E_SHAPE).  Affects only speed, never results beyond
- * rounding order.
+ * problem size; anything else: COLLM_E_SHAPE).  A forced fwd_tile also keeps decode-sized calls on the general path, a
+ * forced bwd_tile the gradients out of the dX GEMM's launch.  Affects only speed, never results beyond rounding order.
  */
 int collm_debug_set_tiles(collm_ctx *ctx, int fwd_tile, int bwd_tile);
 
@@ -355,7 +357,8 @@ int collm_debug_set_tiles(collm_ctx *ctx, int fwd_tile, int bwd_tile);
  * Debug/tuning: into how many slices of K a GEMM with few rows (fewer than 256 tiles of
  * 128x128) is cut across blocks; the slices' fp32 sums are added by a second kernel before the
  * single rounding.  -1: let the library choose; 1: never; 2..64: that many (as far as K and
- * the workspace allow).  bf16 only.  Affects only speed and rounding order.
+ * the workspace allow).  bf16 only.  Any value but -1 also keeps decode-sized calls on the general path and the gradients out of
+ * the dX GEMM's launch.  Affects only speed and rounding order.
  */
 int collm_debug_set_gemm_split(collm_ctx *ctx, int n_slices);
 
@@ -369,8 +372,8 @@ int collm_debug_set_grad_streams(collm_ctx *ctx, int mode);
  * Debug/tuning: which rows the rank-wide passes (h = x A, dh = dy B^T) run as 128-row tiles
  * rather than 16-row items: runs of at least min_rows rows of one adapter whose rank is a
  * multiple of 8.  0: never; -1: let the library choose (every such adapter when the widest
- * rank of the batch is at least 49; for the training rows already from 17).  bf16 only.
- * Affects only speed and rounding order.
+ * rank of the batch is at least 49; for the training rows already from 17).  bf16 only.  Any value but -1 also keeps
+ * decode-sized calls on the general path.  Affects only speed and rounding order.
  */
 int collm_debug_set_wide_pass(collm_ctx *ctx, int min_rows);
 
@@ -415,7 +418,8 @@ int collm_debug_last_call(const collm_ctx *ctx, int32_t *grad_slices, int32_t *m
  * the end of its last by the kernels' own time stamps (HIP events attached to the launches on
  * the call's own stream; no event latency inside the interval; 0 for a pass that launched
  * nothing).  collm_profile_enable(ctx, 1) makes every later call time its passes this way,
- * all on the call's stream, one after the other;
+ * all on the call's stream, one after the other (and the gradients never in the dX GEMM's launch, fp32 passes never two in a
+ * launch: a call may add in another order than the same call without profiling);
  * collm_profile_read synchronises, fills names[i] (static strings) and ms[i] for up to
  * `cap` passes and returns how many there were (or a negative status).
  */

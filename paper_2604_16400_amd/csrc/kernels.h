@@ -245,7 +245,8 @@ hipError_t launch_grad(const GradArgs &a, int n_grad, int rpad, hipStream_t st);
 int grad_lds(int rpad, bool beside_gemm);  // bytes of LDS a block of launch_grad asks for
 constexpr int kSmallTileLds = 2 * (128 + 128) * 128;  // bytes of LDS of a 128x128 GEMM block (two stages); two such blocks run on a CU
 // A decode-sized inference call in two kernels (kernels_decode.hip): y = x W + (s h) B_a for up to kDecodeRows rows, ranks up to
-// kDecodeRank.  The shrink's arguments (x, tables, items of 16 rows, where its sums go) are a SkinnyArgs.
+// kDecodeRank.  The shrink's arguments (x, tables, items of 16 rows, where its sums go) are a SkinnyArgs.  64 rows: the accumulators of four row tiles
+// and two rounds of operands in flight take 450 to 455 of the 512 registers that a wave alone on its SIMD has, and a fifth tile takes 48 more.
 constexpr int kDecodeRows = 64, kDecodeRank = kMaxRank, kDecodeCols = 128, kDecodeRankCols = 64;
 struct DecodeArgs {
     const void *w;            // [K][N] or, K-major, [N][K]; row length ldw

@@ -1,6 +1,6 @@
 // bf16 MFMA kernels of the mixed-batch LoRA linear layer for gfx950 (MI355X, wave64).
 //
-// Three kernels, all built from the same LDS tile format and bf16 MFMA inner product:
+// The general path's three kernels, on bf16 MFMAs (the block work of `skinny` is shared with the decode-sized calls and stands in bf16_device.h):
 //   gemm_lora   y  = x W  + (s h) B_a        (forward;  W and B_a are [K][N])
 //               dx = dy W^T + dh A_a^T       (backward; W and A_a are read [N][K])
 //               One dense GEMM whose K loop is extended by 16-wide steps that multiply the
@@ -12,7 +12,7 @@
 //
 // LDS tile format: a tile holds R rows of 64 bf16 (128 bytes) along the contraction index.
 // The row is cut into eight 16-byte chunks and chunk c of row r is stored at chunk position
-// c ^ ((r ^ (r >> 3)) & 7).  A wave reading one chunk column of 32 consecutive rows, and a
+// c ^ swz(r) (below).  A wave reading one chunk column of 32 consecutive rows, and a
 // wave writing eight consecutive rows of one chunk column, both touch every bank once.
 //
 // MFMA operand layout (v_mfma_f32_32x32x16_bf16): lane l supplies 8 consecutive K values

@@ -7,9 +7,9 @@
 // does the multiplying because its operands come straight from memory: lane l supplies one K value
 // (group l / 16) of row or column l % 16, so a lane that loads four consecutive K values feeds four of them.
 // Measured on 256 -> 256, 64 tokens, rank 8 (us; before: one thread per output of the narrow passes with a serial sum,
-// 64 x 64 LDS tiles): rank-wide passes 22 -> 4.5, gradients 20 -> 4.2, GEMM 35 -> 6.3 on 64 columns a block, on 16 (launch_gemm_f32) less again:
-// the step 27.9 -> 15.5 with the passes that run side by side (dh_dB_f32_kernel); the shorter chains also halve the distance from the 64-bit
-// result (3.3e-7 -> 1.4e-7).
+// 64 x 64 LDS tiles): rank-wide passes 22 -> 4.5, gradients 20 -> 4.2, GEMM 35 -> 3.5 on blocks of 16 columns (launch_gemm_f32); the step of a forward
+// and a backward call, one among others, 27.9 in six kernels -> 17 in four (dh_dB_f32_kernel, dx_dA_f32_kernel); the shorter chains also halve the
+// distance from the 64-bit result (3.3e-7 -> 1.4e-7).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
