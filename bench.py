@@ -36,14 +36,18 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E
 # Bytes between the L2s and the memory side (Infinity Cache + HBM) of one forward-GEMM launch of configuration 5's
 # 8192->28672 projection: rocprofv3 FETCH_SIZE and WRITE_SIZE in KiB, scaled by what the same counters read for a
 # plain 1 GiB copy (x 2.0 and x 1.0; profiles/gemm_lora_config5.txt),
-# with the digest of the kernel source the counters were taken on: a build from other source reports null.
+# with the digest of the sources that the counters were taken on: a build from other sources reports null.
 ROOFLINE_TRAFFIC = {"bytes": (6636726 * 2.0 + 946176 * 1.0) * 1024, "kernels_sha256_16": "a0c855b4596b211f"}
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2604_16400_amd", "csrc", "kernels_bf16.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2604_16400_amd", "csrc", name)  # what the measured kernel is compiled from
+                  for name in ("kernels_bf16.hip", "bf16_device.h", "kernels.h", "plan.h")]
 
 
 def _kernel_digest():
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for path in KERNEL_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def _draw(torch, gen, shape, std, dt):

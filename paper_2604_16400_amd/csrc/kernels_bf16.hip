@@ -80,7 +80,8 @@ __host__ __device__ __forceinline__ void tile_coords(int pid, int tiles_m, int t
 // its L2 fetches the slice's share of the rows once (in the order above, each slice's tiles spread over all XCDs, every XCD fetches nearly all
 // rows of the first operand: 704 rows, 48 tiles of K = 6552, about 87 MB instead of 28 for 23 of operands).  Calls, weights from memory, before /
 // after, us: 128 rows 8192 -> 8192 50.4 / 48.3, 1000 rows 14336 -> 4096 166.0 / 161.5, 300 rows 4096 -> 4096 39.9 / 39.8; forward and
-// backward, 370 rows 2048 -> 7680 88.3 / 83.9, 1006 rows 9328 -> 1256 144.8 / 142.2.
+// backward, 370 rows 2048 -> 7680 88.3 / 83.9, 1006 rows 9328 -> 1256 144.8 / 142.2.  320 drawn forward calls of 65 to 2500 rows 1.04 times as
+// fast, weights of 4 to 64 MB 1.07, larger ones level (0.94 .. 1.08), smaller ones, at 10 to 15 us a call, within what these differ by.
 __host__ __device__ __forceinline__ void slice_coords(int pid, int tiles_m, int tiles_n, int n_slices, int &slice, int &tm, int &tn)
 {
     const int tiles = tiles_m * tiles_n, total = tiles * n_slices;
