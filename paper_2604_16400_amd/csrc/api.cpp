@@ -524,7 +524,7 @@ struct GradsBeside {
 // GEMM blocks on a CU takes 0.9 us (0.48 of one alone, which leaves no place for a gradient), a chunk of 128 rows of a gradient block 1.2; the
 // sums are written and read at 8 TB/s.
 //  - GEMM of two blocks per CU beside the second stream: where the gradients end before its blocks in the places they leave.  Passes (forward and
-//    backward), us: four layers 4096 -> 4096, 2048 tokens, rank 16 603 / 580; 740 tokens 5632 -> 2528 rank 32 448 / 406, 1148 tokens
+//    backward), us: four layers 4096 -> 4096, 2048 tokens, rank 16 590 / 583; 740 tokens 5632 -> 2528 rank 32 448 / 406, 1148 tokens
 //    6496 -> 3072 rank 64 700 / 660; 45 batches 1.009, none slower.  Where they miss it by up to 2.5 as many lose as gain (1096 -> 4864 rank 64
 //    256 / 277, 13072 -> 2360 294 / 280).
 //  - GEMM of one block per CU, or a call on one stream: the number of slices at which GEMM and gradients end first, if it is at most 8 (one

@@ -5,8 +5,9 @@
 //   decode_base    streams the weight (sums of K slices of x W) and, in other blocks of the same grid, the shrink tables (sums of
 //                  K slices of x A_a), all in fp32 to the workspace;
 //   decode_finish  adds the slices in slice order, multiplies bf16(s h) with B_a and rounds y once.
-// Weights from memory, us: eight rows 4096 -> 4096 (33.5 MB) 21 in three kernels, 14.5 in two (base 8 to 9, finish 5); 64 rows of 29 adapters of ranks 8 to 128,
-// 4096 -> 11008 (90 MB of weight, 37 of tables) 49 in four, 40 in two (27, 12).  A plain read of these weights with the same loads takes 8 and 17 us.
+// A call among others, us, weight and tables in the last-level cache / from memory: eight rows 4096 -> 4096 (33.5 MB) 19.8 / 23.3 in three kernels,
+// 12.5 / 16.3 in two (base 8, finish 4); 64 rows of 29 adapters of ranks 8 to 128, 4096 -> 11008 (90 MB of weight, 37 of tables) 44 / 54 in four, 34 / 41 in
+// two (27, 12).  A plain read of these weights with the same loads takes 8 and 17 us.
 // In the 27 us: the rows of x 3, the sums across waves 2, the MFMAs that one wave per SIMD does not hide 4 (measured without them).
 #include "bf16_device.h"
 
